@@ -294,7 +294,7 @@ MDI_API mdi_status mdi_sample_topk(mdi_partition *part, uint32_t seq_id, const v
  * library any: code under HIP graph capture, tight serving loops, harnesses
  * that forbid allocation.  Same arguments, same result (token and logits are
  * bit-identical to mdi_sample_topk's; top_k = 1 gives the greedy token), but
- * the kernels' scratch - the [V] float logits the sampler works on, the
+ * the kernels' scratch - the [V] float logits (when logits_out is NULL), the
  * per-workgroup argmax candidates and the arrival counter - is not taken from
  * the partition's arena: it lives in a fixed array inside the library
  * (1 MiB + 24.25 KiB of device memory per GPU, held until the process ends).

@@ -219,11 +219,17 @@ __global__ __launch_bounds__(kBlock) void k_gemv(GemvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Draw from the top-k tempered pmf (Alg. 1 samples the output distribution).  One workgroup: every thread keeps the
-// best of the logits it owns (index = thread + 1024 j); k rounds of a workgroup-wide argmax (lowest index on ties)
-// pick the candidates in rank order, the owner of a winner strikes it out and rescans only its own elements.
-// Thread 0 then inverts the cumulative distribution at the uniform number of Philox-4x32-10 (Salmon et al., SC'11)
-// for counter (sample, step, 0, 0): weights exp((l_j - l_max) / T) in rank order, binary32, summed sequentially.
+// Draw from the top-k tempered pmf (Alg. 1 samples the output distribution).  One workgroup per sample finds the k
+// largest logits (lowest index on ties), puts them in rank order and inverts the cumulative distribution at the
+// uniform number of Philox-4x32-10 (Salmon et al., SC'11) for counter (sample, step, 0, 0): weights
+// exp((l_j - l_max) / T) in rank order, binary32, summed sequentially.
+//
+// What bounds it is the latency of its dependent rounds, not the 4 V bytes it reads.  k rounds of a workgroup-wide
+// argmax, each with two barriers and a rescan of the winner's elements, took 981 us for 16 samples of 128256 logits
+// at k = 50.  Instead: the k-th largest of the threads' own maxima is a lower bound for the k-th largest logit (the
+// threads' elements are disjoint), so a second look at the logits keeps the few that reach it (on average k times
+// 1.03 of them), and a candidate's rank is the number of better candidates: 33 us for the same draw, two passes over
+// half a megabyte per sample by one workgroup each and about 10 us of selection between and after them.
 __device__ __forceinline__ uint32_t philox4x32_10_first(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
   for (int r = 0; r < 10; ++r) {
     if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
@@ -235,22 +241,44 @@ __device__ __forceinline__ uint32_t philox4x32_10_first(uint32_t c0, uint32_t c1
   return c0;
 }
 
-__device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
-  __shared__ float cv[kMaxTopK];
-  __shared__ int ci[kMaxTopK];
-  __shared__ float rv[16];
-  __shared__ int ri[16];
-  __shared__ int s_win;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float bv; int bi;
-  auto scan = [&]() {
-    bv = -INFINITY; bi = 0x7FFFFFFF;
-    for (int i = tid; i < a.V; i += 1024) {
-      const float v = a.logits[i];
-      if (better(v, i, bv, bi)) { bv = v; bi = i; }
+// Order-preserving image of a float as an unsigned number; 0 for NaN (never a candidate), equal for the two zeros.
+__device__ __forceinline__ uint32_t rank_key(float v) {
+  const uint32_t u = __float_as_uint(v + 0.f);
+  return v != v ? 0u : (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+constexpr int kTopkThreads = 1024;
+constexpr int kTopkCand = 1024;          // candidates a workgroup can hold; more (masses of equal logits) take the rounds
+
+// f(value, index) over this thread's share of v[0 .. n): whole 16-byte pieces dealt round-robin to the threads, eight
+// in flight each, the up to three values before the first aligned piece and after the last one to the first threads.
+template <typename F>
+__device__ __forceinline__ void each_logit(const float* v, int n, F&& f) {
+  const int tid = threadIdx.x;
+  const int head = min((int)((4u - (unsigned)((uintptr_t)v >> 2)) & 3u), n);
+  const int n4 = (n - head) >> 2, tail = head + 4 * n4;
+  const float4* v4 = reinterpret_cast<const float4*>(v + head);
+  if (tid < head) f(v[tid], tid);
+  for (int p0 = tid; p0 < n4; p0 += 8 * kTopkThreads) {
+    float4 t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = v4[min(p0 + j * kTopkThreads, n4 - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int p = p0 + j * kTopkThreads, i = head + 4 * p;
+      if (p < n4) { f(t[j].x, i); f(t[j].y, i + 1); f(t[j].z, i + 2); f(t[j].w, i + 3); }
     }
-  };
-  scan();
+  }
+  if (tid < n - tail) f(v[tail + tid], tail + tid);
+}
+
+// The k best logits one after the other: a workgroup-wide argmax per rank, the owner of a winner then looks for its
+// own next best.  Taken when the logits that reach the bound outnumber the candidate array, or when NaNs leave fewer
+// than k (981 us for the shape above).
+__device__ void topk_rounds(const SampleArgs& a, float* cv, int* ci, float* rv, int* ri, int* s_win) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float bv = -INFINITY; int bi = 0x7FFFFFFF;
+  each_logit(a.logits, a.V, [&](float v, int i) { if (better(v, i, bv, bi)) { bv = v; bi = i; } });
   for (int r = 0; r < a.k; ++r) {
     float wv = bv; int wi = bi;
 #pragma unroll
@@ -261,25 +289,82 @@ __device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
     if (lane == 0) { rv[wave] = wv; ri[wave] = wi; }
     __syncthreads();
     if (tid == 0) {
-      for (int w = 1; w < 16; ++w) if (better(rv[w], ri[w], wv, wi)) { wv = rv[w]; wi = ri[w]; }
-      cv[r] = wv; ci[r] = wi; s_win = wi;
+      for (int w = 1; w < kTopkThreads / 64; ++w) if (better(rv[w], ri[w], wv, wi)) { wv = rv[w]; wi = ri[w]; }
+      cv[r] = wv; ci[r] = wi; *s_win = wi;
     }
     __syncthreads();
-    if (bi == s_win && bi != 0x7FFFFFFF) { a.logits[bi] = -INFINITY; scan(); }   // only the owner's elements change
-  }
-  if (tid == 0) {
-    const float lmax = cv[0];
-    float total = 0.f;
-    for (int j = 0; j < a.k; ++j) { cv[j] = expf((cv[j] - lmax) * a.inv_t); total += cv[j]; }
-    const float u = (float)(philox4x32_10_first(a.ctr0, a.ctr1, 0u, 0u, a.key0, a.key1) >> 8) * (1.0f / 16777216.0f);
-    const float target = u * total;
-    float acc = 0.f;
-    int tok = ci[a.k - 1];
-    for (int j = 0; j < a.k; ++j) {
-      acc += cv[j];
-      if (target < acc) { tok = ci[j]; break; }
+    if (bi == *s_win && bi != 0x7FFFFFFF) {                       // only the owner's elements change
+      const float pv = bv; const int pi = bi;
+      bv = -INFINITY; bi = 0x7FFFFFFF;
+      each_logit(a.logits, a.V, [&](float v, int i) { if (better(pv, pi, v, i) && better(v, i, bv, bi)) { bv = v; bi = i; } });
     }
-    *a.token_out = tok;
+  }
+}
+
+__device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
+  __shared__ float cv[kMaxTopK];
+  __shared__ int ci[kMaxTopK];
+  __shared__ float cand_v[kTopkCand];
+  __shared__ int cand_i[kTopkCand];
+  __shared__ uint32_t keys[kTopkThreads];
+  __shared__ float rv[16];
+  __shared__ int ri[16];
+  __shared__ int s_win, s_n;
+  __shared__ uint32_t s_bound;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid == 0) { s_n = 0; s_bound = 1u; }                        // a short vocabulary: everything is a candidate
+  if (a.V > kTopkCand) {                                          // then at least 256 threads own an element, k is at most 64
+    float best = -INFINITY;
+    each_logit(a.logits, a.V, [&](float v, int) { best = fmaxf(best, v); });   // (fmaxf drops a NaN)
+    keys[tid] = rank_key(best);
+    __syncthreads();
+    if (tid < 64) {
+      // bit by bit, the largest number that at least k of the threads' maxima reach
+      uint32_t mine[kTopkThreads / 64];
+#pragma unroll
+      for (int j = 0; j < kTopkThreads / 64; ++j) mine[j] = keys[lane + 64 * j];
+      uint32_t bound = 0u;
+      for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t trial = bound | (1u << bit);
+        int reach = 0;
+#pragma unroll
+        for (int j = 0; j < kTopkThreads / 64; ++j) reach += __popcll(__ballot(mine[j] >= trial));
+        if (reach >= a.k) bound = trial;
+      }
+      if (lane == 0) s_bound = bound ? bound : 1u;
+    }
+  }
+  __syncthreads();
+  const uint32_t bound = s_bound;
+  each_logit(a.logits, a.V, [&](float v, int i) {
+    if (rank_key(v) >= bound) {
+      const int at = atomicAdd(&s_n, 1);                          // any order: the ranks decide
+      if (at < kTopkCand) { cand_v[at] = v; cand_i[at] = i; }
+    }
+  });
+  __syncthreads();
+  const int n = s_n;
+  if (n < a.k || n > kTopkCand) {
+    topk_rounds(a, cv, ci, rv, ri, &s_win);
+  } else if (tid < n) {
+    const float v = cand_v[tid]; const int i = cand_i[tid];
+    int rank = 0;
+    for (int j = 0; j < n; ++j) rank += better(cand_v[j], cand_i[j], v, i) ? 1 : 0;
+    if (rank < a.k) { cv[rank] = v; ci[rank] = i; }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    // lane j holds weight j (k is at most 64); the running sums in rank order, one addition after the other
+    const float w = lane < a.k ? expf((cv[min(lane, a.k - 1)] - cv[0]) * a.inv_t) : 0.f;
+    float acc = 0.f, upto = 0.f;
+#pragma unroll
+    for (int j = 0; j < kMaxTopK; ++j) {
+      acc += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), j));
+      if (lane == j) upto = acc;
+    }
+    const float u = (float)(philox4x32_10_first(a.ctr0, a.ctr1, 0u, 0u, a.key0, a.key1) >> 8) * (1.0f / 16777216.0f);
+    const unsigned long long past = __ballot(lane < a.k && u * acc < upto);
+    if (lane == 0) *a.token_out = ci[past ? __ffsll((long long)past) - 1 : a.k - 1];
   }
 }
 __global__ __launch_bounds__(1024) void k_sample_topk(SampleArgs a) { sample_topk_body(a); }

@@ -52,7 +52,7 @@ struct mdi_partition {
   // decode scratch
   float *xres = nullptr, *q = nullptr, *o = nullptr, *u = nullptr, *part = nullptr, *amax_val = nullptr;
   int* amax_idx = nullptr;
-  float* logits = nullptr;       // [V] scratch of the stochastic sampler
+  float* logits = nullptr;       // [V] scratch of the stochastic sampler when the caller asks for no logits
   int head_nwg = 0, head_part_floats = 0;   // streaming launch of the output layers (0: per-operation GEMV)
   size_t head_lds = 0;
   // output layers of several samples per pass over the vocabulary matrix (bf16 + RMSNorm heads)
@@ -1055,10 +1055,9 @@ mdi_status mdi_sample_topk(mdi_partition* p, uint32_t seq, const void* act_in, f
   if (!(p->flags & MDI_HAS_HEAD)) return MDI_ERR_STATE;
   const mdi_config& c = p->cfg;
   if (seq >= c.max_seqs || !(temperature > 0.f) || !top_k || top_k > (uint32_t)kMaxTopK) return MDI_ERR_ARG;
-  launch_head(p, act_in, token_out, p->logits, arena_head_scratch(p));
-  if (logits_out && hipMemcpyAsync(logits_out, p->logits, (size_t)c.vocab * 4, hipMemcpyDeviceToDevice, p->stream) != hipSuccess)
-    return MDI_ERR_HIP;
-  SampleArgs sa{p->logits, (int)c.vocab, (int)std::min<uint32_t>(top_k, c.vocab), 1.f / temperature, seq, step,
+  const float* logits = logits_out ? logits_out : p->logits;
+  launch_head(p, act_in, token_out, const_cast<float*>(logits), arena_head_scratch(p));
+  SampleArgs sa{logits, (int)c.vocab, (int)std::min<uint32_t>(top_k, c.vocab), 1.f / temperature, seq, step,
                 (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), token_out};
   launch_sample_topk(p->stream, sa);
   return hip_status();
@@ -1076,14 +1075,13 @@ mdi_status mdi_sample_topk_static(mdi_partition* p, uint32_t seq, const void* ac
   unsigned char* base = nullptr;
   const mdi_status sst = static_scratch(p->device, &base);   // taken at create; here only read
   if (sst != MDI_OK) return sst;
-  float* logits = (float*)(base + kStaticLogitsOff);
+  float* logits = logits_out ? logits_out : (float*)(base + kStaticLogitsOff);
   const HeadScratch hs{(float*)(base + kStaticValOff), (int*)(base + kStaticIdxOff), (tagged_t*)(base + kStaticCandOff),
                        (unsigned*)(base + kStaticCounterOff), (int*)(base + kStaticErrOff)};
   // the array keeps the last call's contents: the arrival counter must start at zero (a fill kernel, not a
   // memset node, so that the call can be captured into a graph); everything else is written before it is read
   launch_fill_u32(p->stream, hs.counter, 1, 0u);
   launch_head(p, act_in, token_out, logits, hs);
-  if (logits_out) launch_copy_rows(p->stream, 4, logits, logits_out, 1, (long)c.vocab, 1, 0);
   SampleArgs sa{logits, (int)c.vocab, (int)std::min<uint32_t>(top_k, c.vocab), 1.f / temperature, seq, step,
                 (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), token_out};
   launch_sample_topk(p->stream, sa);
@@ -1117,8 +1115,7 @@ mdi_status mdi_sample_batch(mdi_partition* p, uint32_t n, const uint32_t* seqs, 
   for (uint32_t i = 0; i < n; i += kMaxBatch) {
     const int m = (int)std::min<uint32_t>(kMaxBatch, n - i);
     float* user = logits_out ? logits_out + (size_t)i * V : nullptr;
-    // the draw overwrites the logits it picks from: with top_k > 1 the pass writes the library's rows
-    float* rows = top_k > 1 ? p->hb_logits : user;
+    float* rows = user ? user : top_k > 1 ? p->hb_logits : nullptr;   // a draw needs them whether the caller does or not
     LogitsBatchArgs a{};
     a.W = p->lm_head; a.N = (int)V; a.Kd = (int)c.d_model;
     for (int j = 0; j < m; ++j) a.x[j] = acts_in[i + j];
@@ -1129,7 +1126,6 @@ mdi_status mdi_sample_batch(mdi_partition* p, uint32_t n, const uint32_t* seqs, 
     a.token_out = tokens_out + i;
     launch_logits_batch(p->stream, p->hb_nwg, p->hb_lds, a);
     if (top_k > 1) {
-      if (user && hipMemcpyAsync(user, rows, (size_t)m * V * 4, hipMemcpyDeviceToDevice, p->stream) != hipSuccess) return MDI_ERR_HIP;
       SampleBatchArgs sb{};
       sb.logits = rows; sb.stride = (long)V; sb.V = (int)V; sb.k = (int)std::min<uint32_t>(top_k, c.vocab);
       sb.inv_t = 1.f / temperature; sb.key0 = (uint32_t)(seed & 0xFFFFFFFFu); sb.key1 = (uint32_t)(seed >> 32);

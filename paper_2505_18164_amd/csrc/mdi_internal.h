@@ -84,7 +84,7 @@ void launch_attn(hipStream_t s, int dtype, const AttnArgs& a);
 // ---- stochastic sampling of the output pmf (Alg. 1) -----------------------
 constexpr int kMaxTopK = 64;
 struct SampleArgs {
-  float* logits;        // [V] fp32; destroyed (the chosen candidates are overwritten)
+  const float* logits;  // [V] fp32
   int V, k;             // k <= kMaxTopK and k <= V
   float inv_t;          // 1 / temperature
   uint32_t ctr0, ctr1;  // counter of the generator: (sample, step)
@@ -94,7 +94,7 @@ struct SampleArgs {
 void launch_sample_topk(hipStream_t s, const SampleArgs& a);
 void launch_row_dots(hipStream_t s, const void* W, int N, int Kd, const float* g, const float* b, float* c1, float* c2);
 struct SampleBatchArgs {              // the same draw for up to 16 samples, one workgroup each
-  float* logits; long stride;         // row j = sample j's logits [V]; destroyed like SampleArgs::logits
+  const float* logits; long stride;   // row j = sample j's logits [V]
   int V, k; float inv_t;
   uint32_t key0, key1;
   int32_t* token_out;                 // [m]
