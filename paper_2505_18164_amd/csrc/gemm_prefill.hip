@@ -1,0 +1,355 @@
+// The matrix products of a first visit (Alg. 1 round 0, Alg. 2 "first iteration"): C[T, N] = A[T, Kd] W[N, Kd]^T with
+// fp32 accumulation, A the activations of T prompt positions, W a weight matrix.  bf16 storage runs on
+// v_mfma_f32_16x16x32_bf16, fp32 storage on v_mfma_f32_16x16x4_f32 (exact fp32 products).
+//
+// One workgroup computes BN weight rows x BT positions, transposed (C^T = W A^T: a lane then owns one position and
+// eight consecutive outputs, so residual, activation and gate/up pairs need no other lane).  A step of the inner
+// dimension is 128 bytes of every row; both operands travel global -> LDS without passing registers
+// (buffer_load_dwordx4 ... lds), a ring of NBW / NBA steps deep, so that a step has one to three steps of arithmetic
+// to arrive; one barrier per step.  Fragments of the next half step are read from LDS between the matrix
+// instructions of the current one.  The 16-byte pieces of a row are permuted by the row number (the permutation is
+// applied to the global address, LDS then holds it for free), which spreads the reads over the banks.
+//
+// What bounds it, measured on the 7B shapes.  With 256 x 256 tiles and long rows the chip's power: the shader clock
+// falls to 1.4 - 1.9 GHz under every variant whose matrix cores are busier, and time follows the energy per product.
+// 16x16x32 instructions take 10 % less of it than 32x32x16 ones (half the accumulator traffic per product): 283
+// against 310 us at 4096 x 4096 x 11008, 1.30 PFLOP/s.  Smaller tiles are bound by what a compute unit pulls out of
+// its die's L2 (about 60 GB/s), few positions by the weights' way from memory.
+#include <algorithm>
+
+#include "device_utils.h"
+
+namespace mdi {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// 64 x 16 bytes global -> LDS: lane l's piece lands at lds + 16 l.  An offset at or past the descriptor's 2^31 - 1
+// bytes reads as zero.
+__device__ __forceinline__ void dma_piece(uint32_t lds, u32x4 rsrc, int voff, int soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ u32x4 buffer_of(const void* p) {
+  const uint64_t a = (uint64_t)p;
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, 0x7FFFFFFFu, 0x00020000u};
+}
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// One 16-byte fragment of each operand: 32 values of the inner dimension over the four lane groups in bf16, 16 in fp32.
+template <typename T> struct Mac;
+template <> struct Mac<bf16_t> {
+  typedef bf16x8 frag;
+  __device__ static __forceinline__ f32x4 go(const frag& w, const frag& a, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, c, 0, 0, 0); }
+};
+template <> struct Mac<float> {
+  typedef f32x4 frag;
+  __device__ static __forceinline__ f32x4 go(const frag& w, const frag& a, f32x4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], a[e], c, 0, 0, 0);
+    return c;
+  }
+};
+
+template <typename T> __device__ __forceinline__ void put8(void* base, long o, const float (&v)[8]);
+template <> __device__ __forceinline__ void put8<float>(void* base, long o, const float (&v)[8]) {
+  f32x4* p = reinterpret_cast<f32x4*>((float*)base + o);
+  p[0] = f32x4{v[0], v[1], v[2], v[3]}; p[1] = f32x4{v[4], v[5], v[6], v[7]};
+}
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16); }
+template <> __device__ __forceinline__ void put8<bf16_t>(void* base, long o, const float (&v)[8]) {
+  *reinterpret_cast<u32x4*>((bf16_t*)base + o) = u32x4{pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7])};
+}
+template <typename T> __device__ __forceinline__ void put4(void* base, long o, float a, float b, float c, float d);
+template <> __device__ __forceinline__ void put4<float>(void* base, long o, float a, float b, float c, float d) {
+  *reinterpret_cast<f32x4*>((float*)base + o) = f32x4{a, b, c, d};
+}
+template <> __device__ __forceinline__ void put4<bf16_t>(void* base, long o, float a, float b, float c, float d) {
+  *reinterpret_cast<u32x2*>((bf16_t*)base + o) = u32x2{pack2(a, b), pack2(c, d)};
+}
+
+// A workgroup is WN x WT wavefronts, each (BN / WN) weight rows x (BT / WT) positions.
+template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
+__global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmArgs a) {
+  typedef Mac<ST> M;
+  constexpr int NW = WN * WT, ES = (int)sizeof(ST);
+  constexpr int TN = BN / WN / 16, TT = BT / WT / 16;   // 16 x 16 tiles per wavefront
+  constexpr int LW = BN / 8 / NW, LA = BT / 8 / NW;     // 1-KiB pieces (8 rows) per wavefront and step
+  constexpr int WB = BN * 128, AB = BT * 128;           // bytes of a step
+  static_assert(TN % 2 == 0 && TT >= 1 && BN % (8 * NW) == 0 && BT % (8 * NW) == 0, "tile shape");
+  static_assert(NBW >= NBA && (NBW == NBA || NBW == NBA + 1) && NBA >= 2, "ring depths");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char gemm_smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)gemm_smem;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave / WT, wt = wave % WT;
+
+  // Workgroup -> tile.  Workgroups are handed to the eight compute dies in turn, and each die has an L2 of its own:
+  // a die takes a contiguous range of tiles, ordered in groups of up to eight position tiles that share a weight
+  // tile while it is in that L2.
+  const int t_tiles = (a.T + BT - 1) / BT, n_tiles = (a.N + BN - 1) / BN, tiles = t_tiles * n_tiles;
+  const int die = blockIdx.x & 7, seq = blockIdx.x >> 3, per_die = (tiles + 7) >> 3;
+  const int idx = die * per_die + seq;
+  if (seq >= per_die || idx >= tiles) return;
+  const int grp = idx / (8 * n_tiles), rem = idx - grp * 8 * n_tiles, in_grp = min(8, t_tiles - grp * 8);
+  const int tile_n = rem / in_grp, tile_t = grp * 8 + rem - tile_n * in_grp;
+  const int n0 = tile_n * BN, t0 = tile_t * BT;
+
+  // This split's steps.  Dies walk them from different starting points: in step they would all ask the same columns
+  // of the activations, and rows a power of two apart of the weights, from memory at once (3 to 9 % on every shape).
+  const int row_bytes = a.Kd * ES, nk_all = (row_bytes + 127) >> 7, per_split = (nk_all + a.S - 1) / a.S;
+  const int k_lo = blockIdx.y * per_split, nk = min(per_split, nk_all - k_lo);
+  const int rot = (die * nk) >> 3;
+  const int tail = row_bytes & 127;                     // bytes of a partial last step: pieces past them are zero
+
+  const u32x4 rw = buffer_of((const char*)a.W + (long)n0 * row_bytes), ra = buffer_of((const char*)a.A + (long)t0 * row_bytes);
+  // Row r of a weight tile keeps its 16-byte piece c at slot c ^ (r bit 1, r bits 3 - 4), of a position tile at
+  // c ^ (r bits 1 - 3): the sixteen rows a fragment read touches then differ in (row parity, slot).
+  auto w_slot = [](int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); };
+  auto a_slot = [](int r) { return (r >> 1) & 7; };
+  int vw[LW], va[LA];                                   // rows past the matrix re-read its last row
+  bool zw[LW], za[LA];                                  // this lane's piece lies past a partial last step
+#pragma unroll
+  for (int i = 0; i < LW; ++i) {
+    const int r = (i * NW + wave) * 8 + (lane >> 3), c = (lane & 7) ^ w_slot(r);
+    vw[i] = min(r, a.N - 1 - n0) * row_bytes + (c << 4); zw[i] = tail && (c << 4) >= tail;
+  }
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int r = (i * NW + wave) * 8 + (lane >> 3), c = (lane & 7) ^ a_slot(r);
+    va[i] = min(r, a.T - 1 - t0) * row_bytes + (c << 4); za[i] = tail && (c << 4) >= tail;
+  }
+  const uint32_t lw0 = lds0 + wave * 1024, la0 = lds0 + NBW * WB + wave * 1024;
+  auto k_of = [&](int kt) { const int k = kt + rot; return k_lo + (k >= nk ? k - nk : k); };
+  auto load_w = [&](int i, int k, int buf) __attribute__((always_inline)) {
+    dma_piece(lw0 + buf * WB + i * NW * 1024, rw, k == nk_all - 1 && zw[i] ? (int)0x80000000 : vw[i], k * 128);
+  };
+  auto load_a = [&](int i, int k, int buf) __attribute__((always_inline)) {
+    dma_piece(la0 + buf * AB + i * NW * 1024, ra, k == nk_all - 1 && za[i] ? (int)0x80000000 : va[i], k * 128);
+  };
+
+  f32x4 acc[TN][TT];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // Fragment addresses.  Position tiles: lane (m = l mod 16, g = l div 16) reads row m.  Weight tiles in pairs: rows
+  // 8 (m / 4) + m mod 4 (+ 4 in the second), so that the pair leaves eight consecutive outputs 8 g .. 8 g + 7 in a lane.
+  const int m = lane & 15, g = lane >> 4;
+  int fa[2], fw[2][2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    fa[s] = m * 128 + (((4 * s + g) ^ a_slot(m)) << 4);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) { const int r = 8 * (m >> 2) + 4 * b + (m & 3); fw[s][b] = r * 128 + (((4 * s + g) ^ w_slot(r)) << 4); }
+  }
+  const unsigned char* w_wave = gemm_smem + wn * (BN / WN) * 128;
+  const unsigned char* a_wave = gemm_smem + NBW * WB + wt * (BT / WT) * 128;
+
+  // fill the rings; the first step waits only for its own pieces
+#pragma unroll
+  for (int p = 0; p < NBW; ++p) {
+    if (p < nk) {
+      const int k = k_of(p);
+      if (p < NBA) {
+#pragma unroll
+        for (int i = 0; i < LA; ++i) load_a(i, k, p);
+      }
+#pragma unroll
+      for (int i = 0; i < LW; ++i) load_w(i, k, p);
+    }
+  }
+  if (nk >= NBW) wait_loads<(NBA - 1) * LA + (NBW - 1) * LW>(); else wait_loads<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  typename M::frag xw[2][TN], xa[2][TT];
+#pragma unroll
+  for (int j = 0; j < TT; ++j) xa[0][j] = *reinterpret_cast<const typename M::frag*>(a_wave + fa[0] + j * 2048);
+#pragma unroll
+  for (int i = 0; i < TN; ++i) xw[0][i] = *reinterpret_cast<const typename M::frag*>(w_wave + fw[0][i & 1] + (i >> 1) * 4096);
+
+  constexpr int NF = TN + TT, NM = TN * TT, NL = LW + LA;
+  int bw = 0, ba = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    const int nbw = bw + 1 == NBW ? 0 : bw + 1, nba = ba + 1 == NBA ? 0 : ba + 1;
+    const bool more_w = kt + NBW < nk, more_a = kt + NBA < nk;
+    const int kw = k_of(kt + NBW), ka = k_of(kt + NBA);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int cur = s, nxt = s ^ 1;
+      const unsigned char* wp = w_wave + (s ? nbw : bw) * WB;      // where the next half step's fragments are
+      const unsigned char* ap = a_wave + (s ? nba : ba) * AB;
+      if (s == 1) {
+        // this wavefront has read all of step kt; the next step must have landed, for every wavefront.  Loads return
+        // in order: what may still be on its way are the pieces issued after the next step's.
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (kt + NBW <= nk) wait_loads<(NBW > NBA ? LW + (NBA - 2) * (LW + LA) : (NBW - 2) * (LW + LA))>(); else wait_loads<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < NM; ++q) {
+        const int i = q / TT, j = q % TT;
+        acc[i][j] = M::go(xw[cur][i], xa[cur][j], acc[i][j]);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          if (f * NM / NF != q) continue;
+          if (f < TT) xa[nxt][f] = *reinterpret_cast<const typename M::frag*>(ap + fa[nxt] + f * 2048);
+          else { const int i2 = f - TT; xw[nxt][i2] = *reinterpret_cast<const typename M::frag*>(wp + fw[nxt][i2 & 1] + (i2 >> 1) * 4096); }
+        }
+        if (s == 1) {                                              // refill the buffers this step has just freed
+#pragma unroll
+          for (int l = 0; l < NL; ++l) {
+            if (l * NM / NL != q) continue;
+            if (l < LA) { if (more_a) load_a(l, ka, ba); }
+            else if (more_w) load_w(l - LA, kw, bw);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);                         // keep this order: reads and loads between the products
+      }
+    }
+    bw = nbw; ba = nba;
+  }
+
+  // ---- epilogue: lane = position t, outputs n .. n + 7 (N is a multiple of 8)
+#pragma unroll
+  for (int j = 0; j < TT; ++j) {
+    const int t = t0 + wt * (BT / WT) + j * 16 + m;
+    const int nb = n0 + wn * (BN / WN) + 8 * g;
+    if (t >= a.T) continue;
+    f32x4 res[TN];
+    if (EPI == GEPI_RESID) {
+#pragma unroll
+      for (int p = 0; p < TN / 2; ++p) {
+        const int n = nb + 32 * p;
+        if (n < a.N) { const f32x4* r = reinterpret_cast<const f32x4*>(a.out_f32 + (long)t * a.N + n); res[2 * p] = r[0]; res[2 * p + 1] = r[1]; }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < TN / 2; ++p) {
+      const int n = nb + 32 * p;
+      if (n >= a.N) continue;
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { v[e] = acc[2 * p][j][e]; v[4 + e] = acc[2 * p + 1][j][e]; }
+      if (EPI == GEPI_PART) {
+        put8<float>(a.out_f32, ((long)blockIdx.y * a.T + t) * a.N + n, v);
+      } else if (EPI == GEPI_SWIGLU) {                             // rows (2f, 2f + 1) = (gate_f, up_f)
+        put4<ST>(a.out_act, (long)t * (a.N >> 1) + (n >> 1), silu_f(v[0]) * v[1], silu_f(v[2]) * v[3], silu_f(v[4]) * v[5], silu_f(v[6]) * v[7]);
+      } else {
+        if (a.bias) {
+          const f32x4* b = reinterpret_cast<const f32x4*>(a.bias + n);
+          const f32x4 b0 = b[0], b1 = b[1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { v[e] += b0[e]; v[4 + e] += b1[e]; }
+        }
+        const long o = (long)t * a.N + n;
+        if (EPI == GEPI_F32_BIAS) {
+          put8<float>(a.out_f32, o, v);
+        } else if (EPI == GEPI_RESID) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { v[e] += res[2 * p][e]; v[4 + e] += res[2 * p + 1][e]; }
+          put8<float>(a.out_f32, o, v);
+          if (a.out_act) {
+            if (a.act_aligned) put8<ST>(a.out_act, o, v);
+            else
+              for (int e = 0; e < 8; ++e) Storage<ST>::put((ST*)a.out_act + o + e, v[e]);
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = a.gelu_tanh ? gelu_tanh_f(v[e]) : gelu_erf_f(v[e]);
+          put8<ST>(a.out_act, o, v);
+        }
+      }
+    }
+  }
+}
+
+// The tile shapes in use (index, BN, BT, wavefronts WN x WT, ring depths; LDS: 128 (NBW BN + NBA BT) bytes) and what
+// plan_gemm goes by, fitted to 7500 measured (T, N, Kd, shape, splits) over the shapes of all the models here, T from
+// 16 to 6000: a round of workgroups takes steps * us + fixed, a last round that is a fraction f full (less power, less
+// traffic) part + (1 - part) f of that, and no product is faster than its weights arrive (tbps).  Picking by these takes
+// 2 % more time than picking the best measured one each time.
+#define MDI_GEMM_SHAPES(X) \
+  X(0, 256, 256, 2, 4, 3, 2) X(1, 192, 256, 2, 4, 3, 2) X(2, 256, 128, 2, 4, 3, 3) X(3, 192, 128, 2, 4, 4, 4) \
+  X(4, 128, 128, 2, 4, 4, 4) X(5, 128, 64, 4, 2, 4, 4) X(6, 64, 64, 2, 2, 4, 4) X(7, 64, 32, 2, 2, 6, 6)
+struct Shape { int BN, BT, resident; float us, fixed, part, tbps; };
+constexpr int kShapes = 8;
+constexpr Shape kShapeBf16[kShapes] = {
+    {256, 256, 1, 1.485f, 14.0f, 0.71f, 4.9f}, {192, 256, 1, 1.228f, 10.6f, 0.71f, 4.9f}, {256, 128, 1, 0.939f, 8.1f, 0.71f, 4.9f},
+    {192, 128, 1, 0.784f, 6.3f, 0.71f, 4.9f},  {128, 128, 1, 0.600f, 4.4f, 0.73f, 4.9f},  {128, 64, 1, 0.441f, 2.35f, 0.79f, 4.9f},
+    {64, 64, 2, 0.538f, 1.82f, 0.60f, 3.9f},   {64, 32, 3, 0.510f, 1.47f, 0.40f, 4.2f}};
+
+template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
+void launch_shape(hipStream_t s, const GemmArgs& a) {
+  constexpr size_t lds = (size_t)128 * (NBW * BN + NBA * BT);
+  static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+  if (lds > 64 * 1024) {                                           // more than a kernel gets by default
+    static const hipError_t raised = hipFuncSetAttribute((const void*)k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)raised;
+  }
+  const int tiles = ((a.T + BT - 1) / BT) * ((a.N + BN - 1) / BN);
+  hipLaunchKernelGGL((k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>), dim3(8 * ((tiles + 7) / 8), a.S), dim3(WN * WT * 64), lds, s, a);
+}
+
+template <typename ST, int EPI>
+void launch_epi(hipStream_t s, int shape, const GemmArgs& a) {
+  switch (shape) {
+#define X(I, BN, BT, WN, WT, NBW, NBA) case I: launch_shape<ST, EPI, BN, BT, WN, WT, NBW, NBA>(s, a); break;
+    MDI_GEMM_SHAPES(X)
+#undef X
+  }
+}
+
+template <typename ST>
+void launch_storage(hipStream_t s, int epi, int shape, const GemmArgs& a) {
+  switch (epi) {
+    case GEPI_F32_BIAS: launch_epi<ST, GEPI_F32_BIAS>(s, shape, a); break;
+    case GEPI_RESID: launch_epi<ST, GEPI_RESID>(s, shape, a); break;
+    case GEPI_PART: launch_epi<ST, GEPI_PART>(s, shape, a); break;
+    case GEPI_SWIGLU: launch_epi<ST, GEPI_SWIGLU>(s, shape, a); break;
+    default: launch_epi<ST, GEPI_GELU>(s, shape, a); break;
+  }
+}
+
+int compute_units() {
+  static const int n_cu = []() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    return n;
+  }();
+  return n_cu;
+}
+
+}  // namespace
+
+GemmPlan plan_gemm(int T, int N, int Kd, size_t part_floats) {
+  const double n_cu = compute_units();
+  const int nk = (2 * Kd + 127) >> 7;
+  GemmPlan best{0, 1};
+  double best_us = 1e30;
+  for (int i = 0; i < kShapes; ++i) {
+    const Shape& sh = kShapeBf16[i];
+    if (sh.BT == 32 && T > 32) continue;                   // a second position tile would read the weights again
+    const double tiles = (double)((T + sh.BT - 1) / sh.BT) * ((N + sh.BN - 1) / sh.BN);
+    for (int S = 1; S <= kMaxKSplits && S <= nk; ++S) {
+      const int per = (nk + S - 1) / S;
+      if ((nk + per - 1) / per != S) continue;             // no split without a step
+      if (S > 1 && (size_t)S * T * N > part_floats) break;
+      const double u = tiles * S / (n_cu * sh.resident), full = (double)(long)u, f = u - full;
+      double us = (full + (f > 0 ? sh.part + (1 - sh.part) * f : 0)) * (per * sh.us + sh.fixed);
+      us = std::max(us, 2.0 * N * Kd / (sh.tbps * 1e6));
+      if (S > 1) us += (double)S * T * N * 4.0 / 4.5e6;    // the partial results are read again (4.5 TB/s)
+      if (us < best_us) { best_us = us; best = GemmPlan{i, S}; }
+    }
+  }
+  return best;
+}
+
+void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a) { launch_storage<bf16_t>(s, epi, shape, a); }
+
+}  // namespace mdi

@@ -62,6 +62,8 @@ struct mdi_partition {
   // prefill scratch
   float *p_xres = nullptr, *p_qkv = nullptr, *p_q = nullptr;
   void *p_xn = nullptr, *p_o = nullptr, *p_u = nullptr;
+  float* p_part = nullptr;       // partial results of products whose inner dimension is split
+  size_t part_cap = 0;           // ... in floats
   bf16_t *p_qb = nullptr, *p_kc = nullptr, *p_vt = nullptr;   // operands of the matrix-core attention of a first visit
   int Tp = 0;                                                 // longest first visit rounded up to whole query blocks
   // host bookkeeping
@@ -238,6 +240,11 @@ size_t carve(mdi_partition* p, void* arena) {
     p->p_q = (float*)cv.take(T * H * h * 4);
     p->p_o = cv.take(T * H * h * B);
     p->p_u = cv.take(T * F * B);
+    if (c.dtype == MDI_BF16) {
+      // few positions are cut into up to kMaxKSplits pieces, more positions into fewer: 4096 rows of partial results
+      p->part_cap = std::min<size_t>(T * kMaxKSplits, 4096) * d;
+      p->p_part = (float*)cv.take(p->part_cap * 4);
+    }
     if (flash_supported(c.dtype, (int)h)) {
       // keys and values^T of every position a first visit in pieces can reach: up to max_ctx, in blocks of 128
       p->Tp = (int)(((size_t)c.max_ctx + 127) / 128 * 128);
@@ -628,11 +635,28 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
   const bool embed = p->flags & MDI_HAS_EMBED, swiglu = c.mlp_kind == MDI_MLP_SWIGLU;
   RowsInArgs ri{acts_in, embed ? IN_TOKEN : ak, p->wte, p->wpe, (int)c.dtype, (int)T, d, p->p_xres, (int)c.vocab, p->err, pos0};
   launch_rows_input(s, ri);
+  // Residual products with few positions split their inner dimension; the norm that follows adds the partial results.
+  int pend_S = 1;
+  const float* pend_bias = nullptr;
+  auto norm = [&](const float* g, const float* b, void* out, void* hand_off) {
+    NormRowsArgs n{p->p_xres, (int)T, d, (int)c.norm_kind, g, b, c.norm_eps, out, ak, pend_S, p->p_part, (long)T * d, pend_bias, hand_off};
+    launch_norm_rows(s, n);
+    pend_S = 1;
+  };
+  const int aligned = ((uintptr_t)acts_out & 15) == 0;
+  auto resid = [&](const void* A, const void* W, const float* bias, int Kd, void* hand_off) {
+    GemmArgs ga{A, W, bias, (int)T, d, Kd, p->p_xres, hand_off, 0, aligned, 1};
+    if (c.dtype != MDI_BF16) { launch_gemm(s, c.dtype, GEPI_RESID, ga); return; }
+    const GemmPlan pl = plan_gemm((int)T, d, Kd, p->part_cap);
+    ga.S = pl.S;
+    if (pl.S > 1) { ga.out_f32 = p->p_part; ga.out_act = nullptr; pend_S = pl.S; pend_bias = bias; }
+    launch_gemm_bf16(s, pl.S > 1 ? GEPI_PART : GEPI_RESID, pl.shape, ga);
+    if (pl.S > 1 && hand_off) norm(nullptr, nullptr, nullptr, hand_off);
+  };
   for (int i = 0; i < p->n_local; ++i) {
     const LayerPacked& L = p->layers[i];
-    NormRowsArgs n1{p->p_xres, (int)T, d, (int)c.norm_kind, L.ln1_g, L.ln1_b, c.norm_eps, p->p_xn, ak};
-    launch_norm_rows(s, n1);
-    GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, p->p_qkv, nullptr};
+    norm(L.ln1_g, L.ln1_b, p->p_xn, nullptr);
+    GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, p->p_qkv, nullptr, 0, 0, 1};
     launch_gemm(s, c.dtype, GEPI_F32_BIAS, g1);
     // Attention on the matrix cores over operand arrays that hold the keys and the transposed values of positions
     // 0 .. pos0 + T - 1: the new ones written by the scatter and the transpose below, the earlier ones (a later piece
@@ -657,14 +681,11 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
       at.part = p->part; at.counters = p->counters; at.out = p->p_o; at.out_stride = (long)H * h; at.out_kind = ak;
       launch_attn(s, c.dtype, at);
     }
-    GemmArgs g2{p->p_o, L.wo, L.bo, (int)T, d, H * h, p->p_xres, nullptr};
-    launch_gemm(s, c.dtype, GEPI_RESID, g2);
-    NormRowsArgs n2{p->p_xres, (int)T, d, (int)c.norm_kind, L.ln2_g, L.ln2_b, c.norm_eps, p->p_xn, ak};
-    launch_norm_rows(s, n2);
-    GemmArgs g3{p->p_xn, L.wup, L.bup, (int)T, swiglu ? 2 * F : F, d, nullptr, p->p_u};
-    launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : (c.mlp_kind == MDI_MLP_GELU_TANH ? GEPI_GELU_TANH : GEPI_GELU_ERF), g3);
-    GemmArgs g4{p->p_u, L.wdown, L.bdown, (int)T, d, F, p->p_xres, i == p->n_local - 1 ? acts_out : nullptr};
-    launch_gemm(s, c.dtype, GEPI_RESID, g4);
+    resid(p->p_o, L.wo, L.bo, H * h, nullptr);
+    norm(L.ln2_g, L.ln2_b, p->p_xn, nullptr);
+    GemmArgs g3{p->p_xn, L.wup, L.bup, (int)T, swiglu ? 2 * F : F, d, nullptr, p->p_u, c.mlp_kind == MDI_MLP_GELU_TANH, 1, 1};
+    launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : GEPI_GELU, g3);
+    resid(p->p_u, L.wdown, L.bdown, F, i == p->n_local - 1 ? acts_out : nullptr);
   }
   p->seq_len[seq] = (uint32_t)pos0 + T;
   return hip_status();

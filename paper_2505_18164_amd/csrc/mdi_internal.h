@@ -111,22 +111,36 @@ struct RowsInArgs {
 };
 void launch_rows_input(hipStream_t s, const RowsInArgs& a);
 
+// Residual rows x [T, d]: adds what the product before left as partial results (S > 1: part[0 .. S - 1], each [T, d]
+// part_stride floats apart, and the product's bias), keeps the sum in x, then normalises it into `out` (nullptr: no
+// norm follows) and / or copies it to act_out.
 struct NormRowsArgs {
-  const float* x; int T, d; int norm_kind; const float* g; const float* b; float eps;
+  float* x; int T, d; int norm_kind; const float* g; const float* b; float eps;
   void* out; int out_kind;
+  int S; const float* part; long part_stride; const float* part_bias;
+  void* act_out;                     // hand-off copy in the storage type (same kind as out) or nullptr
 };
 void launch_norm_rows(hipStream_t s, const NormRowsArgs& a);
 
-enum GemmEpi { GEPI_F32_BIAS = 0, GEPI_RESID = 1, GEPI_SWIGLU = 2, GEPI_GELU_TANH = 3, GEPI_GELU_ERF = 4 };
+enum GemmEpi { GEPI_F32_BIAS = 0, GEPI_RESID = 1, GEPI_SWIGLU = 2, GEPI_GELU = 3, GEPI_PART = 4 };
 struct GemmArgs {
   const void* A;     // [T, Kd] storage dtype
   const void* W;     // [N, Kd] storage dtype
   const float* bias; // [N] or nullptr
-  int T, N, Kd;
-  float* out_f32;    // GEPI_F32_BIAS: [T, N]; GEPI_RESID: residual stream [T, N], updated in place
+  int T, N, Kd;      // N and Kd multiples of 8
+  float* out_f32;    // GEPI_F32_BIAS: [T, N]; GEPI_RESID: residual stream [T, N], updated in place; GEPI_PART: [S][T, N]
   void* out_act;     // SWIGLU: [T, N/2]; GELU: [T, N]; RESID: optional hand-off copy [T, N]; storage dtype
+  int gelu_tanh;     // GELU: the tanh form, else the erf form
+  int act_aligned;   // out_act may be written 16 bytes at a time
+  int S;             // splits of the inner dimension (1 unless GEPI_PART): split s leaves its sums at out_f32 + s T N
 };
-void launch_gemm(hipStream_t s, int dtype, int epi, const GemmArgs& a);
+void launch_gemm(hipStream_t s, int dtype, int epi, GemmArgs a);       // S = 1
+// bf16 products (gemm_prefill.hip): the tile shape for a product, and into how many pieces its inner dimension is cut
+// so that few positions still fill the chip; part_floats = room for partial results, 0 forbids a split.
+constexpr int kMaxKSplits = 16;
+struct GemmPlan { int shape, S; };
+GemmPlan plan_gemm(int T, int N, int Kd, size_t part_floats);
+void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a);
 
 struct RopeScatterArgs {
   const float* qkv;  // [T, (H+2K)h] fp32

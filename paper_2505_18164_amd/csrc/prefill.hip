@@ -1,12 +1,9 @@
 // First-visit kernels: all T prompt positions of a sample go through the local
 // layers at once and fill the sample's KV cache (Alg. 1 round 0, Alg. 2 "first
 // iteration for current sample").  With T rows the linear layers are dense
-// contractions, so in bf16 mode they run on the matrix cores
-// (v_mfma_f32_32x32x16_bf16, LDS-tiled); fp32 mode keeps exact fp32 products on
-// the vector ALUs.
+// contractions, so in bf16 mode they run on the matrix cores (gemm_prefill.hip);
+// fp32 mode keeps exact fp32 products on the vector ALUs.
 #include <algorithm>
-
-#include <mutex>
 
 #include "device_utils.h"
 
@@ -37,33 +34,69 @@ void launch_rows_input(hipStream_t s, const RowsInArgs& a) {
 }
 
 // ---------------------------------------------------------------------------
-// One workgroup per row; d is a multiple of 8, so rows are read as float4 and written four values at a time.
+// One workgroup per row, the row in registers (NV pieces of four values per thread; NV = 0: rows beyond 8192 values
+// are read again for every pass).  Bound by memory: the row is read once - with S partial results of the product
+// before, S times more - and written once or twice.  Adding the partial results here costs no launch and no pass of
+// its own.
+template <int NV>
 __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
   __shared__ float red[8];
   const int t = blockIdx.x, d4 = a.d >> 2;
-  const float4* x = reinterpret_cast<const float4*>(a.x + (long)t * a.d);
+  float4* x = reinterpret_cast<float4*>(a.x + (long)t * a.d);
   const float4* g4 = reinterpret_cast<const float4*>(a.g);
   const float4* b4 = reinterpret_cast<const float4*>(a.b);
-  float mean = 0.f, rstd;
+  constexpr int NR = NV ? NV : 1;
+  float4 v[NR];
+  auto fetch = [&](int i) {                          // the row's piece i with the partial results added, split by split
+    float4 r = x[i];
+    if (a.S > 1) {
+      if (a.part_bias) { const float4 p = reinterpret_cast<const float4*>(a.part_bias)[i]; r.x += p.x; r.y += p.y; r.z += p.z; r.w += p.w; }
+      const float4* p4 = reinterpret_cast<const float4*>(a.part + (long)t * a.d) + i;
+#pragma unroll 4
+      for (int s = 0; s < a.S; ++s) {
+        const float4 p = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p4) + s * a.part_stride);
+        r.x += p.x; r.y += p.y; r.z += p.z; r.w += p.w;
+      }
+      x[i] = r;
+    }
+    if (a.act_out) {
+      const long at = (long)t * a.d + 4 * i;
+      store_kind(a.act_out, a.out_kind, at, r.x); store_kind(a.act_out, a.out_kind, at + 1, r.y);
+      store_kind(a.act_out, a.out_kind, at + 2, r.z); store_kind(a.act_out, a.out_kind, at + 3, r.w);
+    }
+    return r;
+  };
+  auto each = [&](auto&& f) {                        // f(piece, its values)
+    if (NV) {
+#pragma unroll
+      for (int j = 0; j < NR; ++j) { const int i = threadIdx.x + j * kBlock; if (i < d4) f(i, v[j]); }
+    } else {
+      for (int i = threadIdx.x; i < d4; i += kBlock) f(i, x[i]);
+    }
+  };
+  if (NV) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j) { const int i = threadIdx.x + j * kBlock; if (i < d4) v[j] = fetch(i); }
+  } else {
+    for (int i = threadIdx.x; i < d4; i += kBlock) (void)fetch(i);
+  }
+  if (!a.out) return;
+  float mean = 0.f, s2 = 0.f;
   if (a.norm_kind == MDI_NORM_LAYERNORM) {
     float s = 0.f;
-    for (int i = threadIdx.x; i < d4; i += kBlock) { const float4 v = x[i]; s += (v.x + v.y) + (v.z + v.w); }
+    each([&](int, const float4& r) { s += (r.x + r.y) + (r.z + r.w); });
     mean = block_sum(s, red) / (float)a.d;
-    float s2 = 0.f;
-    for (int i = threadIdx.x; i < d4; i += kBlock) {
-      const float4 v = x[i];
-      const float c0 = v.x - mean, c1 = v.y - mean, c2 = v.z - mean, c3 = v.w - mean;
+    each([&](int, const float4& r) {
+      const float c0 = r.x - mean, c1 = r.y - mean, c2 = r.z - mean, c3 = r.w - mean;
       s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
-    }
-    rstd = 1.f / sqrtf(block_sum(s2, red) / (float)a.d + a.eps);
+    });
   } else {
-    float s2 = 0.f;
-    for (int i = threadIdx.x; i < d4; i += kBlock) { const float4 v = x[i]; s2 += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w); }
-    rstd = 1.f / sqrtf(block_sum(s2, red) / (float)a.d + a.eps);
+    each([&](int, const float4& r) { s2 += (r.x * r.x + r.y * r.y) + (r.z * r.z + r.w * r.w); });
   }
-  for (int i = threadIdx.x; i < d4; i += kBlock) {
-    const float4 v = x[i], g = g4[i];
-    float4 o = {(v.x - mean) * rstd * g.x, (v.y - mean) * rstd * g.y, (v.z - mean) * rstd * g.z, (v.w - mean) * rstd * g.w};
+  const float rstd = 1.f / sqrtf(block_sum(s2, red) / (float)a.d + a.eps);
+  each([&](int i, const float4& r) {
+    const float4 g = g4[i];
+    float4 o = {(r.x - mean) * rstd * g.x, (r.y - mean) * rstd * g.y, (r.z - mean) * rstd * g.z, (r.w - mean) * rstd * g.w};
     if (a.b) { const float4 b = b4[i]; o.x += b.x; o.y += b.y; o.z += b.z; o.w += b.w; }
     const long at = (long)t * a.d + 4 * i;
     if (a.out_kind == IN_BF16) {
@@ -74,14 +107,19 @@ __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
     } else {
       *reinterpret_cast<float4*>((float*)a.out + at) = o;
     }
-  }
+  });
 }
 void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
-  hipLaunchKernelGGL(k_norm_rows, dim3(a.T), dim3(kBlock), 0, s, a);
+  const int n = (a.d / 4 + kBlock - 1) / kBlock;
+  if (n <= 1) hipLaunchKernelGGL(k_norm_rows<1>, dim3(a.T), dim3(kBlock), 0, s, a);
+  else if (n <= 2) hipLaunchKernelGGL(k_norm_rows<2>, dim3(a.T), dim3(kBlock), 0, s, a);
+  else if (n <= 4) hipLaunchKernelGGL(k_norm_rows<4>, dim3(a.T), dim3(kBlock), 0, s, a);
+  else if (n <= 8) hipLaunchKernelGGL(k_norm_rows<8>, dim3(a.T), dim3(kBlock), 0, s, a);
+  else hipLaunchKernelGGL(k_norm_rows<0>, dim3(a.T), dim3(kBlock), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------
-// Epilogue shared by both GEMM kernels.  (t, n) is the output coordinate, v the
+// Epilogue of the fp32 GEMM kernel.  (t, n) is the output coordinate, v the
 // accumulated dot product, partner the value of column n^1 (SwiGLU pairs).
 template <int EPI>
 __device__ __forceinline__ void gemm_store(const GemmArgs& a, int out_kind, int t, int n, float v, float partner) {
@@ -99,203 +137,9 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& a, int out_kind, int 
     v += a.out_f32[o];
     a.out_f32[o] = v;
     if (a.out_act) store_kind(a.out_act, out_kind, o, v);
-  } else if (EPI == GEPI_GELU_TANH) {
-    store_kind(a.out_act, out_kind, o, gelu_tanh_f(v));
   } else {
-    store_kind(a.out_act, out_kind, o, gelu_erf_f(v));
+    store_kind(a.out_act, out_kind, o, a.gelu_tanh ? gelu_tanh_f(v) : gelu_erf_f(v));
   }
-}
-
-// ---------------------------------------------------------------------------
-// bf16 GEMM on MFMA: C[T, N] = A[T, Kd] * W[N, Kd]^T, fp32 accumulate.
-// Workgroup tile BM (tokens) x BN (weight rows), K step 64; four wavefronts in a
-// 2 x 2 arrangement, each owning (BM/2) x (BN/2) as MFMA tiles of 32 x 32.
-// Both operands are K-contiguous, so a lane's MFMA fragment (8 consecutive k of
-// one row) is one 16-byte LDS read; LDS rows are padded by 16 bytes, which makes
-// the 16 lanes served together hit 16 different bank groups.  LDS is double
-// buffered and fed from two register stages, so a K step costs one workgroup barrier and a
-// global load has two K steps to arrive.
-constexpr int BK = 64, LDS_STRIDE = BK + 8;
-
-// NW wavefronts in a WM x (NW / WM) arrangement.  Shapes in use: 4 wavefronts (2 x 2) on tiles of 128 x 128 or
-// 128 x 64, two workgroups per compute unit; 8 wavefronts on 256 x 192 (4 x 2) or 128 x 128 (2 x 4), one workgroup
-// per compute unit.  What a compute unit can pull out of L2 per unit of time is the bound on this machine (about 65 GB/s each,
-// measured): a 128 x 128 tile needs 256 bytes of operands per 128 x 128 x 1 products, a 256 x 192 tile 0.58 of that.
-template <int EPI, int BM, int BN, int NW, int WM>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_gemm_bf16(GemmArgs a) {
-  constexpr int kThreads = NW * 64, WN = NW / WM;
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;  // MFMA tiles per wavefront
-  constexpr int PA = BM * 8 / kThreads, PB = BN * 8 / kThreads;   // 16-byte pieces per thread per K step
-  constexpr int PROWS = kThreads / 8;                  // tile rows covered by one piece per thread
-  static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && (BM * 8) % kThreads == 0 && (BN * 8) % kThreads == 0, "tile shape");
-  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_smem[];
-  bf16_t* As = (bf16_t*)gemm_smem;                     // [2][BM][LDS_STRIDE]
-  bf16_t* Bs = As + 2 * BM * LDS_STRIDE;               // [2][BN][LDS_STRIDE]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
-  // Workgroup -> tile.  Workgroups are handed to the eight compute dies in turn (die = id % 8) and each die has an
-  // L2 of its own, so die c takes the tile columns c, c + 8, ... and walks down a column (all row tiles of the same
-  // weight rows) before moving on: the weight tile is fetched from memory once, by one die, while the workgroups
-  // that share it are running; the activation tiles are the ones every column of a die re-uses.
-  const int m_tiles = (a.T + BM - 1) / BM, n_tiles = (a.N + BN - 1) / BN;
-  const int die = blockIdx.x & 7, seq = blockIdx.x >> 3;
-  const int tile_m = seq % m_tiles, tile_n = die + 8 * (seq / m_tiles);
-  if (tile_n >= n_tiles) return;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const bf16_t* A = (const bf16_t*)a.A;
-  const bf16_t* W = (const bf16_t*)a.W;
-  const int Kd = a.Kd;
-
-  // piece p of a tile covers row p / 8, k-offset (p % 8) * 8; rows past the matrix re-read its last row
-  const int prow = tid >> 3, pk = (tid & 7) * 8;
-  const bf16_t* ga[PA];
-  const bf16_t* gb[PB];
-#pragma unroll
-  for (int i = 0; i < PA; ++i) ga[i] = A + (long)min(m0 + prow + i * PROWS, a.T - 1) * Kd + pk;
-#pragma unroll
-  for (int i = 0; i < PB; ++i) gb[i] = W + (long)min(n0 + prow + i * PROWS, a.N - 1) * Kd + pk;
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const u32x4 z4 = {0u, 0u, 0u, 0u};
-  // Two register stages: while step k is multiplied out of LDS, the operands of step k + 1 wait in one stage to be
-  // written to the other LDS buffer and those of step k + 2 are still on their way into the second stage, so a
-  // global load has two K steps of arithmetic to arrive (one is not enough, a third stage costs more registers
-  // than it gains).
-  u32x4 ra0[PA], rb0[PB], ra1[PA], rb1[PB];
-  const int nk = (Kd + BK - 1) / BK;
-  auto fetch_full = [&](u32x4 (&ra)[PA], u32x4 (&rb)[PB], int step) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < PA; ++i) ra[i] = *reinterpret_cast<const u32x4*>(ga[i] + step * BK);
-#pragma unroll
-    for (int i = 0; i < PB; ++i) rb[i] = *reinterpret_cast<const u32x4*>(gb[i] + step * BK);
-  };
-  auto fetch_guarded = [&](u32x4 (&ra)[PA], u32x4 (&rb)[PB], int step) __attribute__((always_inline)) {
-    const bool ok = step * BK + pk < Kd;              // steps past the matrix, and its last columns when Kd % 64 != 0, are zero
-#pragma unroll
-    for (int i = 0; i < PA; ++i) ra[i] = ok ? *reinterpret_cast<const u32x4*>(ga[i] + step * BK) : z4;
-#pragma unroll
-    for (int i = 0; i < PB; ++i) rb[i] = ok ? *reinterpret_cast<const u32x4*>(gb[i] + step * BK) : z4;
-  };
-  auto stash = [&](const u32x4 (&ra)[PA], const u32x4 (&rb)[PB], int buf) __attribute__((always_inline)) {
-    bf16_t* An = As + buf * BM * LDS_STRIDE;
-    bf16_t* Bn = Bs + buf * BN * LDS_STRIDE;
-#pragma unroll
-    for (int i = 0; i < PA; ++i) *reinterpret_cast<u32x4*>(An + (prow + i * PROWS) * LDS_STRIDE + pk) = ra[i];
-#pragma unroll
-    for (int i = 0; i < PB; ++i) *reinterpret_cast<u32x4*>(Bn + (prow + i * PROWS) * LDS_STRIDE + pk) = rb[i];
-  };
-  auto multiply = [&](int buf) __attribute__((always_inline)) {
-    const bf16_t* Ac = As + buf * BM * LDS_STRIDE;
-    const bf16_t* Bc = Bs + buf * BN * LDS_STRIDE;
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 16) {
-      const int kk = ks + (lane >> 5) * 8;
-      bf16x8 fa[TM], fb[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(Ac + (wm + i * 32 + (lane & 31)) * LDS_STRIDE + kk);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(Bc + (wn + j * 32 + (lane & 31)) * LDS_STRIDE + kk);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-  };
-
-  // One K step: multiply the step in LDS buffer `buf`; write the step waiting in a register stage into the other
-  // buffer and refill that stage with step `fstep`; one barrier.  (Letting the two halves of an 8-wavefront
-  // workgroup take the two parts in opposite order, one multiplying while the other moves data, was measured: no
-  // faster.)
-  auto kstep = [&](int buf, u32x4 (&ra)[PA], u32x4 (&rb)[PB], bool move, int fstep, bool full) __attribute__((always_inline)) {
-    multiply(buf);
-    if (move) {
-      stash(ra, rb, buf ^ 1);
-      if (full) fetch_full(ra, rb, fstep); else fetch_guarded(ra, rb, fstep);
-    }
-    __syncthreads();
-  };
-
-  // invariant at an even step k: LDS buffer 0 holds step k, stage 0 step k + 1, stage 1 step k + 2
-  int k = 0;
-  if (5 * BK <= Kd) {
-    // The usual case has its own, branch-free lead-in, so that the loop below is entered with its loads outstanding
-    // in the order the loop itself issues them (the compiler then waits for one stage while the other is in flight).
-    fetch_full(ra0, rb0, 0);
-    stash(ra0, rb0, 0);
-    fetch_full(ra0, rb0, 1);
-    __builtin_amdgcn_sched_barrier(0);              // the two stages' loads must not be interleaved
-    fetch_full(ra1, rb1, 2);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    for (; (k + 5) * BK <= Kd; k += 2) {            // every fetch below is of a whole step inside the matrix
-      kstep(0, ra0, rb0, true, k + 3, true);
-      kstep(1, ra1, rb1, true, k + 4, true);
-    }
-  } else {
-    fetch_guarded(ra0, rb0, 0);
-    stash(ra0, rb0, 0);
-    fetch_guarded(ra0, rb0, 1);
-    fetch_guarded(ra1, rb1, 2);
-    __syncthreads();
-  }
-  for (; k < nk; k += 2) {
-    kstep(0, ra0, rb0, k + 1 < nk, k + 3, false);
-    if (k + 1 < nk) kstep(1, ra1, rb1, k + 2 < nk, k + 4, false);
-  }
-
-  // accumulator layout of the 32x32 MFMA: register r of lane l holds
-  // C[row = 8*(r/4) + 4*(l/32) + r%4][col = l%32].  Per MFMA tile a lane owns one column n and 16 rows:
-  // everything it needs from memory (bias, residual) is fetched before the first store, so the loads
-  // are in flight together instead of one round trip per element.
-  float* __restrict__ out_f32 = a.out_f32;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int n = n0 + wn + j * 32 + (lane & 31);
-      const int tb = m0 + wm + i * 32 + 4 * (lane >> 5);
-      const bool n_ok = n < a.N;
-      const float bias = (EPI != GEPI_SWIGLU && a.bias && n_ok) ? a.bias[n] : 0.f;
-      float res[16];
-      if (EPI == GEPI_RESID) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int t = tb + 8 * (r >> 2) + (r & 3);
-          res[r] = (n_ok && t < a.T) ? out_f32[(long)t * a.N + n] : 0.f;
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int t = tb + 8 * (r >> 2) + (r & 3);
-        float v = acc[i][j][r];
-        if (EPI == GEPI_SWIGLU) {
-          const float partner = __shfl_xor(v, 1, 64);          // column n^1: rows (2f, 2f+1) = (gate_f, up_f)
-          if (n_ok && t < a.T && !(n & 1)) store_kind(a.out_act, IN_BF16, (long)t * (a.N >> 1) + (n >> 1), silu_f(v) * partner);
-        } else if (n_ok && t < a.T) {
-          const long o = (long)t * a.N + n;
-          v += bias;
-          if (EPI == GEPI_F32_BIAS) {
-            out_f32[o] = v;
-          } else if (EPI == GEPI_RESID) {
-            v += res[r];
-            out_f32[o] = v;
-            if (a.out_act) store_kind(a.out_act, IN_BF16, o, v);
-          } else if (EPI == GEPI_GELU_TANH) {
-            store_kind(a.out_act, IN_BF16, o, gelu_tanh_f(v));
-          } else {
-            store_kind(a.out_act, IN_BF16, o, gelu_erf_f(v));
-          }
-        }
-      }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -345,66 +189,15 @@ __global__ __launch_bounds__(kBlock) void k_gemm_f32(GemmArgs a) {
       gemm_store<EPI>(a, IN_F32, m0 + ty * 4 + i, n0 + tx * 4 + j, acc[i][j], acc[i][j ^ 1]);
 }
 
-template <int BM, int BN, int NW, int WM>
-static void launch_gemm_bf16(hipStream_t s, int epi, const GemmArgs& a) {
-  const int m_tiles = (a.T + BM - 1) / BM, n_tiles = (a.N + BN - 1) / BN;
-  const dim3 grid(8 * m_tiles * ((n_tiles + 7) / 8)), block(NW * 64);   // see the tile mapping in the kernel
-  const size_t lds = (size_t)2 * (BM + BN) * LDS_STRIDE * sizeof(bf16_t);
-  if (lds > 64 * 1024) {                             // 256 x 192 tiles need more LDS than a kernel gets by default
-    static std::once_flag raised;
-    std::call_once(raised, [&]() {
-      (void)hipFuncSetAttribute((const void*)k_gemm_bf16<GEPI_F32_BIAS, BM, BN, NW, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipFuncSetAttribute((const void*)k_gemm_bf16<GEPI_RESID, BM, BN, NW, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipFuncSetAttribute((const void*)k_gemm_bf16<GEPI_SWIGLU, BM, BN, NW, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipFuncSetAttribute((const void*)k_gemm_bf16<GEPI_GELU_TANH, BM, BN, NW, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      (void)hipFuncSetAttribute((const void*)k_gemm_bf16<GEPI_GELU_ERF, BM, BN, NW, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
-  }
-  switch (epi) {
-    case GEPI_F32_BIAS: hipLaunchKernelGGL((k_gemm_bf16<GEPI_F32_BIAS, BM, BN, NW, WM>), grid, block, lds, s, a); break;
-    case GEPI_RESID: hipLaunchKernelGGL((k_gemm_bf16<GEPI_RESID, BM, BN, NW, WM>), grid, block, lds, s, a); break;
-    case GEPI_SWIGLU: hipLaunchKernelGGL((k_gemm_bf16<GEPI_SWIGLU, BM, BN, NW, WM>), grid, block, lds, s, a); break;
-    case GEPI_GELU_TANH: hipLaunchKernelGGL((k_gemm_bf16<GEPI_GELU_TANH, BM, BN, NW, WM>), grid, block, lds, s, a); break;
-    default: hipLaunchKernelGGL((k_gemm_bf16<GEPI_GELU_ERF, BM, BN, NW, WM>), grid, block, lds, s, a); break;
-  }
-}
-
-void launch_gemm(hipStream_t s, int dtype, int epi, const GemmArgs& a) {
-  if (dtype == MDI_BF16) {
-    // 256 x 192 tiles (one 8-wavefront workgroup per compute unit) when the grid they give keeps at least 70 % of
-    // the compute units busy over its rounds
-    static const long n_cu = []() {
-      int dev = 0, n = 0;
-      if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-      return (long)n;
-    }();
-    const long big = (long)((a.N + 191) / 192) * ((a.T + 255) / 256);
-    const long rounds = (big + n_cu - 1) / n_cu;
-    if (a.T >= 256 && big * 10 >= rounds * n_cu * 7) { launch_gemm_bf16<256, 192, 8, 4>(s, epi, a); return; }
-    // 256 x 128 tiles when they give one round that keeps at least 70 % of the compute units busy (2048 rows x 4096
-    // outputs: exactly one tile each): a quarter less operand traffic per product than 128 x 128 tiles
-    const long mid = (long)((a.N + 127) / 128) * ((a.T + 255) / 256);
-    if (a.T >= 256 && mid <= n_cu && mid * 10 >= n_cu * 7) { launch_gemm_bf16<256, 128, 8, 4>(s, epi, a); return; }
-    // a grid of 128 x 128 tiles that cannot give every compute unit two 4-wavefront workgroups: one 8-wavefront
-    // workgroup each (a third less operand traffic than two 128 x 64 tiles), or narrower tiles when even that
-    // leaves compute units idle
-    const long tiles = (long)((a.N + 127) / 128) * ((a.T + 127) / 128);
-    // (few rows and a narrow product: even 128 x 64 tiles leave compute units without a workgroup; 64 x 64 tiles give
-    // twice as many)
-    const long narrow = (long)((a.N + 63) / 64) * ((a.T + 127) / 128);
-    if (tiles <= n_cu && 2 * tiles > n_cu) launch_gemm_bf16<128, 128, 8, 2>(s, epi, a);
-    else if (2 * tiles <= n_cu && narrow < n_cu) launch_gemm_bf16<64, 64, 4, 2>(s, epi, a);
-    else if (2 * tiles <= n_cu) launch_gemm_bf16<128, 64, 4, 2>(s, epi, a);
-    else launch_gemm_bf16<128, 128, 4, 2>(s, epi, a);
-    return;
-  }
+void launch_gemm(hipStream_t s, int dtype, int epi, GemmArgs a) {
+  a.S = 1;
+  if (dtype == MDI_BF16) { launch_gemm_bf16(s, epi, plan_gemm(a.T, a.N, a.Kd, 0).shape, a); return; }
   const dim3 grid((a.N + 63) / 64, (a.T + 63) / 64), block(kBlock);
   switch (epi) {
     case GEPI_F32_BIAS: hipLaunchKernelGGL((k_gemm_f32<GEPI_F32_BIAS>), grid, block, 0, s, a); break;
     case GEPI_RESID: hipLaunchKernelGGL((k_gemm_f32<GEPI_RESID>), grid, block, 0, s, a); break;
     case GEPI_SWIGLU: hipLaunchKernelGGL((k_gemm_f32<GEPI_SWIGLU>), grid, block, 0, s, a); break;
-    case GEPI_GELU_TANH: hipLaunchKernelGGL((k_gemm_f32<GEPI_GELU_TANH>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((k_gemm_f32<GEPI_GELU_ERF>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_gemm_f32<GEPI_GELU>), grid, block, 0, s, a); break;
   }
 }
 

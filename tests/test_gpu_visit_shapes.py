@@ -1,0 +1,49 @@
+"""First visits at the numbers of positions and widths where the products' tiles change: one position, one more and one
+less than a tile, inner dimensions that end inside a 128-byte step (520 and 4104 values), and enough positions for the
+largest tiles; the numbers of positions also move how the inner dimension is split.  Against the oracle, every position
+on its own, at the bar of the storage type."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_18164_amd import mdi, synth as S
+from gpu_util import check, dev_acts, host, pair
+
+pytestmark = pytest.mark.gpu
+
+
+def ragged(**kw):
+    base = dict(n_layer=1, d_model=520, n_head=8, n_kv_head=4, head_dim=64, d_ff=4104, vocab=61, max_ctx=2304, dtype=S.DT_BF16)
+    base.update(kw)
+    return S.tiny(**base)
+
+
+GELU = dict(norm_kind=S.NORM_LAYERNORM, mlp_kind=S.MLP_GELU_TANH, has_bias=1)
+
+
+@pytest.mark.parametrize("T,kw", [(T, {}) for T in (1, 31, 32, 33, 64, 65, 130, 257, 700, 2050)] + [(T, GELU) for T in (16, 129, 515)],
+                         ids=lambda v: v if isinstance(v, int) else "gelu" if v else "swiglu")
+def test_first_visits_across_tile_edges(T, kw):
+    cfg = ragged(**kw)
+    w = S.make_weights(cfg, 50, exercise=True)
+    o, g = pair(cfg, w, 0, 1, max_prefill=T)
+    x = S.make_activations(cfg, 51, 0, T)
+    check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", T))
+    y = S.make_activations(cfg, 52, 0, 1)[0]
+    check(g.decode_step(0, dev_acts(y, cfg)), o.decode_step(0, y), cfg, ("later visit after", T))
+    g.sync()
+
+
+@pytest.mark.parametrize("T", [5, 300])
+def test_output_rows_off_a_16_byte_boundary(T):
+    cfg = ragged()
+    w = S.make_weights(cfg, 60, exercise=True)
+    g = mdi.Partition(cfg, w, 0, 1, max_seqs=2)
+    x = dev_acts(S.make_activations(cfg, 61, 0, T), cfg)
+    buf = torch.full((T * 520 + 2,), 7.0, dtype=torch.bfloat16, device="cuda:0")
+    g.prefill(0, x, buf[1:T * 520 + 1].view(T, 520))
+    want = g.prefill(1, x)
+    g.sync()
+    got = host(buf)
+    assert got[0] == 7.0 and got[-1] == 7.0
+    assert np.array_equal(got[1:-1].reshape(T, 520), host(want))
