@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmdi.so")
-SOURCES = ["mdi_api.hip", "decode.hip", "prefill.hip", "gemm_prefill.hip", "step_w4.hip", "step_w8.hip", "attn_prefill.hip"]
+SOURCES = ["mdi_api.hip", "decode.hip", "prefill.hip", "gemm_bf16.hip", "gemm_f32.hip", "step_w4.hip", "step_w8.hip", "attn_prefill.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
@@ -35,7 +35,7 @@ def build(verbose=False):
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,0 +1,39 @@
+// First-visit products with fp32 storage (exact fp32 products): tile shapes and their choice (kernel: gemm_impl.h).
+#include "gemm_impl.h"
+
+namespace mdi {
+namespace {
+
+// index, BN, BT, wavefronts WN x WT, ring depths.  A compute unit's matrix cores take 256 fp32 operations a clock, a
+// sixteenth of the bf16 rate, so small tiles keep them as busy as large ones (within 5 % at every size measured) and
+// divide better; the figures are fitted to 3900 measured (T, N, Kd, shape, splits), T from 1 to 2048, choices 5 % from the
+// best.  On vector ALUs with one 64 x 64 tile shape: 69 / 202 (output and down, mean) / 74 us for QKV / residual
+// products / gate-up of the 304M shape at 100 positions, here 16 / 12 / 33.
+#define MDI_GEMM_SHAPES(X) X(0, 64, 32, 2, 2, 4, 4) X(1, 64, 64, 2, 4, 4, 4)
+constexpr int kShapes = 2;
+constexpr Shape kShape[kShapes] = {{64, 32, 4, 1.055f, 2.36f, 0.29f, 4.5f}, {64, 64, 1, 0.578f, 1.37f, 1.0f, 4.5f}};
+
+template <int EPI>
+void launch_epi(hipStream_t s, int shape, const GemmArgs& a) {
+  switch (shape) {
+#define X(I, BN, BT, WN, WT, NBW, NBA) case I: launch_shape<float, EPI, BN, BT, WN, WT, NBW, NBA>(s, a); break;
+    MDI_GEMM_SHAPES(X)
+#undef X
+  }
+}
+
+}  // namespace
+
+GemmPlan plan_gemm_f32(int T, int N, int Kd, size_t part_floats) { return plan_shape(kShape, kShapes, 4, T, N, Kd, part_floats); }
+
+void launch_gemm_f32(hipStream_t s, int epi, int shape, const GemmArgs& a) {
+  switch (epi) {
+    case GEPI_F32_BIAS: launch_epi<GEPI_F32_BIAS>(s, shape, a); break;
+    case GEPI_RESID: launch_epi<GEPI_RESID>(s, shape, a); break;
+    case GEPI_PART: launch_epi<GEPI_PART>(s, shape, a); break;
+    case GEPI_SWIGLU: launch_epi<GEPI_SWIGLU>(s, shape, a); break;
+    default: launch_epi<GEPI_GELU>(s, shape, a); break;
+  }
+}
+
+}  // namespace mdi

@@ -15,6 +15,10 @@
 // 16x16x32 instructions take 10 % less of it than 32x32x16 ones (half the accumulator traffic per product): 283
 // against 310 us at 4096 x 4096 x 11008, 1.30 PFLOP/s.  Smaller tiles are bound by what a compute unit pulls out of
 // its die's L2 (about 60 GB/s), few positions by the weights' way from memory.
+//
+// Included by gemm_bf16.hip and gemm_f32.hip, which hold the tile shapes of their storage type.
+#pragma once
+
 #include <algorithm>
 
 #include "device_utils.h"
@@ -269,20 +273,10 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   }
 }
 
-// The tile shapes in use (index, BN, BT, wavefronts WN x WT, ring depths; LDS: 128 (NBW BN + NBA BT) bytes) and what
-// plan_gemm goes by, fitted to 7500 measured (T, N, Kd, shape, splits) over the shapes of all the models here, T from
-// 16 to 6000: a round of workgroups takes steps * us + fixed, a last round that is a fraction f full (less power, less
-// traffic) part + (1 - part) f of that, and no product is faster than its weights arrive (tbps).  Picking by these takes
-// 2 % more time than picking the best measured one each time.
-#define MDI_GEMM_SHAPES(X) \
-  X(0, 256, 256, 2, 4, 3, 2) X(1, 192, 256, 2, 4, 3, 2) X(2, 256, 128, 2, 4, 3, 3) X(3, 192, 128, 2, 4, 4, 4) \
-  X(4, 128, 128, 2, 4, 4, 4) X(5, 128, 64, 4, 2, 4, 4) X(6, 64, 64, 2, 2, 4, 4) X(7, 64, 32, 2, 2, 6, 6)
+// What plan_shape goes by: a round of workgroups (`resident` per compute unit) takes steps * us + fixed, a last round
+// that is a fraction f full (less power, less traffic) part + (1 - part) f of that, and no product is faster than its
+// weights arrive (tbps).
 struct Shape { int BN, BT, resident; float us, fixed, part, tbps; };
-constexpr int kShapes = 8;
-constexpr Shape kShapeBf16[kShapes] = {
-    {256, 256, 1, 1.485f, 14.0f, 0.71f, 4.9f}, {192, 256, 1, 1.228f, 10.6f, 0.71f, 4.9f}, {256, 128, 1, 0.939f, 8.1f, 0.71f, 4.9f},
-    {192, 128, 1, 0.784f, 6.3f, 0.71f, 4.9f},  {128, 128, 1, 0.600f, 4.4f, 0.73f, 4.9f},  {128, 64, 1, 0.441f, 2.35f, 0.79f, 4.9f},
-    {64, 64, 2, 0.538f, 1.82f, 0.60f, 3.9f},   {64, 32, 3, 0.510f, 1.47f, 0.40f, 4.2f}};
 
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
 void launch_shape(hipStream_t s, const GemmArgs& a) {
@@ -296,27 +290,7 @@ void launch_shape(hipStream_t s, const GemmArgs& a) {
   hipLaunchKernelGGL((k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>), dim3(8 * ((tiles + 7) / 8), a.S), dim3(WN * WT * 64), lds, s, a);
 }
 
-template <typename ST, int EPI>
-void launch_epi(hipStream_t s, int shape, const GemmArgs& a) {
-  switch (shape) {
-#define X(I, BN, BT, WN, WT, NBW, NBA) case I: launch_shape<ST, EPI, BN, BT, WN, WT, NBW, NBA>(s, a); break;
-    MDI_GEMM_SHAPES(X)
-#undef X
-  }
-}
-
-template <typename ST>
-void launch_storage(hipStream_t s, int epi, int shape, const GemmArgs& a) {
-  switch (epi) {
-    case GEPI_F32_BIAS: launch_epi<ST, GEPI_F32_BIAS>(s, shape, a); break;
-    case GEPI_RESID: launch_epi<ST, GEPI_RESID>(s, shape, a); break;
-    case GEPI_PART: launch_epi<ST, GEPI_PART>(s, shape, a); break;
-    case GEPI_SWIGLU: launch_epi<ST, GEPI_SWIGLU>(s, shape, a); break;
-    default: launch_epi<ST, GEPI_GELU>(s, shape, a); break;
-  }
-}
-
-int compute_units() {
+inline int compute_units() {
   static const int n_cu = []() {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
@@ -325,31 +299,28 @@ int compute_units() {
   return n_cu;
 }
 
-}  // namespace
-
-GemmPlan plan_gemm(int T, int N, int Kd, size_t part_floats) {
+inline GemmPlan plan_shape(const Shape* shapes, int n_shapes, int elem_bytes, int T, int N, int Kd, size_t part_floats) {
   const double n_cu = compute_units();
-  const int nk = (2 * Kd + 127) >> 7;
+  const int nk = (elem_bytes * Kd + 127) >> 7;
   GemmPlan best{0, 1};
   double best_us = 1e30;
-  for (int i = 0; i < kShapes; ++i) {
-    const Shape& sh = kShapeBf16[i];
-    if (sh.BT == 32 && T > 32) continue;                   // a second position tile would read the weights again
+  for (int i = 0; i < n_shapes; ++i) {
+    const Shape& sh = shapes[i];
+    if (elem_bytes == 2 && sh.BT == 32 && T > 32) continue;   // a second position tile would read the weights again
     const double tiles = (double)((T + sh.BT - 1) / sh.BT) * ((N + sh.BN - 1) / sh.BN);
     for (int S = 1; S <= kMaxKSplits && S <= nk; ++S) {
       const int per = (nk + S - 1) / S;
-      if ((nk + per - 1) / per != S) continue;             // no split without a step
+      if ((nk + per - 1) / per != S) continue;                // no split without a step
       if (S > 1 && (size_t)S * T * N > part_floats) break;
       const double u = tiles * S / (n_cu * sh.resident), full = (double)(long)u, f = u - full;
       double us = (full + (f > 0 ? sh.part + (1 - sh.part) * f : 0)) * (per * sh.us + sh.fixed);
-      us = std::max(us, 2.0 * N * Kd / (sh.tbps * 1e6));
-      if (S > 1) us += (double)S * T * N * 4.0 / 4.5e6;    // the partial results are read again (4.5 TB/s)
+      us = std::max(us, (double)elem_bytes * N * Kd / (sh.tbps * 1e6));
+      if (S > 1) us += (double)S * T * N * 4.0 / 4.5e6;       // the partial results are read again (4.5 TB/s)
       if (us < best_us) { best_us = us; best = GemmPlan{i, S}; }
     }
   }
   return best;
 }
 
-void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a) { launch_storage<bf16_t>(s, epi, shape, a); }
-
+}  // namespace
 }  // namespace mdi

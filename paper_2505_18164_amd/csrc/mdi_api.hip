@@ -240,11 +240,9 @@ size_t carve(mdi_partition* p, void* arena) {
     p->p_q = (float*)cv.take(T * H * h * 4);
     p->p_o = cv.take(T * H * h * B);
     p->p_u = cv.take(T * F * B);
-    if (c.dtype == MDI_BF16) {
-      // few positions are cut into up to kMaxKSplits pieces, more positions into fewer: 4096 rows of partial results
-      p->part_cap = std::min<size_t>(T * kMaxKSplits, 4096) * d;
-      p->p_part = (float*)cv.take(p->part_cap * 4);
-    }
+    // few positions are cut into up to kMaxKSplits pieces, more positions into fewer: 4096 rows of partial results
+    p->part_cap = std::min<size_t>(T * kMaxKSplits, 4096) * d;
+    p->p_part = (float*)cv.take(p->part_cap * 4);
     if (flash_supported(c.dtype, (int)h)) {
       // keys and values^T of every position a first visit in pieces can reach: up to max_ctx, in blocks of 128
       p->Tp = (int)(((size_t)c.max_ctx + 127) / 128 * 128);
@@ -646,18 +644,17 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
   const int aligned = ((uintptr_t)acts_out & 15) == 0;
   auto resid = [&](const void* A, const void* W, const float* bias, int Kd, void* hand_off) {
     GemmArgs ga{A, W, bias, (int)T, d, Kd, p->p_xres, hand_off, 0, aligned, 1};
-    if (c.dtype != MDI_BF16) { launch_gemm(s, c.dtype, GEPI_RESID, ga); return; }
-    const GemmPlan pl = plan_gemm((int)T, d, Kd, p->part_cap);
+    const GemmPlan pl = plan_gemm(c.dtype, (int)T, d, Kd, p->part_cap);
     ga.S = pl.S;
     if (pl.S > 1) { ga.out_f32 = p->p_part; ga.out_act = nullptr; pend_S = pl.S; pend_bias = bias; }
-    launch_gemm_bf16(s, pl.S > 1 ? GEPI_PART : GEPI_RESID, pl.shape, ga);
+    launch_gemm(s, c.dtype, pl.S > 1 ? GEPI_PART : GEPI_RESID, pl.shape, ga);
     if (pl.S > 1 && hand_off) norm(nullptr, nullptr, nullptr, hand_off);
   };
   for (int i = 0; i < p->n_local; ++i) {
     const LayerPacked& L = p->layers[i];
     norm(L.ln1_g, L.ln1_b, p->p_xn, nullptr);
     GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, p->p_qkv, nullptr, 0, 0, 1};
-    launch_gemm(s, c.dtype, GEPI_F32_BIAS, g1);
+    launch_gemm(s, c.dtype, GEPI_F32_BIAS, plan_gemm(c.dtype, (int)T, g1.N, d, 0).shape, g1);
     // Attention on the matrix cores over operand arrays that hold the keys and the transposed values of positions
     // 0 .. pos0 + T - 1: the new ones written by the scatter and the transpose below, the earlier ones (a later piece
     // of a first visit) brought from the cache pages first.  The arrays are packed to what this call needs.
@@ -684,7 +681,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     resid(p->p_o, L.wo, L.bo, H * h, nullptr);
     norm(L.ln2_g, L.ln2_b, p->p_xn, nullptr);
     GemmArgs g3{p->p_xn, L.wup, L.bup, (int)T, swiglu ? 2 * F : F, d, nullptr, p->p_u, c.mlp_kind == MDI_MLP_GELU_TANH, 1, 1};
-    launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : GEPI_GELU, g3);
+    launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : GEPI_GELU, plan_gemm(c.dtype, (int)T, g3.N, d, 0).shape, g3);
     resid(p->p_u, L.wdown, L.bdown, F, i == p->n_local - 1 ? acts_out : nullptr);
   }
   p->seq_len[seq] = (uint32_t)pos0 + T;

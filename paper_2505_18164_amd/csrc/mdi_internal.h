@@ -134,13 +134,20 @@ struct GemmArgs {
   int act_aligned;   // out_act may be written 16 bytes at a time
   int S;             // splits of the inner dimension (1 unless GEPI_PART): split s leaves its sums at out_f32 + s T N
 };
-void launch_gemm(hipStream_t s, int dtype, int epi, GemmArgs a);       // S = 1
-// bf16 products (gemm_prefill.hip): the tile shape for a product, and into how many pieces its inner dimension is cut
-// so that few positions still fill the chip; part_floats = room for partial results, 0 forbids a split.
+// gemm_bf16.hip, gemm_f32.hip: the tile shape for a product, and into how many pieces its inner dimension is cut so that
+// few positions still fill the chip; part_floats = room for partial results, 0 forbids a split.
 constexpr int kMaxKSplits = 16;
 struct GemmPlan { int shape, S; };
-GemmPlan plan_gemm(int T, int N, int Kd, size_t part_floats);
+GemmPlan plan_gemm_bf16(int T, int N, int Kd, size_t part_floats);
+GemmPlan plan_gemm_f32(int T, int N, int Kd, size_t part_floats);
 void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a);
+void launch_gemm_f32(hipStream_t s, int epi, int shape, const GemmArgs& a);
+inline GemmPlan plan_gemm(int dtype, int T, int N, int Kd, size_t part_floats) {
+  return dtype == MDI_BF16 ? plan_gemm_bf16(T, N, Kd, part_floats) : plan_gemm_f32(T, N, Kd, part_floats);
+}
+inline void launch_gemm(hipStream_t s, int dtype, int epi, int shape, const GemmArgs& a) {
+  if (dtype == MDI_BF16) launch_gemm_bf16(s, epi, shape, a); else launch_gemm_f32(s, epi, shape, a);
+}
 
 struct RopeScatterArgs {
   const float* qkv;  // [T, (H+2K)h] fp32

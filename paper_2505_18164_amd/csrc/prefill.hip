@@ -1,17 +1,11 @@
 // First-visit kernels: all T prompt positions of a sample go through the local
 // layers at once and fill the sample's KV cache (Alg. 1 round 0, Alg. 2 "first
 // iteration for current sample").  With T rows the linear layers are dense
-// contractions, so in bf16 mode they run on the matrix cores (gemm_prefill.hip);
-// fp32 mode keeps exact fp32 products on the vector ALUs.
-#include <algorithm>
-
+// contractions, which run on the matrix cores (gemm_impl.h); this file holds what
+// stands between them, and the set-up kernels.
 #include "device_utils.h"
 
 namespace mdi {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_rows_input(RowsInArgs a) {
@@ -116,89 +110,6 @@ void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
   else if (n <= 4) hipLaunchKernelGGL(k_norm_rows<4>, dim3(a.T), dim3(kBlock), 0, s, a);
   else if (n <= 8) hipLaunchKernelGGL(k_norm_rows<8>, dim3(a.T), dim3(kBlock), 0, s, a);
   else hipLaunchKernelGGL(k_norm_rows<0>, dim3(a.T), dim3(kBlock), 0, s, a);
-}
-
-// ---------------------------------------------------------------------------
-// Epilogue of the fp32 GEMM kernel.  (t, n) is the output coordinate, v the
-// accumulated dot product, partner the value of column n^1 (SwiGLU pairs).
-template <int EPI>
-__device__ __forceinline__ void gemm_store(const GemmArgs& a, int out_kind, int t, int n, float v, float partner) {
-  if (t >= a.T || n >= a.N) return;
-  if (EPI == GEPI_SWIGLU) {
-    if (n & 1) return;
-    store_kind(a.out_act, out_kind, (long)t * (a.N >> 1) + (n >> 1), silu_f(v) * partner);
-    return;
-  }
-  if (a.bias) v += a.bias[n];
-  const long o = (long)t * a.N + n;
-  if (EPI == GEPI_F32_BIAS) {
-    a.out_f32[o] = v;
-  } else if (EPI == GEPI_RESID) {
-    v += a.out_f32[o];
-    a.out_f32[o] = v;
-    if (a.out_act) store_kind(a.out_act, out_kind, o, v);
-  } else {
-    store_kind(a.out_act, out_kind, o, a.gelu_tanh ? gelu_tanh_f(v) : gelu_erf_f(v));
-  }
-}
-
-// ---------------------------------------------------------------------------
-// fp32 GEMM on the vector ALUs (exact fp32 products; used by the fp32 mode whose
-// parity bar is 1e-4).  64 x 64 tile, K step 16, each thread a 4 x 4 block.
-template <int EPI>
-__global__ __launch_bounds__(kBlock) void k_gemm_f32(GemmArgs a) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;   // n block, t block
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const float* A = (const float*)a.A;
-  const float* W = (const float*)a.W;
-  const int Kd = a.Kd;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < Kd; k0 += 16) {
-    {
-      // 64 rows x 16 k per operand = 1024 values, 4 per thread (one float4 along k)
-      const int r = tid >> 2, kk = (tid & 3) * 4;
-      const int ar = min(m0 + r, a.T - 1), br = min(n0 + r, a.N - 1);
-      float4 va = {0, 0, 0, 0}, vb = {0, 0, 0, 0};
-      if (k0 + kk < Kd) {   // Kd is a multiple of 8, so a float4 never straddles the end
-        va = *reinterpret_cast<const float4*>(A + (long)ar * Kd + k0 + kk);
-        vb = *reinterpret_cast<const float4*>(W + (long)br * Kd + k0 + kk);
-      }
-      __syncthreads();
-      As[kk][r] = va.x; As[kk + 1][r] = va.y; As[kk + 2][r] = va.z; As[kk + 3][r] = va.w;
-      Bs[kk][r] = vb.x; Bs[kk + 1][r] = vb.y; Bs[kk + 2][r] = vb.z; Bs[kk + 3][r] = vb.w;
-      __syncthreads();
-    }
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = As[k][ty * 4 + i]; bv[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      gemm_store<EPI>(a, IN_F32, m0 + ty * 4 + i, n0 + tx * 4 + j, acc[i][j], acc[i][j ^ 1]);
-}
-
-void launch_gemm(hipStream_t s, int dtype, int epi, GemmArgs a) {
-  a.S = 1;
-  if (dtype == MDI_BF16) { launch_gemm_bf16(s, epi, plan_gemm(a.T, a.N, a.Kd, 0).shape, a); return; }
-  const dim3 grid((a.N + 63) / 64, (a.T + 63) / 64), block(kBlock);
-  switch (epi) {
-    case GEPI_F32_BIAS: hipLaunchKernelGGL((k_gemm_f32<GEPI_F32_BIAS>), grid, block, 0, s, a); break;
-    case GEPI_RESID: hipLaunchKernelGGL((k_gemm_f32<GEPI_RESID>), grid, block, 0, s, a); break;
-    case GEPI_SWIGLU: hipLaunchKernelGGL((k_gemm_f32<GEPI_SWIGLU>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((k_gemm_f32<GEPI_GELU>), grid, block, 0, s, a); break;
-  }
 }
 
 // ---------------------------------------------------------------------------

@@ -18,11 +18,13 @@ def ragged(**kw):
     return S.tiny(**base)
 
 
+F32 = dict(dtype=S.DT_F32)
 GELU = dict(norm_kind=S.NORM_LAYERNORM, mlp_kind=S.MLP_GELU_TANH, has_bias=1)
 
 
-@pytest.mark.parametrize("T,kw", [(T, {}) for T in (1, 31, 32, 33, 64, 65, 130, 257, 700, 2050)] + [(T, GELU) for T in (16, 129, 515)],
-                         ids=lambda v: v if isinstance(v, int) else "gelu" if v else "swiglu")
+@pytest.mark.parametrize("T,kw", [(T, {}) for T in (1, 31, 32, 33, 64, 65, 130, 257, 700, 2050)] + [(T, GELU) for T in (16, 129, 515)]
+                         + [(T, F32) for T in (1, 32, 33, 64, 65, 200, 700)] + [(T, dict(GELU, **F32)) for T in (31, 300)],
+                         ids=lambda v: v if isinstance(v, int) else ("f32_" if "dtype" in v else "bf16_") + ("gelu" if "mlp_kind" in v else "swiglu"))
 def test_first_visits_across_tile_edges(T, kw):
     cfg = ragged(**kw)
     w = S.make_weights(cfg, 50, exercise=True)
