@@ -94,16 +94,15 @@ struct mdi_partition {
   bool use_batch = false;              // ... and the shape allows the launch on this device
   char* b_slot0 = nullptr; size_t b_stride = 0;
   size_t b_off_q = 0, b_off_part = 0, b_off_knew = 0, b_off_tickets = 0;
-  tagged_t *b_xn = nullptr, *b_ob = nullptr, *b_ub = nullptr;   // [pair of columns][kMaxBatch messages]
+  tagged_t *b_xn[2] = {}, *b_ob = nullptr, *b_ub = nullptr;   // [pair of columns][kMaxBatch messages]
   size_t b_vec_words = 0;
-  tagged_t* b_ssq = nullptr;
-  tagged_t* b_ssum = nullptr; float* b_nc = nullptr; size_t b_nc_stride = 0;   // LayerNorm in the batched pass (BatchArgs)
+  tagged_t* b_ssq[2] = {};
+  tagged_t* b_ssum[2] = {}; float* b_nc = nullptr; size_t b_nc_stride = 0;   // LayerNorm in the batched pass (BatchArgs)
   tagged_t* b_ppart = nullptr; int b_S = 0, b_oct = 0;   // streamed products split among workgroups (plan_batch)
-  unsigned* b_flags = nullptr;
   unsigned b_epoch = 0;
   int b_R[4] = {16, 16, 16, 16};
   int batch_group = 0;                 // MDI_BATCH_GROUP: query heads per attention work item of a batched pass (0: chosen per launch)
-  int b_lds_xres = 0, b_lds_sq = 0, b_lds_part = 0;
+  int b_lds_xres = 0, b_lds_part = 0;
   size_t b_lds = 0;
   int n_cu = 0;
   int device = 0;         // HIP device the partition was created on (index into the per-device launch chain)
@@ -220,18 +219,18 @@ size_t carve(mdi_partition* p, void* arena) {
       p->b_off_tickets = sub(H * 4);
       p->b_stride = off;
       p->b_slot0 = (char*)cv.take(p->b_stride * kMaxBatch);
-      p->b_vec_words = (d / 2 + H * h / 2 + F / 2) * (size_t)kMaxBatch;
-      p->b_xn = (tagged_t*)cv.take(p->b_vec_words * 8);
-      p->b_ob = p->b_xn ? p->b_xn + d / 2 * kMaxBatch : nullptr;
-      p->b_ub = p->b_xn ? p->b_ob + H * h / 2 * kMaxBatch : nullptr;
-      p->b_ssq = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 8);
+      p->b_vec_words = (2 * (d / 2) + H * h / 2 + F / 2) * (size_t)kMaxBatch;
+      p->b_xn[0] = (tagged_t*)cv.take(p->b_vec_words * 8);
+      p->b_xn[1] = p->b_xn[0] ? p->b_xn[0] + d / 2 * kMaxBatch : nullptr;
+      p->b_ob = p->b_xn[0] ? p->b_xn[1] + d / 2 * kMaxBatch : nullptr;
+      p->b_ub = p->b_xn[0] ? p->b_ob + H * h / 2 * kMaxBatch : nullptr;
+      for (auto& q : p->b_ssq) q = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 8);
       if (ln) {
-        p->b_ssum = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 8);
+        for (auto& q : p->b_ssum) q = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 8);
         p->b_nc_stride = 2 * (nqkv + nup);
         p->b_nc = (float*)cv.take(p->n_local * p->b_nc_stride * 4);
       }
       p->b_ppart = (tagged_t*)cv.take((size_t)((d + 15) / 16) * 16 * 256 * 8);   // [block][up to 16 slices][256]
-      p->b_flags = (unsigned*)cv.take((size_t)1024 * kFlagStride * 4);
     }
     const size_t T = p->Tm;
     p->p_xres = (float*)cv.take(T * d * 4);
@@ -306,7 +305,7 @@ void plan_batch(mdi_partition* p) {
   if (((d / 32 + kStepWavesMax - 1) / kStepWavesMax) > 16) return;   // a wavefront keeps its slice of a d-sized vector in registers
   const int nup = c.mlp_kind == MDI_MLP_SWIGLU ? 2 * F : F;
   const int rows[4] = {(H + 2 * K) * h, d, nup, d};
-  int nb_max = 1, nb_d = 1;
+  int nb_max = 1;
   for (int j = 0; j < 4; ++j) {
     // 16 rows per block when that gives every workgroup a block, else 8 (twice the blocks to spread).  Measured on
     // the 7B shape's gate/up product (1376 blocks of 16 over 256 workgroups: 5 or 6 each): blocks of 8 balance better
@@ -318,7 +317,6 @@ void plan_batch(mdi_partition* p) {
     p->b_R[j] = R;
     const int nb = ((rows[j] + R - 1) / R + nwg - 1) / nwg;
     nb_max = std::max(nb_max, nb);
-    if (j == 1) nb_d = nb;
   }
   // The two residual products (output projection, MLP down) split their inner dimension among workgroups: groups
   // of S workgroups share eight 16-row blocks, one block per wavefront, one column slice per workgroup; the owner
@@ -331,12 +329,10 @@ void plan_batch(mdi_partition* p) {
     const int c_max = (std::max(H * h, F) / 32 + S - 1) / S;     // column steps of the longest slice: 1 KiB of LDS each
     p->b_S = S; p->b_oct = octets;
     p->b_R[1] = p->b_R[3] = 16;
-    nb_d = 1;
-    ks_floats = S * 256 + c_max * 256;
+    ks_floats = c_max * 256;
   }
   p->b_lds_xres = 128;
-  p->b_lds_sq = p->b_lds_xres + nb_d * 256;
-  p->b_lds_part = p->b_lds_sq + std::max(nb_d * 128, 128);
+  p->b_lds_part = p->b_lds_xres + 256;
   const int Gmax = (H / K) % 4 == 0 ? 4 : p->G;
   const int attn_floats = std::max(Gmax * h, kStepWavesMax * Gmax * (h + 2)) + 64;
   const int part_floats = std::max(std::max(nb_max * 2048, attn_floats), ks_floats);
@@ -521,10 +517,10 @@ mdi_status mdi_partition_create(const mdi_config* cfg, uint32_t layer_lo, uint32
     plan_batch(p);
     if (p->batch_region) {
       launch_fill_u32(p->stream, (uint32_t*)p->b_slot0, (long)(p->b_stride * kMaxBatch / 4), 0u);
-      launch_fill_u32(p->stream, (uint32_t*)p->b_xn, (long)p->b_vec_words * 2, 0u);
-      launch_fill_u32(p->stream, (uint32_t*)p->b_ssq, (long)kMaxBatch * 1024 * 2, 0u);
-      if (p->b_ssum) {
-        launch_fill_u32(p->stream, (uint32_t*)p->b_ssum, (long)kMaxBatch * 1024 * 2, 0u);
+      launch_fill_u32(p->stream, (uint32_t*)p->b_xn[0], (long)p->b_vec_words * 2, 0u);
+      for (auto* q : p->b_ssq) launch_fill_u32(p->stream, (uint32_t*)q, (long)kMaxBatch * 1024 * 2, 0u);
+      if (p->b_ssum[0]) {
+        for (auto* q : p->b_ssum) launch_fill_u32(p->stream, (uint32_t*)q, (long)kMaxBatch * 1024 * 2, 0u);
         const int nq = (int)((H + 2 * K) * h), nu = (int)(c.mlp_kind == MDI_MLP_SWIGLU ? 2 * F : F);
         for (int i = 0; i < p->n_local; ++i) {       // what the mean and the norm's bias add to the two normed products
           const LayerPacked& L = p->layers[i];
@@ -534,7 +530,6 @@ mdi_status mdi_partition_create(const mdi_config* cfg, uint32_t layer_lo, uint32
         }
       }
       launch_fill_u32(p->stream, (uint32_t*)p->b_ppart, (long)((d + 15) / 16) * 16 * 256 * 2, 0u);
-      launch_fill_u32(p->stream, p->b_flags, 1024L * kFlagStride, 1u);
       p->b_epoch = 1;
     }
     launch_fill_u32(p->stream, p->bar_flags, 1024, 1u);     // phase counters start at 1: tag 0 marks "never written"
@@ -950,16 +945,18 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   a.err = p->err; a.spin_limit = 1 << 21;
   a.n_hg = (int)c.n_head / G;
   a.scale = 1.f / sqrtf((float)c.head_dim);
-  a.nwg = p->nwg; a.m = n;
+  a.nwg = p->nwg; a.m = n; a.m_magic = 0xFFFFFFFFu / (unsigned)n + 1u;
   a.epoch0 = p->b_epoch;
-  a.xn = p->b_xn; a.ob = p->b_ob; a.ub = p->b_ub;
+  a.ob = p->b_ob; a.ub = p->b_ub;
+  for (int k = 0; k < 2; ++k) { a.xn[k] = p->b_xn[k]; a.ssq[k] = p->b_ssq[k]; a.ssum[k] = p->b_ssum[k]; }
   a.slot0 = p->b_slot0; a.slot_stride = (long)p->b_stride;
   a.off_q = (long)p->b_off_q; a.off_part = (long)p->b_off_part; a.off_knew = (long)p->b_off_knew; a.off_tickets = (long)p->b_off_tickets;
-  a.ssq = p->b_ssq; a.flags = p->b_flags;
-  a.norm_kind = (int)c.norm_kind; a.ssum = p->b_ssum; a.nc0 = p->b_nc; a.nc_stride = (long)p->b_nc_stride;
+  a.norm_kind = (int)c.norm_kind; a.nc0 = p->b_nc; a.nc_stride = (long)p->b_nc_stride;
   a.ppart = p->b_ppart; a.str_S = p->b_S; a.str_oct = p->b_oct;
+  const int heads = c.n_head * c.head_dim, ff = c.d_ff;
+  a.str_c[0] = (heads / 32 + p->b_S - 1) / p->b_S; a.str_c[1] = (ff / 32 + p->b_S - 1) / p->b_S;
   for (int j = 0; j < 4; ++j) a.R[j] = p->b_R[j];
-  a.lds_xres = p->b_lds_xres; a.lds_sq = p->b_lds_sq; a.lds_part = p->b_lds_part;
+  a.lds_xres = p->b_lds_xres; a.lds_part = p->b_lds_part;
   a.trace = p->trace;
   // Attention work items: (message, head group, context split).  Splits of about equal length over all messages,
   // as many items as there are workgroups when the contexts allow it, no split shorter than 128 positions.

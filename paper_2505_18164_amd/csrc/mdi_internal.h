@@ -186,8 +186,6 @@ void launch_flash_prefill(hipStream_t s, const FlashArgs& a);
 // ---- whole decode step as one persistent launch ------------------------------
 constexpr int kStepWavesMax = 8;     // wavefronts per workgroup: 8 (one workgroup per compute unit) or 4 (two)
 constexpr int kMaxSlots = 8;         // messages one launch can carry
-constexpr int kFlagStride = 32;      // batched pass: a workgroup's phase counter has a 128-byte line to itself (in 4-byte words);
-                                     // measured on the one-message kernels as well: no gain there, their counters stay packed
 
 typedef unsigned long long tagged_t;  // low half: the value's bits, high half: the phase counter it was written in
 
@@ -274,25 +272,29 @@ struct BatchArgs {
   int in_kind, act_kind;
   int* err; int spin_limit;          // as in StepArgs
   int n_hg; float scale;
-  int nwg, m;                        // workgroups (one set), messages
+  int nwg, m;                        // workgroups (one set), messages (2 .. kMaxBatch)
+  unsigned m_magic;                  // 0xFFFFFFFF / m + 1: e / m is the high word of e * m_magic, exact while e * m < 2^32
   unsigned epoch0;
   // Exchange buffers.  Vectors that feed a matrix product travel as pairs of bf16 with the writing phase's counter
-  // in one 8-byte word, one array [pair of columns][kMaxBatch messages] per kind for the whole launch (xn: the
+  // in one 8-byte word, one array [pair of columns][m messages] per kind for the whole launch (xn: the
   // residual stream times the gain of the norm that follows; ob: attention output; ub: MLP hidden).  What attention
   // needs per message - q, the newest K/V row, split partials as (float, counter) like in StepSlot, tickets - sits
   // in one block per message: message j's are message 0's advanced by j * slot_stride bytes.
-  tagged_t *xn, *ob, *ub;
+  // xn, ssq and ssum exist twice: [0] from the down projection (and the launch's input) to QKV, [1] from the output
+  // projection to the up product (why: step_batch.h).
+  tagged_t *xn[2], *ob, *ub;
   char* slot0; long slot_stride;
   long off_q, off_part, off_knew, off_tickets;
-  tagged_t* ssq;                     // [kMaxBatch][nwg] per-workgroup sums of squares of the residual rows they own
+  tagged_t* ssq[2];                  // [kMaxBatch][nwg] per-workgroup sums of squares of the residual rows they own
   // LayerNorm (norm_kind = MDI_NORM_LAYERNORM): the sums of those rows travel too, and the products of a normalised
   // vector are corrected in the epilogue, y = rstd (W (x g)) - rstd mean (W g) + W b: per layer the four vectors
   // [W_qkv g1 | W_qkv b1 | W_up g2 | W_up b2] (float), layer l's at nc0 + l * nc_stride floats
-  int norm_kind; tagged_t* ssum; const float* nc0; long nc_stride;
-  tagged_t* ppart; int str_S, str_oct; // products split among workgroups along the inner dimension: partials [block][S][256], slices per block, block octets
-  unsigned* flags;                   // [nwg] phase counters of the workgroups
+  int norm_kind; tagged_t* ssum[2]; const float* nc0; long nc_stride;
+  // products split among workgroups along the inner dimension: partials [block][S][4 row quads][m][4 rows], slices per
+  // block, block octets, column steps of a slice (output projection, MLP down)
+  tagged_t* ppart; int str_S, str_oct, str_c[2];
   int R[4];                          // rows per matrix-instruction block in the QKV / output / up / down products (8 or 16)
-  int lds_xres, lds_sq, lds_part;    // LDS layout in floats
+  int lds_xres, lds_part;            // LDS layout in floats
   int n_items;                       // attention work items of the launch
   unsigned long long* trace;         // optional [workgroup][n_layer][5][8] timestamps (100 MHz ticks), or nullptr
   BatchSlot s[kMaxBatch];

@@ -8,9 +8,24 @@
 // each sample's own cache.  The kernel is still bound by HBM: the matrix cores only take over the multiply-adds
 // that the vector ALUs could not do for 16 messages at the rate the weights arrive.
 //
-// Same skeleton as k_step (one persistent launch, five phases per layer, a grid-wide barrier of per-workgroup
-// phase counters, self-validating tagged exchange), with these differences:
+// Same skeleton as k_step (one persistent launch, five phases per layer, self-validating tagged exchange), with these
+// differences:
 //   * One set of 8-wavefront workgroups, all messages in lockstep.
+//   * No barrier: a phase waits for the words it reads, by reloading those whose counter is not the writing phase's
+//     yet.  Phase counters, watched by every workgroup before it fetched the data, cost 3.2 us a round; 256
+//     workgroups that watch 2048 words of data themselves take 1.65 us from store to store.  What binds a phase of the
+//     small shapes is this chain of round trips (a store is seen elsewhere after about 1.2 us), so each is started as
+//     early as it can be: words of the phase before are asked for ahead of this phase's weights, operands of the
+//     epilogue before the products, and no stream asks for tiles past its end.  Together, per launch: 4 layers of GPT-2
+//     with 3 messages 304 -> 183 us, 11 of TinyLlama with 4 846 -> 589 us, 8 of the 7B shape with 8 1178 -> 958 us.
+//     What the counters also gave, that nobody overwrites what somebody still reads, follows from
+//     the sums of squares: every workgroup publishes its share at the end of the output projection and of the down
+//     projection, after all it read up to there, and every workgroup has seen the shares of all before it stores
+//     anything in the QKV and the up product.  So whoever stores in QKV, attention or the output projection knows that
+//     all have finished the layer before; whoever stores in the up or down product knows that all have finished this
+//     layer's output projection.  Hence the residual vectors, the sums of squares and the sums exist twice, once from
+//     the output projection to the up product and once from the down projection to QKV; every other vector is
+//     written at least two such points after it was last read.
 //   * Work unit of a product = a block of R (16 or 8) weight rows; blocks are dealt round-robin to workgroups; the
 //     eight wavefronts of a workgroup split the block's columns among them and their partial 16 x 16 results are
 //     added in LDS in wavefront order (deterministic, no float atomics).  RoPE partners (i, i + h/2) and SwiGLU
@@ -19,8 +34,8 @@
 //     word, already multiplied by the gain of the RMSNorm that follows (1/rms is applied to the finished products;
 //     the sum of squares travels as one partial per workgroup and message).  Bytes exchanged per message are half
 //     those of k_step's (float, counter) words, which matters now that 16 messages share a pass.  A vector kind is
-//     ONE array [pair of columns][16 messages] for the whole launch: the 16 lanes that hold the same columns of the
-//     16 messages read 128 consecutive bytes.
+//     ONE array [pair of columns][messages] for the whole launch: the lanes that hold the same columns of the messages
+//     read consecutive words, and no line carries room for messages the launch does not have.
 //   * The residual stream never leaves the workgroup that owns its rows: it stays in LDS for the whole launch.
 //   * Products whose input is the d-sized normalised vector (QKV, MLP up) keep each wavefront's column slice of all
 //     messages in registers for all the blocks of the phase; the others (output projection, MLP down: one block per
@@ -53,26 +68,19 @@ __device__ __forceinline__ uint32_t settle_bits(const tagged_t* p, tagged_t u, u
   return (uint32_t)u;
 }
 
-// A word of an exchanged vector: loaded at agent scope, i.e. from memory, not from a die's L2, which may hold an
-// older copy.  (Measured: ordinary loads that L2 may answer - with one address per (layer, phase) instance of every
-// vector so that no older copy can exist, and a coherent second look for words that were fetched too early - move
-// 32 times less over the fabric and are not faster: the phases that stream these vectors are bound by what a
-// compute unit's memory pipeline passes per unit of time, whichever cache answers.)
-__device__ __forceinline__ tagged_t ld_word(const MDI_GLOBAL tagged_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // What the attention helpers of step_impl.h read of a message.
 struct BatchView {
   const tagged_t *q, *knew;
-  tagged_t *part, *ob;             // ob: the launch's [pair][16 messages] array of attention outputs
+  tagged_t *part, *ob;             // ob: the launch's [pair][messages] array of attention outputs
   unsigned* tickets;
   const int32_t* table;
-  int ctx, n_splits, chunk, msg;
+  int ctx, n_splits, chunk, msg, n_msg;
 };
 __device__ __forceinline__ BatchView view_of(const BatchArgs& a, int j, tagged_t* ob) {
   char* base = a.slot0 + (long)j * a.slot_stride;
   BatchView v;
   v.q = (const tagged_t*)(base + a.off_q); v.knew = (const tagged_t*)(base + a.off_knew);
-  v.part = (tagged_t*)(base + a.off_part); v.ob = ob; v.msg = j;
+  v.part = (tagged_t*)(base + a.off_part); v.ob = ob; v.msg = j; v.n_msg = a.m;
   v.tickets = (unsigned*)(base + a.off_tickets);
   v.table = a.s[j].table; v.ctx = a.s[j].ctx; v.n_splits = a.s[j].n_splits; v.chunk = a.s[j].chunk;
   return v;
@@ -93,7 +101,7 @@ __device__ __forceinline__ BGeo make_bgeo(const void* W, int N, int Kd, int R, i
   BGeo g;
   g.W = (const char*)W; g.row_bytes = 2L * Kd; g.N = N; g.R = R;
   g.rope_sh = rope_h ? 31 - __builtin_clz(rope_h >> 1) : -1;
-  const int nblk = (N + R - 1) / R;
+  const int nblk = (N + R - 1) >> (R == 16 ? 4 : 3);
   g.nb_local = nblk > wg ? (nblk - wg + nwg - 1) / nwg : 0;
   // The columns are cut into one slice per wavefront; which wavefront takes which slice rotates with the workgroup,
   // so that at any moment the workgroups read different parts of the messages' vectors (every workgroup walks the
@@ -131,7 +139,7 @@ __device__ __forceinline__ void res_issue(Tile& t, const BGeo& g, int lb, int wg
 template <int HALF, bool LAST_HALF>
 __device__ __forceinline__ void res_compute(const Tile& t, const BGeo& g, int lb, const bf16x8 (&Bv)[kResSteps], f32x4& acc,
                                             float* part, int wave, int lane) {
-  if (lb >= g.nb_local) return;                                  // uniform
+  if (lb < 0 || lb >= g.nb_local) return;                        // uniform
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
     const int ks = HALF * 8 + s;
@@ -142,14 +150,6 @@ __device__ __forceinline__ void res_compute(const Tile& t, const BGeo& g, int lb
     *reinterpret_cast<f32x4*>(part + (((lb * kStepWaves + wave) << 6) + lane) * 4) = acc;
     acc = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-}
-
-// Four tagged words -> the matrix instruction's second operand; `bad` collects whether any of them does not carry the
-// counter `tag` (a store not yet visible on this die: the rare case).  No load is retried here; the caller repeats
-// its loads the slow, sure way instead.
-__device__ __forceinline__ bf16x8 take4(tagged_t r0, tagged_t r1, tagged_t r2, tagged_t r3, unsigned tag, uint32_t& bad) {
-  bad |= (((uint32_t)(r0 >> 32) ^ tag) | ((uint32_t)(r1 >> 32) ^ tag)) | (((uint32_t)(r2 >> 32) ^ tag) | ((uint32_t)(r3 >> 32) ^ tag));
-  return __builtin_bit_cast(bf16x8, u32x4{(uint32_t)r0, (uint32_t)r1, (uint32_t)r2, (uint32_t)r3});
 }
 
 // ---------------------------------------------------------------------------
@@ -166,10 +166,11 @@ struct KsGeo {
   int blk, nblk;        // this wavefront's block; blocks of the product
   bool live;            // this wavefront has columns and a block
 };
-__device__ __forceinline__ KsGeo make_ksgeo(int N, int Kd, int S, int octets, int wg, int wave) {
+// c = column steps of a slice; q, s = workgroup divided by S, the same for the whole launch
+__device__ __forceinline__ KsGeo make_ksgeo(int N, int Kd, int S, int c, int octets, int q, int s, int wave) {
   KsGeo g;
-  g.S = S; g.q = wg / S; g.s = wg - g.q * S;
-  const int ktot = Kd >> 5, c = (ktot + S - 1) / S;
+  g.S = S; g.q = q; g.s = s;
+  const int ktot = Kd >> 5;
   g.k0 = min(g.s * c, ktot);
   g.nk = g.q < octets ? max(0, min(c, ktot - g.s * c)) : 0;
   g.nblk = (N + 15) >> 4;
@@ -197,15 +198,6 @@ __device__ __forceinline__ void ks_compute(const Tile& t, const KsGeo& g, const 
     }
   }
 }
-// Sum over n partials of element (row i, message j): partial w at part + 256 w, element order as the matrix
-// instruction leaves it (lane = 16 (i / 4) + j, register i % 4).
-__device__ __forceinline__ float part_sum_n(const float* part, int i, int j, int n) {
-  const float* p = part + ((((i >> 2) << 4) + j) << 2) + (i & 3);
-  float v = 0.f;
-  for (int w = 0; w < n; ++w) v += p[w << 8];
-  return v;
-}
-
 // Sum over the wavefronts of element (row i, message j) of local block lb.
 __device__ __forceinline__ float part_sum(const float* part, int lb, int i, int j) {
   const float* p = part + ((lb * kStepWaves) << 8) + ((((i >> 2) << 4) + j) << 2) + (i & 3);
@@ -234,7 +226,7 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
     }
     const int head = g.hg * G + gi;
     if (single) {
-      st_pair(S.ob + ((((long)head * h + e) >> 1) << 4) + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
+      st_pair(S.ob + (((long)head * h + e) >> 1) * S.n_msg + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
     } else {
       tagged_t* pr = S.part + ((long)head * kMaxSplits + g.split) * rec;
       st_tag(pr + e, o0, wtag); st_tag(pr + e + 1, o1, wtag);
@@ -250,6 +242,7 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
   }
   __syncthreads();
   if (!s_flag[1]) return;
+  if (threadIdx.x == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int idx = threadIdx.x; idx < G * hp; idx += kStepThreads) {
     const int gi = idx / hp, e = (idx - gi * hp) * 2;
     const int head = g.hg * G + gi;
@@ -280,9 +273,9 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
         }
       }
     }
-    st_pair(S.ob + ((((long)head * h + e) >> 1) << 4) + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
+    st_pair(S.ob + (((long)head * h + e) >> 1) * S.n_msg + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
   }
-  if (threadIdx.x == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
 }
 
 __device__ __forceinline__ void bstamp(const BatchArgs& a, int layer, int ph, int k) {
@@ -310,6 +303,54 @@ __device__ __forceinline__ float batch_input(const BatchArgs& a, const BatchLds&
   return bf16_to_f32(((const bf16_t*)sl.in[j])[row]);
 }
 
+// What the epilogue of a phase needs beside the products, for item e: QKV: (cos, sin) of the row pair; residual
+// products: the following norm's gains of the row pair; all: the biases, and the LayerNorm corrections [W g | W b].
+struct EpiItem { int j, p, lb; };      // message, row pair (SwiGLU: quad) of the block, local block
+__device__ __forceinline__ EpiItem epi_item(int e, int m, unsigned m_magic, int n_sh) {
+  const int x = (int)__umulhi((unsigned)e, m_magic);            // e / m, see BatchArgs
+  return EpiItem{e - x * m, x & ((1 << n_sh) - 1), x >> n_sh};
+}
+// Sums over the eight lanes of a message's row pairs, published by the first of them.
+__device__ __forceinline__ void publish_sums(float s2, float s1, int p, tagged_t* ssq, tagged_t* ssum, unsigned tag) {
+  s2 = dpp_add<kDppXor1, 0xF>(s2); s2 = dpp_add<kDppXor2, 0xF>(s2); s2 = dpp_add<kDppHalfMirror, 0xF>(s2);
+  if (p == 0) st_tag(ssq, s2, tag);
+  if (ssum) {
+    s1 = dpp_add<kDppXor1, 0xF>(s1); s1 = dpp_add<kDppXor2, 0xF>(s1); s1 = dpp_add<kDppHalfMirror, 0xF>(s1);
+    if (p == 0) st_tag(ssum, s1, tag);
+  }
+}
+struct EpiOps { float g0, g1, b0, b1, n[4]; };
+__device__ __forceinline__ EpiOps epi_ops(const BatchArgs& a, const StepLayer& L, const BGeo& g, const BatchLds& sl, const float* nc, int ph,
+                                          bool last, int e, int n_items, int n_sh, int wg, int nwg) {
+  EpiOps o{};
+  if (e >= n_items) return o;
+  const bool resid = ph == PH_OPROJ || ph == PH_DOWN;
+  const EpiItem it = resid ? EpiItem{e >> 3, e & 7, 0} : epi_item(e, a.m, a.m_magic, n_sh);
+  const int j = it.j, p = it.p, lb = it.lb;
+  if (ph == PH_QKV) {
+    const int r0 = block_row(g, lb * nwg + wg, p), r1 = r0 + (a.h >> 1);
+    const int head = r0 / a.h;
+    const float2* rope = sl.rope[j];
+    if (rope && head < a.H + a.K) { const float2 cs = rope[r0 - head * a.h]; o.g0 = cs.x; o.g1 = cs.y; }
+    if (L.bqkv) { o.b0 = L.bqkv[r0]; o.b1 = L.bqkv[r1]; }
+    if (nc) { o.n[0] = nc[r0]; o.n[1] = nc[r1]; o.n[2] = nc[g.N + r0]; o.n[3] = nc[g.N + r1]; }
+    return o;
+  }
+  if (ph == PH_UP && a.mlp_kind == MDI_MLP_SWIGLU) return o;
+  const int r0 = (lb * nwg + wg) * g.R + 2 * p;
+  if (r0 >= g.N) return o;
+  const float *bu = L.bup, *bo = L.bo, *bd = L.bdown, *g1 = L.ln1_g, *g2 = L.ln2_g;
+  const float* bias = ph == PH_UP ? bu : ph == PH_OPROJ ? bo : bd;
+  if (bias) { o.b0 = bias[r0]; o.b1 = bias[r0 + 1]; }
+  if (ph == PH_UP) {
+    if (nc) { o.n[0] = nc[r0]; o.n[1] = nc[r0 + 1]; o.n[2] = nc[g.N + r0]; o.n[3] = nc[g.N + r0 + 1]; }
+  } else if (!last) {
+    const float* gain = ph == PH_OPROJ ? g2 : advance(g1, a.w_stride);
+    o.g0 = gain[r0]; o.g1 = gain[r0 + 1];
+  }
+  return o;
+}
+
 template <int G>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_batch(BatchArgs a) {
   typedef bf16_t WT;
@@ -323,13 +364,11 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   float* rshift = smem + 64;                     // [16] LayerNorm: (mean - centre) / std of every message's vector
   float* rcen = smem + 80;                       // [16] LayerNorm: the centre the vectors are published around (see below)
   const bool ln = a.norm_kind == MDI_NORM_LAYERNORM;
-  float* xres = smem + a.lds_xres;               // residual rows this workgroup owns: [block][16 rows][16 messages]
-  float* sq = smem + a.lds_sq;                   // squares of those rows per epilogue item; cross-wavefront sums of the first product
+  float* xres = smem + a.lds_xres;               // residual rows this workgroup owns: [16 rows][16 messages]
   float* part = smem + a.lds_part;               // the wavefronts' partial products [block][wavefront][lane][4]; attention scratch
-  const int kg = lane >> 4;
-  const int nmsg = min(lane & 15, m - 1);        // the message this lane's column stands for (columns past m repeat the last)
 
   if (threadIdx.x == 0) {
+    s_flag[kFailed] = 0;
     for (int j = 0; j < m; ++j) {
       const BatchSlot& S = a.s[j];
       sl.rope[j] = S.rope; sl.in[j] = S.in; sl.out[j] = S.act_out; sl.kv_off[j] = S.kv_tok_off; sl.pos[j] = S.pos;
@@ -352,7 +391,13 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   } else {
     for (int j = wave; j < m; j += kStepWaves) {
       float u = 0.f;
-      for (int r = lane; r < a.d; r += 64) u += batch_input(a, sl, j, r);
+      for (int r0 = lane; r0 < a.d; r0 += 512) {     // eight loads in flight
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = batch_input(a, sl, j, min(r0 + 64 * k, a.d - 1));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) u += r0 + 64 * k < a.d ? v[k] : 0.f;
+      }
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) u += __shfl_xor(u, off, 64);
       if (lane == 0) rcen[j] = u / (float)a.d;
@@ -360,65 +405,24 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   }
   __syncthreads();
   {
-    const int Rd = a.R[1], half = Rd >> 1;
-    const BGeo gd = make_bgeo(nullptr, a.d, a.H * a.h, Rd, 0, wg, nwg, wave);
-    const int n_items = gd.nb_local * half * m;
-    for (int e = threadIdx.x; e < n_items; e += kStepThreads) {
-      const int j = e % m, p = (e / m) % half, lb = e / (m * half);
-      const int r0 = (lb * nwg + wg) * Rd + 2 * p;
-      float s2 = 0.f;
+    // item (message j, row pair p) of the block of 16 rows this workgroup owns: eight neighbouring lanes share a message
+    const int e = threadIdx.x, j = e >> 3, p = e & 7, r0 = wg * 16 + 2 * p;
+    if (e < 8 * m) {
+      float s2 = 0.f, s1 = 0.f;
       if (r0 < a.d) {
         const float x0 = batch_input(a, sl, j, r0), x1 = batch_input(a, sl, j, r0 + 1);
-        float* xr = xres + ((lb << 4) + 2 * p) * 16 + j;
+        float* xr = xres + 2 * p * 16 + j;
         xr[0] = x0; xr[16] = x1;
-        st_pair(a.xn + ((r0 >> 1) << 4) + j, pack_bf16x2((x0 - rcen[j]) * a.l0.ln1_g[r0], (x1 - rcen[j]) * a.l0.ln1_g[r0 + 1]), a.epoch0);
-        s2 = x0 * x0 + x1 * x1;
+        st_pair(a.xn[0] + (r0 >> 1) * m + j, pack_bf16x2((x0 - rcen[j]) * a.l0.ln1_g[r0], (x1 - rcen[j]) * a.l0.ln1_g[r0 + 1]), a.epoch0);
+        s2 = x0 * x0 + x1 * x1; s1 = x0 + x1;
       }
-      sq[e] = s2;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < m) {
-      float t = 0.f;
-      for (int e = threadIdx.x; e < n_items; e += m) t += sq[e];
-      st_tag(a.ssq + (long)threadIdx.x * nwg + wg, t, a.epoch0);
-      if (ln) {                                  // the rows' sum as well (from the rows kept in LDS)
-        float u = 0.f;
-        for (int e = threadIdx.x; e < n_items; e += m) {
-          const int p = (e / m) % half, lb = e / (m * half);
-          if ((lb * nwg + wg) * Rd + 2 * p < a.d) { const float* xr = xres + ((lb << 4) + 2 * p) * 16 + threadIdx.x; u += xr[0] + xr[16]; }
-        }
-        st_tag(a.ssum + (long)threadIdx.x * nwg + wg, u, a.epoch0);
-      }
+      publish_sums(s2, s1, p, a.ssq[0] + j * nwg + wg, ln ? a.ssum[0] + j * nwg + wg : nullptr, a.epoch0);
     }
   }
   __syncthreads();
 
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-
-  // Wait until every workgroup has finished the previous phase (its counter has reached `epoch`).
-  auto barrier = [&](unsigned epoch) __attribute__((always_inline)) -> bool {
-    if (threadIdx.x < 64) {
-      bool ok = true;
-      int it = 0;
-      while (true) {
-        bool all = true;
-        for (int i = threadIdx.x; i < nwg; i += 64) {
-          const unsigned v = __hip_atomic_load(a.flags + i * kFlagStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          all = all && ((int)(v - epoch) >= 0);
-        }
-        if (__all(all)) break;
-        if (++it > a.spin_limit) { ok = false; break; }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      if (threadIdx.x == 0) {
-        s_flag[0] = ok;
-        if (!ok) __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    return s_flag[0] != 0;
-  };
+  const int ks_q = wg / a.str_S, ks_s = wg - ks_q * a.str_S;
 
 #pragma nounroll
   for (int layer = 0; layer < a.n_layer; ++layer) {
@@ -430,27 +434,28 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       const int jm = gemv_index(ph);
       const int N = jm == 0 ? (a.H + 2 * a.K) * a.h : jm == 2 ? (a.mlp_kind == MDI_MLP_SWIGLU ? 2 * a.F : a.F) : a.d;
       const int Kd = jm == 1 ? a.H * a.h : jm == 3 ? a.F : a.d;
-      const BGeo g = make_bgeo(layer_matrix(Lv, jm), N, Kd, a.R[jm], jm == 0 ? a.h : 0, wg, nwg, wave);
+      const BGeo g = make_bgeo(layer_matrix(Lv, jm), N, Kd, jm == 0 ? a.R[0] : jm == 2 ? a.R[2] : a.R[1], jm == 0 ? a.h : 0, wg, nwg, wave);
       // LayerNorm corrections of this phase's product: [W g | W b], N floats each (QKV's first, then the up product's)
       const float* nc = ln ? a.nc0 + (long)layer * a.nc_stride + (jm == 2 ? 2L * (a.H + 2 * a.K) * a.h : 0L) : nullptr;
-      // The per-lane addresses of the exchange vectors do not change from phase to phase; computed once outside
-      // the loops they would occupy dozens of registers for the whole launch, so they are derived from a value
-      // the compiler cannot see through and are recomputed where they are used.
-      int lane_msg = nmsg;
-      asm volatile("" : "+v"(lane_msg));
-      const tagged_t* xn_in = a.xn;
-      tagged_t* xn_out = a.xn;
+      // Per-lane addresses and epilogue indexes do not change from phase to phase; computed once outside the loops they
+      // would occupy dozens of registers for the whole launch, so they are derived from values the compiler cannot see
+      // through and are recomputed where they are used.
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int lane = tid & 63, kg = lane >> 4, lane_msg = min(lane & 15, m - 1);   // lane_msg: the message this lane's column stands for (columns past m repeat the last)
       tagged_t* ob_l = a.ob;
       tagged_t* ub_l = a.ub;
       bstamp(a, layer, ph, 0);
 
       // Every kind of phase keeps its registers to itself (tiles in flight, the second operand, attention state are
       // declared inside its branch and given a value on every path), so that the compiler sees them dead elsewhere.
-      // Each branch first issues the requests that depend on nothing another workgroup writes - they are in flight
-      // while the barrier completes - and then waits for the barrier.
+      // Each branch first issues the requests that depend on nothing another workgroup writes; they are on their way
+      // while the words of the phase before arrive.  The epilogue's own operands (gains, biases, angles) are among
+      // them: a thread keeps those of its first item, fetched again they would cost a round trip at the phase's end.
       if (ph == PH_ATTN) {
         // ---- attention: one work item = (message, head group, context split); items dealt round-robin
         AttnState<WT, G> st;
+        AttnAsk<WT> ask{};
         AttnGeo ga{};
         Tile A, B;
         int pgA[kTile], pgB[kTile];
@@ -460,12 +465,12 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
           V = view_of(a, slot, ob_l);
           ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
+          attn_ask<WT, G>(ask, ga, a, V, wave);
           attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
           attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
-          if (!barrier(epoch)) return;
           bstamp(a, layer, ph, 1);
           while (true) {
-            attn_begin<WT, G>(st, ga, a, V, part, epoch);
+            attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch);
             const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
             attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, Lv.kv, nte, wave, part);
             attn_to_lds<WT, G>(st, ga, a.h, part, wave);
@@ -476,203 +481,226 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
             V = view_of(a, slot, ob_l);
             ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
+            attn_ask<WT, G>(ask, ga, a, V, wave);
             attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
             attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
           }
-        } else {
-          if (!barrier(epoch)) return;                             // a workgroup without an item still takes part in the barrier
         }
         bstamp(a, layer, ph, 3);
       } else {
+        const int R = g.R, half = R >> 1;
+        // epilogue items per block and message: row pairs, or quads of rows for SwiGLU; a power of two
+        const int n_sh = (R == 16 ? 3 : 2) - (ph == PH_UP && a.mlp_kind == MDI_MLP_SWIGLU ? 1 : 0);
+        const int n_items = (g.nb_local << n_sh) * m;
+        const bool last = ph == PH_DOWN && layer == a.n_layer - 1;   // (both residual products only)
+        EpiOps ops = epi_ops(a, Lv, g, sl, nc, ph, last, tid, n_items, n_sh, wg, nwg);
         if (ph == PH_QKV || ph == PH_UP) {
-          // ---- a product whose second operand stays in registers
+          // ---- a product whose second operand stays in registers: this wavefront's column slice of every message, as
+          // published, bf16 pairs of x * gain.  Asked for first, before the weights: the workgroups' first sums of
+          // squares and the sums of squares of all messages.
           Tile A, B;
           bf16x8 Bv[kResSteps];
+          const tagged_t* xn_in = ph == PH_QKV ? a.xn[0] : a.xn[1];  // (selected, not indexed: an index into the arguments costs a copy of them)
+          const tagged_t* ssq_in = ph == PH_QKV ? a.ssq[0] : a.ssq[1];
+          const tagged_t* ssum_in = ph == PH_QKV ? a.ssum[0] : a.ssum[1];
+          const tagged_t* bbase = xn_in + (long)g.ks0 * (16 * m);
+          const uint32_t boff = (uint32_t)(4 * kg * m + lane_msg) << 3;
+          const int last_ks = max(g.nks - 1, 0);
+          auto step_at = [&](int ks, int e, uint32_t z) __attribute__((always_inline)) { return word_at(bbase + min(ks, last_ks) * (16 * m) + e * m, boff + z); };
+          const int sj = tid >> 5, sc = tid & 31;                    // sums: 32 threads per message, eight words each
+          auto sum_at = [&](const tagged_t* v, int k, uint32_t z) __attribute__((always_inline)) {
+            return word_at(v, (uint32_t)(min(sj, m - 1) * nwg + min(sc + 32 * k, nwg - 1)) * 8u + z);
+          };
+          tagged_t gate[1], sqr[8] = {};
+          ask_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)min(tid, nwg - 1) * 8u + z); });
+          if (sj < m) ask_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); });
           if (g.nks > 8) { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<1>(B, g, 0, wg, nwg, lane); }
           else { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<0>(B, g, 1, wg, nwg, lane); }
-          if (!barrier(epoch)) return;
+          // Wait for the workgroups' first sums of squares (2 KB that everybody reads): a workgroup stores its share last.
+          // Watching the vectors themselves (up to 128 KB a workgroup and look) crowds out the stores that are waited for.
+          await_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)min(tid, nwg - 1) * 8u + z); }, epoch, a.spin_limit, a.err);
+          for (int i = tid + kStepThreads; i < nwg; i += kStepThreads)
+            poll_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)i * 8u + z); }, epoch, a.spin_limit, a.err);
+          __syncthreads();
           bstamp(a, layer, ph, 1);
-          // second operand: this wavefront's column slice of every message, and the messages' 1/rms
-          {
-            // 1/rms: every workgroup published the sum of squares of the rows it owns, per message
-            {
-              const int j = threadIdx.x >> 5, c = threadIdx.x & 31;
-              float t = 0.f;
-              if (j < m) {
-                const tagged_t* src = a.ssq + (long)j * nwg;
-                for (int w0 = c; w0 < nwg; w0 += 256) {
-                  tagged_t raw[8];
+          float sum2 = 0.f, sum1 = 0.f;                              // this thread's share of its message's sums
+          if (sj < m) {
+            await_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); }, epoch, a.spin_limit, a.err);
 #pragma unroll
-                  for (int k = 0; k < 8; ++k) raw[k] = w0 + 32 * k < nwg ? ld_raw(src + w0 + 32 * k) : 0ull;
+            for (int k = 0; k < 8; ++k) sum2 += sc + 32 * k < nwg ? tag_value(sqr[k]) : 0.f;
+            if (ln) {
+              poll_words(sqr, [&](int k, uint32_t z) { return sum_at(ssum_in, k, z); }, epoch, a.spin_limit, a.err);
 #pragma unroll
-                  for (int k = 0; k < 8; ++k)
-                    if (w0 + 32 * k < nwg) t += settle(src + w0 + 32 * k, raw[k], epoch, a.spin_limit, a.err);
-                }
-              }
-#pragma unroll
-              for (int off = 16; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
-              if (!ln) {
-                if (j < m && c == 0) rscale[j] = 1.f / sqrtf(t / (float)a.d + a.eps);
-              } else {
-                // LayerNorm: the sums the same way, then 1/std and mean/std
-                float u = 0.f;
-                if (j < m) {
-                  const tagged_t* src = a.ssum + (long)j * nwg;
-                  for (int w0 = c; w0 < nwg; w0 += 32) u += settle(src + w0, ld_raw(src + w0), epoch, a.spin_limit, a.err);
-                }
-#pragma unroll
-                for (int off = 16; off >= 1; off >>= 1) u += __shfl_xor(u, off, 64);
-                if (j < m && c == 0) {
-                  const float mean = u / (float)a.d;
-                  const float rstd = 1.f / sqrtf(fmaxf(t / (float)a.d - mean * mean, 0.f) + a.eps);
-                  rscale[j] = rstd; rshift[j] = rstd * (mean - rcen[j]);
-                  rcen[j] = mean;                      // what the next norm's vector is published around
-                }
-              }
+              for (int k = 0; k < 8; ++k) sum1 += sc + 32 * k < nwg ? tag_value(sqr[k]) : 0.f;
             }
-            // the slice, as published: bf16 pairs of x * gain
-            const MDI_GLOBAL tagged_t* bbase = (const MDI_GLOBAL tagged_t*)xn_in + ((long)g.ks0 << 8);
-            const uint32_t boff = (uint32_t)((kg << 6) + lane_msg);
-            const int last = max(g.nks - 1, 0);
-            uint32_t bad = 0u;
-#pragma unroll
-            for (int h0 = 0; h0 < kResSteps; h0 += 4) {
-              if (h0 == 0 || h0 < g.nks) {           // uniform: a batch of steps that lies past the slice costs no round trip
-                tagged_t raw[4][4];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {        // steps past the slice repeat its last one: every register gets a value
-                  const MDI_GLOBAL tagged_t* p = bbase + ((long)min(h0 + s, last) << 8) + boff;
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) raw[s][e] = ld_word(p + (e << 4));
-                }
-#pragma unroll
-                for (int s = 0; s < 4; ++s) Bv[h0 + s] = take4(raw[s][0], raw[s][1], raw[s][2], raw[s][3], epoch, bad);
-              } else {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) Bv[h0 + s] = Bv[0];
-              }
-            }
-            if (__any(bad != 0u)) {                  // rare: every step again at agent scope, until its words carry the counter
-#pragma unroll
-              for (int ks = 0; ks < kResSteps; ++ks) {
-                const tagged_t* p = xn_in + ((long)(g.ks0 + min(ks, last)) << 8) + boff;
-                u32x4 bw;
-                bw.x = settle_bits(p, ld_raw(p), epoch, a.spin_limit, a.err); bw.y = settle_bits(p + 16, ld_raw(p + 16), epoch, a.spin_limit, a.err);
-                bw.z = settle_bits(p + 32, ld_raw(p + 32), epoch, a.spin_limit, a.err); bw.w = settle_bits(p + 48, ld_raw(p + 48), epoch, a.spin_limit, a.err);
-                Bv[ks] = __builtin_bit_cast(bf16x8, bw);
-              }
+            for (int w = sc + 256; w < nwg; w += 32) {               // (more than 256 workgroups)
+              auto at = [&](const tagged_t* v, uint32_t z) { return word_at(v, (uint32_t)(sj * nwg + w) * 8u + z); };
+              tagged_t one[1];
+              poll_words(one, [&](int, uint32_t z) { return at(ssq_in, z); }, epoch, a.spin_limit, a.err);
+              sum2 += tag_value(one[0]);
+              if (ln) { poll_words(one, [&](int, uint32_t z) { return at(ssum_in, z); }, epoch, a.spin_limit, a.err); sum1 += tag_value(one[0]); }
             }
           }
+          auto fetch4 = [&](int h0, bf16x8& v0, bf16x8& v1, bf16x8& v2, bf16x8& v3) __attribute__((always_inline)) {
+            if (h0 == 0 || h0 < g.nks) {             // uniform: a batch of steps that lies past the slice costs no round trip
+              tagged_t xr[16];                         // steps past the slice repeat its last one: every register gets a value
+              poll_words(xr, [&](int s, uint32_t z) { return step_at(h0 + (s >> 2), s & 3, z); }, epoch, a.spin_limit, a.err);
+              auto low4 = [&](int s) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, u32x4{(uint32_t)xr[s], (uint32_t)xr[s + 1], (uint32_t)xr[s + 2], (uint32_t)xr[s + 3]}); };
+              v0 = low4(0); v1 = low4(4); v2 = low4(8); v3 = low4(12);
+            } else {
+              v0 = Bv[0]; v1 = Bv[0]; v2 = Bv[0]; v3 = Bv[0];
+            }
+          };
+          fetch4(0, Bv[0], Bv[1], Bv[2], Bv[3]); fetch4(4, Bv[4], Bv[5], Bv[6], Bv[7]);
+          fetch4(8, Bv[8], Bv[9], Bv[10], Bv[11]); fetch4(12, Bv[12], Bv[13], Bv[14], Bv[15]);
           bstamp(a, layer, ph, 2);
           // the stream: two tiles in flight, each multiplied while the other's rows arrive
           if (g.nks > 8) {
 #pragma nounroll
-            for (int lb = 0; lb < g.nb_local; ++lb) {
-              res_compute<0, false>(A, g, lb, Bv, acc, part, wave, lane);
-              res_issue<0>(A, g, lb + 1, wg, nwg, lane);
-              res_compute<1, true>(B, g, lb, Bv, acc, part, wave, lane);
-              res_issue<1>(B, g, lb + 1, wg, nwg, lane);
+            for (int lb = 1; lb < g.nb_local; ++lb) {
+              res_compute<0, false>(A, g, lb - 1, Bv, acc, part, wave, lane);
+              res_issue<0>(A, g, lb, wg, nwg, lane);
+              res_compute<1, true>(B, g, lb - 1, Bv, acc, part, wave, lane);
+              res_issue<1>(B, g, lb, wg, nwg, lane);
             }
+            res_compute<0, false>(A, g, g.nb_local - 1, Bv, acc, part, wave, lane);
+            res_compute<1, true>(B, g, g.nb_local - 1, Bv, acc, part, wave, lane);
           } else {
+            int lb = 0;
 #pragma nounroll
-            for (int lb = 0; lb < g.nb_local; lb += 2) {
+            for (; lb + 2 < g.nb_local; lb += 2) {
               res_compute<0, true>(A, g, lb, Bv, acc, part, wave, lane);
               res_issue<0>(A, g, lb + 2, wg, nwg, lane);
               res_compute<0, true>(B, g, lb + 1, Bv, acc, part, wave, lane);
               res_issue<0>(B, g, lb + 3, wg, nwg, lane);
             }
+            res_compute<0, true>(A, g, lb, Bv, acc, part, wave, lane);
+            res_compute<0, true>(B, g, lb + 1, Bv, acc, part, wave, lane);
+          }
+          bstamp(a, layer, ph, 7);
+          // 1/rms of every message.  The shares of all workgroups have been seen before anything of this phase is stored
+          // (see the top of the file).
+#pragma unroll
+          for (int off = 16; off >= 1; off >>= 1) { sum2 += __shfl_xor(sum2, off, 64); if (ln) sum1 += __shfl_xor(sum1, off, 64); }
+          if (sj < m && sc == 0) {
+            if (!ln) {
+              rscale[sj] = 1.f / sqrtf(sum2 / (float)a.d + a.eps);
+            } else {
+              const float mean = sum1 / (float)a.d;
+              const float rstd = 1.f / sqrtf(fmaxf(sum2 / (float)a.d - mean * mean, 0.f) + a.eps);
+              rscale[sj] = rstd; rshift[sj] = rstd * (mean - rcen[sj]);
+              rcen[sj] = mean;                                       // what the next norm's vector is published around
+            }
           }
         } else {
-          {
-            // ---- a product whose inner dimension is split among workgroups (see KsGeo)
-            const KsGeo kq = make_ksgeo(N, Kd, a.str_S, a.str_oct, wg, wave);
-            Tile A, B;
-            const uint32_t woff = (uint32_t)min(kq.blk * 16 + (lane & 15), N - 1) * (uint32_t)g.row_bytes + (uint32_t)(kg << 4);
-            ks_issue(A, kq, g.W, woff, 0);
-            ks_issue(B, kq, g.W, woff, 1);
-            if (!barrier(epoch)) return;
-            bstamp(a, layer, ph, 1);
-            // the slice of every message's vector, validated word by word, to LDS as [group of 8 columns][message]
-            u32x4* Bs = reinterpret_cast<u32x4*>(part + (a.str_S << 8));
-            {
-              const tagged_t* bvec = ph == PH_OPROJ ? ob_l : ub_l;
-              for (int u0 = threadIdx.x; u0 < kq.nk * 64; u0 += 2 * kStepThreads) {
-                tagged_t raw[2][4];
-                const tagged_t* src[2];
+          // ---- a product whose inner dimension is split among workgroups (see KsGeo)
+          const KsGeo kq = make_ksgeo(N, Kd, a.str_S, ph == PH_OPROJ ? a.str_c[0] : a.str_c[1], a.str_oct, ks_q, ks_s, wave);
+          Tile A, B;
+          const uint32_t woff = (uint32_t)min(kq.blk * 16 + (lane & 15), N - 1) * (uint32_t)g.row_bytes + (uint32_t)(kg << 4);
+          // the slice of every message's vector to LDS as [group of 8 columns][message]
+          u32x4* Bs = reinterpret_cast<u32x4*>(part);
+          const tagged_t* bvec = ph == PH_OPROJ ? ob_l : ub_l;
+          const int n_units = kq.nk * 4 * m;                         // unit: eight columns of one message
+          tagged_t raw[8] = {};
+          int gi[2], n[2];
+          auto unit_of = [&](int u0) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                  const int u = min(u0 + r * kStepThreads, kq.nk * 64 - 1);
-                  const int gi = u >> 4, n = min(u & 15, m - 1);
-                  src[r] = bvec + ((long)(kq.k0 * 4 + gi) << 6) + n;       // pairs 4 (4 k0 + gi) .. + 3, 16 words apart
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) raw[r][e] = ld_raw(src[r] + (e << 4));
-                }
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                  const int u = u0 + r * kStepThreads;
-                  u32x4 v;
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) v[e] = settle_bits(src[r] + (e << 4), raw[r][e], epoch, a.spin_limit, a.err);
-                  if (u < kq.nk * 64) { const int gi = u >> 4; Bs[gi * 16 + ((u & 15) ^ (gi & 15))] = v; }
-                }
-              }
+            for (int r = 0; r < 2; ++r) {
+              const int u = max(min(u0 + r * kStepThreads, n_units - 1), 0);
+              gi[r] = (int)__umulhi((unsigned)u, a.m_magic); n[r] = u - gi[r] * m;
             }
-            __syncthreads();
-            bstamp(a, layer, ph, 2);
-            acc = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (kq.live) {                                             // uniform per wavefront
-              const int nt = ((kq.nk + 7) >> 3) + 1 & ~1;
+          };
+          auto at = [&](int r, uint32_t z) __attribute__((always_inline)) {   // pairs 4 (4 k0 + gi) .. + 3
+            return word_at(bvec + (long)kq.k0 * (16 * m) + (r & 3) * m, (uint32_t)(4 * gi[r >> 2] * m + n[r >> 2]) * 8u + z);
+          };
+          unit_of(tid);
+          if (n_units) ask_words(raw, at);
+          ks_issue(A, kq, g.W, woff, 0);
+          ks_issue(B, kq, g.W, woff, 1);
+          for (int u0 = tid; u0 < n_units; u0 += 2 * kStepThreads) {
+            if (u0 != tid) { unit_of(u0); ask_words(raw, at); }
+            await_words(raw, at, epoch, a.spin_limit, a.err);
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+              if (u0 + r * kStepThreads < n_units)
+                Bs[gi[r] * 16 + (n[r] ^ (gi[r] & 15))] = u32x4{(uint32_t)raw[4 * r], (uint32_t)raw[4 * r + 1], (uint32_t)raw[4 * r + 2], (uint32_t)raw[4 * r + 3]};
+          }
+          __syncthreads();
+          bstamp(a, layer, ph, 2);
+          acc = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (kq.live) {                                             // uniform per wavefront
+            const int nt = ((kq.nk + 7) >> 3) + 1 & ~1;
 #pragma nounroll
-              for (int t = 0; t < nt; t += 2) {
-                ks_compute(A, kq, Bs, t, lane, acc);
-                ks_issue(A, kq, g.W, woff, t + 2);
-                ks_compute(B, kq, Bs, t + 1, lane, acc);
-                ks_issue(B, kq, g.W, woff, t + 3);
-              }
+            for (int t = 2; t < nt; t += 2) {
+              ks_compute(A, kq, Bs, t - 2, lane, acc);
+              ks_issue(A, kq, g.W, woff, t);
+              ks_compute(B, kq, Bs, t - 1, lane, acc);
+              ks_issue(B, kq, g.W, woff, t + 1);
             }
-            // the partial of (block, slice), zeros from a slice without columns, to the block's owner
-            if (kq.q < a.str_oct && kq.blk < kq.nblk) {
-              tagged_t* dst = a.ppart + (((long)kq.blk * kq.S + kq.s) << 8) + (lane << 2);
+            ks_compute(A, kq, Bs, nt - 2, lane, acc);
+            ks_compute(B, kq, Bs, nt - 1, lane, acc);
+          }
+          // the partial of (block, slice), zeros from a slice without columns, to the block's owner
+          if (kq.q < a.str_oct && kq.blk < kq.nblk && (lane & 15) < m) {
+            tagged_t* dst = a.ppart + ((long)((kq.blk * kq.S + kq.s) * 4 + kg) * m + (lane & 15)) * 4;
 #pragma unroll
-              for (int r = 0; r < 4; ++r) st_tag(dst + r, acc[r], wtag);
-            }
-            acc = f32x4{0.f, 0.f, 0.f, 0.f};
-            bstamp(a, layer, ph, 7);
-            // the owner of block wg collects its S partials into the slots the epilogue adds up
+            for (int r = 0; r < 4; ++r) st_tag(dst + r, acc[r], wtag);
+          }
+          acc = f32x4{0.f, 0.f, 0.f, 0.f};
+          bstamp(a, layer, ph, 7);
+          // ---- residual products: x += W v (+ bias) on the 16 rows this workgroup owns; what leaves is x times the gain
+          // of the norm that follows, as bf16 pairs, and this workgroup's share of every message's sum of squares (every
+          // workgroup's, also without rows: see the top of the file).  One lane per (message, row pair), which adds the S
+          // partials in slice order.
+          tagged_t* xn_out = ph == PH_OPROJ ? a.xn[1] : a.xn[0];
+          tagged_t* ssq_out = ph == PH_OPROJ ? a.ssq[1] : a.ssq[0];
+          tagged_t* ssum_out = ph == PH_OPROJ ? a.ssum[1] : a.ssum[0];
+          const int j = tid >> 3, p = tid & 7, r0 = wg * 16 + 2 * p;
+          if (j < m) {
+            float s2 = 0.f, s1 = 0.f;
             if (wg < kq.nblk) {
-              const tagged_t* srcp = a.ppart + ((long)wg * kq.S << 8);
-              for (int u0 = threadIdx.x; u0 < (kq.S << 8); u0 += 4 * kStepThreads) {
-                tagged_t raw[4];
+              const tagged_t* srcp = a.ppart + (long)wg * kq.S * (16 * m);
+              const uint32_t off = (uint32_t)((p >> 1) * m + j) * 32u + (uint32_t)(p & 1) * 16u;
+              float d0 = 0.f, d1 = 0.f;
+              auto add = [&](auto n_const) __attribute__((always_inline)) {
+                constexpr int NS = decltype(n_const)::value;
+                tagged_t raw[2 * NS];                                // slices past the last repeat it
+                poll_words(raw, [&](int k, uint32_t z) { return word_at(srcp + min(k >> 1, kq.S - 1) * (16 * m) + (k & 1), off + z); }, wtag, a.spin_limit, a.err);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) raw[r] = ld_raw(srcp + min(u0 + r * kStepThreads, (kq.S << 8) - 1));
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                  const int u = u0 + r * kStepThreads;
-                  const float v = settle(srcp + min(u, (kq.S << 8) - 1), raw[r], wtag, a.spin_limit, a.err);
-                  if (u < (kq.S << 8)) part[u] = v;
+                for (int k = 0; k < NS; ++k) { d0 += k < kq.S ? tag_value(raw[2 * k]) : 0.f; d1 += k < kq.S ? tag_value(raw[2 * k + 1]) : 0.f; }
+              };
+              if (kq.S <= 8) add(std::integral_constant<int, 8>()); else add(std::integral_constant<int, 16>());
+              if (r0 < g.N) {
+                float* xr = xres + 2 * p * 16 + j;
+                const float x0 = xr[0] + d0 + ops.b0, x1 = xr[16] + d1 + ops.b1;
+                xr[0] = x0; xr[16] = x1;
+                if (last) {
+                  store_kind(sl.out[j], a.act_kind, r0, x0); store_kind(sl.out[j], a.act_kind, r0 + 1, x1);
+                } else {
+                  st_pair(xn_out + (r0 >> 1) * m + j, pack_bf16x2((x0 - rcen[j]) * ops.g0, (x1 - rcen[j]) * ops.g1), wtag);
+                  s2 = x0 * x0 + x1 * x1; s1 = x0 + x1;
                 }
               }
             }
+            if (!last) publish_sums(s2, s1, p, ssq_out + j * nwg + wg, ln ? ssum_out + j * nwg + wg : nullptr, wtag);
           }
         }
         bstamp(a, layer, ph, 3);
-        __syncthreads();                                             // every wavefront's partial products are in LDS
+        if (ph == PH_QKV || ph == PH_UP) __syncthreads();            // every wavefront's partial products are in LDS
         bstamp(a, layer, ph, 4);
 
-        // ---- epilogue: one thread per (block, row pair, message)
-        const int R = g.R, half = R >> 1;
+        // ---- epilogue of the normed products: one thread per (block, row pair or quad, message)
         if (ph == PH_QKV) {
-          for (int e = threadIdx.x; e < g.nb_local * half * m; e += kStepThreads) {
-            const int j = e % m, p = (e / m) % half, lb = e / (m * half);
+          for (int e = tid; e < n_items; e += kStepThreads) {
+            const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
+              const int j = it.j, p = it.p, lb = it.lb;
             const int r0 = block_row(g, lb * nwg + wg, p), r1 = r0 + (a.h >> 1);
             float v0 = part_sum(part, lb, p, j) * rscale[j], v1 = part_sum(part, lb, p + half, j) * rscale[j];
-            if (ln) { v0 += nc[N + r0] - rshift[j] * nc[r0]; v1 += nc[N + r1] - rshift[j] * nc[r1]; }
-            if (Lv.bqkv) { v0 += Lv.bqkv[r0]; v1 += Lv.bqkv[r1]; }
+            if (ln) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }
+            v0 += ops.b0; v1 += ops.b1;
             const int head = r0 / a.h, i = r0 - head * a.h;
-            const float2* rope = sl.rope[j];
-            if (rope && head < a.H + a.K) {
-              const float2 cs = rope[i];
-              const float t0 = v0 * cs.x - v1 * cs.y, t1 = v0 * cs.y + v1 * cs.x;
+            if (sl.rope[j] && head < a.H + a.K) {
+              const float t0 = v0 * ops.g0 - v1 * ops.g1, t1 = v0 * ops.g1 + v1 * ops.g0;
               v0 = t0; v1 = t1;
             }
             char* base = a.slot0 + (long)j * a.slot_stride;
@@ -687,15 +715,16 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
               WT* dst = (WT*)Lv.kv + sl.kv_off[j] + (long)(kvh * 2 + (is_v ? 1 : 0)) * a.pt_h + i;
               Storage<WT>::put(dst, v0); Storage<WT>::put(dst + (a.h >> 1), v1);
               tagged_t* kn = (tagged_t*)(base + a.off_knew) + (long)(is_v ? a.K * a.h : 0) + kvh * a.h + i;
-              st_tag(kn, Storage<WT>::get(dst), wtag); st_tag(kn + (a.h >> 1), Storage<WT>::get(dst + (a.h >> 1)), wtag);
+              st_tag(kn, bf16_to_f32(f32_to_bf16(v0)), wtag); st_tag(kn + (a.h >> 1), bf16_to_f32(f32_to_bf16(v1)), wtag);
             }
+            if (e + kStepThreads < n_items) ops = epi_ops(a, Lv, g, sl, nc, ph, last, e + kStepThreads, n_items, n_sh, wg, nwg);
           }
         } else if (ph == PH_UP) {
           if (a.mlp_kind == MDI_MLP_SWIGLU) {
             // rows (4q .. 4q + 3) = (gate_f, up_f, gate_f+1, up_f+1): one lane of every wavefront's result holds all four
-            const int quads = R >> 2;
-            for (int e = threadIdx.x; e < g.nb_local * quads * m; e += kStepThreads) {
-              const int j = e % m, qd = (e / m) % quads, lb = e / (m * quads);
+            for (int e = tid; e < n_items; e += kStepThreads) {
+              const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
+              const int j = it.j, qd = it.p, lb = it.lb;
               const int r0 = (lb * nwg + wg) * R + 4 * qd;
               if (r0 < g.N) {
                 const float* pp = part + ((lb * kStepWaves) << 8) + (((qd << 4) + j) << 2);
@@ -710,73 +739,32 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
                   v.z += nc[N + r0 + 2] - sh * nc[r0 + 2]; v.w += nc[N + r0 + 3] - sh * nc[r0 + 3];
                 }
                 const float u0 = silu_f(v.x) * v.y, u1 = silu_f(v.z) * v.w;
-                st_pair(ub_l + ((r0 >> 2) << 4) + j, pack_bf16x2(u0, u1), wtag);
+                st_pair(ub_l + (r0 >> 2) * m + j, pack_bf16x2(u0, u1), wtag);
               }
             }
           } else {
             const bool tanh_form = a.mlp_kind == MDI_MLP_GELU_TANH;
-            for (int e = threadIdx.x; e < g.nb_local * half * m; e += kStepThreads) {
-              const int j = e % m, p = (e / m) % half, lb = e / (m * half);
+            for (int e = tid; e < n_items; e += kStepThreads) {
+              const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
+              const int j = it.j, p = it.p, lb = it.lb;
               const int r0 = (lb * nwg + wg) * R + 2 * p;
               if (r0 < g.N) {
                 float v0 = part_sum(part, lb, 2 * p, j) * rscale[j], v1 = part_sum(part, lb, 2 * p + 1, j) * rscale[j];
-                if (ln) { v0 += nc[N + r0] - rshift[j] * nc[r0]; v1 += nc[N + r0 + 1] - rshift[j] * nc[r0 + 1]; }
-                if (Lv.bup) { v0 += Lv.bup[r0]; v1 += Lv.bup[r0 + 1]; }
-                st_pair(ub_l + ((r0 >> 1) << 4) + j, pack_bf16x2(tanh_form ? gelu_tanh_f(v0) : gelu_erf_f(v0), tanh_form ? gelu_tanh_f(v1) : gelu_erf_f(v1)), wtag);
+                if (ln) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }
+                v0 += ops.b0; v1 += ops.b1;
+                st_pair(ub_l + (r0 >> 1) * m + j, pack_bf16x2(tanh_form ? gelu_tanh_f(v0) : gelu_erf_f(v0), tanh_form ? gelu_tanh_f(v1) : gelu_erf_f(v1)), wtag);
               }
-            }
-          }
-        } else {
-          // residual products: x += W v (+ bias) on the rows this workgroup owns; what leaves is x times the gain of the
-          // norm that follows, as bf16 pairs, and this workgroup's share of every message's sum of squares
-          const float* bias = ph == PH_OPROJ ? Lv.bo : Lv.bdown;
-          const bool last = ph == PH_DOWN && layer == a.n_layer - 1;
-          const float* gain = ph == PH_OPROJ ? Lv.ln2_g : advance(Lv.ln1_g, a.w_stride);
-          const int n_items = g.nb_local * half * m;
-          for (int e = threadIdx.x; e < n_items; e += kStepThreads) {
-            const int j = e % m, p = (e / m) % half, lb = e / (m * half);
-            const int r0 = (lb * nwg + wg) * R + 2 * p;
-            float s2 = 0.f;
-            if (r0 < g.N) {
-              float* xr = xres + ((lb << 4) + 2 * p) * 16 + j;
-              const float d0 = part_sum_n(part, 2 * p, j, a.str_S), d1 = part_sum_n(part, 2 * p + 1, j, a.str_S);
-              const float x0 = xr[0] + d0 + (bias ? bias[r0] : 0.f);
-              const float x1 = xr[16] + d1 + (bias ? bias[r0 + 1] : 0.f);
-              xr[0] = x0; xr[16] = x1;
-              if (last) {
-                store_kind(sl.out[j], a.act_kind, r0, x0); store_kind(sl.out[j], a.act_kind, r0 + 1, x1);
-              } else {
-                st_pair(xn_out + ((r0 >> 1) << 4) + j, pack_bf16x2((x0 - rcen[j]) * gain[r0], (x1 - rcen[j]) * gain[r0 + 1]), wtag);
-                s2 = x0 * x0 + x1 * x1;
-              }
-            }
-            sq[e] = s2;
-          }
-          if (!last) {
-            __syncthreads();
-            if ((int)threadIdx.x < m) {
-              float t = 0.f;
-              for (int e = threadIdx.x; e < n_items; e += m) t += sq[e];
-              st_tag(a.ssq + (long)threadIdx.x * nwg + wg, t, wtag);
-              if (ln) {
-                float u = 0.f;
-                for (int e = threadIdx.x; e < n_items; e += m) {
-                  const int p = (e / m) % half, lb = e / (m * half);
-                  if ((lb * nwg + wg) * R + 2 * p < g.N) { const float* xr = xres + ((lb << 4) + 2 * p) * 16 + threadIdx.x; u += xr[0] + xr[16]; }
-                }
-                st_tag(a.ssum + (long)threadIdx.x * nwg + wg, u, wtag);
-              }
+              if (e + kStepThreads < n_items) ops = epi_ops(a, Lv, g, sl, nc, ph, last, e + kStepThreads, n_items, n_sh, wg, nwg);
             }
           }
         }
       }
 
-      // ---- publish: this workgroup is done with the phase
+      // ---- the partial products and the attention's records in LDS have been read
       bstamp(a, layer, ph, 5);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       __syncthreads();
       bstamp(a, layer, ph, 6);
-      if (threadIdx.x == 0) __hip_atomic_store(a.flags + wg * kFlagStride, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (s_flag[kFailed]) return;                                   // a bounded wait expired: everybody else's will, too
     }
   }
 }

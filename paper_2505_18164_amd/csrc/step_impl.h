@@ -46,6 +46,8 @@
 //
 // This file is the kernel's body; step_w4.hip and step_w8.hip compile it for workgroups of four and of
 // eight wavefronts (MDI_STEP_WAVES), each in a namespace of its own with a launcher of its own.
+#include <type_traits>
+
 #include "device_utils.h"
 
 #ifndef MDI_STEP_WAVES
@@ -121,6 +123,43 @@ __device__ __forceinline__ float* lds_red() { extern __shared__ float smem[]; re
 __device__ __forceinline__ int* lds_flag() { extern __shared__ float smem[]; return (int*)(smem + 16); }
 __device__ __forceinline__ float* lds_part() { extern __shared__ float smem[]; return smem + kLdsPart; }
 __device__ __forceinline__ float* lds_vec(int part_floats) { extern __shared__ float smem[]; return smem + kLdsPart + part_floats; }
+
+// N words at once, asked for again until all of a thread's carry the counter `tag`: one round trip however many were
+// early (word by word, eight early words cost eight).  Asked for before a phase's weights, awaited after: loads return
+// in order, and the workgroup that everybody waits for finds its words there.  A wait that expires raises the error word and the workgroup's
+// failure flag.
+constexpr int kFailed = 2;               // index in lds_flag()
+// at(i, z): the address of word i; z is zero, and unknown to the compiler, so that addresses are not kept in registers
+// over the loop.
+__device__ __forceinline__ const MDI_GLOBAL tagged_t* word_at(const tagged_t* base, uint32_t bytes) {
+  return (const MDI_GLOBAL tagged_t*)((const MDI_GLOBAL char*)base + bytes);
+}
+__device__ __forceinline__ tagged_t ld_word(const MDI_GLOBAL tagged_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <int N, typename AT>
+__device__ __forceinline__ void ask_words(tagged_t (&raw)[N], const AT& at) {
+  uint32_t z = 0u;
+  asm volatile("" : "+v"(z));
+#pragma unroll
+  for (int i = 0; i < N; ++i) raw[i] = ld_word(at(i, z));
+}
+template <int N, typename AT>
+__device__ __forceinline__ void await_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err) {
+  int it = 0;
+  while (true) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) bad |= (uint32_t)(raw[i] >> 32) != tag;
+    if (!bad) break;
+    if (++it > spin_limit) { lds_flag()[kFailed] = 1; __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
+    __builtin_amdgcn_s_sleep(1);
+    ask_words(raw, at);
+  }
+}
+template <int N, typename AT>
+__device__ __forceinline__ void poll_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err) {
+  ask_words(raw, at);
+  await_words(raw, at, tag, spin_limit, err);
+}
 
 // ---------------------------------------------------------------------------
 // vector staging: n floats written earlier in this launch by other workgroups -> LDS
@@ -587,17 +626,39 @@ template <typename WT, int G, typename AR, typename SL>
 __device__ __forceinline__ void attn_stream(AttnState<WT, G>& st, Tile& A, Tile& B, int (&pgA)[kTile], int (&pgB)[kTile], const AttnGeo& ga,
                                             const AR& a, const SL& S, const void* kv, int nte, int wave, const float* xs) {
 #pragma nounroll
-  for (int t = 0; t < nte; t += 2) {
-    attn_compute<WT, G>(st, A, ga, a.h, t, wave, xs);
-    attn_issue<WT>(A, pgA, ga, a, S, kv, t + 2, wave);
-    attn_compute<WT, G>(st, B, ga, a.h, t + 1, wave, xs);
-    attn_issue<WT>(B, pgB, ga, a, S, kv, t + 3, wave);
+  for (int t = 2; t < nte; t += 2) {
+    attn_compute<WT, G>(st, A, ga, a.h, t - 2, wave, xs);
+    attn_issue<WT>(A, pgA, ga, a, S, kv, t, wave);
+    attn_compute<WT, G>(st, B, ga, a.h, t - 1, wave, xs);
+    attn_issue<WT>(B, pgB, ga, a, S, kv, t + 1, wave);
+  }
+  if (nte) {                               // (the last two tiles: nothing more to ask for)
+    attn_compute<WT, G>(st, A, ga, a.h, nte - 2, wave, xs);
+    attn_compute<WT, G>(st, B, ga, a.h, nte - 1, wave, xs);
   }
 }
 
-// queries into LDS (pre-scaled); the newest position through coherent loads
+// What attention reads of this launch's QKV product: this thread's word of the queries, and in the last wavefront (the
+// one with the fewest query words) the newest position's K/V row, already rounded to the storage type.
+template <typename WT> struct AttnAsk { tagged_t q[1], kv[2 * Storage<WT>::kVec]; };
 template <typename WT, int G, typename AR, typename SL>
-__device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, const AttnGeo& g, const AR& a, const SL& S, float* qs, unsigned epoch) {
+__device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_q_at(const AttnGeo& g, const AR& a, const SL& S, int i, uint32_t z) {
+  return word_at(S.q + (long)g.hg * G * a.h, (uint32_t)min(i, G * a.h - 1) * 8u + z);
+}
+template <typename WT, typename AR, typename SL>
+__device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_kv_at(const AttnGeo& g, const AR& a, const SL& S, int e, uint32_t z) {
+  constexpr int V = Storage<WT>::kVec;
+  return word_at(S.knew + g.kvh * a.h + (e < V ? (long)e : (long)a.K * a.h + e - V), (uint32_t)g.hoff * 8u + z);
+}
+template <typename WT, int G, typename AR, typename SL>
+__device__ __forceinline__ void attn_ask(AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, int wave) {
+  if (!g.active) return;
+  ask_words(k.q, [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, (int)threadIdx.x, z); });
+  if (g.s1 == S.ctx && wave == kStepWaves - 1) ask_words(k.kv, [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, S, e, z); });
+}
+// queries into LDS (pre-scaled), the newest position into the last wavefront's running sums
+template <typename WT, int G, typename AR, typename SL>
+__device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, float* qs, int wave, unsigned epoch) {
   constexpr int V = Storage<WT>::kVec;
 #pragma unroll
   for (int gi = 0; gi < G; ++gi) {
@@ -605,21 +666,21 @@ __device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, const AttnGeo& 
 #pragma unroll
     for (int e = 0; e < V; ++e) st.o[gi][e] = 0.f;
   }
-  if (g.active)
-    for (int i = threadIdx.x; i < G * a.h; i += kStepThreads)
-      qs[i] = ld_tag(S.q + (long)g.hg * G * a.h + i, epoch, a.spin_limit, a.err) * a.scale;
+  const bool newest = g.active && g.s1 == S.ctx && wave == kStepWaves - 1;
+  if (g.active) {
+    for (int i = threadIdx.x; i < G * a.h; i += kStepThreads) {
+      auto at = [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, i, z); };
+      if (i != (int)threadIdx.x) ask_words(k.q, at);
+      await_words(k.q, at, epoch, a.spin_limit, a.err);
+      qs[i] = tag_value(k.q[0]) * a.scale;
+    }
+    if (newest) await_words(k.kv, [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, S, e, z); }, epoch, a.spin_limit, a.err);
+  }
   __syncthreads();
-  if (g.active && g.s1 == S.ctx && threadIdx.x < 64) {
-    // the newest position: its K/V row (already rounded to the storage type) from the tagged copy
+  if (newest) {
     float kf[V], vf[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) { kf[e] = 0.f; vf[e] = 0.f; }
-    if (g.sub == 0) {
-      const tagged_t* kn = S.knew + g.kvh * a.h + g.hoff;
-      const tagged_t* vn = kn + (long)a.K * a.h;
-#pragma unroll
-      for (int e = 0; e < V; ++e) { kf[e] = ld_tag(kn + e, epoch, a.spin_limit, a.err); vf[e] = ld_tag(vn + e, epoch, a.spin_limit, a.err); }
-    }
+    for (int e = 0; e < V; ++e) { kf[e] = g.sub == 0 ? tag_value(k.kv[e]) : 0.f; vf[e] = g.sub == 0 ? tag_value(k.kv[V + e]) : 0.f; }
     attn_update_f<WT, G>(st, g, a.h, kf, vf, g.sub == 0, qs);
   }
 }
@@ -768,7 +829,8 @@ __device__ __forceinline__ StepLayer layer_at(const AR& a, int layer) {
   return L;
 }
 __device__ __forceinline__ const void* layer_matrix(const StepLayer& L, int j) {
-  return j == 0 ? L.wqkv : j == 1 ? L.wo : j == 2 ? L.wup : L.wdown;
+  const void *w0 = L.wqkv, *w1 = L.wo, *w2 = L.wup, *w3 = L.wdown;   // all read first: a selected field would put the struct into scratch memory
+  return j == 0 ? w0 : j == 1 ? w1 : j == 2 ? w2 : w3;
 }
 
 template <typename WT, int G>
@@ -922,7 +984,9 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
 
         if (ph == PH_ATTN) {
           // ---- attention over the sample's pages -----------------------------------------------------
-          attn_begin<WT, G>(st, ga, a, S, xs, epoch);
+          AttnAsk<WT> ask{};
+          attn_ask<WT, G>(ask, ga, a, S, wave);
+          attn_begin<WT, G>(st, ask, ga, a, S, xs, wave, epoch);
           stamp(a, S, layer, ph, 2);
           const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
           attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, S, L->kv, nte, wave, xs);

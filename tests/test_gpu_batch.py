@@ -59,6 +59,25 @@ def test_batched_pass_against_the_oracle(name, n_msg):
     print(f"{name} x{n_msg}: worst rel-L2 {worst:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("name", ["gqa_h16", "wide", "gpt2_like"])
+def test_the_number_of_messages_changes_from_pass_to_pass(name):
+    """The exchange vectors are packed by the pass's number of messages: passes of different sizes leave words at
+    different places of the same arrays, and none may pass for a later one's."""
+    cfg = S.tiny(n_layer=3, dtype=S.DT_BF16, max_ctx=64, vocab=211, **SHAPES[name])
+    w = scale_matrices(S.make_weights(cfg, 23, exercise=True), 2.0)
+    o, g = pair(cfg, w, 0, 3, embed=True, head=False, max_seqs=16, kv_page_tokens=8)
+    for s, ids in enumerate(S.make_prompts(cfg, 23, 16, 5)):
+        check(g.prefill(s, dev_ids(ids)), o.prefill(s, ids), cfg, ("prefill", s))
+    rng = np.random.default_rng(5)
+    for step, n in enumerate([16, 2, 3, 16, 7, 15, 2, 9, 13, 4]):
+        order = [int(s) for s in rng.permutation(16)[:n]]
+        toks = [int(rng.integers(0, cfg["vocab"])) for _ in order]
+        outs = g.decode_batch(order, [dev_ids([t]) for t in toks])
+        for s, t, got in zip(order, toks, outs):
+            check(got, o.decode_step(s, t), cfg, ("batched decode", step, s))
+    g.sync()
+
+
 @pytest.mark.parametrize("heads", [2, 4])
 @pytest.mark.parametrize("name", ["gqa_h16", "gqa8_h8", "h64", "idle_wavefronts"])
 def test_batched_pass_with_pairs_of_query_heads_and_context_splits(name, heads, monkeypatch):
