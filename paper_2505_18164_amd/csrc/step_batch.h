@@ -124,6 +124,7 @@ __device__ __forceinline__ int block_row(const BGeo& g, int block, int i) {
 // ---------------------------------------------------------------------------
 // products whose second operand stays in registers (QKV, MLP up): Bv[ks] = this wavefront's column step ks of all
 // messages.  A tile is 8 column steps of a block; with more than 8 steps per wavefront a block is two tiles.
+constexpr int kWatchWords = 2048;
 constexpr int kResSteps = 16;          // column steps a wavefront can keep: widths up to 8 * 16 * 32 = 4096
 template <int HALF>
 __device__ __forceinline__ void res_issue(Tile& t, const BGeo& g, int lb, int wg, int nwg, int lane) {
@@ -210,11 +211,11 @@ __device__ __forceinline__ float part_sum(const float* part, int lb, int i, int 
 // Wavefront records -> split partial, or the finished output when there is one split; the last workgroup of a head
 // group to arrive folds the splits in split order (as attn_finish in step_impl.h).  The output leaves as bf16 pairs.
 template <int G>
-__device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchArgs& a, const BatchView& S, const float* sm, int* s_flag, unsigned epoch) {
+__device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchArgs& a, const BatchView& S, const float* sm, int* s_flag, unsigned epoch, int tid) {
   const unsigned wtag = epoch + 1;
   const int h = a.h, rec = h + 2, hp = h >> 1;
   const bool single = S.n_splits == 1;
-  for (int idx = threadIdx.x; idx < G * hp; idx += kStepThreads) {
+  for (int idx = tid; idx < G * hp; idx += kStepThreads) {
     const int gi = idx / hp, e = (idx - gi * hp) * 2;
     float m = -1e30f;
     for (int w = 0; w < kStepWaves; ++w) m = fmaxf(m, sm[(w * G + gi) * rec + h]);
@@ -236,14 +237,14 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
   if (single) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     const unsigned ticket = __hip_atomic_fetch_add(S.tickets + g.hg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_flag[1] = ticket == (unsigned)S.n_splits - 1;
   }
   __syncthreads();
   if (!s_flag[1]) return;
-  if (threadIdx.x == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (int idx = threadIdx.x; idx < G * hp; idx += kStepThreads) {
+  if (tid == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int idx = tid; idx < G * hp; idx += kStepThreads) {
     const int gi = idx / hp, e = (idx - gi * hp) * 2;
     const int head = g.hg * G + gi;
     const tagged_t* pr = S.part + (long)head * kMaxSplits * rec;
@@ -275,7 +276,7 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
     }
     st_pair(S.ob + (((long)head * h + e) >> 1) * S.n_msg + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
   }
-  if (threadIdx.x == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
+  if (tid == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
 }
 
 __device__ __forceinline__ void bstamp(const BatchArgs& a, int layer, int ph, int k) {
@@ -329,9 +330,9 @@ __device__ __forceinline__ EpiOps epi_ops(const BatchArgs& a, const StepLayer& L
   const int j = it.j, p = it.p, lb = it.lb;
   if (ph == PH_QKV) {
     const int r0 = block_row(g, lb * nwg + wg, p), r1 = r0 + (a.h >> 1);
-    const int head = r0 / a.h;
+    const int head = r0 >> (31 - __builtin_clz(a.h));             // (head sizes are powers of two)
     const float2* rope = sl.rope[j];
-    if (rope && head < a.H + a.K) { const float2 cs = rope[r0 - head * a.h]; o.g0 = cs.x; o.g1 = cs.y; }
+    if (rope && head < a.H + a.K) { const float2 cs = rope[r0 & (a.h - 1)]; o.g0 = cs.x; o.g1 = cs.y; }
     if (L.bqkv) { o.b0 = L.bqkv[r0]; o.b1 = L.bqkv[r1]; }
     if (nc) { o.n[0] = nc[r0]; o.n[1] = nc[r1]; o.n[2] = nc[g.N + r0]; o.n[3] = nc[g.N + r1]; }
     return o;
@@ -465,23 +466,23 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
           V = view_of(a, slot, ob_l);
           ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
-          attn_ask<WT, G>(ask, ga, a, V, wave);
+          attn_ask<WT, G>(ask, ga, a, V, wave, epoch, tid);
           attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
           attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
           bstamp(a, layer, ph, 1);
           while (true) {
-            attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch);
+            attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
             const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
             attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, Lv.kv, nte, wave, part);
             attn_to_lds<WT, G>(st, ga, a.h, part, wave);
-            attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch);
+            attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
             item += nwg;
             if (item >= a.n_items) break;
             __syncthreads();                                       // the records in LDS have been read
             while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
             V = view_of(a, slot, ob_l);
             ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
-            attn_ask<WT, G>(ask, ga, a, V, wave);
+            attn_ask<WT, G>(ask, ga, a, V, wave, epoch, tid);
             attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
             attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
           }
@@ -496,8 +497,10 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         EpiOps ops = epi_ops(a, Lv, g, sl, nc, ph, last, tid, n_items, n_sh, wg, nwg);
         if (ph == PH_QKV || ph == PH_UP) {
           // ---- a product whose second operand stays in registers: this wavefront's column slice of every message, as
-          // published, bf16 pairs of x * gain.  Asked for first, before the weights: the workgroups' first sums of
-          // squares and the sums of squares of all messages.
+          // published, bf16 pairs of x * gain.  Asked for first, before the weights: the sums of squares of all
+          // messages.  Vectors of more than kWatchWords words are looked at only after every workgroup's first sum of
+          // squares (which it stores last) is there: 256 workgroups that watch 32 KB each crowd out the stores they wait
+          // for (TinyLlama, 4 messages: 629 us, ungated 644; the 7B shape with 8: 979 and 975).
           Tile A, B;
           bf16x8 Bv[kResSteps];
           const tagged_t* xn_in = ph == PH_QKV ? a.xn[0] : a.xn[1];  // (selected, not indexed: an index into the arguments costs a copy of them)
@@ -511,17 +514,21 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           auto sum_at = [&](const tagged_t* v, int k, uint32_t z) __attribute__((always_inline)) {
             return word_at(v, (uint32_t)(min(sj, m - 1) * nwg + min(sc + 32 * k, nwg - 1)) * 8u + z);
           };
-          tagged_t gate[1], sqr[8] = {};
-          ask_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)min(tid, nwg - 1) * 8u + z); });
-          if (sj < m) ask_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); });
+          tagged_t sqr[8] = {};
+          const bool long_vec = (a.d >> 1) * m > kWatchWords;
+          auto gate_at = [&](int, uint32_t z) __attribute__((always_inline)) { return word_at(ssq_in, (uint32_t)tid * 8u + z); };
+          auto gated = [&](int) __attribute__((always_inline)) { return long_vec && tid < nwg; };
+          tagged_t gate[1];
+          ask_words(gate, gate_at, epoch, gated);
+          if (sj < m) ask_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); }, epoch);
           if (g.nks > 8) { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<1>(B, g, 0, wg, nwg, lane); }
           else { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<0>(B, g, 1, wg, nwg, lane); }
-          // Wait for the workgroups' first sums of squares (2 KB that everybody reads): a workgroup stores its share last.
-          // Watching the vectors themselves (up to 128 KB a workgroup and look) crowds out the stores that are waited for.
-          await_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)min(tid, nwg - 1) * 8u + z); }, epoch, a.spin_limit, a.err);
-          for (int i = tid + kStepThreads; i < nwg; i += kStepThreads)
-            poll_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)i * 8u + z); }, epoch, a.spin_limit, a.err);
-          __syncthreads();
+          if (long_vec) {
+            await_words(gate, gate_at, epoch, a.spin_limit, a.err, gated);
+            for (int i = tid + kStepThreads; i < nwg; i += kStepThreads)
+              poll_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)i * 8u + z); }, epoch, a.spin_limit, a.err);
+            __syncthreads();
+          }
           bstamp(a, layer, ph, 1);
           float sum2 = 0.f, sum1 = 0.f;                              // this thread's share of its message's sums
           if (sj < m) {
@@ -603,23 +610,26 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           const int n_units = kq.nk * 4 * m;                         // unit: eight columns of one message
           tagged_t raw[8] = {};
           int gi[2], n[2];
+          int u_at = tid;
           auto unit_of = [&](int u0) __attribute__((always_inline)) {
+            u_at = u0;
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
-              const int u = max(min(u0 + r * kStepThreads, n_units - 1), 0);
+              const int u = u0 + r * kStepThreads;
               gi[r] = (int)__umulhi((unsigned)u, a.m_magic); n[r] = u - gi[r] * m;
             }
           };
           auto at = [&](int r, uint32_t z) __attribute__((always_inline)) {   // pairs 4 (4 k0 + gi) .. + 3
             return word_at(bvec + (long)kq.k0 * (16 * m) + (r & 3) * m, (uint32_t)(4 * gi[r >> 2] * m + n[r >> 2]) * 8u + z);
           };
+          auto live = [&](int r) __attribute__((always_inline)) { return u_at + (r >> 2) * kStepThreads < n_units; };
           unit_of(tid);
-          if (n_units) ask_words(raw, at);
+          ask_words(raw, at, epoch, live);
           ks_issue(A, kq, g.W, woff, 0);
           ks_issue(B, kq, g.W, woff, 1);
           for (int u0 = tid; u0 < n_units; u0 += 2 * kStepThreads) {
-            if (u0 != tid) { unit_of(u0); ask_words(raw, at); }
-            await_words(raw, at, epoch, a.spin_limit, a.err);
+            if (u0 != tid) { unit_of(u0); ask_words(raw, at, epoch, live); }
+            await_words(raw, at, epoch, a.spin_limit, a.err, live);
 #pragma unroll
             for (int r = 0; r < 2; ++r)
               if (u0 + r * kStepThreads < n_units)
@@ -698,7 +708,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             float v0 = part_sum(part, lb, p, j) * rscale[j], v1 = part_sum(part, lb, p + half, j) * rscale[j];
             if (ln) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }
             v0 += ops.b0; v1 += ops.b1;
-            const int head = r0 / a.h, i = r0 - head * a.h;
+            const int head = r0 >> (31 - __builtin_clz(a.h)), i = r0 & (a.h - 1);
             if (sl.rope[j] && head < a.H + a.K) {
               const float t0 = v0 * ops.g0 - v1 * ops.g1, t1 = v0 * ops.g1 + v1 * ops.g0;
               v0 = t0; v1 = t1;

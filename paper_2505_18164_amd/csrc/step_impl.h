@@ -14,18 +14,20 @@
 // under other messages' weight streams; every message still makes its own pass
 // over the weights.
 //
-//   * phases are separated by a grid-wide barrier built from per-workgroup epoch
-//     flags.  Everything that crosses workgroups (x, q, o, u, attention partials,
-//     the newest K/V row, the flags) is written and read with cache-coherent
-//     (sc1, agent scope) stores and loads, so the barrier needs no L2
-//     write-back/invalidate.  Because such a store can be acknowledged before
-//     every compute die sees it, each exchanged value carries the counter of the
-//     phase that wrote it in the same 8-byte word and readers reload until the
-//     counter is the expected one; the flags only guard against overwriting.
+//   * there is no grid-wide barrier.  Everything that crosses workgroups (x, q, o, u, attention partials, the newest K/V
+//     row) is written and read with cache-coherent (sc1, agent scope) stores and loads, each value with the counter of
+//     the phase that wrote it in the same 8-byte word, and readers reload until the counter is the expected one.
+//     Nothing is overwritten that is still being read, because every phase needs all of the one before: who stores x in
+//     the output projection has read all of o, so every head's attention is done, so every workgroup with QKV rows has
+//     stored them, after it read x; who stores x in the down projection has read all of u, so all have read x for it;
+//     and q, u, o are written a layer after they were read.  (A workgroup without rows in a product does not read its
+//     vector.)  Phase counters watched before the data cost 3.2 us a phase; the data alone take 1.65 us from store to
+//     store (2048 words, 256 workgroups), and for the longest vectors too, waiting for the counters first was slower
+//     (7B shape, one message: 795 against 757 us).  What is left of the counters paces the two sets of workgroups.
 //   * weight and KV-cache addresses do not depend on activations, so every
-//     wavefront keeps two register tiles of 16-byte loads in flight and, while it
-//     finishes a phase, already issues the first two tiles of the NEXT phase; the
-//     barrier latency and the vector staging after it are covered by those loads.
+//     wavefront keeps two register tiles of 16-byte loads in flight and issues the
+//     first two of a phase before the phase's vector is there - but after it has
+//     asked for that vector's first words, which loads return in order.
 //   * the rows a workgroup owns in a phase form one flat sequence of (row pair,
 //     1-KiB chunk) items dealt round-robin to its wavefronts.  At any moment the
 //     workgroup therefore reads consecutive KiB of a row pair (DRAM sees a few
@@ -135,15 +137,18 @@ __device__ __forceinline__ const MDI_GLOBAL tagged_t* word_at(const tagged_t* ba
   return (const MDI_GLOBAL tagged_t*)((const MDI_GLOBAL char*)base + bytes);
 }
 __device__ __forceinline__ tagged_t ld_word(const MDI_GLOBAL tagged_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <int N, typename AT>
-__device__ __forceinline__ void ask_words(tagged_t (&raw)[N], const AT& at) {
+// live(i): whether this thread wants word i at all; the others count as seen (asking for some word again in their
+// place would have every workgroup hammer one line of memory).
+struct AllLive { __device__ __forceinline__ bool operator()(int) const { return true; } };
+template <int N, typename AT, typename LT = AllLive>
+__device__ __forceinline__ void ask_words(tagged_t (&raw)[N], const AT& at, unsigned tag, const LT& live = LT()) {
   uint32_t z = 0u;
   asm volatile("" : "+v"(z));
 #pragma unroll
-  for (int i = 0; i < N; ++i) raw[i] = ld_word(at(i, z));
+  for (int i = 0; i < N; ++i) raw[i] = live(i) ? ld_word(at(i, z)) : (tagged_t)tag << 32;
 }
-template <int N, typename AT>
-__device__ __forceinline__ void await_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err) {
+template <int N, typename AT, typename LT = AllLive>
+__device__ __forceinline__ void await_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
   int it = 0;
   while (true) {
     bool bad = false;
@@ -152,51 +157,78 @@ __device__ __forceinline__ void await_words(tagged_t (&raw)[N], const AT& at, un
     if (!bad) break;
     if (++it > spin_limit) { lds_flag()[kFailed] = 1; __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
     __builtin_amdgcn_s_sleep(1);
-    ask_words(raw, at);
+    ask_words(raw, at, tag, live);
   }
 }
-template <int N, typename AT>
-__device__ __forceinline__ void poll_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err) {
-  ask_words(raw, at);
-  await_words(raw, at, tag, spin_limit, err);
+template <int N, typename AT, typename LT = AllLive>
+__device__ __forceinline__ void poll_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
+  ask_words(raw, at, tag, live);
+  await_words(raw, at, tag, spin_limit, err, live);
 }
 
 // ---------------------------------------------------------------------------
 // vector staging: n floats written earlier in this launch by other workgroups -> LDS
-// With gain != nullptr (RMSNorm) the staged values are x[i] * gain[i] and the return value is this
-// thread's share of sum(x^2); the common factor 1/rms is applied to the finished dot products.
-// The first batch of eight values per thread (and their gains) may have been requested earlier, while the
-// workgroup was finishing its previous phase (`pre`); values that were not there yet carry another tag and are
-// simply loaded again.
-__device__ __forceinline__ float stage_coherent(const tagged_t* src, int n, float* xs, const float* gain, unsigned tag,
-                                                int spin_limit, int* err, bool pre, const tagged_t (&praw)[8],
-                                                const float (&pgain)[8]) {
+// With gain != nullptr (RMSNorm) the staged values are x[i] * gain[i] and the return value is this thread's share of
+// sum(x^2); the common factor 1/rms is applied to the finished dot products.  Otherwise the values are staged as they
+// are and the return value is this thread's share of their sum.
+// The first eight values per thread (and their gains) have been requested before (`raw`, `gv`).
+struct VecAsk { tagged_t raw[8]; float gain[8]; };
+__device__ __forceinline__ void vec_ask(VecAsk& v, const tagged_t* src, int n, const float* gain, unsigned tag, int i0) {
+  ask_words(v.raw, [&](int j, uint32_t z) { return word_at(src, (uint32_t)(i0 + j * kStepThreads) * 8u + z); }, tag,
+            [&](int j) { return i0 + j * kStepThreads < n; });
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v.gain[j] = gain && i0 + j * kStepThreads < n ? gain[i0 + j * kStepThreads] : 1.f;
+}
+__device__ __forceinline__ float stage_coherent(VecAsk& v, const tagged_t* src, int n, float* xs, const float* gain, bool rms, unsigned tag,
+                                                int spin_limit, int* err, int tid) {
   float ss = 0.f;
-  for (int i0 = threadIdx.x; i0 < n; i0 += 8 * kStepThreads) {
-    const bool early = pre && i0 == (int)threadIdx.x;
-    tagged_t raw[8];
-    float gv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {                      // eight loads in flight per thread
-      const int i = i0 + j * kStepThreads;
-      raw[j] = early ? praw[j] : (i < n ? ld_raw(src + i) : 0ull);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int i = i0 + j * kStepThreads;
-      gv[j] = early ? pgain[j] : ((gain && i < n) ? gain[i] : 1.f);
-    }
+  for (int i0 = tid; i0 < n; i0 += 8 * kStepThreads) {
+    if (i0 != tid) vec_ask(v, src, n, gain, tag, i0);
+    await_words(v.raw, [&](int j, uint32_t z) { return word_at(src, (uint32_t)(i0 + j * kStepThreads) * 8u + z); }, tag, spin_limit, err,
+                [&](int j) { return i0 + j * kStepThreads < n; });
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int i = i0 + j * kStepThreads;
       if (i < n) {
-        const float x = settle(src + i, raw[j], tag, spin_limit, err);
-        ss += x * x;
-        xs[i] = gain ? x * gv[j] : x;
+        const float x = tag_value(v.raw[j]);
+        ss += rms ? x * x : x;
+        xs[i] = rms ? x * v.gain[j] : x;
       }
     }
   }
   return ss;
+}
+
+// Sum over the workgroup, every thread gets it.  One barrier; `red` is a strip of kStepWaves floats that the previous
+// call did not use.
+__device__ __forceinline__ float step_sum(float v, float* red, int tid) {
+  const float w = wave_sum_to_lane63(v);
+  if ((tid & 63) == 63) red[tid >> 6] = w;
+  __syncthreads();
+  float t = 0.f;
+#pragma unroll
+  for (int k = 0; k < kStepWaves; ++k) t += red[k];
+  return t;
+}
+
+// LayerNorm of the staged vector, each thread on the elements it staged itself; s = its share of their sum.
+__device__ __forceinline__ void layer_norm(float* xs, int n, float s, float eps, const float* g, const float* b, float* red, int tid) {
+  float gv[2], bv[2];                                  // the first gains and biases are on their way during the sums
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + k * kStepThreads;
+    gv[k] = i < n ? g[i] : 0.f; bv[k] = b && i < n ? b[i] : 0.f;
+  }
+  const float mean = step_sum(s, red, tid) / (float)n;
+  float s2 = 0.f;
+  for (int i = tid; i < n; i += kStepThreads) { const float c = xs[i] - mean; s2 += c * c; }
+  const float rstd = 1.f / sqrtf(step_sum(s2, red + kStepWaves, tid) / (float)n + eps);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = tid + k * kStepThreads;
+    if (i < n) xs[i] = (xs[i] - mean) * rstd * gv[k] + bv[k];
+  }
+  for (int i = tid + 2 * kStepThreads; i < n; i += kStepThreads) xs[i] = (xs[i] - mean) * rstd * g[i] + (b ? b[i] : 0.f);
 }
 
 __device__ __forceinline__ void normalise(float* xs, int n, int norm_kind, float eps, const float* g, const float* b, float* red) {
@@ -274,21 +306,21 @@ __device__ __forceinline__ int geo_row(const Geo& g, int p, int j) {
 
 // the step's own input (token embedding + learned position, or the previous stage's activation)
 template <typename WT>
-__device__ __forceinline__ void stage_input(const StepArgs& a, const StepSlot& S, float* xs, const Geo& gres, unsigned tag) {
+__device__ __forceinline__ void stage_input(const StepArgs& a, const StepSlot& S, float* xs, const Geo& gres, unsigned tag, int tid) {
   const int n = a.d;
   if (S.in_kind == IN_TOKEN) {
     const long tok = checked_token(S.in, 0, a.vocab, a.err);
-    for (int i = threadIdx.x; i < n; i += kStepThreads) {
+    for (int i = tid; i < n; i += kStepThreads) {
       float v = Storage<WT>::get((const WT*)a.wte + tok * n + i);
       if (a.wpe) v += Storage<WT>::get((const WT*)a.wpe + (long)S.pos * n + i);
       xs[i] = v;
     }
   } else {
-    for (int i = threadIdx.x; i < n; i += kStepThreads) xs[i] = load_kind(S.in, S.in_kind, i);
+    for (int i = tid; i < n; i += kStepThreads) xs[i] = load_kind(S.in, S.in_kind, i);
   }
   __syncthreads();
   // rows this workgroup owns in the residual phases get their starting value
-  for (int pl = threadIdx.x; pl < gres.n_pl; pl += kStepThreads) {
+  for (int pl = tid; pl < gres.n_pl; pl += kStepThreads) {
     const int r = 2 * geo_pair(gres, pl);
     st_tag(S.xres + r, xs[r], tag);
     if (r + 1 < n) st_tag(S.xres + r + 1, xs[r + 1], tag);
@@ -371,27 +403,46 @@ __device__ __forceinline__ void gemv_compute(const Tile& t, const Geo& g, int ti
   cur.pl = pl; cur.c = c;
 }
 
+// What a phase's epilogue needs beside the sums, for pair pl: QKV: (cos, sin); all: the biases.  A thread's first pair's
+// are fetched before the stream.
+template <typename T> __device__ __forceinline__ float rounded(float v);   // as the storage type holds it
+template <> __device__ __forceinline__ float rounded<float>(float v) { return v; }
+template <> __device__ __forceinline__ float rounded<bf16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
+struct FinOps { float c, s, b0, b1; int p, r0, r1; };
+__device__ __forceinline__ FinOps fin_ops(int ph, const Geo& g, const StepLayer& L, const StepArgs& a, const StepSlot& S, int pl) {
+  FinOps o{};
+  if (pl >= g.n_pl) return o;
+  o.p = geo_pair(g, pl); o.r0 = geo_row(g, o.p, 0); o.r1 = geo_row(g, o.p, 1);
+  const int r0 = o.r0, r1 = min(o.r1, g.N - 1);
+  const float *bq = L.bqkv, *bu = L.bup, *bo = L.bo, *bd = L.bdown;
+  const float* bias = ph == PH_QKV ? bq : ph == PH_UP ? (a.mlp_kind == MDI_MLP_SWIGLU ? nullptr : bu) : ph == PH_OPROJ ? bo : bd;
+  if (bias) { o.b0 = bias[r0]; o.b1 = bias[r1]; }
+  if (ph == PH_QKV) {
+    const int head = r0 >> (31 - __builtin_clz(a.h));            // (head sizes are powers of two)
+    if (S.rope && head < a.H + a.K) { const float2 cs = S.rope[r0 & (a.h - 1)]; o.c = cs.x; o.s = cs.y; }
+  }
+  return o;
+}
+
 // Sums the wavefront slots of every pair and applies the phase's epilogue.
 template <typename WT>
 __device__ __forceinline__ void gemv_finish(int ph, const Geo& g, const StepLayer* Lp, int layer, const StepArgs& a, const StepSlot& S, const float* part,
-                                            float row_scale, tagged_t x0_pre, tagged_t x1_pre, unsigned epoch) {
+                                            float row_scale, tagged_t x0_pre, tagged_t x1_pre, FinOps ops, unsigned epoch, int tid) {
   const unsigned wtag = epoch + 1;                            // what this phase writes carries the next counter
   const StepLayer& L = *Lp;
   __syncthreads();                                           // all wavefronts' partials are in LDS
   stamp(a, S, layer, ph, 4);
-  for (int pl = threadIdx.x; pl < g.n_pl; pl += kStepThreads) {
+  for (int pl = tid; pl < g.n_pl; pl += kStepThreads) {
     float v0 = 0.f, v1 = 0.f;
 #pragma unroll
     for (int w = 0; w < kStepWaves; ++w) { v0 += part[(pl * 2) * kStepWaves + w]; v1 += part[(pl * 2 + 1) * kStepWaves + w]; }
     v0 *= row_scale; v1 *= row_scale;
-    const int p = geo_pair(g, pl);
-    const int r0 = geo_row(g, p, 0), r1 = geo_row(g, p, 1);
+    const int p = ops.p, r0 = ops.r0, r1 = ops.r1;
     if (ph == PH_QKV) {
-      if (L.bqkv) { v0 += L.bqkv[r0]; v1 += L.bqkv[r1]; }
-      const int head = r0 / a.h, i = r0 - head * a.h;
+      v0 += ops.b0; v1 += ops.b1;
+      const int head = r0 >> (31 - __builtin_clz(a.h)), i = r0 & (a.h - 1);
       if (S.rope && head < a.H + a.K) {
-        const float2 cs = S.rope[i];
-        const float t0 = v0 * cs.x - v1 * cs.y, t1 = v0 * cs.y + v1 * cs.x;
+        const float t0 = v0 * ops.c - v1 * ops.s, t1 = v0 * ops.s + v1 * ops.c;
         v0 = t0; v1 = t1;
       }
       if (head < a.H) {
@@ -404,36 +455,36 @@ __device__ __forceinline__ void gemv_finish(int ph, const Geo& g, const StepLaye
         WT* dst = (WT*)L.kv + S.kv_tok_off + (long)(kvh * 2 + (is_v ? 1 : 0)) * a.pt_h + i;
         Storage<WT>::put(dst, v0); Storage<WT>::put(dst + (a.h >> 1), v1);
         tagged_t* kn = S.knew + (long)(is_v ? a.K * a.h : 0) + kvh * a.h + i;
-        st_tag(kn, Storage<WT>::get(dst), wtag); st_tag(kn + (a.h >> 1), Storage<WT>::get(dst + (a.h >> 1)), wtag);
+        st_tag(kn, rounded<WT>(v0), wtag); st_tag(kn + (a.h >> 1), rounded<WT>(v1), wtag);
       }
     } else if (ph == PH_UP) {
       if (a.mlp_kind == MDI_MLP_SWIGLU) {
         st_tag(S.u + p, silu_f(v0) * v1, wtag);              // rows (2f, 2f+1) = (gate_f, up_f)
       } else {
-        if (L.bup) { v0 += L.bup[r0]; if (r1 < g.N) v1 += L.bup[r1]; }
+        v0 += ops.b0; v1 += ops.b1;
         const bool tanh_form = a.mlp_kind == MDI_MLP_GELU_TANH;
         st_tag(S.u + r0, tanh_form ? gelu_tanh_f(v0) : gelu_erf_f(v0), wtag);
         if (r1 < g.N) st_tag(S.u + r1, tanh_form ? gelu_tanh_f(v1) : gelu_erf_f(v1), wtag);
       }
     } else {                                                  // residual phases
-      const float* bias = ph == PH_OPROJ ? L.bo : L.bdown;
       const bool last = ph == PH_DOWN && layer == a.n_layer - 1;
       const bool two = r1 < g.N;
       // rows of the first kStepThreads pairs were fetched before the stream
-      const bool pre = pl == (int)threadIdx.x;
+      const bool pre = pl == tid;
       // this workgroup wrote these rows itself: two phases ago (output projection) or one (down projection)
       const unsigned rtag = ph == PH_OPROJ ? epoch - 2 : epoch - 1;
       const float x0 = settle(S.xres + r0, pre ? x0_pre : ld_raw(S.xres + r0), rtag, a.spin_limit, a.err);
       const float x1 = two ? settle(S.xres + r1, pre ? x1_pre : ld_raw(S.xres + r1), rtag, a.spin_limit, a.err) : 0.f;
-      v0 += x0 + (bias ? bias[r0] : 0.f);
+      v0 += x0 + ops.b0;
       st_tag(S.xres + r0, v0, wtag);
       if (last) store_kind(S.act_out, a.act_kind, r0, v0);
       if (two) {
-        v1 += x1 + (bias ? bias[r1] : 0.f);
+        v1 += x1 + ops.b1;
         st_tag(S.xres + r1, v1, wtag);
         if (last) store_kind(S.act_out, a.act_kind, r1, v1);
       }
     }
+    if (pl + kStepThreads < g.n_pl) ops = fin_ops(ph, g, L, a, S, pl + kStepThreads);
   }
 }
 
@@ -643,7 +694,7 @@ __device__ __forceinline__ void attn_stream(AttnState<WT, G>& st, Tile& A, Tile&
 template <typename WT> struct AttnAsk { tagged_t q[1], kv[2 * Storage<WT>::kVec]; };
 template <typename WT, int G, typename AR, typename SL>
 __device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_q_at(const AttnGeo& g, const AR& a, const SL& S, int i, uint32_t z) {
-  return word_at(S.q + (long)g.hg * G * a.h, (uint32_t)min(i, G * a.h - 1) * 8u + z);
+  return word_at(S.q + (long)g.hg * G * a.h, (uint32_t)i * 8u + z);
 }
 template <typename WT, typename AR, typename SL>
 __device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_kv_at(const AttnGeo& g, const AR& a, const SL& S, int e, uint32_t z) {
@@ -651,14 +702,14 @@ __device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_kv_at(const AttnGeo& 
   return word_at(S.knew + g.kvh * a.h + (e < V ? (long)e : (long)a.K * a.h + e - V), (uint32_t)g.hoff * 8u + z);
 }
 template <typename WT, int G, typename AR, typename SL>
-__device__ __forceinline__ void attn_ask(AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, int wave) {
+__device__ __forceinline__ void attn_ask(AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, int wave, unsigned epoch, int tid) {
   if (!g.active) return;
-  ask_words(k.q, [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, (int)threadIdx.x, z); });
-  if (g.s1 == S.ctx && wave == kStepWaves - 1) ask_words(k.kv, [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, S, e, z); });
+  ask_words(k.q, [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, tid, z); }, epoch, [&](int) { return tid < G * a.h; });
+  if (g.s1 == S.ctx && wave == kStepWaves - 1) ask_words(k.kv, [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, S, e, z); }, epoch);
 }
 // queries into LDS (pre-scaled), the newest position into the last wavefront's running sums
 template <typename WT, int G, typename AR, typename SL>
-__device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, float* qs, int wave, unsigned epoch) {
+__device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, float* qs, int wave, unsigned epoch, int tid) {
   constexpr int V = Storage<WT>::kVec;
 #pragma unroll
   for (int gi = 0; gi < G; ++gi) {
@@ -668,9 +719,9 @@ __device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, AttnAsk<WT>& k,
   }
   const bool newest = g.active && g.s1 == S.ctx && wave == kStepWaves - 1;
   if (g.active) {
-    for (int i = threadIdx.x; i < G * a.h; i += kStepThreads) {
+    for (int i = tid; i < G * a.h; i += kStepThreads) {
       auto at = [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, i, z); };
-      if (i != (int)threadIdx.x) ask_words(k.q, at);
+      if (i != tid) ask_words(k.q, at, epoch);
       await_words(k.q, at, epoch, a.spin_limit, a.err);
       qs[i] = tag_value(k.q[0]) * a.scale;
     }
@@ -718,12 +769,12 @@ __device__ __forceinline__ void attn_to_lds(AttnState<WT, G>& st, const AttnGeo&
 // Wavefront records -> split partial (or the final output when there is one split);
 // the last workgroup of a head group to arrive folds the splits in split order.
 template <int G, typename AR, typename SL>
-__device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const SL& S, const float* sm, int* s_flag, unsigned epoch) {
+__device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const SL& S, const float* sm, int* s_flag, unsigned epoch, int tid) {
   const unsigned wtag = epoch + 1;
   const int h = a.h, rec = h + 2;
   if (!g.active) return;
   const bool single = S.n_splits == 1;
-  for (int idx = threadIdx.x; idx < G * h; idx += kStepThreads) {
+  for (int idx = tid; idx < G * h; idx += kStepThreads) {
     const int gi = idx / h, e = idx - gi * h;
     float m = -1e30f;
     for (int w = 0; w < kStepWaves; ++w) m = fmaxf(m, sm[(w * G + gi) * rec + h]);
@@ -745,13 +796,14 @@ __device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const
   if (single) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     const unsigned ticket = __hip_atomic_fetch_add(S.tickets + g.hg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s_flag[1] = ticket == (unsigned)S.n_splits - 1;
   }
   __syncthreads();
   if (!s_flag[1]) return;
-  for (int idx = threadIdx.x; idx < G * h; idx += kStepThreads) {
+  if (tid == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int idx = tid; idx < G * h; idx += kStepThreads) {
     const int gi = idx / h, e = idx - gi * h;
     const int head = g.hg * G + gi;
     const tagged_t* pr = S.part + (long)head * kMaxSplits * rec;
@@ -782,7 +834,7 @@ __device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const
     }
     st_tag(S.o + (long)head * h + e, o / l, wtag);
   }
-  if (threadIdx.x == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
 }
 
 // ---------------------------------------------------------------------------
@@ -835,7 +887,6 @@ __device__ __forceinline__ const void* layer_matrix(const StepLayer& L, int j) {
 
 template <typename WT, int G>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(StepArgs a) {
-  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // a set of nwg workgroups takes its messages in turn inside every phase; two sets share the compute units
   const int nwg = a.nwg, wg = blockIdx.x % nwg;
@@ -849,6 +900,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   int* s_flag = lds_flag();
 
   if (threadIdx.x == 0) {
+    s_flag[kFailed] = 0;
     store_geo<WT>(0, (a.H + 2 * a.K) * a.h, a.d, a.h, wg, nwg);       // pairs (i, i + h/2): the RoPE partners
     store_geo<WT>(1, a.d, a.H * a.h, 0, wg, nwg);
     store_geo<WT>(2, a.mlp_kind == MDI_MLP_SWIGLU ? 2 * a.F : a.F, a.d, 0, wg, nwg);
@@ -860,16 +912,9 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   __syncthreads();
 
   float acc0 = 0.f, acc1 = 0.f;
-  AttnState<WT, G> st;
-  AttnGeo ga{};
-  Tile A, B;
-  Cursor ci, cc;                             // the GEMV phases' issue and multiply cursors
-  int pgA[kTile], pgB[kTile];               // page numbers of the attention tiles that go into A and B next
   // requested while finishing the previous (message, phase): the next one's flags and the head of its input vector
-  bool early_flags = false, early_vec = false;
-  unsigned efl[4] = {0u, 0u, 0u, 0u};
-  tagged_t eraw[8] = {0ull, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
-  float egain[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+  bool early = false;
+  VecAsk vec{};
 
 #pragma nounroll
   for (int layer = 0; layer < a.n_layer; ++layer) {
@@ -884,58 +929,56 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         // next phase every workgroup has long finished its previous one.
         const StepSlot& S = a.s[slot];
         const unsigned epoch = S.epoch0 + (unsigned)(layer * 5 + ph);
-        // ---- this phase's first two tiles: their addresses depend on nothing another workgroup writes,
-        //      so they are in flight while the barrier completes and the input vector is staged
+        // per-thread addresses are recomputed in every phase (see k_step_batch)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63;
+        // ---- the head of the input vector is asked for first: loads return in order, and the workgroup that everybody
+        //      waits for finds it there at once instead of behind its weights.
         const int j = gemv_index(ph);
         const Geo g = load_geo(j, layer_matrix(Lv, j), wave);
+        const bool first = ph == PH_QKV && layer == 0;
+        const bool work = g.n_pl > 0;                  // who has no rows in a product reads nothing for it either
+        AttnGeo ga{};
+        Tile A, B;
+        Cursor ci, cc;                       // the GEMV phases' issue and multiply cursors
+        int pgA[kTile], pgB[kTile];         // page numbers of the attention tiles that go into A and B next
+        AttnAsk<WT> ask{};
+        FinOps ops{};
+        auto vec_src = [&](const StepSlot& N, int nph) __attribute__((always_inline)) { return nph == PH_OPROJ ? N.o : nph == PH_DOWN ? N.u : N.xres; };
+        auto vec_len = [&](int nph) __attribute__((always_inline)) { return nph == PH_OPROJ ? a.H * a.h : nph == PH_DOWN ? a.F : a.d; };
+        auto vec_gain = [&](int nph, int nlayer) __attribute__((always_inline)) {
+          const float *g1 = a.l0.ln1_g, *g2 = a.l0.ln2_g;
+          return (nph == PH_QKV || nph == PH_UP) && a.norm_kind == MDI_NORM_RMSNORM ? advance(nph == PH_QKV ? g1 : g2, a.w_stride * nlayer) : nullptr;
+        };
+        auto ask_for = [&](const StepSlot& N, int nph, int nlayer) __attribute__((always_inline)) {
+          const unsigned nepoch = N.epoch0 + (unsigned)(nlayer * 5 + nph);
+          if (!(nph == PH_QKV && nlayer == 0)) vec_ask(vec, vec_src(N, nph), vec_len(nph), vec_gain(nph, nlayer), nepoch, tid);
+        };
+        // ---- then this phase's first two tiles: their addresses depend on nothing another workgroup writes
         if (ph == PH_ATTN) {
+          vec = VecAsk{}; early = false;               // (never asked for ahead of attention: the registers are free)
           ga = make_attn_geo<WT, G>(a, S, wg, wave, lane);
+          attn_ask<WT, G>(ask, ga, a, S, wave, epoch, tid);
           attn_pages(pgA, ga, a, S, 0, wave); attn_pages(pgB, ga, a, S, 1, wave);
           attn_issue<WT>(A, pgA, ga, a, S, L->kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, S, L->kv, 1, wave);
-        } else { ci = cc = cursor_start(g, wave); gemv_issue(A, g, ci, lane); gemv_issue(B, g, ci, lane); }
+        } else if (work || first) {
+          if (!early) ask_for(S, ph, layer);
+          ops = fin_ops(ph, g, Lv, a, S, tid);
+          ci = cc = cursor_start(g, wave); gemv_issue(A, g, ci, lane); gemv_issue(B, g, ci, lane);
+        }
 
         auto early_requests = [&]() __attribute__((always_inline)) {
           // ---- requests for the next (message, phase), answered while this phase is being finished: with two
           //      messages alternating, what the next one needs was published a whole phase ago
-          early_flags = false; early_vec = false;
+          early = false;
           // whatever was requested a phase ago has been used: giving every register a value here, on every path,
           // tells the compiler that none of them is live across the streaming loops above
-#pragma unroll
-          for (int k = 0; k < 4; ++k) efl[k] = 0u;
-#pragma unroll
-          for (int jj = 0; jj < 8; ++jj) { eraw[jj] = 0ull; egain[jj] = 1.f; }
+          vec = VecAsk{};
           if (slot_hi - slot_lo > 1) {
             int nslot = slot + 1, nph = ph, nlayer = layer;
             if (nslot == slot_hi) { nslot = slot_lo; if (++nph == 5) { nph = 0; ++nlayer; } }
-            if (nlayer < a.n_layer) {
-              const StepSlot& N = a.s[nslot];
-              const unsigned nepoch = N.epoch0 + (unsigned)(nlayer * 5 + nph);
-              if (nwg <= 256 && threadIdx.x < 64) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                  const int i = (int)threadIdx.x + 64 * k;
-                  efl[k] = i < nwg ? __hip_atomic_load(N.flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : nepoch;
-                }
-                early_flags = true;
-              }
-              if (nph != PH_ATTN && !(nph == PH_QKV && nlayer == 0)) {
-                const tagged_t* nsrc = nph == PH_OPROJ ? N.o : nph == PH_DOWN ? N.u : N.xres;
-                const int nn = nph == PH_OPROJ ? a.H * a.h : nph == PH_DOWN ? a.F : a.d;
-                const bool nrms = (nph == PH_QKV || nph == PH_UP) && a.norm_kind == MDI_NORM_RMSNORM;
-                const float* ngain = advance(nph == PH_QKV ? a.l0.ln1_g : a.l0.ln2_g, a.w_stride * nlayer);
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                  const int i = (int)threadIdx.x + jj * kStepThreads;
-                  eraw[jj] = i < nn ? ld_raw(nsrc + i) : 0ull;
-                }
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                  const int i = (int)threadIdx.x + jj * kStepThreads;
-                  egain[jj] = (nrms && i < nn) ? ngain[i] : 1.f;
-                }
-                early_vec = true;
-              }
-            }
+            if (nlayer < a.n_layer && nph != PH_ATTN) { ask_for(a.s[nslot], nph, nlayer); early = true; }
           }
         };
 
@@ -947,32 +990,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         const bool pace = a.n_sets == 2 && slot == slot_lo;
         if (pace) other_done = __hip_atomic_load(O.flags + wg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - O.epoch0;
 
-        // ---- wait until every workgroup has finished the previous phase ----------------------------
         stamp(a, S, layer, ph, 0);
-        if (threadIdx.x < 64) {
-          bool ok = true;
-          int it = 0;
-          bool seen = early_flags;                   // the flags requested early may already show everyone
-#pragma unroll
-          for (int k = 0; k < 4; ++k) seen = seen && ((int)(efl[k] - epoch) >= 0);
-          while (!__all(seen)) {
-            bool all = true;
-            for (int i = threadIdx.x; i < nwg; i += 64) {
-              const unsigned v = __hip_atomic_load(S.flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              all = all && ((int)(v - epoch) >= 0);
-            }
-            if (__all(all)) break;
-            if (++it > a.spin_limit) { ok = false; break; }
-            __builtin_amdgcn_s_sleep(1);
-          }
-          if (threadIdx.x == 0) {
-            s_flag[0] = ok;
-            if (!ok) __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-        }
-        __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (!s_flag[0]) return;
         stamp(a, S, layer, ph, 1);
         if (pace) {
           // work left, in (message, phase) units; the set with more of it goes first
@@ -984,56 +1002,55 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
 
         if (ph == PH_ATTN) {
           // ---- attention over the sample's pages -----------------------------------------------------
-          AttnAsk<WT> ask{};
-          attn_ask<WT, G>(ask, ga, a, S, wave);
-          attn_begin<WT, G>(st, ask, ga, a, S, xs, wave, epoch);
+          AttnState<WT, G> st;
+          attn_begin<WT, G>(st, ask, ga, a, S, xs, wave, epoch, tid);
           stamp(a, S, layer, ph, 2);
           const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
           attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, S, L->kv, nte, wave, xs);
           stamp(a, S, layer, ph, 3);
           early_requests();
           attn_to_lds<WT, G>(st, ga, a.h, xs, wave);
-          attn_finish<G>(ga, a, S, xs, s_flag, epoch);
-        } else {
+          attn_finish<G>(ga, a, S, xs, s_flag, epoch, tid);
+        } else if (work || first) {
           // ---- a GEMV phase ----------------------------------------------------------------------------
-          for (int i = threadIdx.x; i < g.n_pl * 2 * kStepWaves; i += kStepThreads) part[i] = 0.f;
+          for (int i = tid; i < g.n_pl * 2 * kStepWaves; i += kStepThreads) part[i] = 0.f;
           const bool normed = ph == PH_QKV || ph == PH_UP;
           const bool fused_rms = normed && a.norm_kind == MDI_NORM_RMSNORM;
-          const float* gain = ph == PH_QKV ? L->ln1_g : L->ln2_g;
+          const float *gain1 = L->ln1_g, *gain2 = L->ln2_g;
+          const float* gain = ph == PH_QKV ? gain1 : gain2;
           float row_scale = 1.f;                       // 1/rms when the norm is folded into the epilogue
+          float share = 0.f;                           // of the sum of squares (RMSNorm) or of the sum
           if (ph == PH_QKV && layer == 0) {
-            stage_input<WT>(a, S, xs, load_geo(1, nullptr, wave), epoch);
-            if (fused_rms) {
-              // same arithmetic, element order and thread mapping as stage_coherent, so that a layer gives the same
-              // bits whether it is the first of its partition or not (where the model is cut changes nothing)
-              __syncthreads();                          // stage_input has read its rows of xs
-              float ss = 0.f;
-              for (int i0 = threadIdx.x; i0 < a.d; i0 += 8 * kStepThreads) {
+            stage_input<WT>(a, S, xs, load_geo(1, nullptr, wave), epoch, tid);
+            // same arithmetic, element order and thread mapping as stage_coherent, so that a layer gives the same
+            // bits whether it is the first of its partition or not (where the model is cut changes nothing)
+            __syncthreads();                            // stage_input has read its rows of xs
+            for (int i0 = tid; i0 < a.d; i0 += 8 * kStepThreads) {
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                  const int i = i0 + jj * kStepThreads;
-                  if (i < a.d) { const float x = xs[i]; ss += x * x; xs[i] = x * gain[i]; }
-                }
+              for (int jj = 0; jj < 8; ++jj) {
+                const int i = i0 + jj * kStepThreads;
+                if (i < a.d) { const float x = xs[i]; share += fused_rms ? x * x : x; if (fused_rms) xs[i] = x * gain[i]; }
               }
-              row_scale = 1.f / sqrtf(block_sum(ss, red) / (float)a.d + a.eps);
             }
           } else {
-            const tagged_t* src = ph == PH_OPROJ ? S.o : ph == PH_DOWN ? S.u : S.xres;
-            const float ss = stage_coherent(src, g.units * Storage<WT>::kVec, xs, fused_rms ? gain : nullptr, epoch, a.spin_limit, a.err,
-                                            early_vec, eraw, egain);
-            if (fused_rms) row_scale = 1.f / sqrtf(block_sum(ss, red) / (float)a.d + a.eps);
+            share = stage_coherent(vec, vec_src(S, ph), vec_len(ph), xs, fused_rms ? gain : nullptr, fused_rms, epoch, a.spin_limit, a.err, tid);
           }
           // zeros behind the vector up to a whole 64-lane chunk (the host sizes the LDS for it): see gemv_compute
-          for (int i = g.units * Storage<WT>::kVec + (int)threadIdx.x; i < g.cpp * 64 * Storage<WT>::kVec; i += kStepThreads) xs[i] = 0.f;
-          __syncthreads();
-          if (normed && !fused_rms) {
-            normalise(xs, a.d, a.norm_kind, a.eps, gain, ph == PH_QKV ? L->ln1_b : L->ln2_b, red);
+          for (int i = g.units * Storage<WT>::kVec + tid; i < g.cpp * 64 * Storage<WT>::kVec; i += kStepThreads) xs[i] = 0.f;
+          if (fused_rms) {
+            row_scale = 1.f / sqrtf(step_sum(share, red, tid) / (float)a.d + a.eps);
+          } else {
+            if (normed) {
+              const float *b1 = L->ln1_b, *b2 = L->ln2_b;
+              layer_norm(xs, a.d, share, a.eps, gain, ph == PH_QKV ? b1 : b2, red, tid);
+            }
             __syncthreads();
           }
+          if (s_flag[kFailed]) return;
           // residual phases: fetch this thread's rows of x now, the stream below hides the latency
           tagged_t x0 = 0ull, x1 = 0ull;
-          if ((ph == PH_OPROJ || ph == PH_DOWN) && (int)threadIdx.x < g.n_pl) {
-            const int r0 = 2 * geo_pair(g, (int)threadIdx.x);
+          if ((ph == PH_OPROJ || ph == PH_DOWN) && tid < g.n_pl) {
+            const int r0 = ops.r0;
             x0 = ld_raw(S.xres + r0);
             if (r0 + 1 < g.N) x1 = ld_raw(S.xres + r0 + 1);
           }
@@ -1041,15 +1058,21 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
 
           const int nte = ((g.n_k + kTile - 1) / kTile + 1) & ~1;
 #pragma nounroll
-          for (int t = 0; t < nte; t += 2) {
-            gemv_compute<WT, true>(A, g, t, cc, wave, lane, xs, part, acc0, acc1);
+          for (int t = 2; t < nte; t += 2) {
+            gemv_compute<WT, true>(A, g, t - 2, cc, wave, lane, xs, part, acc0, acc1);
             gemv_issue(A, g, ci, lane);
-            gemv_compute<WT, true>(B, g, t + 1, cc, wave, lane, xs, part, acc0, acc1);
+            gemv_compute<WT, true>(B, g, t - 1, cc, wave, lane, xs, part, acc0, acc1);
             gemv_issue(B, g, ci, lane);
+          }
+          if (nte) {                                   // (the last two tiles: nothing more to ask for)
+            gemv_compute<WT, true>(A, g, nte - 2, cc, wave, lane, xs, part, acc0, acc1);
+            gemv_compute<WT, true>(B, g, nte - 1, cc, wave, lane, xs, part, acc0, acc1);
           }
           stamp(a, S, layer, ph, 3);
           early_requests();
-          gemv_finish<WT>(ph, g, L, layer, a, S, part, row_scale, x0, x1, epoch);
+          gemv_finish<WT>(ph, g, L, layer, a, S, part, row_scale, x0, x1, ops, epoch, tid);
+        } else {
+          vec = VecAsk{}; early = false;
         }
 
         // ---- publish: this workgroup is done with the phase ---------------------------------------------
@@ -1057,7 +1080,8 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // this thread's stores have completed
         __syncthreads();
         stamp(a, S, layer, ph, 6);
-        if (threadIdx.x == 0) __hip_atomic_store(S.flags + wg, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (s_flag[kFailed]) return;
+        if (a.n_sets == 2 && tid == 0) __hip_atomic_store(S.flags + wg, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
