@@ -20,8 +20,6 @@
 namespace mdi {
 namespace step_w8 {
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-
 constexpr int kHbGroups = 9;          // 16-byte groups of an activation per lane: widths up to 64 * 9 * 8 = 4608
 // Where a wavefront is in its stream: block, how many of the block's column tiles are done, and the tile it started
 // the block with.  Rows are a power of two apart in memory; block b starts at tile b mod (tiles per row) and wraps,

@@ -927,10 +927,14 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   for (int j = 0; j < n; ++j) { ctx_max = std::max(ctx_max, mp[j].ctx); ctx_sum += mp[j].ctx; }
   // Query heads per attention work item: pairs also when one head per item would give more items than workgroups
   // (every message brings n_head of them), so that a workgroup has one item and a kv head's cache is read half as often.
-  // With more items than workgroups even so, four heads take the pass together (one work item then serves a whole
-  // group of the 8B shape; the context splits that fill the grid are folded by one workgroup per item group).
+  // Four heads with their scores on the matrix cores (k_step_batch, Attn4) once every workgroup has 192 positions of
+  // them.  Measured on the 8B shape, 4 layers, one / two / four heads: 8 messages of 1024 positions 507 / 483 / 481 us,
+  // 4 of 2048 484 / 465 / 461, 16 of 1024 636 / 559 / 539, 16 of 2048 794 / 651 / 583; but 16 of 256 523 / 494 / 521 and
+  // 4 of 512 434 / 433 / 454.  Other groups of four: with twice as many items as workgroups.
   const int group = (int)(c.n_head / c.n_kv_head);
-  int G = (n * (int)c.n_head >= 2 * p->nwg && group % 4 == 0) ? 4 : (ctx_max >= p->group_ctx || n * (int)c.n_head > p->nwg) ? p->G : 1;
+  const bool mfma_scores = group % 4 == 0 && c.head_dim == 128 && p->pt % 16 == 0;
+  const bool four = mfma_scores ? ctx_sum * (c.n_head / 4) >= 192L * p->nwg : group % 4 == 0 && n * (int)c.n_head >= 2 * p->nwg;
+  int G = four ? 4 : (ctx_max >= p->group_ctx || n * (int)c.n_head > p->nwg) ? p->G : 1;
   if (p->batch_group && group % p->batch_group == 0) G = p->batch_group;   // test knob, see mdi.h
   a.l0 = p->h_step_layers[0];
   a.w_stride = p->n_local > 1 ? (const char*)p->h_step_layers[1].wqkv - (const char*)p->h_step_layers[0].wqkv : 0;
@@ -979,7 +983,7 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
     item += a.n_hg * s.n_splits;
   }
   a.n_items = item;
-  const mdi_status st = launch_step_serialised(p, [&]() { launch_step_batch(p->stream, G, p->b_lds, a); });
+  const mdi_status st = launch_step_serialised(p, [&]() { launch_step_batch(p->stream, G, G == 4 && mfma_scores, p->b_lds, a); });
   if (st != MDI_OK) return st;
   p->b_epoch += 5u * (unsigned)p->n_local;
   for (int j = 0; j < n; ++j) p->seq_len[seqs[j]] = (uint32_t)mp[j].ctx;

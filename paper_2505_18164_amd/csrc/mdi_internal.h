@@ -313,7 +313,8 @@ struct LogitsBatchArgs {
 bool logits_batch_allow_lds(size_t lds_bytes);
 void launch_logits_batch(hipStream_t s, int nwg, size_t lds_bytes, const LogitsBatchArgs& a);
 
-void launch_step_batch(hipStream_t s, int G, size_t lds_bytes, const BatchArgs& a);
+// G: query heads per attention work item; scores_on_mfma: on the matrix cores (G = 4, heads of 128, pages of a multiple of 16 positions)
+void launch_step_batch(hipStream_t s, int G, bool scores_on_mfma, size_t lds_bytes, const BatchArgs& a);
 bool step_batch_allow_lds(size_t lds_bytes);
 
 // ---- set-up ---------------------------------------------------------------

@@ -54,6 +54,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
 }
+__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 __device__ __forceinline__ void st_pair(tagged_t* p, uint32_t bits, unsigned tag) {
   __hip_atomic_store(p, ((tagged_t)tag << 32) | (tagged_t)bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -279,6 +280,137 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
   if (tid == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
 }
 
+// ---------------------------------------------------------------------------
+// Attention of four query heads that share a kv head, heads of 128, with the scores on the matrix cores.  On the vector
+// ALUs a position costs four heads x (8 multiply-adds, 4 cross-lane adds, two 16-byte reads of q from LDS) per lane
+// before its values are touched, and the phase ran at that pace: 115 us a layer for 16 messages with 6144 positions,
+// where HBM needs 64 us; like this it takes 81 us (the whole 8-layer launch 1835 -> 1475 us).
+//   * A tile is 16 positions of one page (pages and context splits are multiples of 16, so one page number serves it).
+//     Keys in operand order: lane (i = l mod 16, kg = l div 16) holds columns 32 c + 8 kg .. + 7 of position i.
+//   * The queries stay exact: column n of the second operand is head n mod 4, and its columns n div 4 = 0, 1, 2 are three
+//     bf16 parts that add up to the 24 bits of q (the fourth is zero).  Adding the four columns of a head inside a row
+//     of 16 lanes (two rotations) leaves the score of position 4 kg + r in register r of every lane of row kg.
+//   * So a row of 16 lanes works on positions 4 kg .. 4 kg + 3 with running maximum, sum and output of its own, values
+//     as 16-byte pieces (lane = 8 columns); a lane keeps maximum and sum of head n mod 4, and reads another head's weight
+//     out of its quad (DPP).
+template <int QUAD> __device__ __forceinline__ float quad_lane(float v) {       // lane QUAD of every four, to all four
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), QUAD * 0x55, 0xF, 0xF, false));
+}
+template <int K> __device__ __forceinline__ float row_rotate(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + K, 0xF, 0xF, false));
+}
+struct Attn4 {
+  bf16x8 q[4];
+  float m, l, o[4][8];
+  int n_t;                       // tiles of the item's cached positions
+};
+// tile ti of this wavefront; tiles past the item's last re-read the sequence's first
+__device__ __forceinline__ int attn4_tile(const AttnGeo& g, const Attn4& s, int ti, int wave) {
+  const int t = ti * kStepWaves + wave;
+  return t < s.n_t ? g.s0 + 16 * t : -1;
+}
+__device__ __forceinline__ int attn4_page(const AttnGeo& g, const Attn4& s, const BatchView& S, int ti, int wave) {
+  const int base = max(attn4_tile(g, s, ti, wave), 0);
+  return __hip_atomic_load((const MDI_GLOBAL int32_t*)S.table + page_of(g, base), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void attn4_issue(Tile& t, int& pg, const AttnGeo& g, const Attn4& s, const BatchArgs& a, const BatchView& S,
+                                            const void* pool, int ti, int wave, int lane) {
+  const int base0 = attn4_tile(g, s, ti, wave), base = max(base0, 0);
+  const int page = __builtin_amdgcn_readfirstlane(pg);
+  const MDI_GLOBAL char* kb = (const MDI_GLOBAL char*)pool + 2 * (((long)page * a.K + g.kvh) * 2 * a.pt_h + (long)(base - page_of(g, base) * a.pt) * 128);
+  const uint32_t ko = (uint32_t)((lane & 15) * 256 + (lane >> 4) * 16);
+  // a position past the last one has weight zero, and its values must be finite: the last one's
+  const int end = base0 < 0 ? 15 : min(g.s1p - base - 1, 15), row = (lane >> 4) * 4;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    t.r[k] = *reinterpret_cast<const MDI_GLOBAL u32x4*>(kb + ko + 64 * k);
+    t.r[4 + k] = *reinterpret_cast<const MDI_GLOBAL u32x4*>(kb + 2 * a.pt_h + (uint32_t)(min(row + k, end) * 256 + (lane & 15) * 16));
+  }
+  pg = attn4_page(g, s, S, ti + 2, wave);
+}
+__device__ __forceinline__ void attn4_compute(Attn4& s, const Tile& t, const AttnGeo& g, int ti, int wave, int lane) {
+  const int base = attn4_tile(g, s, ti, wave);
+  if (base < 0) return;                                          // uniform
+  f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t.r[k]), s.q[k], c, 0, 0, 0);
+  float sc[4], p[4];
+  bool ok[4];
+  float mn = s.m;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float v = c[r] + row_rotate<4>(c[r]);
+    sc[r] = v + row_rotate<8>(v);
+    ok[r] = base + 4 * (lane >> 4) + r < g.s1p;
+    mn = ok[r] ? fmaxf(mn, sc[r]) : mn;
+  }
+  if (__any(mn != s.m)) {                                        // rare after the first tiles
+    const float alpha = __expf(s.m - mn);
+    s.m = mn; s.l *= alpha;
+    const float al[4] = {quad_lane<0>(alpha), quad_lane<1>(alpha), quad_lane<2>(alpha), quad_lane<3>(alpha)};
+#pragma unroll
+    for (int gi = 0; gi < 4; ++gi)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s.o[gi][e] *= al[gi];
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) { p[r] = ok[r] ? __expf(sc[r] - mn) : 0.f; s.l += p[r]; }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float vf[8];
+    Unpack<bf16_t>::go(t.r[4 + r], vf);
+    const float w[4] = {quad_lane<0>(p[r]), quad_lane<1>(p[r]), quad_lane<2>(p[r]), quad_lane<3>(p[r])};
+#pragma unroll
+    for (int gi = 0; gi < 4; ++gi)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s.o[gi][e] = fmaf(w[gi], vf[e], s.o[gi][e]);
+  }
+}
+// The whole stream of an item, between attn_begin (queries in qs, the newest position in `st`) and attn_to_lds.
+__device__ __forceinline__ void attn4_stream(Attn4& s, AttnState<bf16_t, 4>& st, Tile& A, Tile& B, int& pgA, int& pgB, const AttnGeo& g,
+                                             const BatchArgs& a, const BatchView& S, const void* kv, int wave, int lane, const float* qs) {
+  const int n = lane & 15, part = n >> 2;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float4* qp = reinterpret_cast<const float4*>(qs + (n & 3) * 128 + 32 * k + 8 * (lane >> 4));
+    const float4 lo = qp[0], hi = qp[1];
+    const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t b0 = f32_to_bf16(v[e]);
+      const float r1 = v[e] - bf16_bits_to_f32(b0);
+      const uint32_t b1 = f32_to_bf16(r1);
+      const uint32_t b2 = f32_to_bf16(r1 - bf16_bits_to_f32(b1));
+      const uint32_t b = part == 0 ? b0 : part == 1 ? b1 : part == 2 ? b2 : 0u;
+      if (e & 1) w[e >> 1] |= b << 16; else w[e >> 1] = b;
+    }
+    s.q[k] = __builtin_bit_cast(bf16x8, w);
+  }
+  const float m0 = st.m[0], m1 = st.m[1], m2 = st.m[2], m3 = st.m[3], l0 = st.l[0], l1 = st.l[1], l2 = st.l[2], l3 = st.l[3];
+  s.m = (n & 2) ? ((n & 1) ? m3 : m2) : ((n & 1) ? m1 : m0);
+  s.l = (n & 2) ? ((n & 1) ? l3 : l2) : ((n & 1) ? l1 : l0);
+#pragma unroll
+  for (int gi = 0; gi < 4; ++gi)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.o[gi][e] = st.o[gi][e];
+  const int n_w = (s.n_t - wave + kStepWaves - 1) / kStepWaves, nte = (max(n_w, 0) + 1) & ~1;
+#pragma nounroll
+  for (int t = 2; t < nte; t += 2) {
+    attn4_compute(s, A, g, t - 2, wave, lane);
+    attn4_issue(A, pgA, g, s, a, S, kv, t, wave, lane);
+    attn4_compute(s, B, g, t - 1, wave, lane);
+    attn4_issue(B, pgB, g, s, a, S, kv, t + 1, wave, lane);
+  }
+  if (nte) { attn4_compute(s, A, g, nte - 2, wave, lane); attn4_compute(s, B, g, nte - 1, wave, lane); }
+  st.m[0] = quad_lane<0>(s.m); st.m[1] = quad_lane<1>(s.m); st.m[2] = quad_lane<2>(s.m); st.m[3] = quad_lane<3>(s.m);
+  st.l[0] = quad_lane<0>(s.l); st.l[1] = quad_lane<1>(s.l); st.l[2] = quad_lane<2>(s.l); st.l[3] = quad_lane<3>(s.l);
+#pragma unroll
+  for (int gi = 0; gi < 4; ++gi)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st.o[gi][e] = s.o[gi][e];
+}
+
 __device__ __forceinline__ void bstamp(const BatchArgs& a, int layer, int ph, int k) {
   if (a.trace && threadIdx.x == 0)
     a.trace[(((long)blockIdx.x * a.n_layer + layer) * 5 + ph) * 8 + k] = wall_clock64();
@@ -352,7 +484,8 @@ __device__ __forceinline__ EpiOps epi_ops(const BatchArgs& a, const StepLayer& L
   return o;
 }
 
-template <int G>
+// G query heads per attention work item; kScoresOnMfma: see Attn4 (G = 4)
+template <int G, bool kScoresOnMfma>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_batch(BatchArgs a) {
   typedef bf16_t WT;
   extern __shared__ float smem[];
@@ -455,37 +588,34 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       // them: a thread keeps those of its first item, fetched again they would cost a round trip at the phase's end.
       if (ph == PH_ATTN) {
         // ---- attention: one work item = (message, head group, context split); items dealt round-robin
-        AttnState<WT, G> st;
-        AttnAsk<WT> ask{};
-        AttnGeo ga{};
-        Tile A, B;
-        int pgA[kTile], pgB[kTile];
-        BatchView V{};
-        int item = wg, slot = 0;
-        if (item < a.n_items) {
+        for (int item = wg, slot = 0; item < a.n_items; item += nwg) {
+          if (item != wg) __syncthreads();                           // the records in LDS have been read
           while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
-          V = view_of(a, slot, ob_l);
-          ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
+          const BatchView V = view_of(a, slot, ob_l);
+          const AttnGeo ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
+          AttnState<WT, G> st;
+          AttnAsk<WT> ask{};
+          Tile A, B;
           attn_ask<WT, G>(ask, ga, a, V, wave, epoch, tid);
-          attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
-          attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
-          bstamp(a, layer, ph, 1);
-          while (true) {
+          if constexpr (kScoresOnMfma) {
+            Attn4 s4;
+            s4.n_t = max(ga.s1p - ga.s0 + 15, 0) >> 4;
+            int pgA = attn4_page(ga, s4, V, 0, wave), pgB = attn4_page(ga, s4, V, 1, wave);
+            attn4_issue(A, pgA, ga, s4, a, V, Lv.kv, 0, wave, lane); attn4_issue(B, pgB, ga, s4, a, V, Lv.kv, 1, wave, lane);
+            if (item == wg) bstamp(a, layer, ph, 1);
+            attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
+            attn4_stream(s4, st, A, B, pgA, pgB, ga, a, V, Lv.kv, wave, lane, part);
+          } else {
+            int pgA[kTile], pgB[kTile];
+            attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
+            attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
+            if (item == wg) bstamp(a, layer, ph, 1);
             attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
             const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
             attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, Lv.kv, nte, wave, part);
-            attn_to_lds<WT, G>(st, ga, a.h, part, wave);
-            attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
-            item += nwg;
-            if (item >= a.n_items) break;
-            __syncthreads();                                       // the records in LDS have been read
-            while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
-            V = view_of(a, slot, ob_l);
-            ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
-            attn_ask<WT, G>(ask, ga, a, V, wave, epoch, tid);
-            attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
-            attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
           }
+          attn_to_lds<WT, G>(st, ga, a.h, part, wave);
+          attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
         }
         bstamp(a, layer, ph, 3);
       } else {
@@ -783,17 +913,20 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
 
 bool step_batch_allow_lds(size_t lds) {
   using namespace step_w8;
-  return hipFuncSetAttribute((const void*)k_step_batch<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
-         hipFuncSetAttribute((const void*)k_step_batch<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess &&
-         hipFuncSetAttribute((const void*)k_step_batch<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+  const void* const kernels[] = {(const void*)k_step_batch<1, false>, (const void*)k_step_batch<2, false>, (const void*)k_step_batch<4, false>,
+                                 (const void*)k_step_batch<4, true>};
+  for (const void* k : kernels)
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return false;
+  return true;
 }
 
-void launch_step_batch(hipStream_t s, int G, size_t lds, const BatchArgs& a) {
+void launch_step_batch(hipStream_t s, int G, bool scores_on_mfma, size_t lds, const BatchArgs& a) {
   using namespace step_w8;
   const dim3 grid(a.nwg), block(kStepThreads);
-  if (G == 4) hipLaunchKernelGGL((k_step_batch<4>), grid, block, lds, s, a);
-  else if (G == 2) hipLaunchKernelGGL((k_step_batch<2>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((k_step_batch<1>), grid, block, lds, s, a);
+  if (G == 4 && scores_on_mfma) hipLaunchKernelGGL((k_step_batch<4, true>), grid, block, lds, s, a);
+  else if (G == 4) hipLaunchKernelGGL((k_step_batch<4, false>), grid, block, lds, s, a);
+  else if (G == 2) hipLaunchKernelGGL((k_step_batch<2, false>), grid, block, lds, s, a);
+  else hipLaunchKernelGGL((k_step_batch<1, false>), grid, block, lds, s, a);
 }
 
 }  // namespace mdi

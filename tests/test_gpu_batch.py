@@ -59,6 +59,28 @@ def test_batched_pass_against_the_oracle(name, n_msg):
     print(f"{name} x{n_msg}: worst rel-L2 {worst:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("page", [16, 48, 8])
+@pytest.mark.parametrize("n_head,n_kv_head", [(4, 1), (8, 2)])
+def test_batched_pass_with_four_heads_of_128_per_item(n_head, n_kv_head, page, monkeypatch):
+    """Scores of four query heads on the matrix cores: tiles of 16 positions of one page (pages that are no multiple of
+    16 keep the vector ALUs), contexts at the edges of tiles, of pages and of a split (more than 128 positions)."""
+    monkeypatch.setenv("MDI_BATCH_GROUP", "4")
+    cfg = S.tiny(n_layer=2, dtype=S.DT_BF16, max_ctx=576, vocab=211, d_model=64, n_head=n_head, n_kv_head=n_kv_head, head_dim=128, d_ff=96)
+    w = scale_matrices(S.make_weights(cfg, 31, exercise=True), 2.0)
+    lens = (1, 14, 15, 16, 17, 127, 143, 300, 512)
+    o, g = pair(cfg, w, 0, 2, embed=True, max_seqs=len(lens), kv_page_tokens=page)
+    for s, T in enumerate(lens):
+        ids = S.make_prompts(cfg, 31 + s, 1, T)[0]
+        check(g.prefill(s, dev_ids(ids)), o.prefill(s, ids), cfg, ("prefill", s))
+    rng = np.random.default_rng(7)
+    order = list(range(len(lens)))
+    for step in range(3):
+        toks = [int(rng.integers(0, cfg["vocab"])) for _ in order]
+        for s, t, got in zip(order, toks, g.decode_batch(order, [dev_ids([t]) for t in toks])):
+            check(got, o.decode_step(s, t), cfg, ("batched decode", step, s))
+    g.sync()
+
+
 @pytest.mark.parametrize("name", ["gqa_h16", "wide", "gpt2_like"])
 def test_the_number_of_messages_changes_from_pass_to_pass(name):
     """The exchange vectors are packed by the pass's number of messages: passes of different sizes leave words at
