@@ -25,6 +25,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int BQ = 128;       // queries per workgroup (32 per wavefront)
 constexpr int BK = 64;        // keys per step
 
+// 2^x as the hardware gives it (the scores carry log2 e, see the launch)
+__device__ __forceinline__ float exp2f_raw(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // values of the T new positions: fp32 rows of the fused QKV product -> bf16 [kv head][h][ldk], row t at column
 // pos0 + t; columns up to pos0 + n_cols - 1 are cleared (keys nobody may see, but finite)
 __global__ __launch_bounds__(256) void k_v_transpose(const float* qkv, int T, int n_cols, int pos0, int ldk, int n_rows, int v_off, int h, bf16_t* vt) {
@@ -69,24 +72,28 @@ __global__ __launch_bounds__(256) void k_cache_gather(const bf16_t* pool, const 
   }
 }
 
-// Two groups of four wavefronts work on the same 128 queries: group g takes the key blocks 2 i + g, so the longest
-// workgroup (the last queries, which see every key) has half as many steps in a row, and a SIMD holds two wavefronts
-// whose matrix and softmax arithmetic overlap.  The groups' running (maximum, sum, output) are folded through LDS at
-// the end, group 0 first: the result does not depend on timing.
-template <int HD>
-__global__ __launch_bounds__(512) void k_flash_prefill(FlashArgs a) {
+// A workgroup is NG groups of four wavefronts that work on the same 128 queries; group g takes the key blocks
+// NG i + g.  With two groups the longest workgroup (the last queries, which see every key) has half as many steps in a
+// row and a SIMD holds two wavefronts; the groups' running (maximum, sum, output) are folded through LDS at the end,
+// group 0 first, so the result does not depend on timing.  With one, two workgroups share a compute unit and nothing
+// keeps them in step: one multiplies while the other takes exponentials.
+//
+// What bounds it: a block of 64 keys is 32 matrix instructions and about as much time on the vector ALUs (32 scores per
+// lane: subtract, exponential, sum, maximum, conversion), and a wavefront has one or the other to do.  
+// 6000 positions of the 8B shape: 576 us a layer with the blocks single-buffered between two barriers, the groups in
+// step, base-e exponentials and a rescaling in every block; now 450 us (0.65 PFLOP/s).
+template <int HD, int NG>
+__global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   constexpr int KS = HD + 8;            // LDS row stride of a key (elements): 16 bytes of padding spread the rows over the banks
   constexpr int VS = BK + 4;            // LDS row stride of a value channel: an odd number of 8-byte units
   constexpr int HT = HD / 32;           // 32-channel tiles of the output
   constexpr int KP = BK * HD / 8 / 256; // 16-byte pieces of a key block per thread of a group
   extern __shared__ __attribute__((aligned(16))) unsigned char flash_smem[];
-  bf16_t* Ks_all = (bf16_t*)flash_smem;                 // [2][BK * KS]
-  bf16_t* Vs_all = Ks_all + 2 * BK * KS;                // [2][HD * VS]
+  constexpr int KV = BK * KS + HD * VS;                 // elements of a key block and its values; two blocks per group
 
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // position inside the group
   const int grp = threadIdx.x >> 8;
-  bf16_t* Ks = Ks_all + grp * BK * KS;
-  bf16_t* Vs = Vs_all + grp * HD * VS;
+  bf16_t* bufs = (bf16_t*)flash_smem + grp * 2 * KV;
   const int qb = gridDim.x - 1 - blockIdx.x;                     // the longest rows first
   const int head = blockIdx.y, kvh = head / (a.H / a.K);
   const int q0 = qb * BQ, qw0 = q0 + 32 * wave;
@@ -113,12 +120,12 @@ __global__ __launch_bounds__(512) void k_flash_prefill(FlashArgs a) {
   const bf16_t* vbase = a.vt + (long)kvh * HD * a.ldk;
   const int p0 = a.p0;                                           // position of query 0: keys 0 .. p0 + query are visible
   const int n_kb = min((p0 + q0 + BQ + BK - 1) / BK, a.Tk / BK); // key blocks any query of this workgroup may see
-  const int n_it = (n_kb + 1) / 2;                               // steps: block 2 it + grp each
+  const int n_it = (n_kb + NG - 1) / NG;                         // steps: block NG it + grp each
 
   // staging registers: the next block's keys and values travel global -> registers during the arithmetic
   // (a group whose last step has no block re-reads block 0 and skips the arithmetic)
   u32x4 kreg[KP], vreg[KP];
-  auto fetch = [&](int kb) {
+  auto fetch = [&](int kb) __attribute__((always_inline)) {
     if (kb >= n_kb) kb = 0;
 #pragma unroll
     for (int i = 0; i < KP; ++i) {
@@ -128,7 +135,8 @@ __global__ __launch_bounds__(512) void k_flash_prefill(FlashArgs a) {
       vreg[i] = *reinterpret_cast<const u32x4*>(vbase + (long)c * a.ldk + (long)kb * BK + 8 * j);
     }
   };
-  auto stash = [&]() {
+  auto stash = [&](bf16_t* Ks) __attribute__((always_inline)) {
+    bf16_t* Vs = Ks + BK * KS;
 #pragma unroll
     for (int i = 0; i < KP; ++i) {
       const int p = tid + i * 256;
@@ -141,90 +149,96 @@ __global__ __launch_bounds__(512) void k_flash_prefill(FlashArgs a) {
   };
 
   fetch(grp);
+  stash(bufs);
+  __syncthreads();
   for (int it = 0; it < n_it; ++it) {
-    const int kb = 2 * it + grp;
-    __syncthreads();                                             // everybody is done with the previous blocks
-    stash();
-    __syncthreads();
-    if (it + 1 < n_it) fetch(kb + 2);
+    const int kb = NG * it + grp;
+    const bf16_t* Ks = bufs + (it & 1) * KV;
+    const bf16_t* Vs = Ks + BK * KS;
+    if (it + 1 < n_it) fetch(kb + NG);
     const int k0 = kb * BK;
-    if (kb >= n_kb || k0 > p0 + qw0 + 31) continue;              // no block, or this wavefront's queries see none of these keys
+    if (kb < n_kb && k0 <= p0 + qw0 + 31) {                      // else: no block, or this wavefront's queries see none of these keys
 
-    // ---- S^T = K Q^T: two tiles of 32 keys x 32 queries
-    f32x16 s[2];
+      // ---- S^T = K Q^T: two tiles of 32 keys x 32 queries
+      f32x16 s[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+      for (int t = 0; t < 2; ++t) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
-      const bf16_t* kr = Ks + (32 * t + col) * KS + 8 * half;
+        for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+        const bf16_t* kr = Ks + (32 * t + col) * KS + 8 * half;
 #pragma unroll
-      for (int ks = 0; ks < HD / 16; ++ks)
-        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kr + 16 * ks), qf[ks], s[t], 0, 0, 0);
-    }
-    // ---- causal mask and the lane's share of the row statistics (row of S = column here = this lane's query)
-    float mloc = -1e30f;
-    const bool diag = k0 + BK - 1 > p0 + qw0;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = k0 + 32 * t + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (diag && key > p0 + query) s[t][r] = -1e30f;
-        mloc = fmaxf(mloc, s[t][r]);
+        for (int ks = 0; ks < HD / 16; ++ks)
+          s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kr + 16 * ks), qf[ks], s[t], 0, 0, 0);
       }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-    const float mn = fmaxf(m, mloc);
-    const float alpha = __expf(m - mn);
-    m = mn;
-    float lsum = 0.f;
+      // ---- causal mask and the lane's share of the row statistics (row of S = column here = this lane's query)
+      float mloc = -1e30f;
+      const bool diag = k0 + BK - 1 > p0 + qw0;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { const float p = __expf(s[t][r] - mn); s[t][r] = p; lsum += p; }
-    l = l * alpha + lsum;                                        // the two lanes of a query keep separate sums until the end
-#pragma unroll
-    for (int i = 0; i < HT; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
-
-    // ---- O^T += V^T P^T.  Step (t, pp) contracts keys [32 t + 16 pp, + 16); inside a step this half of the
-    // wavefront supplies keys {0..3, 8..11} + 4 half, which is what registers 8 pp .. 8 pp + 7 of tile t hold
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int pp = 0; pp < 2; ++pp) {
-        bf16x8 pf;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) pf[j] = (__bf16)s[t][8 * pp + j];
-        const bf16_t* vr = Vs + col * VS + 32 * t + 16 * pp + 4 * half;
-#pragma unroll
-        for (int i = 0; i < HT; ++i) {
-          const u32x2 lo = *reinterpret_cast<const u32x2*>(vr + 32 * i * VS);
-          const u32x2 hi = *reinterpret_cast<const u32x2*>(vr + 32 * i * VS + 8);
-          const u32x4 vf = {lo.x, lo.y, hi.x, hi.y};
-          o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf), pf, o[i], 0, 0, 0);
+        for (int r = 0; r < 16; ++r) {
+          const int key = k0 + 32 * t + 8 * (r >> 2) + 4 * half + (r & 3);
+          if (diag && key > p0 + query) s[t][r] = -1e30f;
+          mloc = fmaxf(mloc, s[t][r]);
         }
+      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+      const float mn = fmaxf(m, mloc);
+      if (__any(mn != m)) {                                        // rare after the first blocks
+        const float alpha = exp2f_raw(m - mn);
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int i = 0; i < HT; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
       }
+      float lsum = 0.f;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { const float p = exp2f_raw(s[t][r] - mn); s[t][r] = p; lsum += p; }
+      l += lsum;                                                   // the two lanes of a query keep separate sums until the end
+
+      // ---- O^T += V^T P^T.  Step (t, pp) contracts keys [32 t + 16 pp, + 16); inside a step this half of the
+      // wavefront supplies keys {0..3, 8..11} + 4 half, which is what registers 8 pp .. 8 pp + 7 of tile t hold
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int pp = 0; pp < 2; ++pp) {
+          bf16x8 pf;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) pf[j] = (__bf16)s[t][8 * pp + j];
+          const bf16_t* vr = Vs + col * VS + 32 * t + 16 * pp + 4 * half;
+#pragma unroll
+          for (int i = 0; i < HT; ++i) {
+            const u32x2 lo = *reinterpret_cast<const u32x2*>(vr + 32 * i * VS);
+            const u32x2 hi = *reinterpret_cast<const u32x2*>(vr + 32 * i * VS + 8);
+            const u32x4 vf = {lo.x, lo.y, hi.x, hi.y};
+            o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf), pf, o[i], 0, 0, 0);
+          }
+        }
+    }
+    if (it + 1 < n_it) stash(bufs + ((it + 1) & 1) * KV);        // the block before this one, which everybody has left
+    __syncthreads();
   }
 
   // ---- fold the two groups: group 1 hands its state over through LDS (the K/V area, no longer needed);
   //      element j of thread t at [j][t], so that a wavefront's accesses are consecutive
-  float* fold = (float*)flash_smem;
-  __syncthreads();
-  if (grp == 1) {
+  if constexpr (NG == 2) {
+    float* fold = (float*)flash_smem;
+    if (grp == 1) {
 #pragma unroll
-    for (int i = 0; i < HT; ++i)
+      for (int i = 0; i < HT; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) fold[(i * 16 + r) * 256 + tid] = o[i][r];
-    fold[(HT * 16) * 256 + tid] = m;
-    fold[(HT * 16 + 1) * 256 + tid] = l;
-  }
-  __syncthreads();
-  if (grp == 1) return;
-  {
+        for (int r = 0; r < 16; ++r) fold[(i * 16 + r) * 256 + tid] = o[i][r];
+      fold[(HT * 16) * 256 + tid] = m;
+      fold[(HT * 16 + 1) * 256 + tid] = l;
+    }
+    __syncthreads();
+    if (grp == 1) return;
     const float m1 = fold[(HT * 16) * 256 + tid], l1 = fold[(HT * 16 + 1) * 256 + tid];
     const float mn = fmaxf(m, m1);
-    const float a0 = __expf(m - mn), a1 = __expf(m1 - mn);       // a group that saw no key has m = -1e30, l = 0, o = 0
+    const float a0 = exp2f_raw(m - mn), a1 = exp2f_raw(m1 - mn);   // a group that saw no key has m = -1e30, l = 0, o = 0
     l = l * a0 + l1 * a1;
 #pragma unroll
     for (int i = 0; i < HT; ++i)
@@ -247,12 +261,23 @@ __global__ __launch_bounds__(512) void k_flash_prefill(FlashArgs a) {
   }
 }
 
-template <int HD>
+template <int HD, int NG>
 constexpr size_t flash_lds_bytes() {
-  // two key blocks and two value blocks; the fold at the end needs HD / 2 + 2 floats per thread of one group
-  const size_t kv = (size_t)2 * (BK * (HD + 8) + HD * (BK + 4)) * sizeof(bf16_t);
-  const size_t fold = (size_t)(HD / 2 + 2) * 256 * sizeof(float);
+  // two key blocks and their values per group; the fold at the end needs HD / 2 + 2 floats per thread of one group
+  const size_t kv = (size_t)NG * 2 * (BK * (HD + 8) + HD * (BK + 4)) * sizeof(bf16_t);
+  const size_t fold = NG == 2 ? (size_t)(HD / 2 + 2) * 256 * sizeof(float) : 0;
   return kv > fold ? kv : fold;
+}
+template <int HD, int NG>
+void launch_flash(hipStream_t s, const FlashArgs& a) {
+  constexpr size_t lds = flash_lds_bytes<HD, NG>();
+  if (lds > 64 * 1024) {                                         // above what a kernel gets by default
+    static std::once_flag raised;
+    std::call_once(raised, []() {
+      (void)hipFuncSetAttribute((const void*)k_flash_prefill<HD, NG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    });
+  }
+  hipLaunchKernelGGL((k_flash_prefill<HD, NG>), dim3(a.Tp / BQ, a.H), dim3(256 * NG), lds, s, a);
 }
 
 }  // namespace
@@ -272,17 +297,12 @@ void launch_cache_gather(hipStream_t s, const void* pool, const int32_t* table, 
 }
 
 void launch_flash_prefill(hipStream_t s, const FlashArgs& a) {
-  const dim3 grid(a.Tp / BQ, a.H);
-  if (a.h == 128) {
-    constexpr size_t lds = flash_lds_bytes<128>();               // above the 64 KiB a kernel gets by default
-    static std::once_flag raised;
-    std::call_once(raised, []() {
-      (void)hipFuncSetAttribute((const void*)k_flash_prefill<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
-    hipLaunchKernelGGL(k_flash_prefill<128>, grid, dim3(512), lds, s, a);
-  } else {
-    hipLaunchKernelGGL(k_flash_prefill<64>, grid, dim3(512), flash_lds_bytes<64>(), s, a);
-  }
+  // One group per workgroup once there are half as many more workgroups than compute units, measured on 4 layers: 1536
+  // positions of the 7B shape (384 workgroups) 2815 -> 2774 us, 2048 3432 -> 3381, TinyLlama's 2048 1179 -> 1151; but 1024
+  // (256 workgroups) 1821 -> 1847.
+  const bool one = (a.Tp / BQ) * a.H >= 384;
+  if (a.h == 128) { if (one) launch_flash<128, 1>(s, a); else launch_flash<128, 2>(s, a); }
+  else { if (one) launch_flash<64, 1>(s, a); else launch_flash<64, 2>(s, a); }
 }
 
 }  // namespace mdi

@@ -659,7 +659,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     const float scale = 1.f / sqrtf((float)h);
     if (flash && pos0) launch_cache_gather(s, L.kv, drow, pos0, K, h, p->pt, Tk, p->p_kc, p->p_vt);
     RopeScatterArgs rs{p->p_qkv, (int)T, H, K, h, p->pt, p->rope, flash ? nullptr : p->p_q, L.kv, drow, (int)c.dtype,
-                       flash ? p->p_qb : nullptr, flash ? p->p_kc : nullptr, Tk, Tk - pos0, scale, pos0};
+                       flash ? p->p_qb : nullptr, flash ? p->p_kc : nullptr, Tk, Tk - pos0, scale * 1.44269504f, pos0};   // log2 e: k_flash_prefill's exponentials are powers of two
     launch_rope_scatter(s, rs);
     if (flash) {
       launch_v_transpose(s, p->p_qkv, (int)T, Tk - pos0, pos0, Tk, H, K, h, p->p_vt);
