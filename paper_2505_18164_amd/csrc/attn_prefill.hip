@@ -8,8 +8,15 @@
 // query, so each lane owns one query: its running maximum, its sum and the rescaling of its output
 // are plain per-lane scalars (lanes l and l + 32 share a query and exchange two numbers per block of
 // keys), and P^T leaves the first product in exactly the register layout the second one wants as
-// its B operand, without any data movement.  The price is that the values are needed with the key
-// index contiguous (A operand of V^T P^T), so a small kernel writes V transposed beforehand.
+// its B operand, without any data movement.  The values are needed with the key index
+// contiguous (A operand of V^T P^T): they lie in LDS as they lie in memory, and ds_read_b64_tr_b16 transposes four keys x
+// sixteen channels on the way to the registers.
+//
+// Keys and values are read where they live, in the sample's cache pages, those of this call as well as those of earlier
+// pieces of the visit.  (Two kernels per layer and call used to lay them out for this one, values transposed: 10 us of a
+// layer's 480 at 1024 positions of the 7B shape, 26 of 223 in pieces of 256: visits of 1024 3.63 -> 3.56 ms, in four
+// pieces 7.16 -> 6.41 ms, 333 of TinyLlama 1.15 -> 1.07 ms, 6000 of the 8B shape 22.0 -> 22.4 ms on one machine.
+// Transposing in registers on the way into LDS: 531 us a layer of 6000 positions, 490 as it is.)
 #include <mutex>
 
 #include "device_utils.h"
@@ -25,52 +32,13 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int BQ = 128;       // queries per workgroup (32 per wavefront)
 constexpr int BK = 64;        // keys per step
 
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 read_transposed(const bf16_t* p) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)p));
+}
+
 // 2^x as the hardware gives it (the scores carry log2 e, see the launch)
 __device__ __forceinline__ float exp2f_raw(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// values of the T new positions: fp32 rows of the fused QKV product -> bf16 [kv head][h][ldk], row t at column
-// pos0 + t; columns up to pos0 + n_cols - 1 are cleared (keys nobody may see, but finite)
-__global__ __launch_bounds__(256) void k_v_transpose(const float* qkv, int T, int n_cols, int pos0, int ldk, int n_rows, int v_off, int h, bf16_t* vt) {
-  __shared__ bf16_t tile[64][64 + 2];
-  const int t0 = blockIdx.x * 64, c0 = blockIdx.y * 64;          // 64 positions x 64 channels of the K*h value channels
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int tt = i >> 6, c = i & 63;
-    const int t = t0 + tt;
-    tile[tt][c] = t < T ? f32_to_bf16(qkv[(long)t * n_rows + v_off + c0 + c]) : (bf16_t)0;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int c = i >> 6, tt = i & 63;
-    if (t0 + tt < n_cols) vt[(long)(c0 + c) * ldk + pos0 + t0 + tt] = tile[tt][c];          // channel c0 + c = kv head * h + element
-  }
-}
-
-// A later piece of a first visit attends to the positions already in the cache as well (Alg. 2: the cache is
-// extended, never rebuilt): their keys and values are brought from the sample's pages into the operand arrays, keys
-// as they are, values transposed.  One workgroup per (64 positions, 64 channels of one kv head).
-__global__ __launch_bounds__(256) void k_cache_gather(const bf16_t* pool, const int32_t* table, int n_pos, int K, int h, int pt, int ldk,
-                                                      bf16_t* k_bf, bf16_t* vt) {
-  __shared__ bf16_t tile[64][64 + 2];
-  const int t0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int kvh = c0 / h, e0 = c0 - kvh * h;
-  const long pt_h = (long)pt * h;
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int tt = i >> 6, c = i & 63;
-    const int t = t0 + tt;
-    if (t < n_pos) {
-      const long base = ((long)table[t / pt] * K + kvh) * 2 * pt_h + (long)(t % pt) * h + e0 + c;
-      k_bf[((long)kvh * ldk + t) * h + e0 + c] = pool[base];
-      tile[tt][c] = pool[base + pt_h];
-    } else {
-      tile[tt][c] = (bf16_t)0;
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-    const int c = i >> 6, tt = i & 63;
-    if (t0 + tt < n_pos) vt[(long)(c0 + c) * ldk + t0 + tt] = tile[tt][c];
-  }
-}
 
 // A workgroup is NG groups of four wavefronts that work on the same 128 queries; group g takes the key blocks
 // NG i + g.  With two groups the longest workgroup (the last queries, which see every key) has half as many steps in a
@@ -79,23 +47,27 @@ __global__ __launch_bounds__(256) void k_cache_gather(const bf16_t* pool, const 
 // keeps them in step: one multiplies while the other takes exponentials.
 //
 // What bounds it: a block of 64 keys is 32 matrix instructions and about as much time on the vector ALUs (32 scores per
-// lane: subtract, exponential, sum, maximum, conversion), and a wavefront has one or the other to do.  
+// lane: subtract, exponential, sum, maximum, conversion), and a wavefront has one or the other to do.
 // 6000 positions of the 8B shape: 576 us a layer with the blocks single-buffered between two barriers, the groups in
-// step, base-e exponentials and a rescaling in every block; now 450 us (0.65 PFLOP/s).
+// step, base-e exponentials and a rescaling in every block; now 490 us (0.60 PFLOP/s), of which heads that share keys on
+// one die give 20.
 template <int HD, int NG>
 __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   constexpr int KS = HD + 8;            // LDS row stride of a key (elements): 16 bytes of padding spread the rows over the banks
-  constexpr int VS = BK + 4;            // LDS row stride of a value channel: an odd number of 8-byte units
+  constexpr int VR = HD + 32;           // LDS row stride of a key's values: 16 dwords past a multiple of 64 (heads of 64: 48), so that the
+                                        // eight keys x 32 channels of a transposing read touch every bank twice
   constexpr int HT = HD / 32;           // 32-channel tiles of the output
-  constexpr int KP = BK * HD / 8 / 256; // 16-byte pieces of a key block per thread of a group
   extern __shared__ __attribute__((aligned(16))) unsigned char flash_smem[];
-  constexpr int KV = BK * KS + HD * VS;                 // elements of a key block and its values; two blocks per group
+  constexpr int KV = BK * KS + BK * VR;                 // elements of a key block and its values; two blocks per group
 
   const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // position inside the group
   const int grp = threadIdx.x >> 8;
   bf16_t* bufs = (bf16_t*)flash_smem + grp * 2 * KV;
-  const int qb = gridDim.x - 1 - blockIdx.x;                     // the longest rows first
-  const int head = blockIdx.y, kvh = head / (a.H / a.K);
+  // Workgroups are handed to the eight compute dies in turn, each with an L2 of its own: a die takes heads that follow
+  // each other (they share their keys), longest rows first.
+  const int n_qb = a.Tp / BQ, per_die = (n_qb * a.H + 7) >> 3, idx = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
+  if (idx >= n_qb * a.H) return;
+  const int head = idx / n_qb, qb = n_qb - 1 - (idx - head * n_qb), kvh = head / (a.H / a.K);
   const int q0 = qb * BQ, qw0 = q0 + 32 * wave;
   const int col = lane & 31, half = lane >> 5;
   const int query = qw0 + col;
@@ -116,37 +88,66 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
     for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
   float m = -1e30f, l = 0.f;
 
-  const bf16_t* kbase = a.k + (long)kvh * a.ldk * HD;
-  const bf16_t* vbase = a.vt + (long)kvh * HD * a.ldk;
   const int p0 = a.p0;                                           // position of query 0: keys 0 .. p0 + query are visible
-  const int n_kb = min((p0 + q0 + BQ + BK - 1) / BK, a.Tk / BK); // key blocks any query of this workgroup may see
+  const int n_keys = p0 + a.T, n_kb = min((p0 + q0 + BQ + BK - 1) / BK, (n_keys + BK - 1) / BK); // key blocks any query of this workgroup may see
   const int n_it = (n_kb + NG - 1) / NG;                         // steps: block NG it + grp each
 
-  // staging registers: the next block's keys and values travel global -> registers during the arithmetic
-  // (a group whose last step has no block re-reads block 0 and skips the arithmetic)
-  u32x4 kreg[KP], vreg[KP];
-  auto fetch = [&](int kb) __attribute__((always_inline)) {
-    if (kb >= n_kb) kb = 0;
+  // Staging: the next block's keys and values travel global -> registers during the arithmetic, its page numbers a block
+  // ahead of that.  A thread moves channels 8 oct .. + 7 of KU keys of a block.  Keys past the last repeat
+  // it (no query sees them, but they are finite), a group whose last step has no block re-reads the last key.
+  constexpr int KU = HD / 32;
+  const int oct = tid % (HD / 8), ku = tid / (HD / 8);
+  u32x4 kreg[KU], vreg[KU];
+  int pg[KU];
+  auto key_in = [&](int j) __attribute__((always_inline)) { return ku + j * (2048 / HD); };
+  auto key_of = [&](int kb, int j) __attribute__((always_inline)) { return min(kb * BK + key_in(j), n_keys - 1); };
+  auto page_of = [&](int pos) __attribute__((always_inline)) { return a.pt_sh >= 0 ? pos >> a.pt_sh : (int)__umulhi((unsigned)pos, a.pt_magic); };
+  const bool block_page = a.pt_sh >= 6;                          // a block of 64 keys lies in one page
+  auto pages = [&](int kb) __attribute__((always_inline)) {
+    if (block_page) {
+      int at = min(kb * BK, n_keys - 1) >> a.pt_sh;
+      asm volatile("" : "+v"(at));                               // a vector load: behind a scalar one every read of LDS would have to wait for it
+      pg[0] = a.table[at];
+    } else {
 #pragma unroll
-    for (int i = 0; i < KP; ++i) {
-      const int p = tid + i * 256;                               // piece p: key p / (HD/8), elements 8 (p % (HD/8))
-      kreg[i] = *reinterpret_cast<const u32x4*>(kbase + ((long)kb * BK + p / (HD / 8)) * HD + 8 * (p % (HD / 8)));
-      const int c = p / (BK / 8), j = p % (BK / 8);              // channel c, keys [8 j, 8 j + 8) of the block
-      vreg[i] = *reinterpret_cast<const u32x4*>(vbase + (long)c * a.ldk + (long)kb * BK + 8 * j);
+      for (int j = 0; j < KU; ++j) pg[j] = a.table[page_of(key_of(kb, j))];
     }
+  };
+  auto fetch = [&](int kb) __attribute__((always_inline)) {
+    if (block_page) {                                            // uniform base, 32-bit lane offsets
+      const int page = __builtin_amdgcn_readfirstlane(pg[0]);
+      const char* kp = (const char*)(a.pool + ((long)page * a.K + kvh) * 2 * a.pt * HD);
+      const char* vp = kp + (long)a.pt * HD * 2;
+#pragma unroll
+      for (int j = 0; j < KU; ++j) {
+        const uint32_t off = (uint32_t)((key_of(kb, j) & (a.pt - 1)) * HD + 8 * oct) * 2u;
+        kreg[j] = *reinterpret_cast<const u32x4*>(kp + off);
+        vreg[j] = *reinterpret_cast<const u32x4*>(vp + off);
+      }
+      pages(kb + NG);
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < KU; ++j) {
+      const int pos = key_of(kb, j);
+      const bf16_t* kp = a.pool + (((long)pg[j] * a.K + kvh) * 2 * a.pt + (pos - page_of(pos) * a.pt)) * HD + 8 * oct;
+      kreg[j] = *reinterpret_cast<const u32x4*>(kp);
+      vreg[j] = *reinterpret_cast<const u32x4*>(kp + (long)a.pt * HD);
+    }
+    pages(kb + NG);
   };
   auto stash = [&](bf16_t* Ks) __attribute__((always_inline)) {
     bf16_t* Vs = Ks + BK * KS;
 #pragma unroll
-    for (int i = 0; i < KP; ++i) {
-      const int p = tid + i * 256;
-      *reinterpret_cast<u32x4*>(Ks + (p / (HD / 8)) * KS + 8 * (p % (HD / 8))) = kreg[i];
-      const int c = p / (BK / 8), j = p % (BK / 8);
-      u32x2* d = reinterpret_cast<u32x2*>(Vs + c * VS + 8 * j);  // 8-byte aligned: VS * 2 is a multiple of 8
-      d[0] = u32x2{vreg[i].x, vreg[i].y};
-      d[1] = u32x2{vreg[i].z, vreg[i].w};
+    for (int j = 0; j < KU; ++j) {
+      *reinterpret_cast<u32x4*>(Ks + key_in(j) * KS + 8 * oct) = kreg[j];
+      *reinterpret_cast<u32x4*>(Vs + key_in(j) * VR + 8 * oct) = vreg[j];
     }
   };
+
+  pages(grp);
+  // Of every 16 lanes, lane j names key j / 4 and channels 4 (j mod 4) .. + 3 and receives channel j of the four keys.
+  const int v_lane = (4 * half + ((lane & 15) >> 2)) * VR + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
   fetch(grp);
   stash(bufs);
@@ -208,11 +209,10 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
           bf16x8 pf;
 #pragma unroll
           for (int j = 0; j < 8; ++j) pf[j] = (__bf16)s[t][8 * pp + j];
-          const bf16_t* vr = Vs + col * VS + 32 * t + 16 * pp + 4 * half;
 #pragma unroll
           for (int i = 0; i < HT; ++i) {
-            const u32x2 lo = *reinterpret_cast<const u32x2*>(vr + 32 * i * VS);
-            const u32x2 hi = *reinterpret_cast<const u32x2*>(vr + 32 * i * VS + 8);
+            const bf16_t* vr = Vs + v_lane + (32 * t + 16 * pp) * VR + 32 * i;
+            const u32x2 lo = read_transposed(vr), hi = read_transposed(vr + 8 * VR);
             const u32x4 vf = {lo.x, lo.y, hi.x, hi.y};
             o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf), pf, o[i], 0, 0, 0);
           }
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
 template <int HD, int NG>
 constexpr size_t flash_lds_bytes() {
   // two key blocks and their values per group; the fold at the end needs HD / 2 + 2 floats per thread of one group
-  const size_t kv = (size_t)NG * 2 * (BK * (HD + 8) + HD * (BK + 4)) * sizeof(bf16_t);
+  const size_t kv = (size_t)NG * 2 * BK * (HD + 8 + HD + 32) * sizeof(bf16_t);
   const size_t fold = NG == 2 ? (size_t)(HD / 2 + 2) * 256 * sizeof(float) : 0;
   return kv > fold ? kv : fold;
 }
@@ -277,24 +277,12 @@ void launch_flash(hipStream_t s, const FlashArgs& a) {
       (void)hipFuncSetAttribute((const void*)k_flash_prefill<HD, NG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
   }
-  hipLaunchKernelGGL((k_flash_prefill<HD, NG>), dim3(a.Tp / BQ, a.H), dim3(256 * NG), lds, s, a);
+  hipLaunchKernelGGL((k_flash_prefill<HD, NG>), dim3(8 * ((a.Tp / BQ * a.H + 7) / 8)), dim3(256 * NG), lds, s, a);
 }
 
 }  // namespace
 
 bool flash_supported(int dtype, int h) { return dtype == MDI_BF16 && (h == 64 || h == 128); }
-
-void launch_v_transpose(hipStream_t s, const float* qkv, int T, int n_cols, int pos0, int ldk, int H, int K, int h, bf16_t* vt) {
-  const dim3 grid((n_cols + 63) / 64, K * h / 64);
-  hipLaunchKernelGGL(k_v_transpose, grid, dim3(256), 0, s, qkv, T, n_cols, pos0, ldk, (H + 2 * K) * h, (H + K) * h, h, vt);
-}
-
-void launch_cache_gather(hipStream_t s, const void* pool, const int32_t* table, int n_pos, int K, int h, int pt, int ldk,
-                         bf16_t* k_bf, bf16_t* vt) {
-  if (n_pos <= 0) return;
-  const dim3 grid((n_pos + 63) / 64, K * h / 64);
-  hipLaunchKernelGGL(k_cache_gather, grid, dim3(256), 0, s, (const bf16_t*)pool, table, n_pos, K, h, pt, ldk, k_bf, vt);
-}
 
 void launch_flash_prefill(hipStream_t s, const FlashArgs& a) {
   // One group per workgroup once there are half as many more workgroups than compute units, measured on 4 layers: 1536

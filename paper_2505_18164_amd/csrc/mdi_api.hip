@@ -64,8 +64,7 @@ struct mdi_partition {
   void *p_xn = nullptr, *p_o = nullptr, *p_u = nullptr;
   float* p_part = nullptr;       // partial results of products whose inner dimension is split
   size_t part_cap = 0;           // ... in floats
-  bf16_t *p_qb = nullptr, *p_kc = nullptr, *p_vt = nullptr;   // operands of the matrix-core attention of a first visit
-  int Tp = 0;                                                 // longest first visit rounded up to whole query blocks
+  bf16_t* p_qb = nullptr;        // queries of the matrix-core attention of a first visit
   // host bookkeeping
   std::vector<uint32_t> seq_len;
   std::vector<int32_t> host_tables;   // mirror of `tables`, source of the async page-table copies
@@ -242,13 +241,7 @@ size_t carve(mdi_partition* p, void* arena) {
     // few positions are cut into up to kMaxKSplits pieces, more positions into fewer: 4096 rows of partial results
     p->part_cap = std::min<size_t>(T * kMaxKSplits, 4096) * d;
     p->p_part = (float*)cv.take(p->part_cap * 4);
-    if (flash_supported(c.dtype, (int)h)) {
-      // keys and values^T of every position a first visit in pieces can reach: up to max_ctx, in blocks of 128
-      p->Tp = (int)(((size_t)c.max_ctx + 127) / 128 * 128);
-      p->p_qb = (bf16_t*)cv.take(T * H * h * 2);
-      p->p_kc = (bf16_t*)cv.take((size_t)K * p->Tp * h * 2);
-      p->p_vt = (bf16_t*)cv.take((size_t)K * h * p->Tp * 2);
-    }
+    if (flash_supported(c.dtype, (int)h)) p->p_qb = (bf16_t*)cv.take(T * H * h * 2);
   }
   return (cv.off + 255) & ~(size_t)255;
 }
@@ -650,20 +643,15 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     norm(L.ln1_g, L.ln1_b, p->p_xn, nullptr);
     GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, p->p_qkv, nullptr, 0, 0, 1};
     launch_gemm(s, c.dtype, GEPI_F32_BIAS, plan_gemm(c.dtype, (int)T, g1.N, d, 0).shape, g1);
-    // Attention on the matrix cores over operand arrays that hold the keys and the transposed values of positions
-    // 0 .. pos0 + T - 1: the new ones written by the scatter and the transpose below, the earlier ones (a later piece
-    // of a first visit) brought from the cache pages first.  The arrays are packed to what this call needs.
     const bool flash = p->p_qb != nullptr;
-    const int Tp = ((int)T + 127) / 128 * 128;
-    const int Tk = (pos0 + (int)T + 127) / 128 * 128;      // keys, padded; at most p->Tp
     const float scale = 1.f / sqrtf((float)h);
-    if (flash && pos0) launch_cache_gather(s, L.kv, drow, pos0, K, h, p->pt, Tk, p->p_kc, p->p_vt);
     RopeScatterArgs rs{p->p_qkv, (int)T, H, K, h, p->pt, p->rope, flash ? nullptr : p->p_q, L.kv, drow, (int)c.dtype,
-                       flash ? p->p_qb : nullptr, flash ? p->p_kc : nullptr, Tk, Tk - pos0, scale * 1.44269504f, pos0};   // log2 e: k_flash_prefill's exponentials are powers of two
+                       flash ? p->p_qb : nullptr, scale * 1.44269504f, pos0};   // log2 e: k_flash_prefill's exponentials are powers of two
     launch_rope_scatter(s, rs);
     if (flash) {
-      launch_v_transpose(s, p->p_qkv, (int)T, Tk - pos0, pos0, Tk, H, K, h, p->p_vt);
-      FlashArgs fa{p->p_qb, p->p_kc, p->p_vt, (bf16_t*)p->p_o, (int)T, Tp, H, K, h, pos0, Tk, Tk};
+      const bool pow2 = (p->pt & (p->pt - 1)) == 0;
+      FlashArgs fa{p->p_qb, (const bf16_t*)L.kv, drow, (bf16_t*)p->p_o, (int)T, ((int)T + 127) / 128 * 128, H, K, h, pos0,
+                   p->pt, pow2 ? __builtin_ctz((unsigned)p->pt) : -1, pow2 ? 0u : 0xFFFFFFFFu / (unsigned)p->pt + 1u};
       launch_flash_prefill(s, fa);
     } else {
       AttnArgs at{};

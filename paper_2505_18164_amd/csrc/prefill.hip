@@ -118,10 +118,6 @@ void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
 __global__ __launch_bounds__(kBlock) void k_rope_scatter(RopeScatterArgs a) {
   const int t = blockIdx.x, h = a.h, half = h >> 1;
   const int n_heads = a.H + 2 * a.K;
-  if (t >= a.T) {                                   // padding rows of the attention operand: keys nobody may see, but finite
-    for (int i = threadIdx.x; i < a.K * h; i += kBlock) a.k_bf[((long)(i / h) * a.ldk + a.pos0 + t) * h + i % h] = 0;
-    return;
-  }
   const float* row = a.qkv + (long)t * n_heads * h;
   const int pos = a.pos0 + t;
   const int page = a.table[pos / a.pt], slot = pos % a.pt;
@@ -164,16 +160,11 @@ __global__ __launch_bounds__(kBlock) void k_rope_scatter(RopeScatterArgs a) {
       const long o = (((long)page * a.K + kvh) * 2 + (is_v ? 1 : 0)) * pt_h + (long)slot * h + i;
       put4(a.pool, bf, o, v0);
       put4(a.pool, bf, o + half, v1);
-      if (a.k_bf && !is_v) {
-        const long k = ((long)kvh * a.ldk + pos) * h + i;
-        put4(a.k_bf, true, k, v0);
-        put4(a.k_bf, true, k + half, v1);
-      }
     }
   }
 }
 void launch_rope_scatter(hipStream_t s, const RopeScatterArgs& a) {
-  hipLaunchKernelGGL(k_rope_scatter, dim3(a.k_bf ? a.n_rows : a.T), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_rope_scatter, dim3(a.T), dim3(kBlock), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------

@@ -49,3 +49,25 @@ def test_output_rows_off_a_16_byte_boundary(T):
     got = host(buf)
     assert got[0] == 7.0 and got[-1] == 7.0
     assert np.array_equal(got[1:-1].reshape(T, 520), host(want))
+
+
+@pytest.mark.parametrize("page,heads,kv,h,cuts", [(64, 4, 2, 128, (130, 62, 1, 200)), (128, 4, 4, 64, (1, 127, 129, 64)), (48, 4, 1, 128, (100, 93, 7)),
+                                                  (16, 4, 2, 64, (15, 17, 96, 200)), (5, 2, 2, 64, (64, 70)), (64, 32, 8, 64, (1600,)),
+                                                  (24, 32, 4, 128, (1540, 3))])
+def test_first_visits_read_keys_and_values_from_the_pages(page, heads, kv, h, cuts):
+    """Pages that hold a block of 64 keys and pages that do not, both head sizes, pieces that end inside pages and blocks,
+    and enough query blocks for workgroups of one group of wavefronts (384 of them); every position on its own."""
+    cfg = S.tiny(n_layer=1, d_model=64, n_head=heads, n_kv_head=kv, head_dim=h, d_ff=96, vocab=61, max_ctx=1664, dtype=S.DT_BF16)
+    w = S.make_weights(cfg, 70, exercise=True)
+    o, g = pair(cfg, w, 0, 1, max_prefill=max(cuts), kv_page_tokens=page, max_seqs=2)
+    g.prefill(1, dev_acts(S.make_activations(cfg, 72, 1, 33), cfg))     # the sample's pages do not begin the pool
+    T = sum(cuts)
+    x = S.make_activations(cfg, 71, 0, T)
+    want = o.prefill(0, x)
+    at = 0
+    for n in cuts:
+        check(g.prefill_chunk(0, dev_acts(x[at:at + n], cfg)), want[at:at + n], cfg, ("piece at", at))
+        at += n
+    y = S.make_activations(cfg, 73, 0, 1)[0]
+    check(g.decode_step(0, dev_acts(y, cfg)), o.decode_step(0, y), cfg, ("later visit after", T))
+    g.sync()
