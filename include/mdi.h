@@ -400,9 +400,11 @@ MDI_API mdi_status mdi_partition_info(const mdi_partition *part, uint32_t what, 
  * Profiling aid for the persistent decode kernel: when trace is not NULL, every
  * following decode step records, per workgroup, layer and phase (QKV, attention,
  * output projection, MLP up, MLP down), up to eight 100 MHz timestamps: 0 phase
- * entered (first tiles issued), 1 barrier passed, 2 input vector staged, 3 first
- * wavefront done streaming, 4 all wavefronts done (GEMV phases), 5 results
- * stored, 6 stores acknowledged; slot 7 is unused.  trace: device buffer of
+ * entered, 1 first tiles issued, 2 input vector staged, 3 first wavefront done
+ * streaming, 4 all wavefronts done (GEMV phases), 5 results stored, 6 all
+ * wavefronts done with the phase; slot 7: the products themselves done (launches
+ * whose messages share the weights).  A launch or phase that has no such moment
+ * leaves a slot as it was.  trace: device buffer of
  * uint64 [2][workgroups][local layers][5][8] (mdi_partition_info gives the workgroup
  * count; a launch that carries several messages, see mdi_decode_steps, records the
  * first message of each of its two sets of workgroups, first and second half),

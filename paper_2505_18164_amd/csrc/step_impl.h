@@ -10,7 +10,7 @@
 // (Sec. III-A: the input queue; Sec. III-C: several samples in flight).  In the
 // latter a set of workgroups takes its messages in turn inside every phase and
 // two sets share each compute unit, so that the serial part of one message's
-// phase boundary (flags, vector staging, cross-wavefront sums, epilogue) runs
+// phase boundary (vector staging, cross-wavefront sums, epilogue) runs
 // under other messages' weight streams; every message still makes its own pass
 // over the weights.
 //
@@ -70,11 +70,9 @@ constexpr int kTile = 4;                 // items per register tile (two 16-byte
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Tile { u32x4 r[2 * kTile]; };
 
-// Tagged exchange.  A workgroup that has seen every flag of a barrier may still be ahead of the data
-// another compute die wrote before raising its flag (a store is acknowledged before every die can
-// read it back), so the data validates itself: value and the writing phase's counter travel in one
-// 8-byte store, and a reader that finds another counter simply loads again.  Flags then only protect
-// buffers from being overwritten while still in use, which needs no ordering between stores.
+// Tagged exchange.  A store is acknowledged before every compute die can read it back, so a flag raised after it
+// proves nothing to a reader; the data validates itself: value and the writing phase's counter travel in one 8-byte
+// store, and a reader that finds another counter simply loads again.  No ordering between stores is needed.
 __device__ __forceinline__ void st_tag(tagged_t* p, float v, unsigned tag) {
   __hip_atomic_store(p, ((tagged_t)tag << 32) | (tagged_t)__float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -89,9 +87,6 @@ __device__ __forceinline__ float settle(const tagged_t* p, tagged_t u, unsigned 
     u = ld_raw(p);
   }
   return tag_value(u);
-}
-__device__ __forceinline__ float ld_tag(const tagged_t* p, unsigned tag, int spin_limit, int* err) {
-  return settle(p, ld_raw(p), tag, spin_limit, err);
 }
 
 template <typename T> struct Unpack;
@@ -912,7 +907,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   __syncthreads();
 
   float acc0 = 0.f, acc1 = 0.f;
-  // requested while finishing the previous (message, phase): the next one's flags and the head of its input vector
+  // requested while finishing the previous (message, phase): the head of the next one's input vector
   bool early = false;
   VecAsk vec{};
 
@@ -924,7 +919,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
     for (int ph = 0; ph < 5; ++ph) {
 #pragma nounroll
       for (int slot = slot_lo; slot < slot_hi; ++slot) {
-        // Messages alternate inside a phase: while this message's flags and input vector make their round trips,
+        // Messages alternate inside a phase: while this message's input vector makes its round trip,
         // the memory system is still busy with the other message's stream, and by the time a message reaches its
         // next phase every workgroup has long finished its previous one.
         const StepSlot& S = a.s[slot];
@@ -994,7 +989,8 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         stamp(a, S, layer, ph, 1);
         if (pace) {
           // work left, in (message, phase) units; the set with more of it goes first
-          const int seen = __builtin_amdgcn_readfirstlane((int)other_done), total = a.n_layer * 5;
+          // (launches of one message leave the counters behind: before the other set's first phase they say nothing)
+          const int total = a.n_layer * 5, seen = min(max(__builtin_amdgcn_readfirstlane((int)other_done), 0), total);
           const int left = (total - (layer * 5 + ph)) * (slot_hi - slot_lo);
           const int other_left = (total - seen) * (a.set_lo[2 - set] - a.set_lo[1 - set]);
           if (left > other_left || (left == other_left && set == 1)) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
