@@ -43,13 +43,17 @@
 //     first is served first by a compute unit's memory pipeline and finishes a
 //     fifth earlier.
 //
-// Every spin is bounded: a workgroup that waits longer than `spin_limit` polls
-// raises the partition's error flag and leaves, and so does every other one.
+// Every spin is bounded: a wait of more than `spin_limit` polls raises the
+// partition's error word, the other waits of that workgroup end with it, and the
+// workgroup leaves at the end of the phase at the latest.  What it stored in that phase is
+// worthless (the error word says so); everybody who needs its words later
+// expires in the same way.
 //
 // This file is the kernel's body; step_w4.hip and step_w8.hip compile it for workgroups of four and of
 // eight wavefronts (MDI_STEP_WAVES), each in a namespace of its own with a launcher of its own.
 #include <type_traits>
 
+#include "bounded_wait.h"
 #include "device_utils.h"
 
 #ifndef MDI_STEP_WAVES
@@ -78,11 +82,23 @@ __device__ __forceinline__ void st_tag(tagged_t* p, float v, unsigned tag) {
 }
 __device__ __forceinline__ tagged_t ld_raw(const tagged_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float tag_value(tagged_t u) { return __uint_as_float((uint32_t)u); }
-// Returns the value once its tag is `tag`; gives up (error flag) after spin_limit reloads.
+// A wait that expires raises the partition's error word and its workgroup's failure flag (an index in lds_flag()); the
+// other waits of the workgroup then end at their next look at the flag.
+constexpr int kFailed = 2;
+__device__ __forceinline__ int* lds_flag() { extern __shared__ float smem[]; return (int*)(smem + 16); }
+__device__ __forceinline__ bool poll_again(int& polls, int spin_limit, int* err) {
+  return may_poll_again(
+      polls, spin_limit, [&]() { return __hip_atomic_load(lds_flag() + kFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0; },
+      [&]() {
+        __hip_atomic_store(lds_flag() + kFailed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      });
+}
+// Returns the value once its tag is `tag`, or whatever is there when the wait ends otherwise.
 __device__ __forceinline__ float settle(const tagged_t* p, tagged_t u, unsigned tag, int spin_limit, int* err) {
   int it = 0;
   while ((uint32_t)(u >> 32) != tag) {
-    if (++it > spin_limit) { __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
+    if (!poll_again(it, spin_limit, err)) break;
     __builtin_amdgcn_s_sleep(1);
     u = ld_raw(p);
   }
@@ -117,15 +133,12 @@ __device__ __forceinline__ void stamp(const StepArgs& a, const StepSlot& S, int 
 // [128, 128+part_floats) pair partials, then the vector.
 constexpr int kLdsPart = 128;
 __device__ __forceinline__ float* lds_red() { extern __shared__ float smem[]; return smem; }
-__device__ __forceinline__ int* lds_flag() { extern __shared__ float smem[]; return (int*)(smem + 16); }
 __device__ __forceinline__ float* lds_part() { extern __shared__ float smem[]; return smem + kLdsPart; }
 __device__ __forceinline__ float* lds_vec(int part_floats) { extern __shared__ float smem[]; return smem + kLdsPart + part_floats; }
 
 // N words at once, asked for again until all of a thread's carry the counter `tag`: one round trip however many were
 // early (word by word, eight early words cost eight).  Asked for before a phase's weights, awaited after: loads return
-// in order, and the workgroup that everybody waits for finds its words there.  A wait that expires raises the error word and the workgroup's
-// failure flag.
-constexpr int kFailed = 2;               // index in lds_flag()
+// in order, and the workgroup that everybody waits for finds its words there.
 // at(i, z): the address of word i; z is zero, and unknown to the compiler, so that addresses are not kept in registers
 // over the loop.
 __device__ __forceinline__ const MDI_GLOBAL tagged_t* word_at(const tagged_t* base, uint32_t bytes) {
@@ -150,7 +163,7 @@ __device__ __forceinline__ void await_words(tagged_t (&raw)[N], const AT& at, un
 #pragma unroll
     for (int i = 0; i < N; ++i) bad |= (uint32_t)(raw[i] >> 32) != tag;
     if (!bad) break;
-    if (++it > spin_limit) { lds_flag()[kFailed] = 1; __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
+    if (!poll_again(it, spin_limit, err)) break;
     __builtin_amdgcn_s_sleep(1);
     ask_words(raw, at, tag, live);
   }
