@@ -17,8 +17,6 @@
 // layer's 480 at 1024 positions of the 7B shape, 26 of 223 in pieces of 256: visits of 1024 3.63 -> 3.56 ms, in four
 // pieces 7.16 -> 6.41 ms, 333 of TinyLlama 1.15 -> 1.07 ms, 6000 of the 8B shape 22.0 -> 22.4 ms on one machine.
 // Transposing in registers on the way into LDS: 531 us a layer of 6000 positions, 490 as it is.)
-#include <mutex>
-
 #include "device_utils.h"
 
 namespace mdi {
@@ -269,20 +267,20 @@ constexpr size_t flash_lds_bytes() {
   return kv > fold ? kv : fold;
 }
 template <int HD, int NG>
-void launch_flash(hipStream_t s, const FlashArgs& a) {
+bool allow_flash() {                                             // 64 KiB is what a kernel gets by default
   constexpr size_t lds = flash_lds_bytes<HD, NG>();
-  if (lds > 64 * 1024) {                                         // above what a kernel gets by default
-    static std::once_flag raised;
-    std::call_once(raised, []() {
-      (void)hipFuncSetAttribute((const void*)k_flash_prefill<HD, NG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
-  }
-  hipLaunchKernelGGL((k_flash_prefill<HD, NG>), dim3(8 * ((a.Tp / BQ * a.H + 7) / 8)), dim3(256 * NG), lds, s, a);
+  return lds <= 64 * 1024 || hipFuncSetAttribute((const void*)k_flash_prefill<HD, NG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+}
+template <int HD, int NG>
+void launch_flash(hipStream_t s, const FlashArgs& a) {
+  hipLaunchKernelGGL((k_flash_prefill<HD, NG>), dim3(8 * ((a.Tp / BQ * a.H + 7) / 8)), dim3(256 * NG), (flash_lds_bytes<HD, NG>()), s, a);
 }
 
 }  // namespace
 
 bool flash_supported(int dtype, int h) { return dtype == MDI_BF16 && (h == 64 || h == 128); }
+
+bool allow_flash_lds() { return allow_flash<64, 1>() && allow_flash<64, 2>() && allow_flash<128, 1>() && allow_flash<128, 2>(); }
 
 void launch_flash_prefill(hipStream_t s, const FlashArgs& a) {
   // One group per workgroup once there are half as many more workgroups than compute units, measured on 4 layers: 1536

@@ -25,9 +25,20 @@ void launch_epi(hipStream_t s, int shape, const GemmArgs& a) {
   }
 }
 
+template <int EPI>
+bool allow_epi() {
+#define X(I, BN, BT, WN, WT, NBW, NBA) && allow_shape<bf16_t, EPI, BN, BT, WN, WT, NBW, NBA>()
+  return true MDI_GEMM_SHAPES(X);
+#undef X
+}
+
 }  // namespace
 
-GemmPlan plan_gemm_bf16(int T, int N, int Kd, size_t part_floats) { return plan_shape(kShape, kShapes, 2, T, N, Kd, part_floats); }
+GemmPlan plan_gemm_bf16(int n_cu, int T, int N, int Kd, size_t part_floats) { return plan_shape(kShape, kShapes, 2, n_cu, T, N, Kd, part_floats); }
+
+bool allow_gemm_lds_bf16() {
+  return allow_epi<GEPI_F32_BIAS>() && allow_epi<GEPI_RESID>() && allow_epi<GEPI_PART>() && allow_epi<GEPI_SWIGLU>() && allow_epi<GEPI_GELU>();
+}
 
 void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a) {
   switch (epi) {

@@ -278,29 +278,24 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
 // weights arrive (tbps).
 struct Shape { int BN, BT, resident; float us, fixed, part, tbps; };
 
+// Lets the current device's copy of the kernel have its LDS: a kernel gets 64 KiB by default.
+template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
+bool allow_shape() {
+  constexpr size_t lds = (size_t)128 * (NBW * BN + NBA * BT);
+  static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+  return lds <= 64 * 1024 || hipFuncSetAttribute((const void*)k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+}
+
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
 void launch_shape(hipStream_t s, const GemmArgs& a) {
   constexpr size_t lds = (size_t)128 * (NBW * BN + NBA * BT);
-  static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-  if (lds > 64 * 1024) {                                           // more than a kernel gets by default
-    static const hipError_t raised = hipFuncSetAttribute((const void*)k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)raised;
-  }
   const int tiles = ((a.T + BT - 1) / BT) * ((a.N + BN - 1) / BN);
   hipLaunchKernelGGL((k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>), dim3(8 * ((tiles + 7) / 8), a.S), dim3(WN * WT * 64), lds, s, a);
 }
 
-inline int compute_units() {
-  static const int n_cu = []() {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    return n;
-  }();
-  return n_cu;
-}
-
-inline GemmPlan plan_shape(const Shape* shapes, int n_shapes, int elem_bytes, int T, int N, int Kd, size_t part_floats) {
-  const double n_cu = compute_units();
+inline GemmPlan plan_shape(const Shape* shapes, int n_shapes, int elem_bytes, int compute_units, int T, int N, int Kd, size_t part_floats) {
+  const double n_cu = compute_units > 0 ? compute_units : 256;
   const int nk = (elem_bytes * Kd + 127) >> 7;
   GemmPlan best{0, 1};
   double best_us = 1e30;

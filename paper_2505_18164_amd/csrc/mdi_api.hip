@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "mdi_internal.h"
+#include "once_per_device.h"
 
 using namespace mdi;
 
@@ -340,7 +341,7 @@ void plan_batch(mdi_partition* p) {
 // streams could each be given a part of the compute units and wait for the rest for ever (their bounded
 // waits would turn that into MDI_ERR_HIP).  So, per device, an event orders a partition's persistent launch
 // after the previous one of any other partition.
-constexpr int kMaxDevices = 64;
+constexpr int kMaxDevices = OncePerDevice::kDevices;
 struct LaunchChain {
   std::mutex mutex;
   hipEvent_t event = nullptr;
@@ -394,6 +395,9 @@ mdi_status static_scratch(int device, unsigned char** out) {
   *out = g_scratch_ptr[device];
   return MDI_OK;
 }
+
+// The first-visit kernels that use more than 64 KiB of LDS.
+OncePerDevice g_prefill_lds;
 
 // device-to-device copy of a [rows, cols] matrix into rows r*mul + off of dst
 void put_rows(mdi_partition* p, const void* src, const void* dst, size_t rows, size_t cols, int esz, long mul = 1, long off = 0) {
@@ -506,6 +510,10 @@ mdi_status mdi_partition_create(const mdi_config* cfg, uint32_t layer_lo, uint32
     if (dev < 0 || dev >= kMaxDevices) { delete p; return MDI_ERR_ARG; }
     p->n_cu = n_cu;
     p->device = dev;
+    if (!g_prefill_lds.run(dev, []() { return allow_gemm_lds_bf16() && allow_gemm_lds_f32() && allow_flash_lds(); })) {
+      delete p;
+      return MDI_ERR_HIP;
+    }
     plan_step(p, n_cu);
     plan_batch(p);
     if (p->batch_region) {
@@ -632,7 +640,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
   const int aligned = ((uintptr_t)acts_out & 15) == 0;
   auto resid = [&](const void* A, const void* W, const float* bias, int Kd, void* hand_off) {
     GemmArgs ga{A, W, bias, (int)T, d, Kd, p->p_xres, hand_off, 0, aligned, 1};
-    const GemmPlan pl = plan_gemm(c.dtype, (int)T, d, Kd, p->part_cap);
+    const GemmPlan pl = plan_gemm(c.dtype, p->n_cu, (int)T, d, Kd, p->part_cap);
     ga.S = pl.S;
     if (pl.S > 1) { ga.out_f32 = p->p_part; ga.out_act = nullptr; pend_S = pl.S; pend_bias = bias; }
     launch_gemm(s, c.dtype, pl.S > 1 ? GEPI_PART : GEPI_RESID, pl.shape, ga);
@@ -642,7 +650,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     const LayerPacked& L = p->layers[i];
     norm(L.ln1_g, L.ln1_b, p->p_xn, nullptr);
     GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, p->p_qkv, nullptr, 0, 0, 1};
-    launch_gemm(s, c.dtype, GEPI_F32_BIAS, plan_gemm(c.dtype, (int)T, g1.N, d, 0).shape, g1);
+    launch_gemm(s, c.dtype, GEPI_F32_BIAS, plan_gemm(c.dtype, p->n_cu, (int)T, g1.N, d, 0).shape, g1);
     const bool flash = p->p_qb != nullptr;
     const float scale = 1.f / sqrtf((float)h);
     RopeScatterArgs rs{p->p_qkv, (int)T, H, K, h, p->pt, p->rope, flash ? nullptr : p->p_q, L.kv, drow, (int)c.dtype,
@@ -664,7 +672,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     resid(p->p_o, L.wo, L.bo, H * h, nullptr);
     norm(L.ln2_g, L.ln2_b, p->p_xn, nullptr);
     GemmArgs g3{p->p_xn, L.wup, L.bup, (int)T, swiglu ? 2 * F : F, d, nullptr, p->p_u, c.mlp_kind == MDI_MLP_GELU_TANH, 1, 1};
-    launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : GEPI_GELU, plan_gemm(c.dtype, (int)T, g3.N, d, 0).shape, g3);
+    launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : GEPI_GELU, plan_gemm(c.dtype, p->n_cu, (int)T, g3.N, d, 0).shape, g3);
     resid(p->p_u, L.wdown, L.bdown, F, i == p->n_local - 1 ? acts_out : nullptr);
   }
   p->seq_len[seq] = (uint32_t)pos0 + T;

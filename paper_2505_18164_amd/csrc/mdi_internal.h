@@ -138,12 +138,15 @@ struct GemmArgs {
 // few positions still fill the chip; part_floats = room for partial results, 0 forbids a split.
 constexpr int kMaxKSplits = 16;
 struct GemmPlan { int shape, S; };
-GemmPlan plan_gemm_bf16(int T, int N, int Kd, size_t part_floats);
-GemmPlan plan_gemm_f32(int T, int N, int Kd, size_t part_floats);
+GemmPlan plan_gemm_bf16(int n_cu, int T, int N, int Kd, size_t part_floats);
+GemmPlan plan_gemm_f32(int n_cu, int T, int N, int Kd, size_t part_floats);
+// Once per device, with it current, before the first launch there: kernels with more than 64 KiB of LDS are let have it.
+bool allow_gemm_lds_bf16();
+bool allow_gemm_lds_f32();
 void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a);
 void launch_gemm_f32(hipStream_t s, int epi, int shape, const GemmArgs& a);
-inline GemmPlan plan_gemm(int dtype, int T, int N, int Kd, size_t part_floats) {
-  return dtype == MDI_BF16 ? plan_gemm_bf16(T, N, Kd, part_floats) : plan_gemm_f32(T, N, Kd, part_floats);
+inline GemmPlan plan_gemm(int dtype, int n_cu, int T, int N, int Kd, size_t part_floats) {
+  return dtype == MDI_BF16 ? plan_gemm_bf16(n_cu, T, N, Kd, part_floats) : plan_gemm_f32(n_cu, T, N, Kd, part_floats);
 }
 inline void launch_gemm(hipStream_t s, int dtype, int epi, int shape, const GemmArgs& a) {
   if (dtype == MDI_BF16) launch_gemm_bf16(s, epi, shape, a); else launch_gemm_f32(s, epi, shape, a);
@@ -174,6 +177,7 @@ struct FlashArgs {
   int pt, pt_sh; unsigned pt_magic;   // positions per page; log2 of it, or -1 and pos / pt = high word of pos * pt_magic (0xFFFFFFFF / pt + 1)
 };
 bool flash_supported(int dtype, int h);
+bool allow_flash_lds();    // as allow_gemm_lds_bf16
 void launch_flash_prefill(hipStream_t s, const FlashArgs& a);
 
 // ---- whole decode step as one persistent launch ------------------------------
