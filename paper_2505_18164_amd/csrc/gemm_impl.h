@@ -34,7 +34,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // 64 x 16 bytes global -> LDS: lane l's piece lands at lds + 16 l.  An offset at or past the descriptor's 2^31 - 1
 // bytes reads as zero.
 __device__ __forceinline__ void dma_piece(uint32_t lds, u32x4 rsrc, int voff, int soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
 }
 __device__ __forceinline__ u32x4 buffer_of(const void* p) {
   const uint64_t a = (uint64_t)p;
