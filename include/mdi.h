@@ -399,12 +399,14 @@ MDI_API mdi_status mdi_partition_info(const mdi_partition *part, uint32_t what, 
 /*
  * Profiling aid for the persistent decode kernel: when trace is not NULL, every
  * following decode step records, per workgroup, layer and phase (QKV, attention,
- * output projection, MLP up, MLP down), up to eight 100 MHz timestamps: 0 phase
- * entered, 1 first tiles issued, 2 input vector staged, 3 first wavefront done
- * streaming, 4 all wavefronts done (GEMV phases), 5 results stored, 6 all
- * wavefronts done with the phase; slot 7: the products themselves done (launches
- * whose messages share the weights).  A launch or phase that has no such moment
- * leaves a slot as it was.  trace: device buffer of
+ * output projection, MLP up, MLP down), up to eight 100 MHz timestamps of the
+ * workgroup's first thread: 0 phase entered, 1 its first tiles issued, 2 its input
+ * vector there, 3 its stream multiplied, 4 that of every wavefront (products whose
+ * wavefronts' sums meet in the workgroup), 7 the partial sums handed to the rows'
+ * owners (residual products of launches whose messages share the weights), 5 its
+ * results stored, 6 all wavefronts done with the phase.  In this order, and of a
+ * phase's first attention work item in launches whose messages share the weights;
+ * a phase without such a moment leaves the slot as it was.  trace: device buffer of
  * uint64 [2][workgroups][local layers][5][8] (mdi_partition_info gives the workgroup
  * count; a launch that carries several messages, see mdi_decode_steps, records the
  * first message of each of its two sets of workgroups, first and second half),

@@ -207,7 +207,7 @@ struct StepSlot {
   unsigned *tickets, *flags; unsigned epoch0;
   int n_splits, chunk;
   void* act_out;
-  unsigned long long* trace;         // optional [workgroup][n_layer * 5 phases][4] timestamps (100 MHz ticks), or nullptr
+  unsigned long long* trace;         // optional [workgroup][n_layer][5 phases][8] timestamps (100 MHz ticks), or nullptr
 };
 struct StepArgs {
   StepLayer l0;                      // first local layer; layer i's pointers are these advanced by i strides

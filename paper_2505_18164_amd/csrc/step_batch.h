@@ -604,6 +604,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             attn4_issue(A, pgA, ga, s4, a, V, Lv.kv, 0, wave, lane); attn4_issue(B, pgB, ga, s4, a, V, Lv.kv, 1, wave, lane);
             if (item == wg) bstamp(a, layer, ph, 1);
             attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
+            if (item == wg) bstamp(a, layer, ph, 2);
             attn4_stream(s4, st, A, B, pgA, pgB, ga, a, V, Lv.kv, wave, lane, part);
           } else {
             int pgA[kTile], pgB[kTile];
@@ -611,13 +612,14 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
             if (item == wg) bstamp(a, layer, ph, 1);
             attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
+            if (item == wg) bstamp(a, layer, ph, 2);
             const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
             attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, Lv.kv, nte, wave, part);
           }
+          if (item == wg) bstamp(a, layer, ph, 3);
           attn_to_lds<WT, G>(st, ga, a.h, part, wave);
           attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
         }
-        bstamp(a, layer, ph, 3);
       } else {
         const int R = g.R, half = R >> 1;
         // epilogue items per block and message: row pairs, or quads of rows for SwiGLU; a power of two
@@ -653,13 +655,13 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           if (sj < m) ask_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); }, epoch);
           if (g.nks > 8) { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<1>(B, g, 0, wg, nwg, lane); }
           else { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<0>(B, g, 1, wg, nwg, lane); }
+          bstamp(a, layer, ph, 1);
           if (long_vec) {
             await_words(gate, gate_at, epoch, a.spin_limit, a.err, gated);
             for (int i = tid + kStepThreads; i < nwg; i += kStepThreads)
               poll_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)i * 8u + z); }, epoch, a.spin_limit, a.err);
             __syncthreads();
           }
-          bstamp(a, layer, ph, 1);
           float sum2 = 0.f, sum1 = 0.f;                              // this thread's share of its message's sums
           if (sj < m) {
             await_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); }, epoch, a.spin_limit, a.err);
@@ -714,7 +716,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             res_compute<0, true>(A, g, lb, Bv, acc, part, wave, lane);
             res_compute<0, true>(B, g, lb + 1, Bv, acc, part, wave, lane);
           }
-          bstamp(a, layer, ph, 7);
+          bstamp(a, layer, ph, 3);
           // 1/rms of every message.  The shares of all workgroups have been seen before anything of this phase is stored
           // (see the top of the file).
 #pragma unroll
@@ -757,6 +759,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           ask_words(raw, at, epoch, live);
           ks_issue(A, kq, g.W, woff, 0);
           ks_issue(B, kq, g.W, woff, 1);
+          bstamp(a, layer, ph, 1);
           for (int u0 = tid; u0 < n_units; u0 += 2 * kStepThreads) {
             if (u0 != tid) { unit_of(u0); ask_words(raw, at, epoch, live); }
             await_words(raw, at, epoch, a.spin_limit, a.err, live);
@@ -780,6 +783,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             ks_compute(A, kq, Bs, nt - 2, lane, acc);
             ks_compute(B, kq, Bs, nt - 1, lane, acc);
           }
+          bstamp(a, layer, ph, 3);
           // the partial of (block, slice), zeros from a slice without columns, to the block's owner
           if (kq.q < a.str_oct && kq.blk < kq.nblk && (lane & 15) < m) {
             tagged_t* dst = a.ppart + ((long)((kq.blk * kq.S + kq.s) * 4 + kg) * m + (lane & 15)) * 4;
@@ -825,9 +829,10 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             if (!last) publish_sums(s2, s1, p, ssq_out + j * nwg + wg, ln ? ssum_out + j * nwg + wg : nullptr, wtag);
           }
         }
-        bstamp(a, layer, ph, 3);
-        if (ph == PH_QKV || ph == PH_UP) __syncthreads();            // every wavefront's partial products are in LDS
-        bstamp(a, layer, ph, 4);
+        if (ph == PH_QKV || ph == PH_UP) {
+          __syncthreads();                                           // every wavefront's partial products are in LDS
+          bstamp(a, layer, ph, 4);
+        }
 
         // ---- epilogue of the normed products: one thread per (block, row pair or quad, message)
         if (ph == PH_QKV) {

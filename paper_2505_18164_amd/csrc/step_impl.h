@@ -937,6 +937,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         // next phase every workgroup has long finished its previous one.
         const StepSlot& S = a.s[slot];
         const unsigned epoch = S.epoch0 + (unsigned)(layer * 5 + ph);
+        stamp(a, S, layer, ph, 0);
         // per-thread addresses are recomputed in every phase (see k_step_batch)
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
@@ -998,7 +999,6 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         const bool pace = a.n_sets == 2 && slot == slot_lo;
         if (pace) other_done = __hip_atomic_load(O.flags + wg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - O.epoch0;
 
-        stamp(a, S, layer, ph, 0);
         stamp(a, S, layer, ph, 1);
         if (pace) {
           // work left, in (message, phase) units; the set with more of it goes first
