@@ -612,15 +612,6 @@ __device__ __forceinline__ void attn_update_f(AttnState<WT, G>& st, const AttnGe
   }
 }
 
-template <typename WT, int G>
-__device__ __forceinline__ void attn_update(AttnState<WT, G>& st, const AttnGeo& g, int h, const u32x4& kq, const u32x4& vq,
-                                            bool valid, const float* qs) {
-  float kf[Storage<WT>::kVec], vf[Storage<WT>::kVec];
-  Unpack<WT>::go(kq, kf);
-  Unpack<WT>::go(vq, vf);
-  attn_update_f<WT, G>(st, g, h, kf, vf, valid, qs);
-}
-
 // One tile = kTile cached positions per lane group.  The scores of all of them first, then ONE rescaling of the running
 // sums to the new maximum, then the weighted values: a rescaling per position (as attn_update_f does for the single
 // newest row) costs as many multiplications as the values themselves.
