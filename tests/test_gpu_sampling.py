@@ -53,3 +53,46 @@ def test_masses_of_equal_logits(distinct):
     cfg, g = head(3000 if distinct == 1 else 4000, 4, lambda m: np.tile(m[:distinct] * np.float32(10.0), (m.shape[0] // distinct, 1)))
     check_draws(cfg, g, 20, n=3)
     check_draws(cfg, g, 64, n=1)
+
+
+# what the logits are beside a few ordinary ones, how many are ordinary, vocabulary, k: a few NaNs among the candidates
+# (both sides of the size from which the bound is looked for); fewer than k numbers, which leaves the ranks to the rounds
+# (also where threads own no element); -inf en masse, where the bound is -inf and everything reaches it; -inf that is
+# ranked but never drawn
+@pytest.mark.parametrize("rest,ordinary,vocab,top_k", [("nan", 90, 97, 20), ("nan", 1000, 1024, 64), ("nan", 4000, 4099, 50),
+                                                       ("nan", 14, 97, 64), ("nan", 10, 1025, 50), ("nan", 3, 33001, 64),
+                                                       ("-inf", 10, 1000, 50), ("-inf", 10, 1025, 50), ("-inf", 10, 33001, 64),
+                                                       ("-inf", 3000, 4099, 64)])
+def test_logits_that_are_no_ordinary_numbers(rest, ordinary, vocab, top_k):
+    rows = np.random.default_rng(vocab).permutation(vocab)[ordinary:]
+
+    def mat(m):
+        m = m * np.float32(10.0)
+        m[rows] = 0.0
+        m[rows, 0] = np.nan if rest == "nan" else -np.inf            # times a positive activation
+        return m
+
+    cfg, g = head(vocab, 6, mat)
+    n, seed, temperature = 3, 77, 0.9
+    acts = [S.make_activations(cfg, 8, s, 1)[0] for s in range(n)]
+    for a in acts:
+        a[0] = 2.0
+    xs = [dev_acts(a, cfg) for a in acts]
+    lg = torch.empty((n, vocab), dtype=torch.float32, device="cuda:0")
+    decided, rounds = 0, 6
+    for count in (n, 1):                                             # the shared vocabulary pass and the one-sample kernel
+        for step in range(rounds):
+            toks = host(g.sample_batch(list(range(count)), xs[:count], temperature, top_k, seed, [step] * count, logits_out=lg)).astype(np.int64)
+            got = host(lg)
+            for i in range(count):
+                assert np.isfinite(got[i]).sum() == ordinary
+                assert not np.isposinf(got[i]).any()
+                numbers = np.where(np.isnan(got[i]), np.float32(-np.inf), got[i])
+                u = O.uniform01(seed, i, step)
+                pmf = O.topk_pmf(numbers.astype(np.float64), temperature, top_k)
+                assert pmf.get(int(toks[i]), 0.0) > 0.0, (i, step)
+                if np.abs(np.cumsum(list(pmf.values())) - u).min() > 1e-5:
+                    decided += 1
+                    assert int(toks[i]) == O.sample_topk(numbers, temperature, top_k, u), (i, step)
+    assert decided >= 0.9 * rounds * (n + 1)
+    g.sync()
