@@ -53,8 +53,8 @@
  * Results are within the parity bar either way; the order of additions differs.
  * MDI_BATCH_GROUP = 1, 2 or 4 fixes the number of query heads per attention
  * work item of mdi_decode_batch (by default chosen per call from the number of
- * messages and the longest context); used by tests to reach every variant on
- * small shapes.
+ * messages and their contexts); used by tests to reach every variant on small
+ * shapes.
  */
 #ifndef MDI_H
 #define MDI_H

@@ -273,10 +273,11 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   }
 }
 
-// What plan_shape goes by: a round of workgroups (`resident` per compute unit) takes steps * us + fixed, a last round
-// that is a fraction f full (less power, less traffic) part + (1 - part) f of that, and no product is faster than its
-// weights arrive (tbps).
-struct Shape { int BN, BT, resident; float us, fixed, part, tbps; };
+// What plan_shape goes by: a round of workgroups (`round` per compute unit) takes steps * us + fixed, a last round that is
+// a fraction f full part + (1 - part) f of that, and no product is faster than its weights arrive (tbps).  All are fitted
+// to measured times and none is a count of what fits: the small shapes' `round` is one more workgroup than the LDS of a
+// compute unit holds (the next starts as soon as one ends).
+struct Shape { int BN, BT, round; float us, fixed, part, tbps; };
 
 // Lets the current device's copy of the kernel have its LDS: a kernel gets 64 KiB by default.
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
@@ -307,7 +308,7 @@ inline GemmPlan plan_shape(const Shape* shapes, int n_shapes, int elem_bytes, in
       const int per = (nk + S - 1) / S;
       if ((nk + per - 1) / per != S) continue;                // no split without a step
       if (S > 1 && (size_t)S * T * N > part_floats) break;
-      const double u = tiles * S / (n_cu * sh.resident), full = (double)(long)u, f = u - full;
+      const double u = tiles * S / (n_cu * sh.round), full = (double)(long)u, f = u - full;
       double us = (full + (f > 0 ? sh.part + (1 - sh.part) * f : 0)) * (per * sh.us + sh.fixed);
       us = std::max(us, (double)elem_bytes * N * Kd / (sh.tbps * 1e6));
       if (S > 1) us += (double)S * T * N * 4.0 / 4.5e6;       // the partial results are read again (4.5 TB/s)

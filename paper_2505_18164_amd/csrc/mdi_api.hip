@@ -56,7 +56,7 @@ struct mdi_partition {
   float* logits = nullptr;       // [V] scratch of the stochastic sampler when the caller asks for no logits
   int head_nwg = 0, head_part_floats = 0;   // streaming launch of the output layers (0: per-operation GEMV)
   size_t head_lds = 0;
-  // output layers of several samples per pass over the vocabulary matrix (bf16 + RMSNorm heads)
+  // output layers of several samples per pass over the vocabulary matrix (bf16 heads)
   int hb_nwg = 0; size_t hb_lds = 0;
   tagged_t* hb_cand = nullptr; tagged_t* cand = nullptr; int* herr = nullptr; float* hb_logits = nullptr;
   unsigned* counters = nullptr;  // [H] attention + [1] argmax
@@ -90,7 +90,7 @@ struct mdi_partition {
     unsigned epoch = 0;
   } sc[kMaxSlots];
   // decode of several queued messages with one pass over the weights (step_batch.h)
-  bool batch_region = false;           // the arena holds the exchange region of that launch (bf16 storage, RMSNorm)
+  bool batch_region = false;           // the arena holds the exchange region of that launch (bf16 storage)
   bool use_batch = false;              // ... and the shape allows the launch on this device
   char* b_slot0 = nullptr; size_t b_stride = 0;
   size_t b_off_q = 0, b_off_part = 0, b_off_knew = 0, b_off_tickets = 0;

@@ -192,10 +192,10 @@ struct StepLayer {                   // device-resident, one per local layer
   void* kv;                          // this layer's pages
 };
 
-// What belongs to one message (one sequence's new token) inside a launch.  A launch carries one or two messages:
-// with two, every phase runs for message 0 and then for message 1, so that the exchange between workgroups that
-// ends one message's phase is covered by the other message's weight streaming.  Each message has its own exchange
-// buffers, flags and counters.
+// What belongs to one message (one sequence's new token) inside a launch.  A launch carries up to kMaxSlots messages:
+// a set of workgroups runs every phase for its messages in turn, so that the exchange between workgroups that ends
+// one message's phase is covered by the other messages' weight streaming.  Each message has its own exchange buffers,
+// tickets and counters; the phase counters (flags) of a set's first message are what the other set paces itself by.
 struct StepSlot {
   const void* in; int in_kind;
   int pos, ctx;                      // position of the new token, context length including it
@@ -245,7 +245,7 @@ struct LogitsArgs {
 };
 void launch_logits(hipStream_t s, int dtype, int nwg, size_t lds_bytes, const LogitsArgs& a);
 
-// ---- decode step of several queued messages with ONE pass over the weights (step_w8.hip) ----------------
+// ---- decode step of several queued messages with ONE pass over the weights (step_batch.h) ----------------
 // The messages waiting in the node's input queue (Sec. III-A; several samples are in flight, Sec. III-C) are
 // taken through every layer together: a weight tile is fetched once and multiplied with all their vectors on the
 // matrix cores (the messages are the second operand's columns), attention stays per sample.

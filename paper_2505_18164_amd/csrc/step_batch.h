@@ -44,7 +44,7 @@
 // Needs bf16 storage and widths that are multiples of 32; other shapes keep one pass per message.  With LayerNorm the vectors still travel as x * gain: the mean and the norm's bias enter the finished
 // products through two precomputed vectors per matrix (W g and W b), see BatchArgs.
 //
-// Included by step_w8.hip after step_impl.h (shares its exchange, attention and barrier helpers).
+// Included by step_w8.hip after step_impl.h (shares its exchange, wait and attention helpers).
 namespace mdi {
 namespace step_w8 {
 
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         if (ph == PH_QKV) {
           for (int e = tid; e < n_items; e += kStepThreads) {
             const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
-              const int j = it.j, p = it.p, lb = it.lb;
+            const int j = it.j, p = it.p, lb = it.lb;
             const int r0 = block_row(g, lb * nwg + wg, p), r1 = r0 + (a.h >> 1);
             float v0 = part_sum(part, lb, p, j) * rscale[j], v1 = part_sum(part, lb, p + half, j) * rscale[j];
             if (ln) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }

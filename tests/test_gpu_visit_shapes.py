@@ -71,3 +71,16 @@ def test_first_visits_read_keys_and_values_from_the_pages(page, heads, kv, h, cu
     y = S.make_activations(cfg, 73, 0, 1)[0]
     check(g.decode_step(0, dev_acts(y, cfg)), o.decode_step(0, y), cfg, ("later visit after", T))
     g.sync()
+
+
+@pytest.mark.parametrize("kw", [{}, GELU, F32], ids=["bf16_rms", "bf16_ln", "f32_rms"])
+@pytest.mark.parametrize("d", [1016, 1032, 2056, 4104, 8184, 8200])
+def test_norms_across_row_widths(d, kw):
+    """A row is held in 1, 2, 4 or 8 pieces per thread, beyond 8192 values in none; few positions, so that the products
+    before the norms leave partial results to add (their inner dimension, 2048, is split)."""
+    cfg = S.tiny(n_layer=2, d_model=d, n_head=32, n_kv_head=2, head_dim=64, d_ff=2048, vocab=61, max_ctx=16, **{"dtype": S.DT_BF16, **kw})
+    w = S.make_weights(cfg, 90, exercise=True)
+    o, g = pair(cfg, w, 0, 2)
+    x = S.make_activations(cfg, 91, 0, 5)
+    check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", d))
+    g.sync()
