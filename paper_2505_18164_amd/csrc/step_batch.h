@@ -238,13 +238,9 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
   if (single) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
-  if (tid == 0) {
-    const unsigned ticket = __hip_atomic_fetch_add(S.tickets + g.hg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_flag[1] = ticket == (unsigned)S.n_splits - 1;
-  }
+  if (tid == 0) s_flag[1] = last_of(S.tickets + g.hg, (unsigned)S.n_splits);
   __syncthreads();
   if (!s_flag[1]) return;
-  if (tid == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int idx = tid; idx < G * hp; idx += kStepThreads) {
     const int gi = idx / hp, e = (idx - gi * hp) * 2;
     const int head = g.hg * G + gi;
@@ -277,7 +273,6 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
     }
     st_pair(S.ob + (((long)head * h + e) >> 1) * S.n_msg + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
   }
-  if (tid == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
 }
 
 // ---------------------------------------------------------------------------

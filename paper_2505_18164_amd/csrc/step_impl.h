@@ -765,6 +765,11 @@ __device__ __forceinline__ void attn_to_lds(AttnState<WT, G>& st, const AttnGeo&
   __syncthreads();
 }
 
+// Counts an arrival; whether it was the last of n.  The count wraps to zero with that one, in the same operation: a store
+// of zero after it would have to be seen everywhere before the next layer's first arrival, and nothing waits for it - a
+// phase waits for data, of which the other wavefronts' may be out first.
+__device__ __forceinline__ bool last_of(unsigned* arrivals, unsigned n) { return atomicInc(arrivals, n - 1u) == n - 1u; }
+
 // Wavefront records -> split partial (or the final output when there is one split);
 // the last workgroup of a head group to arrive folds the splits in split order.
 template <int G, typename AR, typename SL>
@@ -795,13 +800,9 @@ __device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const
   if (single) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
-  if (tid == 0) {
-    const unsigned ticket = __hip_atomic_fetch_add(S.tickets + g.hg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_flag[1] = ticket == (unsigned)S.n_splits - 1;
-  }
+  if (tid == 0) s_flag[1] = last_of(S.tickets + g.hg, (unsigned)S.n_splits);
   __syncthreads();
   if (!s_flag[1]) return;
-  if (tid == 0) __hip_atomic_store(S.tickets + g.hg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int idx = tid; idx < G * h; idx += kStepThreads) {
     const int gi = idx / h, e = idx - gi * h;
     const int head = g.hg * G + gi;
@@ -833,7 +834,6 @@ __device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const
     }
     st_tag(S.o + (long)head * h + e, o / l, wtag);
   }
-  if (tid == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the ticket is back at zero before anything later is published
 }
 
 // ---------------------------------------------------------------------------
