@@ -1,6 +1,6 @@
 """First visits at the numbers of positions and widths where the products' tiles change: one position, one more and one
 less than a tile, inner dimensions that end inside a 128-byte step (520 and 4104 values), and enough positions for the
-largest tiles; the numbers of positions also move how the inner dimension is split.  Against the oracle, every position
+larger tiles; the numbers of positions also move how the inner dimension is split.  Against the oracle, every position
 on its own, at the bar of the storage type."""
 import numpy as np
 import pytest
@@ -33,6 +33,23 @@ def test_first_visits_across_tile_edges(T, kw):
     check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", T))
     y = S.make_activations(cfg, 52, 0, 1)[0]
     check(g.decode_step(0, dev_acts(y, cfg)), o.decode_step(0, y), cfg, ("later visit after", T))
+    g.sync()
+
+
+# ... and the sizes at which the choice of tiles falls on the (product, tile shape) pairs that neither these nor the
+# benchmark shapes reach: every shape in every epilogue it can have, none of the sizes a multiple of its tiles
+@pytest.mark.parametrize("dtype,d,heads,kv,h,d_ff,T", [
+    (S.DT_BF16, 72, 2, 2, 64, 24, 9), (S.DT_BF16, 3080, 2, 2, 64, 520, 1300), (S.DT_BF16, 1032, 2, 2, 64, 6152, 1300),
+    (S.DT_BF16, 72, 32, 8, 64, 2056, 2050), (S.DT_BF16, 3080, 2, 2, 64, 2056, 3000), (S.DT_BF16, 72, 2, 2, 64, 6152, 2050),
+    (S.DT_BF16, 3080, 64, 32, 128, 24, 700), (S.DT_BF16, 6152, 2, 2, 64, 24, 2050),
+    (S.DT_F32, 520, 24, 8, 64, 72, 300), (S.DT_F32, 3080, 2, 2, 64, 72, 257), (S.DT_F32, 2056, 2, 2, 64, 1032, 700), (S.DT_F32, 2056, 2, 2, 64, 520, 700)])
+def test_first_visits_with_every_tile_shape(dtype, d, heads, kv, h, d_ff, T):
+    mlp = {} if (dtype, d_ff) == (S.DT_F32, 520) else GELU           # (gate and up, the others: one matrix and biases)
+    cfg = S.tiny(n_layer=1, d_model=d, n_head=heads, n_kv_head=kv, head_dim=h, d_ff=d_ff, vocab=61, max_ctx=T, **{**mlp, "dtype": dtype})
+    w = S.make_weights(cfg, 55, exercise=True)
+    o, g = pair(cfg, w, 0, 1, max_prefill=T)
+    x = S.make_activations(cfg, 56, 0, T)
+    check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", T))
     g.sync()
 
 
