@@ -10,11 +10,12 @@
 // instructions of the current one.  The 16-byte pieces of a row are permuted by the row number (the permutation is
 // applied to the global address, LDS then holds it for free), which spreads the reads over the banks.
 //
-// What bounds it, measured on the 7B shapes.  With 256 x 256 tiles and long rows the chip's power: the shader clock
-// falls to 1.4 - 1.9 GHz under every variant whose matrix cores are busier, and time follows the energy per product.
-// 16x16x32 instructions take 10 % less of it than 32x32x16 ones (half the accumulator traffic per product): 283
-// against 310 us at 4096 x 4096 x 11008, 1.30 PFLOP/s.  Smaller tiles are bound by what a compute unit pulls out of
-// its die's L2 (about 60 GB/s), few positions by the weights' way from memory.
+// What bounds it, by the counters of the large products of the 7B and 8B shapes (1024 and 2048 positions): the matrix
+// cores work in 47 - 58 % of the cycles, at a clock of 2.1 - 2.3 GHz where 2.4 is the highest.  So most of what is missing
+// is a stall inside the step, a smaller part the clock: a step of a 192 x 256 tile takes about 2700 cycles, of which 1536
+// are matrix instructions.  Which wait it is has not been found out.  16x16x32 instructions against 32x32x16 ones, half
+// the accumulator traffic per product: 283 against 310 us at 4096 x 4096 x 11008 (1.30 PFLOP/s).  Products of few
+// positions are bound by the weights' way from memory through few tiles.
 //
 // Included by gemm_bf16.hip and gemm_f32.hip, which hold the tile shapes of their storage type.
 #pragma once
