@@ -16,7 +16,7 @@
 //   * Logits (optional) are written from the accumulators; every lane keeps the best (value, row) of its sample,
 //     folded per wavefront, per workgroup, and by the last workgroup to arrive (lowest index on exact ties).
 //
-// Included by step_w8.hip after step_batch.h.
+// Included by heads.hip after step_mfma.h.
 namespace mdi {
 namespace step_w8 {
 

@@ -94,7 +94,7 @@ struct mdi_partition {
   bool use_batch = false;              // ... and the shape allows the launch on this device
   char* b_slot0 = nullptr; size_t b_stride = 0;
   size_t b_off_q = 0, b_off_part = 0, b_off_knew = 0, b_off_tickets = 0;
-  tagged_t *b_xn[2] = {}, *b_ob = nullptr, *b_ub = nullptr;   // [pair of columns][kMaxBatch messages]
+  tagged_t *b_xn[2] = {}, *b_ob = nullptr, *b_ub = nullptr;   // exchange vectors, see BatchArgs
   size_t b_vec_words = 0;
   tagged_t* b_ssq[2] = {};
   tagged_t* b_ssum[2] = {}; float* b_nc = nullptr; size_t b_nc_stride = 0;   // LayerNorm in the batched pass (BatchArgs)
@@ -102,7 +102,6 @@ struct mdi_partition {
   unsigned b_epoch = 0;
   int b_R[4] = {16, 16, 16, 16};
   int batch_group = 0;                 // MDI_BATCH_GROUP: query heads per attention work item of a batched pass (0: chosen per launch)
-  int b_lds_xres = 0, b_lds_part = 0;
   size_t b_lds = 0;
   int n_cu = 0;
   int device = 0;         // HIP device the partition was created on (index into the per-device launch chain)
@@ -289,6 +288,11 @@ void plan_step(mdi_partition* p, int n_cu) {
   p->use_step = true;
 }
 
+const void* batch_kernel(const mdi_partition* p, int G, bool scores_on_mfma) {
+  const bool swiglu = p->cfg.mlp_kind == MDI_MLP_SWIGLU;
+  return p->cfg.norm_kind == MDI_NORM_LAYERNORM ? step_batch_kernel<true>(G, scores_on_mfma, swiglu) : step_batch_kernel<false>(G, scores_on_mfma, swiglu);
+}
+
 // Decides whether several queued messages can share one pass over the weights (step_batch.h) and lays out its LDS.
 void plan_batch(mdi_partition* p) {
   const mdi_config& c = p->cfg;
@@ -301,6 +305,8 @@ void plan_batch(mdi_partition* p) {
   const int rows[4] = {(H + 2 * K) * h, d, nup, d};
   int nb_max = 1;
   for (int j = 0; j < 4; ++j) {
+    if ((size_t)rows[j] * (j == 1 ? H * h : j == 3 ? F : d) * 2 >= (size_t)1 << 31) return;   // offsets into a matrix are 31-bit
+
     // 16 rows per block when that gives every workgroup a block, else 8 (twice the blocks to spread).  Measured on
     // the 7B shape's gate/up product (1376 blocks of 16 over 256 workgroups: 5 or 6 each): blocks of 8 balance better
     // (10 or 11 each) but every load and matrix instruction then carries half the rows, and the phase took twice as long.
@@ -325,14 +331,14 @@ void plan_batch(mdi_partition* p) {
     p->b_R[1] = p->b_R[3] = 16;
     ks_floats = c_max * 256;
   }
-  p->b_lds_xres = 128;
-  p->b_lds_part = p->b_lds_xres + 256;
   const int Gmax = (H / K) % 4 == 0 ? 4 : p->G;
   const int attn_floats = std::max(Gmax * h, kStepWavesMax * Gmax * (h + 2)) + 64;
   const int part_floats = std::max(std::max(nb_max * 2048, attn_floats), ks_floats);
-  p->b_lds = (size_t)(p->b_lds_part + part_floats) * sizeof(float);
+  p->b_lds = (size_t)(kBatchLdsPart + part_floats) * sizeof(float);
   if (p->b_lds > 160 * 1024) return;
-  if (p->b_lds > 64 * 1024 && !step_batch_allow_lds(p->b_lds)) return;
+  if (p->b_lds > 64 * 1024)
+    for (int k = 0; k < 4; ++k)
+      if (hipFuncSetAttribute(batch_kernel(p, k == 3 ? 4 : 1 << k, k == 3), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->b_lds) != hipSuccess) return;
   p->use_batch = true;
 }
 
@@ -735,13 +741,20 @@ mdi_status plan_message(mdi_partition* p, uint32_t seq, MessagePlan* m) {
 // Query heads per attention work item for a launch whose longest context is ctx (see plan_step).
 int step_group(const mdi_partition* p, int ctx) { return ctx >= p->group_ctx ? p->G : 1; }
 
-// Arguments of the persistent step kernel that do not depend on the message; G = query heads per attention work item.
-void fill_step_shared(const mdi_partition* p, int G, StepArgs* a) {
+// Arguments of the persistent step kernel that do not depend on the message; G = query heads per attention work item, n =
+// messages of the launch.
+void fill_step_shared(const mdi_partition* p, int G, int n, StepArgs* a) {
   const mdi_config& c = p->cfg;
   a->l0 = p->h_step_layers[0];
   a->w_stride = p->n_local > 1 ? (const char*)p->h_step_layers[1].wqkv - (const char*)p->h_step_layers[0].wqkv : 0;
   a->kv_stride = p->n_local > 1 ? (const char*)p->h_step_layers[1].kv - (const char*)p->h_step_layers[0].kv : 0;
   a->n_layer = p->n_local;
+  const int waves = n >= 2 ? 4 : kStepWavesMax;
+  const long heads = (long)c.n_head * c.head_dim, nup = c.mlp_kind == MDI_MLP_SWIGLU ? 2L * c.d_ff : c.d_ff;
+  a->pr[0] = gemv_geo(a->l0.wqkv, a->l0.bqkv, heads + 2L * c.n_kv_head * c.head_dim, c.d_model, (int)p->esz, p->nwg, waves);
+  a->pr[1] = gemv_geo(a->l0.wo, a->l0.bo, c.d_model, heads, (int)p->esz, p->nwg, waves);
+  a->pr[2] = gemv_geo(a->l0.wup, a->l0.bup, nup, c.d_model, (int)p->esz, p->nwg, waves);
+  a->pr[3] = gemv_geo(a->l0.wdown, a->l0.bdown, c.d_model, c.d_ff, (int)p->esz, p->nwg, waves);
   a->d = c.d_model; a->H = c.n_head; a->K = c.n_kv_head; a->h = c.head_dim; a->F = c.d_ff; a->pt = p->pt;
   a->pt_h = (long)p->pt * c.head_dim;
   a->norm_kind = c.norm_kind; a->mlp_kind = c.mlp_kind; a->eps = c.norm_eps;
@@ -782,7 +795,7 @@ mdi_status launch_messages(mdi_partition* p, int n, const uint32_t* seqs, const 
   int ctx = 0;
   for (int m = 0; m < n; ++m) ctx = std::max(ctx, mp[m].ctx);
   const int G = step_group(p, ctx);
-  fill_step_shared(p, G, &a);
+  fill_step_shared(p, G, n, &a);
   a.n_slots = n;
   a.n_sets = n >= 2 ? 2 : 1;             // two sets of 4-wavefront workgroups share the compute units
   a.nwg = p->nwg;
@@ -794,8 +807,8 @@ mdi_status launch_messages(mdi_partition* p, int n, const uint32_t* seqs, const 
     if (second < n) a.s[second].trace = p->trace + (size_t)a.nwg * p->n_local * 40;
   }
   const mdi_status st = launch_step_serialised(p, [&]() {
-    if (n == 1) launch_step_w8(p->stream, p->cfg.dtype, G, a.nwg, p->step_lds, a);
-    else launch_step_w4(p->stream, p->cfg.dtype, G, a.nwg, p->step_lds, a);
+    if (n == 1) (p->cfg.dtype == MDI_BF16 ? launch_step_w8_bf16 : launch_step_w8_f32)(p->stream, G, a.nwg, p->step_lds, a);
+    else (p->cfg.dtype == MDI_BF16 ? launch_step_w4_bf16 : launch_step_w4_f32)(p->stream, G, a.nwg, p->step_lds, a);
   });
   if (st != MDI_OK) return st;
   p->epoch += 5u * (unsigned)p->n_local;
@@ -955,8 +968,17 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   a.ppart = p->b_ppart; a.str_S = p->b_S; a.str_oct = p->b_oct;
   const int heads = c.n_head * c.head_dim, ff = c.d_ff;
   a.str_c[0] = (heads / 32 + p->b_S - 1) / p->b_S; a.str_c[1] = (ff / 32 + p->b_S - 1) / p->b_S;
-  for (int j = 0; j < 4; ++j) a.R[j] = p->b_R[j];
-  a.lds_xres = p->b_lds_xres; a.lds_part = p->b_lds_part;
+  const int rows[4] = {(int)((c.n_head + 2 * c.n_kv_head) * c.head_dim), (int)c.d_model, (int)(c.mlp_kind == MDI_MLP_SWIGLU ? 2 * c.d_ff : c.d_ff), (int)c.d_model};
+  const int cols[4] = {(int)c.d_model, heads, (int)c.d_model, ff};
+  const void* const mats[4] = {a.l0.wqkv, a.l0.wo, a.l0.wup, a.l0.wdown};
+  const float* const bias[4] = {a.l0.bqkv, a.l0.bo, a.l0.bup, a.l0.bdown};
+  for (int j = 0; j < 4; ++j) {
+    const int R = p->b_R[j], nblk = (rows[j] + R - 1) / R;
+    a.pr[j] = BatchProduct{mats[j], bias[j], rows[j], 2 * cols[j], (unsigned)rows[j] * 2u * (unsigned)cols[j], R, nblk / a.nwg, nblk % a.nwg};
+  }
+  a.res_c = ((int)c.d_model / 32 + kStepWavesMax - 1) / kStepWavesMax;
+  a.rope = p->rope;
+  a.sq_stride = (a.nwg + 255) & ~255;
   a.trace = p->trace;
   // Attention work items: (message, head group, context split).  Splits of about equal length over all messages,
   // as many items as there are workgroups when the contexts allow it, no split shorter than 128 positions.
@@ -969,7 +991,6 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
     BatchSlot& s = a.s[j];
     s.in = ins[j]; s.act_out = outs[j];
     s.pos = mp[j].len; s.ctx = mp[j].ctx;
-    s.rope = p->rope ? p->rope + (size_t)mp[j].len * (c.head_dim / 2) : nullptr;
     s.table = mp[j].drow; s.table_entry = mp[j].new_entry; s.new_page = mp[j].page;
     s.kv_tok_off = (long)mp[j].page * c.n_kv_head * 2 * a.pt_h + (long)mp[j].slot * c.head_dim;
     int ch = chunk;
@@ -979,7 +1000,10 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
     item += a.n_hg * s.n_splits;
   }
   a.n_items = item;
-  const mdi_status st = launch_step_serialised(p, [&]() { launch_step_batch(p->stream, G, G == 4 && mfma_scores, p->b_lds, a); });
+  const mdi_status st = launch_step_serialised(p, [&]() {
+    void* args[] = {&a};
+    (void)hipLaunchKernel(batch_kernel(p, G, G == 4 && mfma_scores), dim3(a.nwg), dim3(64 * kStepWavesMax), args, p->b_lds, p->stream);
+  });
   if (st != MDI_OK) return st;
   p->b_epoch += 5u * (unsigned)p->n_local;
   for (int j = 0; j < n; ++j) p->seq_len[seqs[j]] = (uint32_t)mp[j].ctx;
@@ -1038,7 +1062,7 @@ unsigned next_head_tag() {
 void launch_head(mdi_partition* p, const void* act_in, int32_t* token_out, float* logits, const HeadScratch& hs) {
   const mdi_config& c = p->cfg;
   if (p->head_nwg) {
-    LogitsArgs a{p->lm_head, (int)c.vocab, (int)c.d_model, act_in, act_kind(c), (int)c.norm_kind, p->lnf_g, p->lnf_b, c.norm_eps,
+    LogitsArgs a{gemv_geo(p->lm_head, nullptr, (long)c.vocab, (long)c.d_model, (int)p->esz, p->head_nwg, kStepWavesMax), (int)c.vocab, (int)c.d_model, act_in, act_kind(c), (int)c.norm_kind, p->lnf_g, p->lnf_b, c.norm_eps,
                  logits, hs.cand, next_head_tag(), hs.counter, token_out, p->head_part_floats, hs.err, 1 << 21};
     launch_logits(p->stream, c.dtype, p->head_nwg, p->head_lds, a);
     return;

@@ -209,7 +209,29 @@ struct StepSlot {
   void* act_out;
   unsigned long long* trace;         // optional [workgroup][n_layer][5 phases][8] timestamps (100 MHz ticks), or nullptr
 };
+// One of the matrices a decode step multiplies a vector with, and how its row pairs are dealt to the workgroups (Geo in
+// step_impl.h).
+struct GemvGeo {
+  const void* W; const float* bias;  // [N, Kd] storage dtype; [N] or nullptr
+  int N, units, cpp;                 // rows; 16-byte units per row; 64-lane chunks per row
+  int bshift, own_q, own_r;          // blocks of 2^bshift pairs; blocks of a workgroup: own_q, and one more of the first own_r workgroups
+  int last_wg, last_short;           // the workgroup with the last block, and the pairs missing in that
+  int dq, dr, cpp_magic;             // wavefronts div and mod cpp; 65536 / cpp + 1: w / cpp = w * cpp_magic >> 16 for w < 16
+};
+inline GemvGeo gemv_geo(const void* W, const float* bias, long N, long Kd, int elem_bytes, int nwg, int waves) {
+  GemvGeo g{};
+  g.W = W; g.bias = bias; g.N = (int)N; g.units = (int)(Kd * elem_bytes / 16); g.cpp = (g.units + 63) / 64;
+  const long pairs = (N + 1) / 2, pair_bytes = 2 * Kd * elem_bytes;
+  // larger blocks only while they still divide evenly among the workgroups (balance comes first)
+  while (g.bshift < 3 && (pair_bytes << g.bshift) < 65536 && pairs % ((long)nwg << (g.bshift + 1)) == 0) ++g.bshift;
+  const long B = 1L << g.bshift, nblk = (pairs + B - 1) / B;
+  g.own_q = (int)(nblk / nwg); g.own_r = (int)(nblk % nwg);
+  g.last_wg = (int)((nblk - 1) % nwg); g.last_short = (int)(nblk * B - pairs);
+  g.dq = waves / g.cpp; g.dr = waves % g.cpp; g.cpp_magic = 65536 / g.cpp + 1;
+  return g;
+}
 struct StepArgs {
+  GemvGeo pr[4];                     // QKV (pairs: RoPE partners), output projection, up, down
   StepLayer l0;                      // first local layer; layer i's pointers are these advanced by i strides
   long w_stride, kv_stride;          // bytes between consecutive layers' packed weights / page pools
   int n_layer;
@@ -226,14 +248,15 @@ struct StepArgs {
   int set_lo[3];                     // [set_lo[i], set_lo[i + 1]), alternating between them inside every phase
   StepSlot s[kMaxSlots];
 };
-// workgroups of 8 wavefronts (n_sets must be 1) / of 4 wavefronts
-void launch_step_w8(hipStream_t s, int dtype, int G, int nwg, size_t lds_bytes, const StepArgs& a);
-void launch_step_w4(hipStream_t s, int dtype, int G, int nwg, size_t lds_bytes, const StepArgs& a);
+// workgroups of 8 wavefronts (one message, n_sets must be 1) / of 4 wavefronts
+void launch_step_w8_bf16(hipStream_t s, int G, int nwg, size_t lds_bytes, const StepArgs& a);
+void launch_step_w8_f32(hipStream_t s, int G, int nwg, size_t lds_bytes, const StepArgs& a);
+void launch_step_w4_bf16(hipStream_t s, int G, int nwg, size_t lds_bytes, const StepArgs& a);
+void launch_step_w4_f32(hipStream_t s, int G, int nwg, size_t lds_bytes, const StepArgs& a);
 
-
-// Output layers as one streaming launch (step_w8.hip): final norm, vocabulary projection, greedy argmax.
+// Output layers as one streaming launch (heads.hip): final norm, vocabulary projection, greedy argmax.
 struct LogitsArgs {
-  const void* W; int N, Kd;          // vocabulary matrix [N, Kd], storage dtype
+  GemvGeo geo; int N, Kd;            // vocabulary matrix [N, Kd], storage dtype
   const void* x; int x_kind;         // activation [Kd]
   int norm_kind; const float* g; const float* b; float eps;
   float* out;                        // logits [N] or nullptr
@@ -253,7 +276,6 @@ constexpr int kMaxBatch = 16;        // messages one pass can carry: the matrix 
 
 struct BatchSlot {                   // what belongs to one message of the launch
   const void* in;                    // token id (int32) or activation [d] in storage dtype
-  const float2* rope;                // (cos, sin)[h/2] of its position, or nullptr
   const int32_t* table; int32_t* table_entry;
   void* act_out;
   long kv_tok_off;                   // element offset of K[kv head 0][slot] of the new token inside a layer's pool
@@ -261,8 +283,17 @@ struct BatchSlot {                   // what belongs to one message of the launc
   int n_splits, chunk;               // context splits of its attention
   int item_lo;                       // its attention work items are item_lo .. item_lo + n_hg * n_splits - 1
 };
+struct BatchProduct {                // one of a layer's four matrices (the first layer's)
+  const void* W; const float* bias;  // [N, Kd] bf16, N * row_bytes < 2^31; [N] or nullptr
+  int N, row_bytes; unsigned bytes;
+  int R;                             // rows per matrix-instruction block (8 or 16)
+  int nb_q, nb_r;                    // blocks of a workgroup: nb_q, and one more of the first nb_r workgroups
+};
 struct BatchArgs {
   StepLayer l0; long w_stride, kv_stride; int n_layer;
+  BatchProduct pr[4];                // QKV, output projection, up, down
+  int res_c;                         // column steps of a wavefront's slice in the normed products
+  const float2* rope;                // [max_ctx][h/2] (cos, sin), or nullptr
   int d, H, K, h, F, pt; long pt_h;
   int mlp_kind; float eps;
   const void* wte; const void* wpe; int vocab;
@@ -273,7 +304,7 @@ struct BatchArgs {
   unsigned m_magic;                  // 0xFFFFFFFF / m + 1: e / m is the high word of e * m_magic, exact while e * m < 2^32
   unsigned epoch0;
   // Exchange buffers.  Vectors that feed a matrix product travel as pairs of bf16 with the writing phase's counter
-  // in one 8-byte word, one array [pair of columns][m messages] per kind for the whole launch (xn: the
+  // in one 8-byte word, one array [group of 4 pairs][m messages][4] per kind for the whole launch (xn: the
   // residual stream times the gain of the norm that follows; ob: attention output; ub: MLP hidden).  What attention
   // needs per message - q, the newest K/V row, split partials as (float, counter) like in StepSlot, tickets - sits
   // in one block per message: message j's are message 0's advanced by j * slot_stride bytes.
@@ -282,7 +313,7 @@ struct BatchArgs {
   tagged_t *xn[2], *ob, *ub;
   char* slot0; long slot_stride;
   long off_q, off_part, off_knew, off_tickets;
-  tagged_t* ssq[2];                  // [kMaxBatch][nwg] per-workgroup sums of squares of the residual rows they own
+  tagged_t* ssq[2]; int sq_stride;   // [kMaxBatch][sq_stride] per-workgroup sums of squares of the residual rows they own (nwg, rounded up to 256)
   // LayerNorm (norm_kind = MDI_NORM_LAYERNORM): the sums of those rows travel too, and the products of a normalised
   // vector are corrected in the epilogue, y = rstd (W (x g)) - rstd mean (W g) + W b: per layer the four vectors
   // [W_qkv g1 | W_qkv b1 | W_up g2 | W_up b2] (float), layer l's at nc0 + l * nc_stride floats
@@ -290,13 +321,12 @@ struct BatchArgs {
   // products split among workgroups along the inner dimension: partials [block][S][4 row quads][m][4 rows], slices per
   // block, block octets, column steps of a slice (output projection, MLP down)
   tagged_t* ppart; int str_S, str_oct, str_c[2];
-  int R[4];                          // rows per matrix-instruction block in the QKV / output / up / down products (8 or 16)
-  int lds_xres, lds_part;            // LDS layout in floats
   int n_items;                       // attention work items of the launch
   unsigned long long* trace;         // optional [workgroup][n_layer][5][8] timestamps (100 MHz ticks), or nullptr
   BatchSlot s[kMaxBatch];
 };
-// Output layers of up to kMaxBatch samples with one pass over the vocabulary matrix (step_w8.hip; bf16).
+constexpr int kBatchLdsXres = 128, kBatchLdsPart = kBatchLdsXres + 256;   // LDS layout of that launch, in floats
+// Output layers of up to kMaxBatch samples with one pass over the vocabulary matrix (heads.hip; bf16).
 struct LogitsBatchArgs {
   const void* W; int N, Kd;          // vocabulary matrix [N, Kd] bf16; Kd a multiple of 32, N * Kd * 2 < 2^32
   const void* x[kMaxBatch]; int m;   // activations [Kd] bf16, 16-byte aligned, one per sample
@@ -310,9 +340,11 @@ struct LogitsBatchArgs {
 bool logits_batch_allow_lds(size_t lds_bytes);
 void launch_logits_batch(hipStream_t s, int nwg, size_t lds_bytes, const LogitsBatchArgs& a);
 
-// G: query heads per attention work item; scores_on_mfma: on the matrix cores (G = 4, heads of 128, pages of a multiple of 16 positions)
-void launch_step_batch(hipStream_t s, int G, bool scores_on_mfma, size_t lds_bytes, const BatchArgs& a);
-bool step_batch_allow_lds(size_t lds_bytes);
+// The kernel for a norm (kLn: LayerNorm, else RMSNorm).  G: query heads per attention work item; scores_on_mfma: on the matrix
+// cores (G = 4, heads of 128, pages of a multiple of 16 positions)
+template <bool kLn> const void* step_batch_kernel(int G, bool scores_on_mfma, bool swiglu);
+template <> const void* step_batch_kernel<true>(int G, bool scores_on_mfma, bool swiglu);
+template <> const void* step_batch_kernel<false>(int G, bool scores_on_mfma, bool swiglu);
 
 // ---- set-up ---------------------------------------------------------------
 void launch_rope_table(hipStream_t s, float2* table, int max_ctx, int h, double base);

@@ -30,44 +30,33 @@
 //     eight wavefronts of a workgroup split the block's columns among them and their partial 16 x 16 results are
 //     added in LDS in wavefront order (deterministic, no float atomics).  RoPE partners (i, i + h/2) and SwiGLU
 //     partners (gate_f, up_f) sit in the same block, so the epilogue of a row pair needs no other workgroup.
+//   * What a phase boundary costs beyond the exchange is instructions: the two wavefronts of a SIMD issue theirs in turn.
+//     With one body for all norms, MLPs and phases a wavefront executed 700 scalar and 800 vector instructions per phase,
+//     and 300 to 430 scalar registers lived in lanes of vector registers.  Now norm and MLP kind are template arguments,
+//     every phase is code of its own that loads what it needs of the arguments when it starts (85 to 108 such lanes, here
+//     and in k_step 45 to 60), words are requested two at a time through buffer descriptors and without branches, and
+//     a wavefront polls as one.  4 layers of GPT-2 with 3 messages 199 -> 174 us, TinyLlama starter with 4 634 -> 581, 8
+//     layers of the 7B shape with 8 1029 -> 979, of the 8B shape with 16 and 6144 positions 1504 -> 1419; one message
+//     (k_step): 4 fp32 GPT-2 layers with output layers 202 -> 152, 8 of the 7B shape 763 -> 704.
 //   * Vectors that feed a product cross workgroups as bf16 PAIRS with the writing phase's counter in one 8-byte
 //     word, already multiplied by the gain of the RMSNorm that follows (1/rms is applied to the finished products;
 //     the sum of squares travels as one partial per workgroup and message).  Bytes exchanged per message are half
 //     those of k_step's (float, counter) words, which matters now that 16 messages share a pass.  A vector kind is
-//     ONE array [pair of columns][messages] for the whole launch: the lanes that hold the same columns of the messages
-//     read consecutive words, and no line carries room for messages the launch does not have.
+//     ONE array [group of 4 pairs][messages][4] for the whole launch: the eight columns that a lane of the matrix
+//     instruction takes are 32 consecutive bytes, and no line carries room for messages the launch does not have.
 //   * The residual stream never leaves the workgroup that owns its rows: it stays in LDS for the whole launch.
 //   * Products whose input is the d-sized normalised vector (QKV, MLP up) keep each wavefront's column slice of all
 //     messages in registers for all the blocks of the phase; the others (output projection, MLP down: one block per
 //     workgroup at the benchmark shapes, a long inner dimension) split the inner dimension among workgroups, so
-//     that a workgroup reads a fraction of the vectors, and exchange 16 x 16 partial results (see KsGeo).
+//     that a workgroup reads a fraction of the vectors, and exchange 16 x 16 partial results (split, below).
 // Needs bf16 storage and widths that are multiples of 32; other shapes keep one pass per message.  With LayerNorm the vectors still travel as x * gain: the mean and the norm's bias enter the finished
 // products through two precomputed vectors per matrix (W g and W b), see BatchArgs.
 //
-// Included by step_w8.hip after step_impl.h (shares its exchange, wait and attention helpers).
+// step_batch_ln.hip and step_batch_rms.hip compile it for one norm each (MDI_BATCH_LN).
+#include "step_mfma.h"
+
 namespace mdi {
 namespace step_w8 {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
-}
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-__device__ __forceinline__ void st_pair(tagged_t* p, uint32_t bits, unsigned tag) {
-  __hip_atomic_store(p, ((tagged_t)tag << 32) | (tagged_t)bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// The low word of *p once its counter is `tag` (see settle in step_impl.h).
-__device__ __forceinline__ uint32_t settle_bits(const tagged_t* p, tagged_t u, unsigned tag, int spin_limit, int* err) {
-  int it = 0;
-  while ((uint32_t)(u >> 32) != tag) {
-    if (++it > spin_limit) { __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
-    __builtin_amdgcn_s_sleep(1);
-    u = ld_raw(p);
-  }
-  return (uint32_t)u;
-}
 
 // What the attention helpers of step_impl.h read of a message.
 struct BatchView {
@@ -89,115 +78,60 @@ __device__ __forceinline__ BatchView view_of(const BatchArgs& a, int j, tagged_t
 
 
 // ---------------------------------------------------------------------------
-// geometry of a product (all values uniform across the wavefront)
-struct BGeo {
-  const char* W;        // matrix [N, Kd] bf16, row-major
-  long row_bytes;
-  int N, R;             // rows; rows per block (16 or 8)
-  int rope_sh;          // >= 0: rows pair as RoPE partners (i, i + h/2), h = 2 << rope_sh; -1: rows (2p, 2p + 1)
-  int nb_local;         // this workgroup's blocks: its block lb is block lb * nwg + wg of the matrix
-  int ks0, nks;         // this wavefront's column steps [ks0, ks0 + nks), 32 columns each (products with a resident operand)
-};
-__device__ __forceinline__ BGeo make_bgeo(const void* W, int N, int Kd, int R, int rope_h, int wg, int nwg, int wave) {
-  BGeo g;
-  g.W = (const char*)W; g.row_bytes = 2L * Kd; g.N = N; g.R = R;
-  g.rope_sh = rope_h ? 31 - __builtin_clz(rope_h >> 1) : -1;
-  const int nblk = (N + R - 1) >> (R == 16 ? 4 : 3);
-  g.nb_local = nblk > wg ? (nblk - wg + nwg - 1) / nwg : 0;
-  // The columns are cut into one slice per wavefront; which wavefront takes which slice rotates with the workgroup,
-  // so that at any moment the workgroups read different parts of the messages' vectors (every workgroup walks the
-  // same vectors: in step they would all queue up at the same few memory channels).
-  const int total = Kd >> 5, c = (total + kStepWaves - 1) / kStepWaves;
-  g.ks0 = ((wave + wg) & (kStepWaves - 1)) * c;
-  g.nks = max(0, min(c, total - g.ks0));
-  if (g.nks == 0) g.ks0 = 0;          // a wavefront without columns still issues its (unused) loads inside the matrix
-  return g;
-}
-// Row of the matrix that row i (< R) of block `block` stands for.  With RoPE pairing a block is R/2 consecutive
-// rows of a head's first half followed by their partners in the second half.
-__device__ __forceinline__ int block_row(const BGeo& g, int block, int i) {
-  if (g.rope_sh < 0) return block * g.R + i;
-  const int hsh = 31 - __builtin_clz(g.R >> 1);            // log2 of the rows a block takes of a half head
-  const int bsh = g.rope_sh - hsh;                           // log2 of the blocks per head
-  const int head = block >> bsh, off = (block & ((1 << bsh) - 1)) << hsh;
-  return (head << (g.rope_sh + 1)) + off + (i & ((g.R >> 1) - 1)) + ((i >> hsh) << g.rope_sh);
-}
-// ---------------------------------------------------------------------------
-// products whose second operand stays in registers (QKV, MLP up): Bv[ks] = this wavefront's column step ks of all
-// messages.  A tile is 8 column steps of a block; with more than 8 steps per wavefront a block is two tiles.
-constexpr int kWatchWords = 2048;
-constexpr int kResSteps = 16;          // column steps a wavefront can keep: widths up to 8 * 16 * 32 = 4096
-template <int HALF>
-__device__ __forceinline__ void res_issue(Tile& t, const BGeo& g, int lb, int wg, int nwg, int lane) {
-  const int i = lane & (g.R - 1) & 15, kg = lane >> 4;
-  const int row = min(block_row(g, min(lb, max(g.nb_local - 1, 0)) * nwg + wg, i), g.N - 1);
-  const uint32_t woff = (uint32_t)row * (uint32_t)g.row_bytes + (uint32_t)(kg << 4);
-  const MDI_GLOBAL char* base = (const MDI_GLOBAL char*)g.W + ((long)g.ks0 << 6);
-  const int last = max(g.nks - 1 - HALF * 8, 0);
+// Waits until both words of all of a thread's pieces carry the counter `tag`; ask() asks for the pieces again.
+template <int N, typename ASK>
+__device__ __forceinline__ void await_two(u32x4 (&raw)[N], const ASK& ask, bool live, unsigned tag, int spin_limit, int* err) {
+  poll_while([&]() {
+    uint32_t bad = 0;
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    t.r[s] = *reinterpret_cast<const MDI_GLOBAL u32x4*>(base + ((long)(HALF * 8 + min(s, last)) << 6) + woff);
+    for (int i = 0; i < N; ++i) bad |= (raw[i].y ^ tag) | (raw[i].w ^ tag);
+    return live && bad != 0;
+  }, ask, spin_limit, err);
 }
-template <int HALF, bool LAST_HALF>
-__device__ __forceinline__ void res_compute(const Tile& t, const BGeo& g, int lb, const bf16x8 (&Bv)[kResSteps], f32x4& acc,
-                                            float* part, int wave, int lane) {
-  if (lb < 0 || lb >= g.nb_local) return;                        // uniform
+// Eight column steps of 16 weight rows as the matrix instruction's first operand: lane (i = l mod 16, kg = l div 16) takes
+// 16 bytes of row i.  off: the lane's offset; `uniform`: the first row's and column's; n: steps there are
+// (fewer than eight: the last one again).  Always eight loads, so that the compiler can tell how many are on their way;
+// where there is nothing to load (!on) they read nothing.
+__device__ __forceinline__ void w_issue(Tile& t, Buffer b, uint32_t off, uint32_t uniform, int n, bool on) {
+  off = on ? off : kNowhere;
+  uniform = on ? uniform : 0u;           // (what lies outside is told by off + uniform not exceeding 32 bits)
+  if (n >= 8) {
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    const int ks = HALF * 8 + s;
-    if (ks < g.nks)                                              // uniform
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t.r[s]), Bv[ks], acc, 0, 0, 0);
+    for (int s = 0; s < 8; ++s) t.r[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off + s * 64, (int)uniform, 0));
+  } else {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) t.r[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, (int)uniform + max(min(s, n - 1), 0) * 64, 0));
   }
-  if (LAST_HALF) {
-    *reinterpret_cast<f32x4*>(part + (((lb * kStepWaves + wave) << 6) + lane) * 4) = acc;
-    acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+}
+__device__ __forceinline__ f32x4 mac(const u32x4& w, const u32x4& v, f32x4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, v), acc, 0, 0, 0);
 }
 
-// ---------------------------------------------------------------------------
-// Streamed products with the inner dimension split among workgroups.  Every workgroup used to read the whole
-// vector of all messages for its one block of rows: 256 copies of it through the dies' L2s, twice the bytes of
-// the matrix itself in the MLP down projection.  Here workgroup (q, s) takes column slice s of the eight row
-// blocks 8 q .. 8 q + 7, one block per wavefront: it reads 1 / S of the vector - once, validated, into LDS, from
-// where its eight wavefronts take the matrix instruction's second operand - and hands the 16 x 16 partial result
-// of every block, as tagged words, to the workgroup that owns the block's residual rows, which adds the S partials
-// in slice order.
-struct KsGeo {
-  int S, q, s;          // slices per block; this workgroup's block octet and slice (q >= octets: no work)
-  int k0, nk;           // the slice: column steps [k0, k0 + nk)
-  int blk, nblk;        // this wavefront's block; blocks of the product
-  bool live;            // this wavefront has columns and a block
-};
-// c = column steps of a slice; q, s = workgroup divided by S, the same for the whole launch
-__device__ __forceinline__ KsGeo make_ksgeo(int N, int Kd, int S, int c, int octets, int q, int s, int wave) {
-  KsGeo g;
-  g.S = S; g.q = q; g.s = s;
-  const int ktot = Kd >> 5;
-  g.k0 = min(g.s * c, ktot);
-  g.nk = g.q < octets ? max(0, min(c, ktot - g.s * c)) : 0;
-  g.nblk = (N + 15) >> 4;
-  g.blk = g.q * kStepWaves + wave;
-  g.live = g.nk > 0 && g.blk < g.nblk;
-  return g;
-}
-// column steps 8 t .. 8 t + 7 of the slice (steps past its end repeat its last one)
-__device__ __forceinline__ void ks_issue(Tile& t, const KsGeo& g, const char* W, uint32_t woff, int ti) {
-  const MDI_GLOBAL char* base = (const MDI_GLOBAL char*)W + ((long)g.k0 << 6);
-  const int last = max(g.nk - 1, 0);
+constexpr int kWatchWords = 2048;
+constexpr int kResSteps = 16;          // column steps a wavefront can keep: widths up to 8 * 16 * 32 = 4096
+// Eight steps of a normed product, the second operand in registers; n as in w_issue.
+template <int HALF>
+__device__ __forceinline__ void res_compute(const Tile& t, const u32x4 (&Bv)[kResSteps], int n, f32x4& acc) {
+  if (n >= 8) {
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    t.r[s] = *reinterpret_cast<const MDI_GLOBAL u32x4*>(base + ((long)min(ti * 8 + s, last) << 6) + woff);
-}
-__device__ __forceinline__ void ks_compute(const Tile& t, const KsGeo& g, const u32x4* Bs, int ti, int lane, f32x4& acc) {
-  const int n = lane & 15, kg = lane >> 4;
+    for (int s = 0; s < 8; ++s) acc = mac(t.r[s], Bv[HALF * 8 + s], acc);
+  } else {
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    const int ks = ti * 8 + s;
-    if (ks < g.nk) {                                             // uniform
-      const int gi = ks * 4 + kg;
-      const u32x4 b = Bs[gi * 16 + (n ^ (gi & 15))];
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t.r[s]), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-    }
+    for (int s = 0; s < 7; ++s)
+      if (s < n) acc = mac(t.r[s], Bv[HALF * 8 + s], acc);
+  }
+}
+// Eight steps of a split product, the second operand in LDS as [group of 8 columns][message ^ (group mod 16)]; vb: the
+// lane's byte offset of step s = 0 .. 3 of every four.
+__device__ __forceinline__ void ks_compute(const Tile& t, const char* Bs, const uint32_t (&vb)[4], int n, f32x4& acc) {
+  auto v = [&](int s) __attribute__((always_inline)) { return *reinterpret_cast<const u32x4*>(Bs + vb[s & 3] + (s >> 2) * 4096); };
+  if (n >= 8) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) acc = mac(t.r[s], v(s), acc);
+  } else {
+#pragma unroll
+    for (int s = 0; s < 7; ++s)
+      if (s < n) acc = mac(t.r[s], v(s), acc);
   }
 }
 // Sum over the wavefronts of element (row i, message j) of local block lb.
@@ -208,6 +142,10 @@ __device__ __forceinline__ float part_sum(const float* part, int lb, int i, int 
   for (int w = 0; w < kStepWaves; ++w) v += p[w << 8];
   return v;
 }
+
+// Where pair `pair` of message j stands in an exchange vector: [group of 4 pairs][message][pair of the group], so that the 8
+// columns a lane of the matrix instruction takes are 32 consecutive bytes.
+__device__ __forceinline__ int vec_word(int pair, int j, int m) { return (((pair >> 2) * m + j) << 2) + (pair & 3); }
 
 // Wavefront records -> split partial, or the finished output when there is one split; the last workgroup of a head
 // group to arrive folds the splits in split order (as attn_finish in step_impl.h).  The output leaves as bf16 pairs.
@@ -228,7 +166,7 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
     }
     const int head = g.hg * G + gi;
     if (single) {
-      st_pair(S.ob + (((long)head * h + e) >> 1) * S.n_msg + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
+      st_pair(S.ob + vec_word((head * h + e) >> 1, S.msg, S.n_msg), pack_bf16x2(o0 / l, o1 / l), wtag);
     } else {
       tagged_t* pr = S.part + ((long)head * kMaxSplits + g.split) * rec;
       st_tag(pr + e, o0, wtag); st_tag(pr + e + 1, o1, wtag);
@@ -271,7 +209,7 @@ __device__ __forceinline__ void attn_finish_pairs(const AttnGeo& g, const BatchA
         }
       }
     }
-    st_pair(S.ob + (((long)head * h + e) >> 1) * S.n_msg + S.msg, pack_bf16x2(o0 / l, o1 / l), wtag);
+    st_pair(S.ob + vec_word((head * h + e) >> 1, S.msg, S.n_msg), pack_bf16x2(o0 / l, o1 / l), wtag);
   }
 }
 
@@ -413,97 +351,56 @@ __device__ __forceinline__ void bstamp(const BatchArgs& a, int layer, int ph, in
 
 // Per-message values that a thread needs for a message index of its own (a kernel argument cannot be indexed per lane).
 struct BatchLds {
-  const float2* rope[kMaxBatch];
   const void* in[kMaxBatch];
   void* out[kMaxBatch];
   long kv_off[kMaxBatch];
   long tok[kMaxBatch];
-  int pos[kMaxBatch];
+  int pos[kMaxBatch], item_lo[kMaxBatch];
 };
 
 // Element `row` of message j's input vector (the token's embedding plus learned position, or the previous stage's activation).
 __device__ __forceinline__ float batch_input(const BatchArgs& a, const BatchLds& sl, int j, int row) {
   if (a.in_kind == IN_TOKEN) {
-    float v = bf16_to_f32(((const bf16_t*)a.wte)[sl.tok[j] * a.d + row]);
-    if (a.wpe) v += bf16_to_f32(((const bf16_t*)a.wpe)[(long)sl.pos[j] * a.d + row]);
+    float v = bf16_to_f32(((const MDI_GLOBAL bf16_t*)a.wte)[sl.tok[j] * a.d + row]);
+    if (a.wpe) v += bf16_to_f32(((const MDI_GLOBAL bf16_t*)a.wpe)[(long)sl.pos[j] * a.d + row]);
     return v;
   }
-  return bf16_to_f32(((const bf16_t*)sl.in[j])[row]);
+  return bf16_to_f32(((const MDI_GLOBAL bf16_t*)sl.in[j])[row]);
 }
 
-// What the epilogue of a phase needs beside the products, for item e: QKV: (cos, sin) of the row pair; residual
-// products: the following norm's gains of the row pair; all: the biases, and the LayerNorm corrections [W g | W b].
-struct EpiItem { int j, p, lb; };      // message, row pair (SwiGLU: quad) of the block, local block
-__device__ __forceinline__ EpiItem epi_item(int e, int m, unsigned m_magic, int n_sh) {
-  const int x = (int)__umulhi((unsigned)e, m_magic);            // e / m, see BatchArgs
-  return EpiItem{e - x * m, x & ((1 << n_sh) - 1), x >> n_sh};
-}
-// Sums over the eight lanes of a message's row pairs, published by the first of them.
-__device__ __forceinline__ void publish_sums(float s2, float s1, int p, tagged_t* ssq, tagged_t* ssum, unsigned tag) {
-  s2 = dpp_add<kDppXor1, 0xF>(s2); s2 = dpp_add<kDppXor2, 0xF>(s2); s2 = dpp_add<kDppHalfMirror, 0xF>(s2);
-  if (p == 0) st_tag(ssq, s2, tag);
-  if (ssum) {
-    s1 = dpp_add<kDppXor1, 0xF>(s1); s1 = dpp_add<kDppXor2, 0xF>(s1); s1 = dpp_add<kDppHalfMirror, 0xF>(s1);
-    if (p == 0) st_tag(ssum, s1, tag);
-  }
-}
-struct EpiOps { float g0, g1, b0, b1, n[4]; };
-__device__ __forceinline__ EpiOps epi_ops(const BatchArgs& a, const StepLayer& L, const BGeo& g, const BatchLds& sl, const float* nc, int ph,
-                                          bool last, int e, int n_items, int n_sh, int wg, int nwg) {
-  EpiOps o{};
-  if (e >= n_items) return o;
-  const bool resid = ph == PH_OPROJ || ph == PH_DOWN;
-  const EpiItem it = resid ? EpiItem{e >> 3, e & 7, 0} : epi_item(e, a.m, a.m_magic, n_sh);
-  const int j = it.j, p = it.p, lb = it.lb;
-  if (ph == PH_QKV) {
-    const int r0 = block_row(g, lb * nwg + wg, p), r1 = r0 + (a.h >> 1);
-    const int head = r0 >> (31 - __builtin_clz(a.h));             // (head sizes are powers of two)
-    const float2* rope = sl.rope[j];
-    if (rope && head < a.H + a.K) { const float2 cs = rope[r0 & (a.h - 1)]; o.g0 = cs.x; o.g1 = cs.y; }
-    if (L.bqkv) { o.b0 = L.bqkv[r0]; o.b1 = L.bqkv[r1]; }
-    if (nc) { o.n[0] = nc[r0]; o.n[1] = nc[r1]; o.n[2] = nc[g.N + r0]; o.n[3] = nc[g.N + r1]; }
-    return o;
-  }
-  if (ph == PH_UP && a.mlp_kind == MDI_MLP_SWIGLU) return o;
-  const int r0 = (lb * nwg + wg) * g.R + 2 * p;
-  if (r0 >= g.N) return o;
-  const float *bu = L.bup, *bo = L.bo, *bd = L.bdown, *g1 = L.ln1_g, *g2 = L.ln2_g;
-  const float* bias = ph == PH_UP ? bu : ph == PH_OPROJ ? bo : bd;
-  if (bias) { o.b0 = bias[r0]; o.b1 = bias[r0 + 1]; }
-  if (ph == PH_UP) {
-    if (nc) { o.n[0] = nc[r0]; o.n[1] = nc[r0 + 1]; o.n[2] = nc[g.N + r0]; o.n[3] = nc[g.N + r0 + 1]; }
-  } else if (!last) {
-    const float* gain = ph == PH_OPROJ ? g2 : advance(g1, a.w_stride);
-    o.g0 = gain[r0]; o.g1 = gain[r0 + 1];
-  }
-  return o;
+// Sums over the eight lanes of a message's row pairs, published by the first of them.  Workgroup wg's share is word wg of a
+// message's row; the words from nwg to the row's end (a multiple of 256) are published too, as zeros, so that readers need
+// not tell them apart.
+__device__ __forceinline__ void publish_sum(float v, int p, tagged_t* row, int wg, int nwg, int stride, unsigned tag) {
+  v = dpp_add<kDppXor1, 0xF>(v); v = dpp_add<kDppXor2, 0xF>(v); v = dpp_add<kDppHalfMirror, 0xF>(v);
+  if (p == 0)
+    for (int w = wg; w < stride; w += nwg) st_tag(row + w, w == wg ? v : 0.f, tag);
 }
 
-// G query heads per attention work item; kScoresOnMfma: see Attn4 (G = 4)
-template <int G, bool kScoresOnMfma>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_batch(BatchArgs a) {
+// G query heads per attention work item; kScoresOnMfma: see Attn4 (G = 4).
+template <int G, bool kScoresOnMfma, bool kLn, bool kSwiglu>
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_batch(BatchArgs a0) {
   typedef bf16_t WT;
   extern __shared__ float smem[];
   __shared__ BatchLds sl;
-  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wg = blockIdx.x, nwg = a.nwg, m = a.m;
+  const int wg = blockIdx.x, nwg = a0.nwg, m = a0.m;
   int* s_flag = lds_flag();
   float* rscale = smem + 32;                     // [16] 1/rms (LayerNorm: 1/std) of every message's vector in the normed products
   float* rshift = smem + 64;                     // [16] LayerNorm: (mean - centre) / std of every message's vector
   float* rcen = smem + 80;                       // [16] LayerNorm: the centre the vectors are published around (see below)
-  const bool ln = a.norm_kind == MDI_NORM_LAYERNORM;
-  float* xres = smem + a.lds_xres;               // residual rows this workgroup owns: [16 rows][16 messages]
-  float* part = smem + a.lds_part;               // the wavefronts' partial products [block][wavefront][lane][4]; attention scratch
+  float* xres = smem + kBatchLdsXres;            // residual rows this workgroup owns: [16 rows][16 messages]
+  float* part = smem + kBatchLdsPart;            // the wavefronts' partial products [block][wavefront][lane][4]; attention scratch
 
-  if (threadIdx.x == 0) {
-    s_flag[kFailed] = 0;
-    for (int j = 0; j < m; ++j) {
-      const BatchSlot& S = a.s[j];
-      sl.rope[j] = S.rope; sl.in[j] = S.in; sl.out[j] = S.act_out; sl.kv_off[j] = S.kv_tok_off; sl.pos[j] = S.pos;
-      sl.tok[j] = a.in_kind == IN_TOKEN ? checked_token(S.in, 0, a.vocab, a.err) : 0;
-      if (wg == 0 && S.table_entry) *S.table_entry = S.new_page;    // for later launches: no position before the newest lies on a page that starts now
-    }
+  if (threadIdx.x == 0) s_flag[kFailed] = 0;
+  if ((int)threadIdx.x < m) {                    // a lane per message
+    const int j = threadIdx.x;
+    const BatchArgs& a = args_again<BatchArgs>();
+    const MDI_GLOBAL BatchSlot& S = *(const MDI_GLOBAL BatchSlot*)&a.s[j];
+    sl.in[j] = S.in; sl.out[j] = S.act_out; sl.kv_off[j] = S.kv_tok_off; sl.pos[j] = S.pos; sl.item_lo[j] = S.item_lo;
+    sl.tok[j] = a.in_kind == IN_TOKEN ? checked_token(S.in, 0, a.vocab, a.err) : 0;
+    if (wg == 0 && S.table_entry) *S.table_entry = S.new_page;      // for later launches: no position before the newest lies on a page that starts now
+    rcen[j] = 0.f;
   }
   __syncthreads();
 
@@ -515,26 +412,26 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   // x g itself would cost accuracy whenever |mean| >> std.  c is the mean of the message's vector at the previous
   // norm of the launch (every workgroup computes it, from the same sums in the same order), for the first norm the
   // mean of the input vector, which every workgroup forms here for itself.
-  if (!ln) {
-    if (threadIdx.x < kMaxBatch) rcen[threadIdx.x] = 0.f;
-  } else {
+  if constexpr (kLn) {
+    const int lane = threadIdx.x & 63;
     for (int j = wave; j < m; j += kStepWaves) {
       float u = 0.f;
-      for (int r0 = lane; r0 < a.d; r0 += 512) {     // eight loads in flight
+      for (int r0 = lane; r0 < a0.d; r0 += 512) {    // eight loads in flight
         float v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = batch_input(a, sl, j, min(r0 + 64 * k, a.d - 1));
+        for (int k = 0; k < 8; ++k) v[k] = batch_input(a0, sl, j, min(r0 + 64 * k, a0.d - 1));
 #pragma unroll
-        for (int k = 0; k < 8; ++k) u += r0 + 64 * k < a.d ? v[k] : 0.f;
+        for (int k = 0; k < 8; ++k) u += r0 + 64 * k < a0.d ? v[k] : 0.f;
       }
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) u += __shfl_xor(u, off, 64);
-      if (lane == 0) rcen[j] = u / (float)a.d;
+      if (lane == 0) rcen[j] = u / (float)a0.d;
     }
+    __syncthreads();
   }
-  __syncthreads();
   {
     // item (message j, row pair p) of the block of 16 rows this workgroup owns: eight neighbouring lanes share a message
+    const BatchArgs& a = args_again<BatchArgs>();
     const int e = threadIdx.x, j = e >> 3, p = e & 7, r0 = wg * 16 + 2 * p;
     if (e < 8 * m) {
       float s2 = 0.f, s1 = 0.f;
@@ -542,391 +439,522 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         const float x0 = batch_input(a, sl, j, r0), x1 = batch_input(a, sl, j, r0 + 1);
         float* xr = xres + 2 * p * 16 + j;
         xr[0] = x0; xr[16] = x1;
-        st_pair(a.xn[0] + (r0 >> 1) * m + j, pack_bf16x2((x0 - rcen[j]) * a.l0.ln1_g[r0], (x1 - rcen[j]) * a.l0.ln1_g[r0 + 1]), a.epoch0);
+        const MDI_GLOBAL float* gain = (const MDI_GLOBAL float*)a.l0.ln1_g;
+        st_pair(a.xn[0] + vec_word(r0 >> 1, j, m), pack_bf16x2((x0 - rcen[j]) * gain[r0], (x1 - rcen[j]) * gain[r0 + 1]), a.epoch0);
         s2 = x0 * x0 + x1 * x1; s1 = x0 + x1;
       }
-      publish_sums(s2, s1, p, a.ssq[0] + j * nwg + wg, ln ? a.ssum[0] + j * nwg + wg : nullptr, a.epoch0);
+      publish_sum(s2, p, a.ssq[0] + j * a.sq_stride, wg, nwg, a.sq_stride, a.epoch0);
+      if constexpr (kLn) publish_sum(s1, p, a.ssum[0] + j * a.sq_stride, wg, nwg, a.sq_stride, a.epoch0);
     }
   }
   __syncthreads();
 
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  const int ks_q = wg / a.str_S, ks_s = wg - ks_q * a.str_S;
+  const int ks_q = wg / a0.str_S, ks_s = wg - ks_q * a0.str_S;
+  long w_off = 0, kv_off = 0;                    // bytes from the first layer's matrices / pages to this layer's
+  unsigned epoch = a0.epoch0;                    // what the phase that runs expects its input's words to carry; it writes epoch + 1
 
 #pragma nounroll
-  for (int layer = 0; layer < a.n_layer; ++layer) {
-    const StepLayer Lv = layer_at(a, layer);
-#pragma nounroll
-    for (int ph = 0; ph < 5; ++ph) {
-      const unsigned epoch = a.epoch0 + (unsigned)(layer * 5 + ph);
+  for (int layer = 0; layer < a0.n_layer; ++layer) {
+    // Every kind of phase keeps its registers to itself (tiles in flight, the second operand, attention state are
+    // declared inside it and given a value on every path), so that the compiler sees them dead elsewhere.
+    // Each first issues the requests that depend on nothing another workgroup writes; they are on their way
+    // while the words of the phase before arrive.  The epilogue's own operands (gains, biases, angles) are among
+    // them: a thread keeps those of its first item, fetched again they would cost a round trip at the phase's end.
+    // Per-lane addresses and epilogue indexes do not change from phase to phase; computed once outside the loops they
+    // would occupy dozens of registers for the whole launch, so they are derived from a thread index the compiler cannot see
+    // through and are recomputed where they are used.
+
+    // ---- a product whose second operand stays in registers: this wavefront's column slice of every message, as
+    // published, bf16 pairs of x * gain.
+    auto normed = [&](auto ph_const) __attribute__((always_inline)) -> bool {
+      constexpr int ph = decltype(ph_const)::value;
+      constexpr bool up = ph == PH_UP, quads = up && kSwiglu;
+      const BatchArgs& a = args_again<BatchArgs>();
+      const BatchProduct& P = a.pr[ph == PH_QKV ? 0 : 2];
       const unsigned wtag = epoch + 1;
-      const int jm = gemv_index(ph);
-      const int N = jm == 0 ? (a.H + 2 * a.K) * a.h : jm == 2 ? (a.mlp_kind == MDI_MLP_SWIGLU ? 2 * a.F : a.F) : a.d;
-      const int Kd = jm == 1 ? a.H * a.h : jm == 3 ? a.F : a.d;
-      const BGeo g = make_bgeo(layer_matrix(Lv, jm), N, Kd, jm == 0 ? a.R[0] : jm == 2 ? a.R[2] : a.R[1], jm == 0 ? a.h : 0, wg, nwg, wave);
-      // LayerNorm corrections of this phase's product: [W g | W b], N floats each (QKV's first, then the up product's)
-      const float* nc = ln ? a.nc0 + (long)layer * a.nc_stride + (jm == 2 ? 2L * (a.H + 2 * a.K) * a.h : 0L) : nullptr;
-      // Per-lane addresses and epilogue indexes do not change from phase to phase; computed once outside the loops they
-      // would occupy dozens of registers for the whole launch, so they are derived from values the compiler cannot see
-      // through and are recomputed where they are used.
       int tid = threadIdx.x;
       asm volatile("" : "+v"(tid));
-      const int lane = tid & 63, kg = lane >> 4, lane_msg = min(lane & 15, m - 1);   // lane_msg: the message this lane's column stands for (columns past m repeat the last)
-      tagged_t* ob_l = a.ob;
-      tagged_t* ub_l = a.ub;
+      const int lane = tid & 63, kg = lane >> 4, n = lane & 15;
       bstamp(a, layer, ph, 0);
-
-      // Every kind of phase keeps its registers to itself (tiles in flight, the second operand, attention state are
-      // declared inside its branch and given a value on every path), so that the compiler sees them dead elsewhere.
-      // Each branch first issues the requests that depend on nothing another workgroup writes; they are on their way
-      // while the words of the phase before arrive.  The epilogue's own operands (gains, biases, angles) are among
-      // them: a thread keeps those of its first item, fetched again they would cost a round trip at the phase's end.
-      if (ph == PH_ATTN) {
-        // ---- attention: one work item = (message, head group, context split); items dealt round-robin
-        for (int item = wg, slot = 0; item < a.n_items; item += nwg) {
-          if (item != wg) __syncthreads();                           // the records in LDS have been read
-          while (slot + 1 < m && item >= a.s[slot + 1].item_lo) ++slot;
-          const BatchView V = view_of(a, slot, ob_l);
-          const AttnGeo ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
-          AttnState<WT, G> st;
-          AttnAsk<WT> ask{};
-          Tile A, B;
-          attn_ask<WT, G>(ask, ga, a, V, wave, epoch, tid);
-          if constexpr (kScoresOnMfma) {
-            Attn4 s4;
-            s4.n_t = max(ga.s1p - ga.s0 + 15, 0) >> 4;
-            int pgA = attn4_page(ga, s4, V, 0, wave), pgB = attn4_page(ga, s4, V, 1, wave);
-            attn4_issue(A, pgA, ga, s4, a, V, Lv.kv, 0, wave, lane); attn4_issue(B, pgB, ga, s4, a, V, Lv.kv, 1, wave, lane);
-            if (item == wg) bstamp(a, layer, ph, 1);
-            attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
-            if (item == wg) bstamp(a, layer, ph, 2);
-            attn4_stream(s4, st, A, B, pgA, pgB, ga, a, V, Lv.kv, wave, lane, part);
-          } else {
-            int pgA[kTile], pgB[kTile];
-            attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
-            attn_issue<WT>(A, pgA, ga, a, V, Lv.kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, Lv.kv, 1, wave);
-            if (item == wg) bstamp(a, layer, ph, 1);
-            attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
-            if (item == wg) bstamp(a, layer, ph, 2);
-            const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
-            attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, Lv.kv, nte, wave, part);
-          }
-          if (item == wg) bstamp(a, layer, ph, 3);
-          attn_to_lds<WT, G>(st, ga, a.h, part, wave);
-          attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
+      const int R = P.R, half = R >> 1, r_sh = R == 16 ? 4 : 3, rb = P.row_bytes, N = P.N;
+      const int nb = P.nb_q + (wg < P.nb_r ? 1 : 0);               // this workgroup's blocks: block lb * nwg + wg of the matrix
+      // The columns are cut into one slice per wavefront; which wavefront takes which slice rotates with the workgroup,
+      // so that at any moment the workgroups read different parts of the messages' vectors (every workgroup walks the
+      // same vectors: in step they would all queue up at the same few memory channels).
+      const int slice = (wave + wg) & (kStepWaves - 1), ks0 = slice * a.res_c, nks = max(0, min(a.res_c, (a.d >> 5) - ks0));
+      // Row of the matrix that row i (< R) of a block stands for.  QKV: R/2 consecutive rows of a head's first half followed by
+      // their RoPE partners in the second half (head sizes are powers of two); otherwise row block * R + i.
+      const int hh_sh = 30 - __builtin_clz(a.h);                    // log2(h / 2)
+      auto first_row = [&](int block) __attribute__((always_inline)) {
+        if (up) return block << r_sh;
+        const int hsh = r_sh - 1, bsh = hh_sh - hsh;                // log2 of the rows a block takes of a half head, of the blocks per head
+        return ((block >> bsh) << (hh_sh + 1)) + ((block & ((1 << bsh) - 1)) << hsh);
+      };
+      // ---- requests
+      const Buffer sqb = buffer_at(up ? a.ssq[1] : a.ssq[0]), smb = buffer_at(kLn ? (up ? a.ssum[1] : a.ssum[0]) : nullptr);
+      const int stride = a.sq_stride;
+      const bool long_vec = (a.d >> 1) * m > kWatchWords;
+      tagged_t gate[1];
+      auto gate_at = [&](int, uint32_t z) __attribute__((always_inline)) { return (uint32_t)tid * 8u + z; };
+      auto gated = [&](int) __attribute__((always_inline)) { return long_vec && tid < stride; };
+      ask_words(gate, sqb, gate_at, gated);
+      // the sums: 32 threads per message, eight words each
+      const int sj = tid >> 5, sc = tid & 31;
+      const bool sums = sj < m;
+      const uint32_t s_off = sums ? (uint32_t)(sj * stride + 2 * sc) * 8u : kNowhere;
+      u32x4 sq[4], sm[4];
+      auto ask_sq = [&]() __attribute__((always_inline)) {
+        const uint32_t o = fresh(s_off);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sq[k] = ld_two(sqb, o + k * 512, 0);
+      };
+      auto ask_sm = [&]() __attribute__((always_inline)) {
+        const uint32_t o = fresh(s_off);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sm[k] = ld_two(smb, o + k * 512, 0);
+      };
+      ask_sq();
+      if constexpr (kLn) ask_sm();
+      // the epilogue's items: (block, message, row pair or quad of rows), the latter neighbours
+      constexpr int kQ = quads ? 1 : 0;
+      const int n_sh = r_sh - 1 - kQ, n_items = (nb << n_sh) * m;
+      struct Item { int j, p, lb, r0, r1; };
+      auto item_at = [&](int e) __attribute__((always_inline)) {
+        Item it;
+        const int x = e >> n_sh;
+        it.p = e & ((1 << n_sh) - 1);
+        it.lb = (int)__umulhi((unsigned)x, a.m_magic);             // x / m, see BatchArgs
+        it.j = x - it.lb * m;
+        const int f = first_row(it.lb * nwg + wg);
+        it.r0 = up ? f + ((2 << kQ) * it.p) : f + it.p;
+        it.r1 = up ? it.r0 + 1 : it.r0 + (2 << hh_sh >> 1);
+        return it;
+      };
+      struct Ops { float c, s, b0, b1, n[4]; };
+      const Buffer biasb = buffer_at(P.bias ? (const char*)P.bias + w_off : nullptr);
+      // LayerNorm corrections of this phase's product: [W g | W b], N floats each (QKV's first, then the up product's)
+      const float* ncp = kLn ? a.nc0 + (long)layer * a.nc_stride + (up ? 2L * a.pr[0].N : 0L) : nullptr;
+      const Buffer n0b = buffer_at(ncp), n1b = buffer_at(kLn ? ncp + N : nullptr), ropeb = buffer_at(a.rope);
+      auto ops_of = [&](const Item& it, bool own) __attribute__((always_inline)) {
+        Ops o{};
+        if constexpr (quads) return o;
+        const uint32_t o0 = own ? (uint32_t)it.r0 * 4u : kNowhere, o1 = own ? (uint32_t)it.r1 * 4u : kNowhere;
+        o.b0 = ld_f32(biasb, o0); o.b1 = ld_f32(biasb, o1);
+        if constexpr (!up) {
+          const uint32_t at = (uint32_t)((sl.pos[it.j] << hh_sh) + (it.r0 & ((1 << hh_sh) - 1))) * 8u;
+          const u32x2 cs = __builtin_amdgcn_raw_buffer_load_b64(ropeb, (int)(own ? at : kNowhere), 0, 0);
+          o.c = __uint_as_float(cs.x); o.s = __uint_as_float(cs.y);
         }
-      } else {
-        const int R = g.R, half = R >> 1;
-        // epilogue items per block and message: row pairs, or quads of rows for SwiGLU; a power of two
-        const int n_sh = (R == 16 ? 3 : 2) - (ph == PH_UP && a.mlp_kind == MDI_MLP_SWIGLU ? 1 : 0);
-        const int n_items = (g.nb_local << n_sh) * m;
-        const bool last = ph == PH_DOWN && layer == a.n_layer - 1;   // (both residual products only)
-        EpiOps ops = epi_ops(a, Lv, g, sl, nc, ph, last, tid, n_items, n_sh, wg, nwg);
-        if (ph == PH_QKV || ph == PH_UP) {
-          // ---- a product whose second operand stays in registers: this wavefront's column slice of every message, as
-          // published, bf16 pairs of x * gain.  Asked for first, before the weights: the sums of squares of all
-          // messages.  Vectors of more than kWatchWords words are looked at only after every workgroup's first sum of
-          // squares (which it stores last) is there: 256 workgroups that watch 32 KB each crowd out the stores they wait
-          // for (TinyLlama, 4 messages: 629 us, ungated 644; the 7B shape with 8: 979 and 975).
-          Tile A, B;
-          bf16x8 Bv[kResSteps];
-          const tagged_t* xn_in = ph == PH_QKV ? a.xn[0] : a.xn[1];  // (selected, not indexed: an index into the arguments costs a copy of them)
-          const tagged_t* ssq_in = ph == PH_QKV ? a.ssq[0] : a.ssq[1];
-          const tagged_t* ssum_in = ph == PH_QKV ? a.ssum[0] : a.ssum[1];
-          const tagged_t* bbase = xn_in + (long)g.ks0 * (16 * m);
-          const uint32_t boff = (uint32_t)(4 * kg * m + lane_msg) << 3;
-          const int last_ks = max(g.nks - 1, 0);
-          auto step_at = [&](int ks, int e, uint32_t z) __attribute__((always_inline)) { return word_at(bbase + min(ks, last_ks) * (16 * m) + e * m, boff + z); };
-          const int sj = tid >> 5, sc = tid & 31;                    // sums: 32 threads per message, eight words each
-          auto sum_at = [&](const tagged_t* v, int k, uint32_t z) __attribute__((always_inline)) {
-            return word_at(v, (uint32_t)(min(sj, m - 1) * nwg + min(sc + 32 * k, nwg - 1)) * 8u + z);
-          };
-          tagged_t sqr[8] = {};
-          const bool long_vec = (a.d >> 1) * m > kWatchWords;
-          auto gate_at = [&](int, uint32_t z) __attribute__((always_inline)) { return word_at(ssq_in, (uint32_t)tid * 8u + z); };
-          auto gated = [&](int) __attribute__((always_inline)) { return long_vec && tid < nwg; };
-          tagged_t gate[1];
-          ask_words(gate, gate_at, epoch, gated);
-          if (sj < m) ask_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); }, epoch);
-          if (g.nks > 8) { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<1>(B, g, 0, wg, nwg, lane); }
-          else { res_issue<0>(A, g, 0, wg, nwg, lane); res_issue<0>(B, g, 1, wg, nwg, lane); }
-          bstamp(a, layer, ph, 1);
-          if (long_vec) {
-            await_words(gate, gate_at, epoch, a.spin_limit, a.err, gated);
-            for (int i = tid + kStepThreads; i < nwg; i += kStepThreads)
-              poll_words(gate, [&](int, uint32_t z) { return word_at(ssq_in, (uint32_t)i * 8u + z); }, epoch, a.spin_limit, a.err);
-            __syncthreads();
-          }
-          float sum2 = 0.f, sum1 = 0.f;                              // this thread's share of its message's sums
-          if (sj < m) {
-            await_words(sqr, [&](int k, uint32_t z) { return sum_at(ssq_in, k, z); }, epoch, a.spin_limit, a.err);
+        if constexpr (kLn) { o.n[0] = ld_f32(n0b, o0); o.n[1] = ld_f32(n0b, o1); o.n[2] = ld_f32(n1b, o0); o.n[3] = ld_f32(n1b, o1); }
+        return o;
+      };
+      Ops ops{};
+      if constexpr (!quads) {
+        const Item it = item_at(tid < n_items ? tid : 0);
+        ops = ops_of(it, tid < n_items && it.r1 < N);
+      }
+      // the first two tiles of weights
+      Tile A, B;
+      const Buffer wb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.W + w_off), 0, (int)P.bytes, 0x00020000);
+      const int wi = n & (R - 1);
+      const uint32_t w_lane = (uint32_t)((up ? wi : (wi & (half - 1)) + (wi >= half ? 1 << hh_sh : 0)) * rb + (kg << 4));
+      auto issue = [&](Tile& t, int lb, int h8) __attribute__((always_inline)) {
+        w_issue(t, wb, w_lane, (uint32_t)(first_row(lb * nwg + wg) * rb + ks0 * 64 + h8 * 512), nks - 8 * h8, lb < nb && nks > 0);
+      };
+      const bool two = nks > 8;                                     // two tiles per block, else one
+      if (two) { issue(A, 0, 0); issue(B, 0, 1); } else { issue(A, 0, 0); issue(B, 1, 0); }
+      bstamp(a, layer, ph, 1);
+      // ---- Vectors of more than kWatchWords words are looked at only after every workgroup's first sum of
+      // squares (which it stores last) is there: 256 workgroups that watch 32 KB each crowd out the stores they wait
+      // for (TinyLlama, 4 messages: 629 us, ungated 644; the 7B shape with 8: 979 and 975).
+      if (long_vec) {
+        await_words(gate, sqb, gate_at, epoch, a.spin_limit, a.err, gated);
+        for (int i = tid + kStepThreads; i < stride; i += kStepThreads)
+          poll_words(gate, sqb, [&](int, uint32_t z) { return (uint32_t)i * 8u + z; }, epoch, a.spin_limit, a.err);
+        __syncthreads();
+      }
+      float sum2 = 0.f, sum1 = 0.f;                                 // this thread's share of its message's sums
+      await_two(sq, ask_sq, sums, epoch, a.spin_limit, a.err);
+      if constexpr (kLn) await_two(sm, ask_sm, sums, epoch, a.spin_limit, a.err);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) sum2 += sc + 32 * k < nwg ? tag_value(sqr[k]) : 0.f;
-            if (ln) {
-              poll_words(sqr, [&](int k, uint32_t z) { return sum_at(ssum_in, k, z); }, epoch, a.spin_limit, a.err);
-#pragma unroll
-              for (int k = 0; k < 8; ++k) sum1 += sc + 32 * k < nwg ? tag_value(sqr[k]) : 0.f;
-            }
-            for (int w = sc + 256; w < nwg; w += 32) {               // (more than 256 workgroups)
-              auto at = [&](const tagged_t* v, uint32_t z) { return word_at(v, (uint32_t)(sj * nwg + w) * 8u + z); };
-              tagged_t one[1];
-              poll_words(one, [&](int, uint32_t z) { return at(ssq_in, z); }, epoch, a.spin_limit, a.err);
-              sum2 += tag_value(one[0]);
-              if (ln) { poll_words(one, [&](int, uint32_t z) { return at(ssum_in, z); }, epoch, a.spin_limit, a.err); sum1 += tag_value(one[0]); }
-            }
-          }
-          auto fetch4 = [&](int h0, bf16x8& v0, bf16x8& v1, bf16x8& v2, bf16x8& v3) __attribute__((always_inline)) {
-            if (h0 == 0 || h0 < g.nks) {             // uniform: a batch of steps that lies past the slice costs no round trip
-              tagged_t xr[16];                         // steps past the slice repeat its last one: every register gets a value
-              poll_words(xr, [&](int s, uint32_t z) { return step_at(h0 + (s >> 2), s & 3, z); }, epoch, a.spin_limit, a.err);
-              auto low4 = [&](int s) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, u32x4{(uint32_t)xr[s], (uint32_t)xr[s + 1], (uint32_t)xr[s + 2], (uint32_t)xr[s + 3]}); };
-              v0 = low4(0); v1 = low4(4); v2 = low4(8); v3 = low4(12);
-            } else {
-              v0 = Bv[0]; v1 = Bv[0]; v2 = Bv[0]; v3 = Bv[0];
-            }
-          };
-          fetch4(0, Bv[0], Bv[1], Bv[2], Bv[3]); fetch4(4, Bv[4], Bv[5], Bv[6], Bv[7]);
-          fetch4(8, Bv[8], Bv[9], Bv[10], Bv[11]); fetch4(12, Bv[12], Bv[13], Bv[14], Bv[15]);
-          bstamp(a, layer, ph, 2);
-          // the stream: two tiles in flight, each multiplied while the other's rows arrive
-          if (g.nks > 8) {
-#pragma nounroll
-            for (int lb = 1; lb < g.nb_local; ++lb) {
-              res_compute<0, false>(A, g, lb - 1, Bv, acc, part, wave, lane);
-              res_issue<0>(A, g, lb, wg, nwg, lane);
-              res_compute<1, true>(B, g, lb - 1, Bv, acc, part, wave, lane);
-              res_issue<1>(B, g, lb, wg, nwg, lane);
-            }
-            res_compute<0, false>(A, g, g.nb_local - 1, Bv, acc, part, wave, lane);
-            res_compute<1, true>(B, g, g.nb_local - 1, Bv, acc, part, wave, lane);
-          } else {
-            int lb = 0;
-#pragma nounroll
-            for (; lb + 2 < g.nb_local; lb += 2) {
-              res_compute<0, true>(A, g, lb, Bv, acc, part, wave, lane);
-              res_issue<0>(A, g, lb + 2, wg, nwg, lane);
-              res_compute<0, true>(B, g, lb + 1, Bv, acc, part, wave, lane);
-              res_issue<0>(B, g, lb + 3, wg, nwg, lane);
-            }
-            res_compute<0, true>(A, g, lb, Bv, acc, part, wave, lane);
-            res_compute<0, true>(B, g, lb + 1, Bv, acc, part, wave, lane);
-          }
-          bstamp(a, layer, ph, 3);
-          // 1/rms of every message.  The shares of all workgroups have been seen before anything of this phase is stored
-          // (see the top of the file).
-#pragma unroll
-          for (int off = 16; off >= 1; off >>= 1) { sum2 += __shfl_xor(sum2, off, 64); if (ln) sum1 += __shfl_xor(sum1, off, 64); }
-          if (sj < m && sc == 0) {
-            if (!ln) {
-              rscale[sj] = 1.f / sqrtf(sum2 / (float)a.d + a.eps);
-            } else {
-              const float mean = sum1 / (float)a.d;
-              const float rstd = 1.f / sqrtf(fmaxf(sum2 / (float)a.d - mean * mean, 0.f) + a.eps);
-              rscale[sj] = rstd; rshift[sj] = rstd * (mean - rcen[sj]);
-              rcen[sj] = mean;                                       // what the next norm's vector is published around
-            }
-          }
-        } else {
-          // ---- a product whose inner dimension is split among workgroups (see KsGeo)
-          const KsGeo kq = make_ksgeo(N, Kd, a.str_S, ph == PH_OPROJ ? a.str_c[0] : a.str_c[1], a.str_oct, ks_q, ks_s, wave);
-          Tile A, B;
-          const uint32_t woff = (uint32_t)min(kq.blk * 16 + (lane & 15), N - 1) * (uint32_t)g.row_bytes + (uint32_t)(kg << 4);
-          // the slice of every message's vector to LDS as [group of 8 columns][message]
-          u32x4* Bs = reinterpret_cast<u32x4*>(part);
-          const tagged_t* bvec = ph == PH_OPROJ ? ob_l : ub_l;
-          const int n_units = kq.nk * 4 * m;                         // unit: eight columns of one message
-          tagged_t raw[8] = {};
-          int gi[2], n[2];
-          int u_at = tid;
-          auto unit_of = [&](int u0) __attribute__((always_inline)) {
-            u_at = u0;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-              const int u = u0 + r * kStepThreads;
-              gi[r] = (int)__umulhi((unsigned)u, a.m_magic); n[r] = u - gi[r] * m;
-            }
-          };
-          auto at = [&](int r, uint32_t z) __attribute__((always_inline)) {   // pairs 4 (4 k0 + gi) .. + 3
-            return word_at(bvec + (long)kq.k0 * (16 * m) + (r & 3) * m, (uint32_t)(4 * gi[r >> 2] * m + n[r >> 2]) * 8u + z);
-          };
-          auto live = [&](int r) __attribute__((always_inline)) { return u_at + (r >> 2) * kStepThreads < n_units; };
-          unit_of(tid);
-          ask_words(raw, at, epoch, live);
-          ks_issue(A, kq, g.W, woff, 0);
-          ks_issue(B, kq, g.W, woff, 1);
-          bstamp(a, layer, ph, 1);
-          for (int u0 = tid; u0 < n_units; u0 += 2 * kStepThreads) {
-            if (u0 != tid) { unit_of(u0); ask_words(raw, at, epoch, live); }
-            await_words(raw, at, epoch, a.spin_limit, a.err, live);
-#pragma unroll
-            for (int r = 0; r < 2; ++r)
-              if (u0 + r * kStepThreads < n_units)
-                Bs[gi[r] * 16 + (n[r] ^ (gi[r] & 15))] = u32x4{(uint32_t)raw[4 * r], (uint32_t)raw[4 * r + 1], (uint32_t)raw[4 * r + 2], (uint32_t)raw[4 * r + 3]};
-          }
-          __syncthreads();
-          bstamp(a, layer, ph, 2);
-          acc = f32x4{0.f, 0.f, 0.f, 0.f};
-          if (kq.live) {                                             // uniform per wavefront
-            const int nt = ((kq.nk + 7) >> 3) + 1 & ~1;
-#pragma nounroll
-            for (int t = 2; t < nt; t += 2) {
-              ks_compute(A, kq, Bs, t - 2, lane, acc);
-              ks_issue(A, kq, g.W, woff, t);
-              ks_compute(B, kq, Bs, t - 1, lane, acc);
-              ks_issue(B, kq, g.W, woff, t + 1);
-            }
-            ks_compute(A, kq, Bs, nt - 2, lane, acc);
-            ks_compute(B, kq, Bs, nt - 1, lane, acc);
-          }
-          bstamp(a, layer, ph, 3);
-          // the partial of (block, slice), zeros from a slice without columns, to the block's owner
-          if (kq.q < a.str_oct && kq.blk < kq.nblk && (lane & 15) < m) {
-            tagged_t* dst = a.ppart + ((long)((kq.blk * kq.S + kq.s) * 4 + kg) * m + (lane & 15)) * 4;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) st_tag(dst + r, acc[r], wtag);
-          }
-          acc = f32x4{0.f, 0.f, 0.f, 0.f};
-          bstamp(a, layer, ph, 7);
-          // ---- residual products: x += W v (+ bias) on the 16 rows this workgroup owns; what leaves is x times the gain
-          // of the norm that follows, as bf16 pairs, and this workgroup's share of every message's sum of squares (every
-          // workgroup's, also without rows: see the top of the file).  One lane per (message, row pair), which adds the S
-          // partials in slice order.
-          tagged_t* xn_out = ph == PH_OPROJ ? a.xn[1] : a.xn[0];
-          tagged_t* ssq_out = ph == PH_OPROJ ? a.ssq[1] : a.ssq[0];
-          tagged_t* ssum_out = ph == PH_OPROJ ? a.ssum[1] : a.ssum[0];
-          const int j = tid >> 3, p = tid & 7, r0 = wg * 16 + 2 * p;
-          if (j < m) {
-            float s2 = 0.f, s1 = 0.f;
-            if (wg < kq.nblk) {
-              const tagged_t* srcp = a.ppart + (long)wg * kq.S * (16 * m);
-              const uint32_t off = (uint32_t)((p >> 1) * m + j) * 32u + (uint32_t)(p & 1) * 16u;
-              float d0 = 0.f, d1 = 0.f;
-              auto add = [&](auto n_const) __attribute__((always_inline)) {
-                constexpr int NS = decltype(n_const)::value;
-                tagged_t raw[2 * NS];                                // slices past the last repeat it
-                poll_words(raw, [&](int k, uint32_t z) { return word_at(srcp + min(k >> 1, kq.S - 1) * (16 * m) + (k & 1), off + z); }, wtag, a.spin_limit, a.err);
-#pragma unroll
-                for (int k = 0; k < NS; ++k) { d0 += k < kq.S ? tag_value(raw[2 * k]) : 0.f; d1 += k < kq.S ? tag_value(raw[2 * k + 1]) : 0.f; }
-              };
-              if (kq.S <= 8) add(std::integral_constant<int, 8>()); else add(std::integral_constant<int, 16>());
-              if (r0 < g.N) {
-                float* xr = xres + 2 * p * 16 + j;
-                const float x0 = xr[0] + d0 + ops.b0, x1 = xr[16] + d1 + ops.b1;
-                xr[0] = x0; xr[16] = x1;
-                if (last) {
-                  store_kind(sl.out[j], a.act_kind, r0, x0); store_kind(sl.out[j], a.act_kind, r0 + 1, x1);
-                } else {
-                  st_pair(xn_out + (r0 >> 1) * m + j, pack_bf16x2((x0 - rcen[j]) * ops.g0, (x1 - rcen[j]) * ops.g1), wtag);
-                  s2 = x0 * x0 + x1 * x1; s1 = x0 + x1;
-                }
-              }
-            }
-            if (!last) publish_sums(s2, s1, p, ssq_out + j * nwg + wg, ln ? ssum_out + j * nwg + wg : nullptr, wtag);
-          }
-        }
-        if (ph == PH_QKV || ph == PH_UP) {
-          __syncthreads();                                           // every wavefront's partial products are in LDS
-          bstamp(a, layer, ph, 4);
-        }
-
-        // ---- epilogue of the normed products: one thread per (block, row pair or quad, message)
-        if (ph == PH_QKV) {
-          for (int e = tid; e < n_items; e += kStepThreads) {
-            const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
-            const int j = it.j, p = it.p, lb = it.lb;
-            const int r0 = block_row(g, lb * nwg + wg, p), r1 = r0 + (a.h >> 1);
-            float v0 = part_sum(part, lb, p, j) * rscale[j], v1 = part_sum(part, lb, p + half, j) * rscale[j];
-            if (ln) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }
-            v0 += ops.b0; v1 += ops.b1;
-            const int head = r0 >> (31 - __builtin_clz(a.h)), i = r0 & (a.h - 1);
-            if (sl.rope[j] && head < a.H + a.K) {
-              const float t0 = v0 * ops.g0 - v1 * ops.g1, t1 = v0 * ops.g1 + v1 * ops.g0;
-              v0 = t0; v1 = t1;
-            }
-            char* base = a.slot0 + (long)j * a.slot_stride;
-            if (head < a.H) {
-              tagged_t* q = (tagged_t*)(base + a.off_q);
-              st_tag(q + r0, v0, wtag); st_tag(q + r1, v1, wtag);
-            } else {
-              // the cache row is for later launches (plain stores); this launch's attention takes the same
-              // rounded values from the tagged copy
-              const bool is_v = head >= a.H + a.K;
-              const int kvh = head - a.H - (is_v ? a.K : 0);
-              WT* dst = (WT*)Lv.kv + sl.kv_off[j] + (long)(kvh * 2 + (is_v ? 1 : 0)) * a.pt_h + i;
-              Storage<WT>::put(dst, v0); Storage<WT>::put(dst + (a.h >> 1), v1);
-              tagged_t* kn = (tagged_t*)(base + a.off_knew) + (long)(is_v ? a.K * a.h : 0) + kvh * a.h + i;
-              st_tag(kn, bf16_to_f32(f32_to_bf16(v0)), wtag); st_tag(kn + (a.h >> 1), bf16_to_f32(f32_to_bf16(v1)), wtag);
-            }
-            if (e + kStepThreads < n_items) ops = epi_ops(a, Lv, g, sl, nc, ph, last, e + kStepThreads, n_items, n_sh, wg, nwg);
-          }
-        } else if (ph == PH_UP) {
-          if (a.mlp_kind == MDI_MLP_SWIGLU) {
-            // rows (4q .. 4q + 3) = (gate_f, up_f, gate_f+1, up_f+1): one lane of every wavefront's result holds all four
-            for (int e = tid; e < n_items; e += kStepThreads) {
-              const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
-              const int j = it.j, qd = it.p, lb = it.lb;
-              const int r0 = (lb * nwg + wg) * R + 4 * qd;
-              if (r0 < g.N) {
-                const float* pp = part + ((lb * kStepWaves) << 8) + (((qd << 4) + j) << 2);
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int w = 0; w < kStepWaves; ++w) { const f32x4 t = *reinterpret_cast<const f32x4*>(pp + (w << 8)); v += t; }
-                const float rs = rscale[j];
-                v *= rs;
-                if (ln) {
-                  const float sh = rshift[j];
-                  v.x += nc[N + r0] - sh * nc[r0]; v.y += nc[N + r0 + 1] - sh * nc[r0 + 1];
-                  v.z += nc[N + r0 + 2] - sh * nc[r0 + 2]; v.w += nc[N + r0 + 3] - sh * nc[r0 + 3];
-                }
-                const float u0 = silu_f(v.x) * v.y, u1 = silu_f(v.z) * v.w;
-                st_pair(ub_l + (r0 >> 2) * m + j, pack_bf16x2(u0, u1), wtag);
-              }
-            }
-          } else {
-            const bool tanh_form = a.mlp_kind == MDI_MLP_GELU_TANH;
-            for (int e = tid; e < n_items; e += kStepThreads) {
-              const EpiItem it = epi_item(e, m, a.m_magic, n_sh);
-              const int j = it.j, p = it.p, lb = it.lb;
-              const int r0 = (lb * nwg + wg) * R + 2 * p;
-              if (r0 < g.N) {
-                float v0 = part_sum(part, lb, 2 * p, j) * rscale[j], v1 = part_sum(part, lb, 2 * p + 1, j) * rscale[j];
-                if (ln) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }
-                v0 += ops.b0; v1 += ops.b1;
-                st_pair(ub_l + (r0 >> 1) * m + j, pack_bf16x2(tanh_form ? gelu_tanh_f(v0) : gelu_erf_f(v0), tanh_form ? gelu_tanh_f(v1) : gelu_erf_f(v1)), wtag);
-              }
-              if (e + kStepThreads < n_items) ops = epi_ops(a, Lv, g, sl, nc, ph, last, e + kStepThreads, n_items, n_sh, wg, nwg);
-            }
-          }
+      for (int k = 0; k < 4; ++k) {
+        sum2 += __uint_as_float(sq[k].x) + __uint_as_float(sq[k].z);
+        if constexpr (kLn) sum1 += __uint_as_float(sm[k].x) + __uint_as_float(sm[k].z);
+      }
+      for (int w = 256 + 2 * sc; w < stride && sums; w += 64) {     // (more than 256 workgroups)
+        u32x4 one[1];
+        auto ask1 = [&](Buffer b) __attribute__((always_inline)) { one[0] = ld_two(b, fresh((uint32_t)(sj * stride + w) * 8u), 0); };
+        ask1(sqb);
+        await_two(one, [&]() { ask1(sqb); }, true, epoch, a.spin_limit, a.err);
+        sum2 += __uint_as_float(one[0].x) + __uint_as_float(one[0].z);
+        if constexpr (kLn) {
+          ask1(smb);
+          await_two(one, [&]() { ask1(smb); }, true, epoch, a.spin_limit, a.err);
+          sum1 += __uint_as_float(one[0].x) + __uint_as_float(one[0].z);
         }
       }
-
-      // ---- the partial products and the attention's records in LDS have been read
+      // the vectors: steps of 32 columns, 32 bytes per lane and step; steps past the slice repeat its last one
+      u32x4 Bv[kResSteps];
+      const Buffer vb = buffer_at(up ? a.xn[1] : a.xn[0]);
+      const bool has = n < m && nks > 0;
+      const uint32_t v_off = has ? (uint32_t)(kg * m + n) * 32u : kNowhere;
+      const uint32_t v_step = (uint32_t)m * 128u, v_base = (uint32_t)ks0 * v_step;
+      auto fetch = [&](auto first, auto count) __attribute__((always_inline)) {
+        constexpr int k0 = decltype(first)::value, kn = decltype(count)::value;
+        u32x4 raw[2 * kn];
+        auto ask = [&]() __attribute__((always_inline)) {
+          const uint32_t o = fresh(v_off);
+#pragma unroll
+          for (int k = 0; k < kn; ++k) {
+            const uint32_t u = v_base + (uint32_t)max(min(k0 + k, nks - 1), 0) * v_step;
+            raw[2 * k] = ld_two(vb, o, u); raw[2 * k + 1] = ld_two(vb, o + 16, u);
+          }
+        };
+        ask();
+        await_two(raw, ask, has, epoch, a.spin_limit, a.err);
+#pragma unroll
+        for (int k = 0; k < kn; ++k) Bv[k0 + k] = u32x4{raw[2 * k].x, raw[2 * k].z, raw[2 * k + 1].x, raw[2 * k + 1].z};
+      };
+      auto none = [&](auto first, auto count) __attribute__((always_inline)) {
+        constexpr int k0 = decltype(first)::value, kn = decltype(count)::value;
+#pragma unroll
+        for (int k = 0; k < kn; ++k) Bv[k0 + k] = Bv[0];
+      };
+      constexpr std::integral_constant<int, 0> c0{}; constexpr std::integral_constant<int, 4> c4{};
+      constexpr std::integral_constant<int, 8> c8{}; constexpr std::integral_constant<int, 12> c12{};
+      fetch(c0, c4);
+      if (nks > 4) fetch(c4, c4); else none(c4, c4);
+      if (nks > 8) { fetch(c8, c4); fetch(c12, c4); } else { none(c8, c4); none(c12, c4); }
+      bstamp(a, layer, ph, 2);
+      // ---- the stream: two tiles in flight, each multiplied while the other's rows arrive
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      f32x4* pw = reinterpret_cast<f32x4*>(part) + (wave << 6) + lane;
+      auto put = [&](int lb) __attribute__((always_inline)) { pw[lb * (kStepWaves * 64)] = acc; acc = f32x4{0.f, 0.f, 0.f, 0.f}; };
+      if (two) {
+#pragma nounroll
+        for (int lb = 0; lb < nb; ++lb) {
+          res_compute<0>(A, Bv, nks, acc);
+          issue(A, lb + 1, 0);
+          res_compute<1>(B, Bv, nks - 8, acc);
+          issue(B, lb + 1, 1);
+          put(lb);
+        }
+      } else {
+        int lb = 0;
+#pragma nounroll
+        for (; lb + 1 < nb; lb += 2) {
+          res_compute<0>(A, Bv, nks, acc);
+          issue(A, lb + 2, 0);
+          put(lb);
+          res_compute<0>(B, Bv, nks, acc);
+          issue(B, lb + 3, 0);
+          put(lb + 1);
+        }
+        if (lb < nb) { res_compute<0>(A, Bv, nks, acc); put(lb); }
+      }
+      bstamp(a, layer, ph, 3);
+      // 1/rms of every message.  The shares of all workgroups have been seen before anything of this phase is stored
+      // (see the top of the file).
+      auto over32 = [&](float v) __attribute__((always_inline)) {
+        v = dpp_add<kDppXor1, 0xF>(v); v = dpp_add<kDppXor2, 0xF>(v); v = dpp_add<kDppHalfMirror, 0xF>(v); v = dpp_add<kDppMirror, 0xF>(v);
+        return v + __shfl_xor(v, 16, 64);
+      };
+      sum2 = over32(sum2);
+      if constexpr (kLn) sum1 = over32(sum1);
+      if (sums && sc == 0) {
+        if constexpr (!kLn) {
+          rscale[sj] = 1.f / sqrtf(sum2 / (float)a.d + a.eps);
+        } else {
+          const float mean = sum1 / (float)a.d;
+          const float rstd = 1.f / sqrtf(fmaxf(sum2 / (float)a.d - mean * mean, 0.f) + a.eps);
+          rscale[sj] = rstd; rshift[sj] = rstd * (mean - rcen[sj]);
+          rcen[sj] = mean;                                          // what the next norm's vector is published around
+        }
+      }
+      __syncthreads();                                              // every wavefront's partial products are in LDS
+      bstamp(a, layer, ph, 4);
+      // ---- epilogue: one thread per (block, message, row pair or quad)
+      for (int e = tid; e < n_items; e += kStepThreads) {
+        const Item it = item_at(e);
+        const int j = it.j, p = it.p, lb = it.lb, r0 = it.r0, r1 = it.r1;
+        if (quads) {
+          // rows (4q .. 4q + 3) = (gate_f, up_f, gate_f+1, up_f+1): one lane of every wavefront's result holds all four
+          if (r0 >= N) continue;
+          const float* pp = part + ((lb * kStepWaves) << 8) + (((p << 4) + j) << 2);
+          f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int w = 0; w < kStepWaves; ++w) { const f32x4 t = *reinterpret_cast<const f32x4*>(pp + (w << 8)); v += t; }
+          v *= rscale[j];
+          if constexpr (kLn) {
+            const MDI_GLOBAL float* nc = (const MDI_GLOBAL float*)ncp;
+            const float sh = rshift[j];
+            v.x += nc[N + r0] - sh * nc[r0]; v.y += nc[N + r0 + 1] - sh * nc[r0 + 1];
+            v.z += nc[N + r0 + 2] - sh * nc[r0 + 2]; v.w += nc[N + r0 + 3] - sh * nc[r0 + 3];
+          }
+          st_pair(a.ub + vec_word(r0 >> 2, j, m), pack_bf16x2(silu_f(v.x) * v.y, silu_f(v.z) * v.w), wtag);
+          continue;
+        }
+        if (up && r0 >= N) continue;
+        if (e != tid) ops = ops_of(it, r1 < N);
+        float v0 = part_sum(part, lb, up ? 2 * p : p, j) * rscale[j], v1 = part_sum(part, lb, up ? 2 * p + 1 : p + half, j) * rscale[j];
+        if constexpr (kLn) { v0 += ops.n[2] - rshift[j] * ops.n[0]; v1 += ops.n[3] - rshift[j] * ops.n[1]; }
+        v0 += ops.b0; v1 += ops.b1;
+        if (up) {
+          const bool tanh_form = a.mlp_kind == MDI_MLP_GELU_TANH;
+          st_pair(a.ub + vec_word(r0 >> 1, j, m), pack_bf16x2(tanh_form ? gelu_tanh_f(v0) : gelu_erf_f(v0), tanh_form ? gelu_tanh_f(v1) : gelu_erf_f(v1)), wtag);
+          continue;
+        }
+        const int head = r0 >> (hh_sh + 1), i = r0 & ((2 << hh_sh) - 1);
+        if (a.rope && head < a.H + a.K) {
+          const float t0 = v0 * ops.c - v1 * ops.s, t1 = v0 * ops.s + v1 * ops.c;
+          v0 = t0; v1 = t1;
+        }
+        char* base = a.slot0 + (long)j * a.slot_stride;
+        if (head < a.H) {
+          tagged_t* q = (tagged_t*)(base + a.off_q);
+          st_tag(q + r0, v0, wtag); st_tag(q + r1, v1, wtag);
+        } else {
+          // the cache row is for later launches (plain stores); this launch's attention takes the same
+          // rounded values from the tagged copy
+          const bool is_v = head >= a.H + a.K;
+          const int kvh = head - a.H - (is_v ? a.K : 0);
+          MDI_GLOBAL WT* dst = (MDI_GLOBAL WT*)((char*)a.l0.kv + kv_off) + sl.kv_off[j] + (long)(kvh * 2 + (is_v ? 1 : 0)) * a.pt_h + i;
+          dst[0] = f32_to_bf16(v0); dst[1 << hh_sh] = f32_to_bf16(v1);
+          tagged_t* kn = (tagged_t*)(base + a.off_knew) + (is_v ? a.K * a.h : 0) + kvh * a.h + i;
+          st_tag(kn, bf16_to_f32(f32_to_bf16(v0)), wtag); st_tag(kn + (1 << hh_sh), bf16_to_f32(f32_to_bf16(v1)), wtag);
+        }
+      }
+      // ---- the partial products in LDS have been read
       bstamp(a, layer, ph, 5);
       __syncthreads();
       bstamp(a, layer, ph, 6);
-      if (s_flag[kFailed]) return;                                   // a bounded wait expired: everybody else's will, too
-    }
+      epoch = wtag;
+      return !s_flag[kFailed];                                      // a bounded wait expired: everybody else's will, too
+    };
+
+    // ---- attention: one work item = (message, head group, context split); items dealt round-robin
+    auto attention = [&]() __attribute__((always_inline)) -> bool {
+      constexpr int ph = PH_ATTN;
+      const BatchArgs& a = args_again<BatchArgs>();
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int lane = tid & 63;
+      const void* kv = (const char*)a.l0.kv + kv_off;
+      bstamp(a, layer, ph, 0);
+      for (int item = wg; item < a.n_items; item += nwg) {
+        if (item != wg) __syncthreads();                            // the records in LDS have been read
+        const int slot = __popcll(__ballot(lane < m && item >= sl.item_lo[min(lane, m - 1)])) - 1;
+        const BatchView V = view_of(a, slot, a.ob);
+        const AttnGeo ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
+        AttnState<WT, G> st;
+        AttnAsk<WT> ask;
+        Tile A, B;
+        attn_ask<WT, G>(ask, ga, a, V, wave, tid);
+        if constexpr (kScoresOnMfma) {
+          Attn4 s4;
+          s4.n_t = max(ga.s1p - ga.s0 + 15, 0) >> 4;
+          int pgA = attn4_page(ga, s4, V, 0, wave), pgB = attn4_page(ga, s4, V, 1, wave);
+          attn4_issue(A, pgA, ga, s4, a, V, kv, 0, wave, lane); attn4_issue(B, pgB, ga, s4, a, V, kv, 1, wave, lane);
+          if (item == wg) bstamp(a, layer, ph, 1);
+          attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
+          if (item == wg) bstamp(a, layer, ph, 2);
+          attn4_stream(s4, st, A, B, pgA, pgB, ga, a, V, kv, wave, lane, part);
+        } else {
+          int pgA[kTile], pgB[kTile];
+          attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
+          attn_issue<WT>(A, pgA, ga, a, V, kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, kv, 1, wave);
+          if (item == wg) bstamp(a, layer, ph, 1);
+          attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
+          if (item == wg) bstamp(a, layer, ph, 2);
+          const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
+          attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, kv, nte, wave, part);
+        }
+        if (item == wg) bstamp(a, layer, ph, 3);
+        attn_to_lds<WT, G>(st, ga, a.h, part, wave);
+        attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
+      }
+      // ---- the records in LDS have been read
+      bstamp(a, layer, ph, 5);
+      __syncthreads();
+      bstamp(a, layer, ph, 6);
+      ++epoch;
+      return !s_flag[kFailed];
+    };
+
+    // ---- a product whose inner dimension is split among workgroups.  Every workgroup used to read the whole
+    // vector of all messages for its one block of rows: 256 copies of it through the dies' L2s, twice the bytes of
+    // the matrix itself in the MLP down projection.  Here workgroup (q, s) takes column slice s of the eight row
+    // blocks 8 q .. 8 q + 7, one block per wavefront: it reads 1 / S of the vector - once, validated, into LDS, from
+    // where its eight wavefronts take the matrix instruction's second operand - and hands the 16 x 16 partial result
+    // of every block, as tagged words, to the workgroup that owns the block's residual rows, which adds the S partials
+    // in slice order.
+    auto split = [&](auto ph_const) __attribute__((always_inline)) -> bool {
+      constexpr int ph = decltype(ph_const)::value;
+      constexpr bool down = ph == PH_DOWN;
+      const BatchArgs& a = args_again<BatchArgs>();
+      const BatchProduct& P = a.pr[down ? 3 : 1];
+      const unsigned wtag = epoch + 1;
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int lane = tid & 63, kg = lane >> 4, n = lane & 15;
+      bstamp(a, layer, ph, 0);
+      const int rb = P.row_bytes, S = a.str_S, c = a.str_c[down ? 1 : 0], nblk = (a.d + 15) >> 4;
+      const int ktot = rb >> 6, k0 = min(ks_s * c, ktot), nk = ks_q < a.str_oct ? max(0, min(c, ktot - ks_s * c)) : 0;   // column steps of the slice
+      const int blk = ks_q * kStepWaves + wave;                     // this wavefront's block
+      const bool has = ks_q < a.str_oct && blk < nblk, live = has && nk > 0;
+      // the slice of every message's vector to LDS; unit: eight columns of one message
+      const Buffer vb = buffer_at(down ? a.ub : a.ob);
+      const int n_units = nk * 4 * m;
+      const uint32_t v_base = (uint32_t)k0 * (uint32_t)m * 128u;
+      u32x4 raw[2][4];
+      auto ask = [&](u32x4 (&r)[4], int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint32_t o = fresh(u + k * kStepThreads < n_units ? (uint32_t)(u + k * kStepThreads) * 32u : kNowhere);
+          r[2 * k] = ld_two(vb, o, v_base); r[2 * k + 1] = ld_two(vb, o + 16, v_base);
+        }
+      };
+      ask(raw[0], tid);
+      if (n_units > 2 * kStepThreads) ask(raw[1], tid + 2 * kStepThreads);
+      // the rows this workgroup owns: what their epilogue needs
+      const int j = tid >> 3, p = tid & 7, r0 = wg * 16 + 2 * p;
+      const bool mine = j < m && r0 < a.d, last = down && layer == a.n_layer - 1;
+      const uint32_t o0 = mine ? (uint32_t)r0 * 4u : kNowhere;
+      const Buffer biasb = buffer_at(P.bias ? (const char*)P.bias + w_off : nullptr);
+      const Buffer gainb = buffer_at(last ? nullptr : down ? (const char*)a.l0.ln1_g + w_off + a.w_stride : (const char*)a.l0.ln2_g + w_off);
+      auto two_at = [&](Buffer b) __attribute__((always_inline)) { return __builtin_amdgcn_raw_buffer_load_b64(b, (int)o0, 0, 0); };
+      const u32x2 bias = two_at(biasb), gain = two_at(gainb);
+      // weights
+      Tile A, B;
+      const Buffer wb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.W + w_off), 0, (int)P.bytes, 0x00020000);
+      const uint32_t w_lane = (uint32_t)(n * rb + (kg << 4)), w_base = (uint32_t)(blk * 16 * rb + k0 * 64);
+      auto issue = [&](Tile& t, int ti) __attribute__((always_inline)) { w_issue(t, wb, w_lane, w_base + ti * 512, nk - ti * 8, live && ti * 8 < nk); };
+      issue(A, 0);
+      issue(B, 1);
+      bstamp(a, layer, ph, 1);
+      char* Bs = reinterpret_cast<char*>(part);
+      auto stage = [&](u32x4 (&r)[4], int u) __attribute__((always_inline)) {
+        // (pieces past the last unit are zeros: only a thread with none of a piece may skip its counter)
+        const bool l0 = u < n_units, l1 = u + kStepThreads < n_units;
+        poll_while([&]() {
+          const uint32_t bad0 = (r[0].y ^ epoch) | (r[0].w ^ epoch) | (r[1].y ^ epoch) | (r[1].w ^ epoch);
+          const uint32_t bad1 = (r[2].y ^ epoch) | (r[2].w ^ epoch) | (r[3].y ^ epoch) | (r[3].w ^ epoch);
+          return (l0 && bad0 != 0) || (l1 && bad1 != 0);
+        }, [&]() { ask(r, u); }, a.spin_limit, a.err);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const int uk = u + k * kStepThreads, gi = (int)__umulhi((unsigned)uk, a.m_magic), nm = uk - gi * m;
+          if (uk < n_units) *reinterpret_cast<u32x4*>(Bs + gi * 256 + ((nm ^ (gi & 15)) << 4)) = u32x4{r[2 * k].x, r[2 * k].z, r[2 * k + 1].x, r[2 * k + 1].z};
+        }
+      };
+      if (n_units <= 2 * kStepThreads) {
+        stage(raw[0], tid);
+      } else {
+        for (int u = tid; u < n_units; u += 4 * kStepThreads) {
+          stage(raw[0], u);
+          ask(raw[0], u + 4 * kStepThreads);
+          stage(raw[1], u + 2 * kStepThreads);
+          ask(raw[1], u + 6 * kStepThreads);
+        }
+      }
+      __syncthreads();
+      bstamp(a, layer, ph, 2);
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      if (live) {                                                   // uniform per wavefront
+        uint32_t vl[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) { const int gi = s * 4 + kg; vl[s] = (uint32_t)(gi * 256 + ((n ^ gi) << 4)); }
+        const char* bs = Bs;
+        const int nt = (nk + 7) >> 3;
+        int t = 0;
+#pragma nounroll
+        for (; t + 2 < nt; t += 2) {
+          ks_compute(A, bs, vl, 8, acc);
+          issue(A, t + 2);
+          ks_compute(B, bs + 8192, vl, 8, acc);
+          issue(B, t + 3);
+          bs += 16384;
+        }
+        ks_compute(A, bs, vl, nk - t * 8, acc);
+        ks_compute(B, bs + 8192, vl, nk - t * 8 - 8, acc);
+      }
+      bstamp(a, layer, ph, 3);
+      // the partial of (block, slice), zeros from a slice without columns, to the block's owner
+      const Buffer pb = buffer_at(a.ppart);
+      {
+        const uint32_t o = has && n < m ? (uint32_t)(kg * m + n) * 32u : kNowhere, u = has ? (uint32_t)((blk * S + ks_s) * m) * 128u : 0u;
+        st_two(pb, o, u, acc[0], acc[1], wtag); st_two(pb, o + 16, u, acc[2], acc[3], wtag);
+      }
+      bstamp(a, layer, ph, 7);
+      // ---- residual products: x += W v (+ bias) on the 16 rows this workgroup owns; what leaves is x times the gain
+      // of the norm that follows, as bf16 pairs, and this workgroup's share of every message's sum of squares (every
+      // workgroup's, also without rows: see the top of the file).  One lane per (message, row pair), which adds the S
+      // partials in slice order.
+      if (j < m) {
+        float s2 = 0.f, s1 = 0.f;
+        if (wg < nblk) {
+          const uint32_t off = (uint32_t)((p >> 1) * m + j) * 32u + (uint32_t)(p & 1) * 16u;
+          float d0 = 0.f, d1 = 0.f;
+          for (int k0s = 0; k0s < S; k0s += 8) {
+            u32x4 r[8];                                             // slices past the last repeat it
+            auto ask_parts = [&]() __attribute__((always_inline)) {
+              const uint32_t o = fresh(off);
+#pragma unroll
+              for (int k = 0; k < 8; ++k) r[k] = ld_two(pb, o, (uint32_t)((wg * S + min(k0s + k, S - 1)) * m) * 128u);
+            };
+            ask_parts();
+            await_two(r, ask_parts, true, wtag, a.spin_limit, a.err);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) { d0 += k0s + k < S ? __uint_as_float(r[k].x) : 0.f; d1 += k0s + k < S ? __uint_as_float(r[k].z) : 0.f; }
+          }
+          if (mine) {
+            float* xr = xres + 2 * p * 16 + j;
+            const float x0 = xr[0] + d0 + __uint_as_float(bias.x), x1 = xr[16] + d1 + __uint_as_float(bias.y);
+            xr[0] = x0; xr[16] = x1;
+            if (last) {
+              MDI_GLOBAL bf16_t* y = (MDI_GLOBAL bf16_t*)sl.out[j] + r0;
+              y[0] = f32_to_bf16(x0); y[1] = f32_to_bf16(x1);
+            } else {
+              st_pair((down ? a.xn[0] : a.xn[1]) + vec_word(r0 >> 1, j, m),
+                      pack_bf16x2((x0 - rcen[j]) * __uint_as_float(gain.x), (x1 - rcen[j]) * __uint_as_float(gain.y)), wtag);
+              s2 = x0 * x0 + x1 * x1; s1 = x0 + x1;
+            }
+          }
+        }
+        if (!last) {
+          publish_sum(s2, p, (down ? a.ssq[0] : a.ssq[1]) + j * a.sq_stride, wg, nwg, a.sq_stride, wtag);
+          if constexpr (kLn) publish_sum(s1, p, (down ? a.ssum[0] : a.ssum[1]) + j * a.sq_stride, wg, nwg, a.sq_stride, wtag);
+        }
+      }
+      // ---- the vector's slice in LDS has been read
+      bstamp(a, layer, ph, 5);
+      __syncthreads();
+      bstamp(a, layer, ph, 6);
+      epoch = wtag;
+      return !s_flag[kFailed];
+    };
+
+    if (!normed(std::integral_constant<int, PH_QKV>())) return;
+    if (!attention()) return;
+    if (!split(std::integral_constant<int, PH_OPROJ>())) return;
+    if (!normed(std::integral_constant<int, PH_UP>())) return;
+    if (!split(std::integral_constant<int, PH_DOWN>())) return;
+    w_off += a0.w_stride; kv_off += a0.kv_stride;
   }
 }
 
 }  // namespace step_w8
 
-bool step_batch_allow_lds(size_t lds) {
-  using namespace step_w8;
-  const void* const kernels[] = {(const void*)k_step_batch<1, false>, (const void*)k_step_batch<2, false>, (const void*)k_step_batch<4, false>,
-                                 (const void*)k_step_batch<4, true>};
-  for (const void* k : kernels)
-    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return false;
-  return true;
+namespace step_w8 {
+template <bool kLn, bool kSwiglu> const void* step_batch_kernel(int G, bool scores_on_mfma) {
+  if (G == 4) return scores_on_mfma ? (const void*)k_step_batch<4, true, kLn, kSwiglu> : (const void*)k_step_batch<4, false, kLn, kSwiglu>;
+  return G == 2 ? (const void*)k_step_batch<2, false, kLn, kSwiglu> : (const void*)k_step_batch<1, false, kLn, kSwiglu>;
 }
+}  // namespace step_w8
 
-void launch_step_batch(hipStream_t s, int G, bool scores_on_mfma, size_t lds, const BatchArgs& a) {
-  using namespace step_w8;
-  const dim3 grid(a.nwg), block(kStepThreads);
-  if (G == 4 && scores_on_mfma) hipLaunchKernelGGL((k_step_batch<4, true>), grid, block, lds, s, a);
-  else if (G == 4) hipLaunchKernelGGL((k_step_batch<4, false>), grid, block, lds, s, a);
-  else if (G == 2) hipLaunchKernelGGL((k_step_batch<2, false>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((k_step_batch<1, false>), grid, block, lds, s, a);
+// The kernel of a norm: G query heads per attention work item, their scores on the matrix cores (G = 4) or not, MLP kind.
+template <> const void* step_batch_kernel<MDI_BATCH_LN>(int G, bool scores_on_mfma, bool swiglu) {
+  return swiglu ? step_w8::step_batch_kernel<MDI_BATCH_LN, true>(G, scores_on_mfma) : step_w8::step_batch_kernel<MDI_BATCH_LN, false>(G, scores_on_mfma);
 }
 
 }  // namespace mdi

@@ -1,63 +1,15 @@
-// Decode steps of a whole partition as ONE persistent kernel launch.
-//
-// A later visit of a sample (Sec. III-D) pushes a single position through every
-// local layer; each layer is five dependent matrix-vector / attention phases whose
-// inputs are full vectors produced by the previous phase.  Launching them as
-// separate kernels leaves the memory system idle at every boundary (drain, launch,
-// ramp-up).  Here workgroups stay resident for the whole launch - one of eight
-// wavefronts per compute unit for a launch that carries one message, two of four
-// wavefronts for a launch that carries the queued messages of several samples
-// (Sec. III-A: the input queue; Sec. III-C: several samples in flight).  In the
-// latter a set of workgroups takes its messages in turn inside every phase and
-// two sets share each compute unit, so that the serial part of one message's
-// phase boundary (vector staging, cross-wavefront sums, epilogue) runs
-// under other messages' weight streams; every message still makes its own pass
-// over the weights.
-//
-//   * there is no grid-wide barrier.  Everything that crosses workgroups (x, q, o, u, attention partials, the newest K/V
-//     row) is written and read with cache-coherent (sc1, agent scope) stores and loads, each value with the counter of
-//     the phase that wrote it in the same 8-byte word, and readers reload until the counter is the expected one.
-//     Nothing is overwritten that is still being read, because every phase needs all of the one before: who stores x in
-//     the output projection has read all of o, so every head's attention is done, so every workgroup with QKV rows has
-//     stored them, after it read x; who stores x in the down projection has read all of u, so all have read x for it;
-//     and q, u, o are written a layer after they were read.  (A workgroup without rows in a product does not read its
-//     vector.)  Phase counters watched before the data cost 3.2 us a phase; the data alone take 1.65 us from store to
-//     store (2048 words, 256 workgroups), and for the longest vectors too, waiting for the counters first was slower
-//     (7B shape, one message: 795 against 757 us).  What is left of the counters paces the two sets of workgroups.
-//   * weight and KV-cache addresses do not depend on activations, so every
-//     wavefront keeps two register tiles of 16-byte loads in flight and issues the
-//     first two of a phase before the phase's vector is there - but after it has
-//     asked for that vector's first words, which loads return in order.
-//   * the rows a workgroup owns in a phase form one flat sequence of (row pair,
-//     1-KiB chunk) items dealt round-robin to its wavefronts.  At any moment the
-//     workgroup therefore reads consecutive KiB of a row pair (DRAM sees a few
-//     wide sequential streams instead of thousands of narrow ones), and the
-//     wavefronts stay balanced whatever the shape.  A wavefront's share of a pair
-//     goes to an LDS slot of its own; slots are summed in wavefront order
-//     (deterministic, no float atomics; the order depends on the number of
-//     wavefronts, which is why launches of one and of several messages may differ
-//     in the last bits).
-//   * in a launch with two sets of workgroups, each workgroup compares once per
-//     phase the work it has left with that of the other set and takes the higher
-//     wave priority when it has more: left alone, the set that was dispatched
-//     first is served first by a compute unit's memory pipeline and finishes a
-//     fifth earlier.
-//
-// Every spin is bounded: a wait of more than `spin_limit` polls raises the
-// partition's error word, the other waits of that workgroup end with it, and the
-// workgroup leaves at the end of the phase at the latest.  What it stored in that phase is
-// worthless (the error word says so); everybody who needs its words later
-// expires in the same way.
-//
-// This file is the kernel's body; step_w4.hip and step_w8.hip compile it for workgroups of four and of
-// eight wavefronts (MDI_STEP_WAVES), each in a namespace of its own with a launcher of its own.
+// What the persistent decode kernels (step_kernel.h, step_batch.h) and the streaming output layers (head_one.h,
+// head_batch.h) share: the exchange between workgroups, requests, staging, the geometry and the streaming loop of a
+// matrix-vector product, attention over the cache pages.  Compiled for workgroups of MDI_STEP_WAVES wavefronts, in a
+// namespace of its own for each.
+#pragma once
 #include <type_traits>
 
 #include "bounded_wait.h"
 #include "device_utils.h"
 
 #ifndef MDI_STEP_WAVES
-#error "include from step_w4.hip / step_w8.hip, which define MDI_STEP_WAVES"
+#error "MDI_STEP_WAVES: wavefronts per workgroup"
 #endif
 #define MDI_STEP_CAT2(a, b) a##b
 #define MDI_STEP_CAT(a, b) MDI_STEP_CAT2(a, b)
@@ -65,43 +17,52 @@
 namespace mdi {
 namespace MDI_STEP_CAT(step_w, MDI_STEP_WAVES) {
 
+#define MDI_GLOBAL __attribute__((address_space(1)))
+
 constexpr int kStepWaves = MDI_STEP_WAVES;       // wavefronts per workgroup
 constexpr int kStepThreads = 64 * kStepWaves;
 
-#define MDI_GLOBAL __attribute__((address_space(1)))
 
 constexpr int kTile = 4;                 // items per register tile (two 16-byte loads each)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 struct Tile { u32x4 r[2 * kTile]; };
 
 // Tagged exchange.  A store is acknowledged before every compute die can read it back, so a flag raised after it
 // proves nothing to a reader; the data validates itself: value and the writing phase's counter travel in one 8-byte
 // store, and a reader that finds another counter simply loads again.  No ordering between stores is needed.
 __device__ __forceinline__ void st_tag(tagged_t* p, float v, unsigned tag) {
-  __hip_atomic_store(p, ((tagged_t)tag << 32) | (tagged_t)__float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store((MDI_GLOBAL tagged_t*)p, ((tagged_t)tag << 32) | (tagged_t)__float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ tagged_t ld_raw(const tagged_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ tagged_t ld_raw(const tagged_t* p) { return __hip_atomic_load((const MDI_GLOBAL tagged_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float tag_value(tagged_t u) { return __uint_as_float((uint32_t)u); }
 // A wait that expires raises the partition's error word and its workgroup's failure flag (an index in lds_flag()); the
 // other waits of the workgroup then end at their next look at the flag.
 constexpr int kFailed = 2;
 __device__ __forceinline__ int* lds_flag() { extern __shared__ float smem[]; return (int*)(smem + 16); }
+// (The same for all lanes of the wavefront that are active: its loops have no lanes to keep apart.)
 __device__ __forceinline__ bool poll_again(int& polls, int spin_limit, int* err) {
   return may_poll_again(
-      polls, spin_limit, [&]() { return __hip_atomic_load(lds_flag() + kFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0; },
+      polls, spin_limit, [&]() { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(lds_flag() + kFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0; },
       [&]() {
         __hip_atomic_store(lds_flag() + kFailed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store((MDI_GLOBAL int*)err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       });
+}
+// Asks again while any lane of the wavefront misses something: bad() says whether this one does.  A loop that lanes leave
+// one by one keeps a copy of every word asked for, and moves all of them in every round.
+template <typename BAD, typename ASK>
+__device__ __forceinline__ void poll_while(const BAD& bad, const ASK& ask, int spin_limit, int* err) {
+  int it = 0;
+  while (__ballot(bad()) != 0) {
+    if (!poll_again(it, spin_limit, err)) break;
+    __builtin_amdgcn_s_sleep(1);
+    ask();
+  }
 }
 // Returns the value once its tag is `tag`, or whatever is there when the wait ends otherwise.
 __device__ __forceinline__ float settle(const tagged_t* p, tagged_t u, unsigned tag, int spin_limit, int* err) {
-  int it = 0;
-  while ((uint32_t)(u >> 32) != tag) {
-    if (!poll_again(it, spin_limit, err)) break;
-    __builtin_amdgcn_s_sleep(1);
-    u = ld_raw(p);
-  }
+  poll_while([&]() { return (uint32_t)(u >> 32) != tag; }, [&]() { u = ld_raw(p); }, spin_limit, err);
   return tag_value(u);
 }
 
@@ -120,6 +81,37 @@ template <> struct Unpack<bf16_t> {
   }
 };
 
+// Loads through buffer descriptors.  An offset of kNowhere, or a descriptor of nothing, reads as zero and touches no
+// memory, so a lane without a word, or an absent bias, needs no branch around its load (which would merge the loaded
+// register with another value, and where the compiler copies to do so it waits for the load there and then), and an
+// address costs one register and an immediate instead of two additions.
+typedef __amdgpu_buffer_rsrc_t Buffer;
+constexpr uint32_t kNowhere = 0x80000000u;
+__device__ __forceinline__ Buffer buffer_at(const void* p) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, p ? 0x7FFFFFFF : 0, 0x00020000); }
+__device__ __forceinline__ float ld_f32(Buffer b, uint32_t off) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0)); }
+constexpr int kAgentScope = 0x10;        // the sc1 bit: the load is answered by what all dies see
+__device__ __forceinline__ tagged_t ld_word(Buffer b, uint32_t off) {
+  return __builtin_bit_cast(tagged_t, __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, kAgentScope));
+}
+
+// The kernel's arguments, as if read for the first time: a phase loads what it needs of them when it starts, instead of
+// keeping everything that some phase needs in scalar registers (of which there are not nearly enough) all the time.
+template <typename AR>
+__device__ __forceinline__ const AR& args_again() {
+  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const AR*)(const __attribute__((address_space(4))) AR*)p;
+}
+// Two exchanged words as one 16-byte piece.  Each of them carries its own counter, so only 8 bytes need to be seen whole.
+__device__ __forceinline__ u32x4 ld_two(Buffer b, uint32_t off, uint32_t uniform) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, (int)uniform, kAgentScope));
+}
+__device__ __forceinline__ void st_two(Buffer b, uint32_t off, uint32_t uniform, float v0, float v1, unsigned tag) {
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(v0), tag, __float_as_uint(v1), tag}, b, (int)off, (int)uniform, kAgentScope);
+}
+// An offset that the compiler takes for a new one, so that a poll's loads are not taken for those of the one before.
+__device__ __forceinline__ uint32_t fresh(uint32_t off) { asm volatile("" : "+v"(off)); return off; }
+
 enum StepPhase { PH_QKV = 0, PH_ATTN = 1, PH_OPROJ = 2, PH_UP = 3, PH_DOWN = 4 };
 
 // optional timeline for profiling: thread 0 of every workgroup records a 100 MHz timestamp
@@ -129,7 +121,7 @@ __device__ __forceinline__ void stamp(const StepArgs& a, const StepSlot& S, int 
 }
 
 
-// LDS map (floats): [0,16) reduction scratch, [16,20) flags, [20,56) phase geometry,
+// LDS map (floats): [0,16) reduction scratch, [16,20) flags,
 // [128, 128+part_floats) pair partials, then the vector.
 constexpr int kLdsPart = 128;
 __device__ __forceinline__ float* lds_red() { extern __shared__ float smem[]; return smem; }
@@ -139,39 +131,30 @@ __device__ __forceinline__ float* lds_vec(int part_floats) { extern __shared__ f
 // N words at once, asked for again until all of a thread's carry the counter `tag`: one round trip however many were
 // early (word by word, eight early words cost eight).  Asked for before a phase's weights, awaited after: loads return
 // in order, and the workgroup that everybody waits for finds its words there.
-// at(i, z): the address of word i; z is zero, and unknown to the compiler, so that addresses are not kept in registers
-// over the loop.
-__device__ __forceinline__ const MDI_GLOBAL tagged_t* word_at(const tagged_t* base, uint32_t bytes) {
-  return (const MDI_GLOBAL tagged_t*)((const MDI_GLOBAL char*)base + bytes);
-}
-__device__ __forceinline__ tagged_t ld_word(const MDI_GLOBAL tagged_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// live(i): whether this thread wants word i at all; the others count as seen (asking for some word again in their
-// place would have every workgroup hammer one line of memory).
+// at(i, z): byte offset of word i; z is zero, and unknown to the compiler, so that the loads of one poll are not taken for
+// those of the one before.  live(i): whether this thread wants word i at all; the others count as seen (asking for some
+// word again in their place would have every workgroup hammer one line of memory).
 struct AllLive { __device__ __forceinline__ bool operator()(int) const { return true; } };
 template <int N, typename AT, typename LT = AllLive>
-__device__ __forceinline__ void ask_words(tagged_t (&raw)[N], const AT& at, unsigned tag, const LT& live = LT()) {
+__device__ __forceinline__ void ask_words(tagged_t (&raw)[N], Buffer b, const AT& at, const LT& live = LT()) {
   uint32_t z = 0u;
   asm volatile("" : "+v"(z));
 #pragma unroll
-  for (int i = 0; i < N; ++i) raw[i] = live(i) ? ld_word(at(i, z)) : (tagged_t)tag << 32;
+  for (int i = 0; i < N; ++i) raw[i] = ld_word(b, live(i) ? at(i, z) : kNowhere);
 }
 template <int N, typename AT, typename LT = AllLive>
-__device__ __forceinline__ void await_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
-  int it = 0;
-  while (true) {
-    bool bad = false;
+__device__ __forceinline__ void await_words(tagged_t (&raw)[N], Buffer b, const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
+  poll_while([&]() {
+    uint32_t bad = 0;
 #pragma unroll
-    for (int i = 0; i < N; ++i) bad |= (uint32_t)(raw[i] >> 32) != tag;
-    if (!bad) break;
-    if (!poll_again(it, spin_limit, err)) break;
-    __builtin_amdgcn_s_sleep(1);
-    ask_words(raw, at, tag, live);
-  }
+    for (int i = 0; i < N; ++i) bad |= live(i) ? (uint32_t)(raw[i] >> 32) ^ tag : 0u;
+    return bad != 0;
+  }, [&]() { ask_words(raw, b, at, live); }, spin_limit, err);
 }
 template <int N, typename AT, typename LT = AllLive>
-__device__ __forceinline__ void poll_words(tagged_t (&raw)[N], const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
-  ask_words(raw, at, tag, live);
-  await_words(raw, at, tag, spin_limit, err, live);
+__device__ __forceinline__ void poll_words(tagged_t (&raw)[N], Buffer b, const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
+  ask_words(raw, b, at, live);
+  await_words(raw, b, at, tag, spin_limit, err, live);
 }
 
 // ---------------------------------------------------------------------------
@@ -179,29 +162,38 @@ __device__ __forceinline__ void poll_words(tagged_t (&raw)[N], const AT& at, uns
 // With gain != nullptr (RMSNorm) the staged values are x[i] * gain[i] and the return value is this thread's share of
 // sum(x^2); the common factor 1/rms is applied to the finished dot products.  Otherwise the values are staged as they
 // are and the return value is this thread's share of their sum.
-// The first eight values per thread (and their gains) have been requested before (`raw`, `gv`).
-struct VecAsk { tagged_t raw[8]; float gain[8]; };
-__device__ __forceinline__ void vec_ask(VecAsk& v, const tagged_t* src, int n, const float* gain, unsigned tag, int i0) {
-  ask_words(v.raw, [&](int j, uint32_t z) { return word_at(src, (uint32_t)(i0 + j * kStepThreads) * 8u + z); }, tag,
-            [&](int j) { return i0 + j * kStepThreads < n; });
+// A thread takes pairs tid, tid + threads, ...; its first four (and their gains) have been requested before.
+struct VecAsk { u32x4 raw[4]; u32x2 gain[4]; };
+__device__ __forceinline__ void vec_words(VecAsk& v, const tagged_t* src, int n, int q0) {
+  const Buffer b = buffer_at(src);
+  const uint32_t o = fresh((uint32_t)q0 * 16u);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) v.gain[j] = gain && i0 + j * kStepThreads < n ? gain[i0 + j * kStepThreads] : 1.f;
+  for (int j = 0; j < 4; ++j) v.raw[j] = ld_two(b, 2 * (q0 + j * kStepThreads) < n ? o + (uint32_t)(j * kStepThreads) * 16u : kNowhere, 0);
 }
-__device__ __forceinline__ float stage_coherent(VecAsk& v, const tagged_t* src, int n, float* xs, const float* gain, bool rms, unsigned tag,
-                                                int spin_limit, int* err, int tid) {
-  float ss = 0.f;
-  for (int i0 = tid; i0 < n; i0 += 8 * kStepThreads) {
-    if (i0 != tid) vec_ask(v, src, n, gain, tag, i0);
-    await_words(v.raw, [&](int j, uint32_t z) { return word_at(src, (uint32_t)(i0 + j * kStepThreads) * 8u + z); }, tag, spin_limit, err,
-                [&](int j) { return i0 + j * kStepThreads < n; });
+__device__ __forceinline__ void vec_ask(VecAsk& v, const tagged_t* src, int n, const float* gain, int q0) {
+  vec_words(v, src, n, q0);
+  const Buffer gb = buffer_at(gain);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int i = i0 + j * kStepThreads;
-      if (i < n) {
-        const float x = tag_value(v.raw[j]);
-        ss += rms ? x * x : x;
-        xs[i] = rms ? x * v.gain[j] : x;
-      }
+  for (int j = 0; j < 4; ++j)
+    v.gain[j] = __builtin_amdgcn_raw_buffer_load_b64(gb, 2 * (q0 + j * kStepThreads) < n ? (q0 + j * kStepThreads) * 8 : (int)kNowhere, 0, 0);
+}
+template <bool kRms>
+__device__ __forceinline__ float stage_coherent(VecAsk& v, const tagged_t* src, int n, float* xs, const float* gain, unsigned tag, int spin_limit, int* err, int tid) {
+  float ss = 0.f;
+  for (int q0 = tid; 2 * q0 < n; q0 += 4 * kStepThreads) {
+    if (q0 != tid) vec_ask(v, src, n, kRms ? gain : nullptr, q0);
+    poll_while([&]() {
+      uint32_t bad = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bad |= 2 * (q0 + j * kStepThreads) < n ? (v.raw[j].y ^ tag) | (v.raw[j].w ^ tag) : 0u;
+      return bad != 0;
+    }, [&]() { vec_words(v, src, n, q0); }, spin_limit, err);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = q0 + j * kStepThreads;
+      const float x0 = __uint_as_float(v.raw[j].x), x1 = __uint_as_float(v.raw[j].z);   // (zeros past the end)
+      ss += kRms ? x0 * x0 : x0; ss += kRms ? x1 * x1 : x1;
+      if (2 * q < n) *reinterpret_cast<float2*>(xs + 2 * q) = kRms ? float2{x0 * __uint_as_float(v.gain[j].x), x1 * __uint_as_float(v.gain[j].y)} : float2{x0, x1};
     }
   }
   return ss;
@@ -219,24 +211,28 @@ __device__ __forceinline__ float step_sum(float v, float* red, int tid) {
   return t;
 }
 
-// LayerNorm of the staged vector, each thread on the elements it staged itself; s = its share of their sum.
-__device__ __forceinline__ void layer_norm(float* xs, int n, float s, float eps, const float* g, const float* b, float* red, int tid) {
-  float gv[2], bv[2];                                  // the first gains and biases are on their way during the sums
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = tid + k * kStepThreads;
-    gv[k] = i < n ? g[i] : 0.f; bv[k] = b && i < n ? b[i] : 0.f;
-  }
+// LayerNorm of the staged vector, each thread on the pairs it staged itself; s = its share of their sum.
+__device__ __forceinline__ void layer_norm(float* xs, int n, float s, float eps, Buffer g, Buffer b, float* red, int tid) {
+  auto two = [&](Buffer p, int q) __attribute__((always_inline)) {
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(p, 2 * q < n ? q * 8 : (int)kNowhere, 0, 0);
+    return float2{__uint_as_float(v.x), __uint_as_float(v.y)};
+  };
+  auto apply = [&](int q, const float2& gv, const float2& bv, float mean, float rstd) __attribute__((always_inline)) {
+    if (2 * q >= n) return;
+    float2* p = reinterpret_cast<float2*>(xs) + q;
+    const float2 x = *p;
+    *p = float2{(x.x - mean) * rstd * gv.x + bv.x, (x.y - mean) * rstd * gv.y + bv.y};
+  };
+  const float2 g0 = two(g, tid), b0 = two(b, tid);      // the first gains and biases are on their way during the sums
   const float mean = step_sum(s, red, tid) / (float)n;
   float s2 = 0.f;
-  for (int i = tid; i < n; i += kStepThreads) { const float c = xs[i] - mean; s2 += c * c; }
-  const float rstd = 1.f / sqrtf(step_sum(s2, red + kStepWaves, tid) / (float)n + eps);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = tid + k * kStepThreads;
-    if (i < n) xs[i] = (xs[i] - mean) * rstd * gv[k] + bv[k];
+  for (int q = tid; 2 * q < n; q += kStepThreads) {
+    const float2 x = reinterpret_cast<const float2*>(xs)[q];
+    s2 += (x.x - mean) * (x.x - mean); s2 += (x.y - mean) * (x.y - mean);
   }
-  for (int i = tid + 2 * kStepThreads; i < n; i += kStepThreads) xs[i] = (xs[i] - mean) * rstd * g[i] + (b ? b[i] : 0.f);
+  const float rstd = 1.f / sqrtf(step_sum(s2, red + kStepWaves, tid) / (float)n + eps);
+  apply(tid, g0, b0, mean, rstd);
+  for (int q = tid + kStepThreads; 2 * q < n; q += kStepThreads) apply(q, two(g, q), two(b, q), mean, rstd);
 }
 
 __device__ __forceinline__ void normalise(float* xs, int n, int norm_kind, float eps, const float* g, const float* b, float* red) {
@@ -259,46 +255,37 @@ __device__ __forceinline__ void normalise(float* xs, int n, int norm_kind, float
 // ---------------------------------------------------------------------------
 // GEMV phase geometry (all values uniform across the wavefront)
 struct Geo {
-  const void* W;
+  const char* W;
   int N, units, cpp;     // rows, 16-byte units per row, 64-lane chunks per row
-  int rope_h;            // > 0: pair (i, i + h/2) inside heads of size h; 0: rows (2p, 2p + 1)
+  int row_bytes;
   int p_lo, n_pl;        // this workgroup owns n_pl pairs: blocks of 2^bshift consecutive pairs, block b of the
   int bshift, nwg;       // matrix going to workgroup b % nwg (p_lo = workgroup index).  At any moment the grid
                          // reads one contiguous window of the matrix, and a workgroup stays >= 64 KiB in place.
   int n_k;               // this wavefront's items: item k is flat index wave + 8k, flat = pair * cpp + chunk
   int dq, dr;            // 8 / cpp and 8 % cpp: how (pair, chunk) moves from one item to the next
-  int rsh, rmask, rmul, rstep;   // first row of pair p = (p >> rsh) * rmul + (p & rmask); its partner rstep rows on
+  int pl0, c0;           // the wavefront's first item
+  // first row of pair p = (p >> rsh) * rmul + (p & rmask), its partner rstep rows on: rows (2p, 2p + 1), or RoPE partners
+  // (i, i + h/2) inside heads of h rows (head sizes are powers of two)
+  int rsh, rmask, rmul, rstep;
 };
-// The two pairings as one branch-free formula (head sizes are powers of two): rows (2p, 2p + 1), or RoPE partners
-// (i, i + h/2) inside heads of h rows.
-__device__ __forceinline__ void geo_rows(Geo& g) {
-  if (g.rope_h) {
-    const int half = g.rope_h >> 1;
-    g.rsh = 31 - __builtin_clz(half); g.rmask = half - 1; g.rmul = g.rope_h; g.rstep = half;
+template <typename WT, bool kRope>
+__device__ __forceinline__ Geo make_geo(const GemvGeo& P, long w_off, int wg, int nwg, int wave, int h) {
+  Geo g;
+  g.W = (const char*)P.W + w_off;
+  g.N = P.N; g.units = P.units; g.cpp = P.cpp; g.row_bytes = P.units * 16;
+  g.p_lo = wg; g.nwg = nwg; g.bshift = P.bshift;
+  const int own = P.own_q + (wg < P.own_r ? 1 : 0);
+  g.n_pl = (own << P.bshift) - (wg == P.last_wg ? P.last_short : 0);
+  const int flat = g.n_pl * g.cpp;
+  g.n_k = flat > wave ? (flat - wave + kStepWaves - 1) / kStepWaves : 0;
+  g.dq = P.dq; g.dr = P.dr;
+  g.pl0 = (int)((unsigned)(wave * P.cpp_magic) >> 16); g.c0 = wave - g.pl0 * g.cpp;
+  if (kRope) {
+    const int half = h >> 1;
+    g.rsh = 31 - __builtin_clz(half); g.rmask = half - 1; g.rmul = h; g.rstep = half;
   } else {
     g.rsh = 0; g.rmask = 0; g.rmul = 2; g.rstep = 1;
   }
-}
-
-template <typename WT>
-__device__ __forceinline__ Geo make_geo(const void* W, int N, int Kd, int rope_h, int wg, int nwg, int wave) {
-  constexpr int V = Storage<WT>::kVec;
-  Geo g;
-  g.W = W; g.N = N; g.units = Kd / V; g.cpp = (g.units + 63) >> 6; g.rope_h = rope_h;
-  const int pairs = (N + 1) >> 1;
-  g.p_lo = wg; g.nwg = nwg;
-  g.bshift = 0;
-  const long pair_bytes = 2L * Kd * (long)sizeof(WT);
-  // larger blocks only while they still divide evenly among the workgroups (balance comes first)
-  while (g.bshift < 3 && (pair_bytes << g.bshift) < 65536 && pairs % (nwg << (g.bshift + 1)) == 0) ++g.bshift;
-  const int B = 1 << g.bshift, nblk = (pairs + B - 1) >> g.bshift;
-  const int own = nblk > wg ? (nblk - wg + nwg - 1) / nwg : 0;
-  g.n_pl = own * B;
-  if (own > 0 && wg + (own - 1) * nwg == nblk - 1) g.n_pl -= nblk * B - pairs;   // the matrix's last block may be short
-  const int flat = g.n_pl * g.cpp;
-  g.n_k = flat > wave ? (flat - wave + kStepWaves - 1) / kStepWaves : 0;
-  g.dq = kStepWaves / g.cpp; g.dr = kStepWaves - g.dq * g.cpp;
-  geo_rows(g);
   return g;
 }
 __device__ __forceinline__ void geo_next(const Geo& g, int& pl, int& c) {
@@ -312,9 +299,11 @@ __device__ __forceinline__ int geo_row(const Geo& g, int p, int j) {
   return (p >> g.rsh) * g.rmul + (p & g.rmask) + j * g.rstep;
 }
 
-// the step's own input (token embedding + learned position, or the previous stage's activation)
-template <typename WT>
-__device__ __forceinline__ void stage_input(const StepArgs& a, const StepSlot& S, float* xs, const Geo& gres, unsigned tag, int tid) {
+// the step's own input (token embedding + learned position, or the previous stage's activation), staged as stage_coherent
+// does it - same arithmetic, element order and thread mapping, so that a layer gives the same bits whether it is the first
+// of its partition or not (where the model is cut changes nothing); gres: the residual phases' rows
+template <typename WT, bool kLn>
+__device__ __forceinline__ float stage_input(const StepArgs& a, const StepSlot& S, float* xs, const float* gain, const Geo& gres, unsigned tag, int tid) {
   const int n = a.d;
   if (S.in_kind == IN_TOKEN) {
     const long tok = checked_token(S.in, 0, a.vocab, a.err);
@@ -333,42 +322,49 @@ __device__ __forceinline__ void stage_input(const StepArgs& a, const StepSlot& S
     st_tag(S.xres + r, xs[r], tag);
     if (r + 1 < n) st_tag(S.xres + r + 1, xs[r + 1], tag);
   }
+  __syncthreads();                                   // those rows have been read
+  float ss = 0.f;
+  for (int q = tid; 2 * q < n; q += kStepThreads) {
+    float2* p = reinterpret_cast<float2*>(xs) + q;
+    const float2 x = *p;
+    ss += kLn ? x.x : x.x * x.x; ss += kLn ? x.y : x.y * x.y;
+    if (!kLn) { const MDI_GLOBAL float* g = (const MDI_GLOBAL float*)gain; *p = float2{x.x * g[2 * q], x.y * g[2 * q + 1]}; }
+  }
+  return ss;
 }
 
 // Where a wavefront stands in its items (local pair, chunk of the row): tiles are issued, and multiplied, in order, so
 // each side keeps a cursor and moves it item by item instead of dividing the item index again for every tile.
 struct Cursor {
   int pl, c;
-  int row_pl;                          // the local pair whose row addresses b0, b1 hold (-1: none yet)
-  const MDI_GLOBAL u32x4 *b0, *b1;     // (issue side only) a pair's rows stay the same over its chunks
+  int row_pl;                          // the local pair whose rows b0, b1 are (-1: none yet)
+  Buffer b0, b1;                       // (issue side only) a pair's rows, each as long as a row; they stay the same over its chunks
 };
-__device__ __forceinline__ Cursor cursor_start(const Geo& g, int wave) {
+__device__ __forceinline__ Cursor cursor_start(const Geo& g) {
   Cursor cur;
-  cur.pl = wave / g.cpp; cur.c = wave - cur.pl * g.cpp;
-  cur.row_pl = -1; cur.b0 = nullptr; cur.b1 = nullptr;
+  cur.pl = g.pl0; cur.c = g.c0; cur.row_pl = -1; cur.b0 = cur.b1 = buffer_at(nullptr);
   return cur;
 }
 
 // Every call issues exactly 2 * kTile loads, whatever the geometry: a fixed number of loads per tile is what lets
 // the compiler wait for one tile while the next stays in flight (its counters cannot follow conditional loads).
-// Items past the end of the wavefront's share need no case of their own: their pair index lies past the matrix and
-// is clamped to its last row, lanes past the end of a row read the row's first bytes; gemv_compute skips the former
+// Items past the end of the wavefront's share, and lanes past the end of a row, read nothing; gemv_compute skips the former
 // and masks the latter or multiplies them by zeros.  All of this is scalar arithmetic, which the wavefronts of a
 // compute unit share one unit for, on the critical path of a phase's start: it is kept short.
 __device__ __forceinline__ void gemv_issue(Tile& t, const Geo& g, Cursor& cur, int lane) {
-  const MDI_GLOBAL u32x4* W = (const MDI_GLOBAL u32x4*)g.W;
   int pl = cur.pl, c = cur.c;
 #pragma unroll
   for (int s = 0; s < kTile; ++s) {
+    const bool own = pl < g.n_pl;
     if (pl != cur.row_pl) {                                     // uniform; long rows keep a pair for several items
-      const int r0 = min(geo_row(g, geo_pair(g, pl), 0), g.N - 1), r1 = min(r0 + g.rstep, g.N - 1);
-      cur.b0 = W + (long)r0 * g.units;
-      cur.b1 = W + (long)r1 * g.units;
+      const int r0 = own ? geo_row(g, geo_pair(g, pl), 0) : 0, r1 = min(r0 + g.rstep, g.N - 1);
+      cur.b0 = __builtin_amdgcn_make_buffer_rsrc((void*)(g.W + (long)r0 * g.row_bytes), 0, g.row_bytes, 0x00020000);
+      cur.b1 = __builtin_amdgcn_make_buffer_rsrc((void*)(g.W + (long)r1 * g.row_bytes), 0, g.row_bytes, 0x00020000);
       cur.row_pl = pl;
     }
-    const int off = c * 64 + (c * 64 + lane < g.units ? lane : 0);   // unit 0 of the chunk always exists
-    t.r[2 * s] = cur.b0[off];
-    t.r[2 * s + 1] = cur.b1[off];
+    const int off = own ? lane * 16 : (int)kNowhere, at = own ? c * 1024 : 0;
+    t.r[2 * s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(cur.b0, off, at, 0));
+    t.r[2 * s + 1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(cur.b1, off, at, 0));
     geo_next(g, pl, c);
   }
   cur.pl = pl; cur.c = c;
@@ -416,37 +412,42 @@ __device__ __forceinline__ void gemv_compute(const Tile& t, const Geo& g, int ti
 template <typename T> __device__ __forceinline__ float rounded(float v);   // as the storage type holds it
 template <> __device__ __forceinline__ float rounded<float>(float v) { return v; }
 template <> __device__ __forceinline__ float rounded<bf16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
+template <typename T> __device__ __forceinline__ T stored(float v);
+template <> __device__ __forceinline__ float stored<float>(float v) { return v; }
+template <> __device__ __forceinline__ bf16_t stored<bf16_t>(float v) { return f32_to_bf16(v); }
 struct FinOps { float c, s, b0, b1; int p, r0, r1; };
-__device__ __forceinline__ FinOps fin_ops(int ph, const Geo& g, const StepLayer& L, const StepArgs& a, const StepSlot& S, int pl) {
+template <int ph, bool kSwiglu>
+__device__ __forceinline__ FinOps fin_ops(const Geo& g, const StepArgs& a, const StepSlot& S, long w_off, int pl) {
   FinOps o{};
-  if (pl >= g.n_pl) return o;
-  o.p = geo_pair(g, pl); o.r0 = geo_row(g, o.p, 0); o.r1 = geo_row(g, o.p, 1);
-  const int r0 = o.r0, r1 = min(o.r1, g.N - 1);
-  const float *bq = L.bqkv, *bu = L.bup, *bo = L.bo, *bd = L.bdown;
-  const float* bias = ph == PH_QKV ? bq : ph == PH_UP ? (a.mlp_kind == MDI_MLP_SWIGLU ? nullptr : bu) : ph == PH_OPROJ ? bo : bd;
-  if (bias) { o.b0 = bias[r0]; o.b1 = bias[r1]; }
-  if (ph == PH_QKV) {
-    const int head = r0 >> (31 - __builtin_clz(a.h));            // (head sizes are powers of two)
-    if (S.rope && head < a.H + a.K) { const float2 cs = S.rope[r0 & (a.h - 1)]; o.c = cs.x; o.s = cs.y; }
+  const bool own = pl < g.n_pl;
+  o.p = geo_pair(g, own ? pl : 0); o.r0 = geo_row(g, o.p, 0); o.r1 = geo_row(g, o.p, 1);
+  if constexpr (!(ph == PH_UP && kSwiglu)) {
+    const float* bias = a.pr[ph == PH_QKV ? 0 : ph - 1].bias;
+    const Buffer b = buffer_at(bias ? (const char*)bias + w_off : nullptr);
+    o.b0 = ld_f32(b, own ? (uint32_t)o.r0 * 4u : kNowhere);
+    o.b1 = ld_f32(b, own && o.r1 < g.N ? (uint32_t)o.r1 * 4u : kNowhere);
+  }
+  if constexpr (ph == PH_QKV) {
+    const bool turned = own && (o.r0 >> (31 - __builtin_clz(a.h))) < a.H + a.K;   // (head sizes are powers of two)
+    const u32x2 cs = __builtin_amdgcn_raw_buffer_load_b64(buffer_at(S.rope), turned ? (o.r0 & (a.h - 1)) * 8 : (int)kNowhere, 0, 0);
+    o.c = __uint_as_float(cs.x); o.s = __uint_as_float(cs.y);
   }
   return o;
 }
 
-// Sums the wavefront slots of every pair and applies the phase's epilogue.
-template <typename WT>
-__device__ __forceinline__ void gemv_finish(int ph, const Geo& g, const StepLayer* Lp, int layer, const StepArgs& a, const StepSlot& S, const float* part,
-                                            float row_scale, tagged_t x0_pre, tagged_t x1_pre, FinOps ops, unsigned epoch, int tid) {
+// Sums the wavefront slots of every pair and applies the phase's epilogue; kv: this layer's pages.
+template <typename WT, int ph, bool kSwiglu>
+__device__ __forceinline__ void gemv_finish(const Geo& g, int layer, const StepArgs& a, const StepSlot& S, char* kv, const float* part,
+                                            float row_scale, tagged_t x0_pre, tagged_t x1_pre, FinOps ops, long w_off, unsigned epoch, int tid) {
   const unsigned wtag = epoch + 1;                            // what this phase writes carries the next counter
-  const StepLayer& L = *Lp;
-  __syncthreads();                                           // all wavefronts' partials are in LDS
-  stamp(a, S, layer, ph, 4);
   for (int pl = tid; pl < g.n_pl; pl += kStepThreads) {
     float v0 = 0.f, v1 = 0.f;
 #pragma unroll
     for (int w = 0; w < kStepWaves; ++w) { v0 += part[(pl * 2) * kStepWaves + w]; v1 += part[(pl * 2 + 1) * kStepWaves + w]; }
     v0 *= row_scale; v1 *= row_scale;
+    if (pl != tid) ops = fin_ops<ph, kSwiglu>(g, a, S, w_off, pl);
     const int p = ops.p, r0 = ops.r0, r1 = ops.r1;
-    if (ph == PH_QKV) {
+    if constexpr (ph == PH_QKV) {
       v0 += ops.b0; v1 += ops.b1;
       const int head = r0 >> (31 - __builtin_clz(a.h)), i = r0 & (a.h - 1);
       if (S.rope && head < a.H + a.K) {
@@ -460,13 +461,13 @@ __device__ __forceinline__ void gemv_finish(int ph, const Geo& g, const StepLaye
         // rounded values from the tagged copy
         const bool is_v = head >= a.H + a.K;
         const int kvh = head - a.H - (is_v ? a.K : 0);
-        WT* dst = (WT*)L.kv + S.kv_tok_off + (long)(kvh * 2 + (is_v ? 1 : 0)) * a.pt_h + i;
-        Storage<WT>::put(dst, v0); Storage<WT>::put(dst + (a.h >> 1), v1);
-        tagged_t* kn = S.knew + (long)(is_v ? a.K * a.h : 0) + kvh * a.h + i;
+        MDI_GLOBAL WT* dst = (MDI_GLOBAL WT*)kv + S.kv_tok_off + (long)(kvh * 2 + (is_v ? 1 : 0)) * a.pt_h + i;
+        dst[0] = stored<WT>(v0); dst[a.h >> 1] = stored<WT>(v1);
+        tagged_t* kn = S.knew + (is_v ? a.K * a.h : 0) + kvh * a.h + i;
         st_tag(kn, rounded<WT>(v0), wtag); st_tag(kn + (a.h >> 1), rounded<WT>(v1), wtag);
       }
-    } else if (ph == PH_UP) {
-      if (a.mlp_kind == MDI_MLP_SWIGLU) {
+    } else if constexpr (ph == PH_UP) {
+      if constexpr (kSwiglu) {
         st_tag(S.u + p, silu_f(v0) * v1, wtag);              // rows (2f, 2f+1) = (gate_f, up_f)
       } else {
         v0 += ops.b0; v1 += ops.b1;
@@ -492,7 +493,6 @@ __device__ __forceinline__ void gemv_finish(int ph, const Geo& g, const StepLaye
         if (last) store_kind(S.act_out, a.act_kind, r1, v1);
       }
     }
-    if (pl + kStepThreads < g.n_pl) ops = fin_ops(ph, g, L, a, S, pl + kStepThreads);
   }
 }
 
@@ -691,20 +691,20 @@ __device__ __forceinline__ void attn_stream(AttnState<WT, G>& st, Tile& A, Tile&
 // What attention reads of this launch's QKV product: this thread's word of the queries, and in the last wavefront (the
 // one with the fewest query words) the newest position's K/V row, already rounded to the storage type.
 template <typename WT> struct AttnAsk { tagged_t q[1], kv[2 * Storage<WT>::kVec]; };
-template <typename WT, int G, typename AR, typename SL>
-__device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_q_at(const AttnGeo& g, const AR& a, const SL& S, int i, uint32_t z) {
-  return word_at(S.q + (long)g.hg * G * a.h, (uint32_t)i * 8u + z);
+template <int G, typename AR>
+__device__ __forceinline__ uint32_t attn_q_at(const AttnGeo& g, const AR& a, int i, uint32_t z) {
+  return (uint32_t)(g.hg * G * a.h + i) * 8u + z;
 }
-template <typename WT, typename AR, typename SL>
-__device__ __forceinline__ const MDI_GLOBAL tagged_t* attn_kv_at(const AttnGeo& g, const AR& a, const SL& S, int e, uint32_t z) {
+template <typename WT, typename AR>
+__device__ __forceinline__ uint32_t attn_kv_at(const AttnGeo& g, const AR& a, int e, uint32_t z) {
   constexpr int V = Storage<WT>::kVec;
-  return word_at(S.knew + g.kvh * a.h + (e < V ? (long)e : (long)a.K * a.h + e - V), (uint32_t)g.hoff * 8u + z);
+  return (uint32_t)(g.kvh * a.h + (e < V ? e : a.K * a.h + e - V) + g.hoff) * 8u + z;
 }
 template <typename WT, int G, typename AR, typename SL>
-__device__ __forceinline__ void attn_ask(AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, int wave, unsigned epoch, int tid) {
-  if (!g.active) return;
-  ask_words(k.q, [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, tid, z); }, epoch, [&](int) { return tid < G * a.h; });
-  if (g.s1 == S.ctx && wave == kStepWaves - 1) ask_words(k.kv, [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, S, e, z); }, epoch);
+__device__ __forceinline__ void attn_ask(AttnAsk<WT>& k, const AttnGeo& g, const AR& a, const SL& S, int wave, int tid) {
+  const bool newest = g.active && g.s1 == S.ctx && wave == kStepWaves - 1;
+  ask_words(k.q, buffer_at(S.q), [&](int, uint32_t z) { return attn_q_at<G>(g, a, tid, z); }, [&](int) { return g.active && tid < G * a.h; });
+  ask_words(k.kv, buffer_at(S.knew), [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, e, z); }, [&](int) { return newest; });
 }
 // queries into LDS (pre-scaled), the newest position into the last wavefront's running sums
 template <typename WT, int G, typename AR, typename SL>
@@ -719,12 +719,12 @@ __device__ __forceinline__ void attn_begin(AttnState<WT, G>& st, AttnAsk<WT>& k,
   const bool newest = g.active && g.s1 == S.ctx && wave == kStepWaves - 1;
   if (g.active) {
     for (int i = tid; i < G * a.h; i += kStepThreads) {
-      auto at = [&](int, uint32_t z) { return attn_q_at<WT, G>(g, a, S, i, z); };
-      if (i != tid) ask_words(k.q, at, epoch);
-      await_words(k.q, at, epoch, a.spin_limit, a.err);
+      auto at = [&](int, uint32_t z) { return attn_q_at<G>(g, a, i, z); };
+      if (i != tid) ask_words(k.q, buffer_at(S.q), at);
+      await_words(k.q, buffer_at(S.q), at, epoch, a.spin_limit, a.err);
       qs[i] = tag_value(k.q[0]) * a.scale;
     }
-    if (newest) await_words(k.kv, [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, S, e, z); }, epoch, a.spin_limit, a.err);
+    if (newest) await_words(k.kv, buffer_at(S.knew), [&](int e, uint32_t z) { return attn_kv_at<WT>(g, a, e, z); }, epoch, a.spin_limit, a.err);
   }
   __syncthreads();
   if (newest) {
@@ -838,380 +838,5 @@ __device__ __forceinline__ void attn_finish(const AttnGeo& g, const AR& a, const
 
 // ---------------------------------------------------------------------------
 
-// Geometry of the four GEMV phases lives in LDS as plain integers (it depends on the workgroup
-// only); a phase reloads what it needs, so only two geometries are ever live in registers.
-constexpr int kGeoInts = 10;
-__device__ __forceinline__ int* lds_geo() { extern __shared__ float smem[]; return (int*)(smem + 16) + 4; }   // 32 ints after the flags
-
-template <typename WT>
-__device__ __forceinline__ void store_geo(int j, int N, int Kd, int rope_h, int wg, int nwg) {
-  const Geo g = make_geo<WT>(nullptr, N, Kd, rope_h, wg, nwg, 0);
-  int* o = lds_geo() + j * kGeoInts;
-  o[0] = g.N; o[1] = g.units; o[2] = g.cpp; o[3] = g.rope_h; o[4] = g.p_lo; o[5] = g.n_pl; o[6] = g.dq; o[7] = g.dr; o[8] = g.bshift; o[9] = g.nwg;
-}
-__device__ __forceinline__ Geo load_geo(int j, const void* W, int wave) {
-  const int* o = lds_geo() + j * kGeoInts;
-  Geo g;
-  g.W = W;
-  g.N = __builtin_amdgcn_readfirstlane(o[0]); g.units = __builtin_amdgcn_readfirstlane(o[1]);
-  g.cpp = __builtin_amdgcn_readfirstlane(o[2]); g.rope_h = __builtin_amdgcn_readfirstlane(o[3]);
-  g.p_lo = __builtin_amdgcn_readfirstlane(o[4]); g.n_pl = __builtin_amdgcn_readfirstlane(o[5]);
-  g.dq = __builtin_amdgcn_readfirstlane(o[6]); g.dr = __builtin_amdgcn_readfirstlane(o[7]);
-  g.bshift = __builtin_amdgcn_readfirstlane(o[8]); g.nwg = __builtin_amdgcn_readfirstlane(o[9]);
-  const int flat = g.n_pl * g.cpp;
-  g.n_k = flat > wave ? (flat - wave + kStepWaves - 1) / kStepWaves : 0;
-  geo_rows(g);
-  return g;
-}
-// GEMV phases in order: 0 = QKV, 1 = output projection, 2 = MLP up, 3 = MLP down
-__device__ __forceinline__ int gemv_index(int ph) { return ph == PH_QKV ? 0 : ph - 1; }
-// Every layer occupies an identically laid out block of the arena, so layer i's pointers are
-// the first layer's advanced by i strides: no pointer has to be fetched from memory.
-template <typename T> __device__ __forceinline__ T* advance(T* p, long bytes) { return p ? (T*)((char*)p + bytes) : p; }
-__device__ __forceinline__ const void* advance(const void* p, long bytes) { return p ? (const void*)((const char*)p + bytes) : p; }
-template <typename AR>
-__device__ __forceinline__ StepLayer layer_at(const AR& a, int layer) {
-  const long w = a.w_stride * layer, kv = a.kv_stride * layer;
-  StepLayer L;
-  L.wqkv = advance(a.l0.wqkv, w); L.wo = advance(a.l0.wo, w); L.wup = advance(a.l0.wup, w); L.wdown = advance(a.l0.wdown, w);
-  L.bqkv = advance(a.l0.bqkv, w); L.bo = advance(a.l0.bo, w); L.bup = advance(a.l0.bup, w); L.bdown = advance(a.l0.bdown, w);
-  L.ln1_g = advance(a.l0.ln1_g, w); L.ln1_b = advance(a.l0.ln1_b, w); L.ln2_g = advance(a.l0.ln2_g, w); L.ln2_b = advance(a.l0.ln2_b, w);
-  L.kv = advance(a.l0.kv, kv);
-  return L;
-}
-__device__ __forceinline__ const void* layer_matrix(const StepLayer& L, int j) {
-  const void *w0 = L.wqkv, *w1 = L.wo, *w2 = L.wup, *w3 = L.wdown;   // all read first: a selected field would put the struct into scratch memory
-  return j == 0 ? w0 : j == 1 ? w1 : j == 2 ? w2 : w3;
-}
-
-template <typename WT, int G>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step(StepArgs a) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // a set of nwg workgroups takes its messages in turn inside every phase; two sets share the compute units
-  const int nwg = a.nwg, wg = blockIdx.x % nwg;
-  const int set = (int)blockIdx.x / nwg;
-  const int slot_lo = a.set_lo[set], slot_hi = a.set_lo[set + 1];
-  // the other set's first message: how far its workgroup of the same index has come is what this one paces itself by
-  const StepSlot& O = a.s[a.set_lo[a.n_sets == 2 ? (set ^ 1) : 0]];
-  float* part = lds_part();
-  float* xs = lds_vec(a.part_floats);
-  float* red = lds_red();
-  int* s_flag = lds_flag();
-
-  if (threadIdx.x == 0) {
-    s_flag[kFailed] = 0;
-    store_geo<WT>(0, (a.H + 2 * a.K) * a.h, a.d, a.h, wg, nwg);       // pairs (i, i + h/2): the RoPE partners
-    store_geo<WT>(1, a.d, a.H * a.h, 0, wg, nwg);
-    store_geo<WT>(2, a.mlp_kind == MDI_MLP_SWIGLU ? 2 * a.F : a.F, a.d, 0, wg, nwg);
-    store_geo<WT>(3, a.d, a.F, 0, wg, nwg);
-    if (wg == 0)
-      for (int m = 0; m < a.n_slots; ++m)
-        if (a.s[m].table_entry) *a.s[m].table_entry = a.s[m].new_page;
-  }
-  __syncthreads();
-
-  float acc0 = 0.f, acc1 = 0.f;
-  // requested while finishing the previous (message, phase): the head of the next one's input vector
-  bool early = false;
-  VecAsk vec{};
-
-#pragma nounroll
-  for (int layer = 0; layer < a.n_layer; ++layer) {
-    const StepLayer Lv = layer_at(a, layer);
-    const StepLayer* L = &Lv;
-#pragma nounroll
-    for (int ph = 0; ph < 5; ++ph) {
-#pragma nounroll
-      for (int slot = slot_lo; slot < slot_hi; ++slot) {
-        // Messages alternate inside a phase: while this message's input vector makes its round trip,
-        // the memory system is still busy with the other message's stream, and by the time a message reaches its
-        // next phase every workgroup has long finished its previous one.
-        const StepSlot& S = a.s[slot];
-        const unsigned epoch = S.epoch0 + (unsigned)(layer * 5 + ph);
-        stamp(a, S, layer, ph, 0);
-        // per-thread addresses are recomputed in every phase (see k_step_batch)
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        const int lane = tid & 63;
-        // ---- the head of the input vector is asked for first: loads return in order, and the workgroup that everybody
-        //      waits for finds it there at once instead of behind its weights.
-        const int j = gemv_index(ph);
-        const Geo g = load_geo(j, layer_matrix(Lv, j), wave);
-        const bool first = ph == PH_QKV && layer == 0;
-        const bool work = g.n_pl > 0;                  // who has no rows in a product reads nothing for it either
-        AttnGeo ga{};
-        Tile A, B;
-        Cursor ci, cc;                       // the GEMV phases' issue and multiply cursors
-        int pgA[kTile], pgB[kTile];         // page numbers of the attention tiles that go into A and B next
-        AttnAsk<WT> ask{};
-        FinOps ops{};
-        auto vec_src = [&](const StepSlot& N, int nph) __attribute__((always_inline)) { return nph == PH_OPROJ ? N.o : nph == PH_DOWN ? N.u : N.xres; };
-        auto vec_len = [&](int nph) __attribute__((always_inline)) { return nph == PH_OPROJ ? a.H * a.h : nph == PH_DOWN ? a.F : a.d; };
-        auto vec_gain = [&](int nph, int nlayer) __attribute__((always_inline)) {
-          const float *g1 = a.l0.ln1_g, *g2 = a.l0.ln2_g;
-          return (nph == PH_QKV || nph == PH_UP) && a.norm_kind == MDI_NORM_RMSNORM ? advance(nph == PH_QKV ? g1 : g2, a.w_stride * nlayer) : nullptr;
-        };
-        auto ask_for = [&](const StepSlot& N, int nph, int nlayer) __attribute__((always_inline)) {
-          const unsigned nepoch = N.epoch0 + (unsigned)(nlayer * 5 + nph);
-          if (!(nph == PH_QKV && nlayer == 0)) vec_ask(vec, vec_src(N, nph), vec_len(nph), vec_gain(nph, nlayer), nepoch, tid);
-        };
-        // ---- then this phase's first two tiles: their addresses depend on nothing another workgroup writes
-        if (ph == PH_ATTN) {
-          vec = VecAsk{}; early = false;               // (never asked for ahead of attention: the registers are free)
-          ga = make_attn_geo<WT, G>(a, S, wg, wave, lane);
-          attn_ask<WT, G>(ask, ga, a, S, wave, epoch, tid);
-          attn_pages(pgA, ga, a, S, 0, wave); attn_pages(pgB, ga, a, S, 1, wave);
-          attn_issue<WT>(A, pgA, ga, a, S, L->kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, S, L->kv, 1, wave);
-        } else if (work || first) {
-          if (!early) ask_for(S, ph, layer);
-          ops = fin_ops(ph, g, Lv, a, S, tid);
-          ci = cc = cursor_start(g, wave); gemv_issue(A, g, ci, lane); gemv_issue(B, g, ci, lane);
-        }
-
-        auto early_requests = [&]() __attribute__((always_inline)) {
-          // ---- requests for the next (message, phase), answered while this phase is being finished: with two
-          //      messages alternating, what the next one needs was published a whole phase ago
-          early = false;
-          // whatever was requested a phase ago has been used: giving every register a value here, on every path,
-          // tells the compiler that none of them is live across the streaming loops above
-          vec = VecAsk{};
-          if (slot_hi - slot_lo > 1) {
-            int nslot = slot + 1, nph = ph, nlayer = layer;
-            if (nslot == slot_hi) { nslot = slot_lo; if (++nph == 5) { nph = 0; ++nlayer; } }
-            if (nlayer < a.n_layer && nph != PH_ATTN) { ask_for(a.s[nslot], nph, nlayer); early = true; }
-          }
-        };
-
-        // Two sets share a compute unit's memory pipeline, and the hardware serves the older wavefronts (the set
-        // that was dispatched first) or the higher priority first; left alone, one set finishes a fifth earlier
-        // and the other runs the rest of the launch on half the wavefronts.  So the set that is behind takes the
-        // higher priority, phase by phase.
-        unsigned other_done = 0u;
-        const bool pace = a.n_sets == 2 && slot == slot_lo;
-        if (pace) other_done = __hip_atomic_load(O.flags + wg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - O.epoch0;
-
-        stamp(a, S, layer, ph, 1);
-        if (pace) {
-          // work left, in (message, phase) units; the set with more of it goes first
-          // (launches of one message leave the counters behind: before the other set's first phase they say nothing)
-          const int total = a.n_layer * 5, seen = min(max(__builtin_amdgcn_readfirstlane((int)other_done), 0), total);
-          const int left = (total - (layer * 5 + ph)) * (slot_hi - slot_lo);
-          const int other_left = (total - seen) * (a.set_lo[2 - set] - a.set_lo[1 - set]);
-          if (left > other_left || (left == other_left && set == 1)) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
-        }
-
-        if (ph == PH_ATTN) {
-          // ---- attention over the sample's pages -----------------------------------------------------
-          AttnState<WT, G> st;
-          attn_begin<WT, G>(st, ask, ga, a, S, xs, wave, epoch, tid);
-          stamp(a, S, layer, ph, 2);
-          const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
-          attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, S, L->kv, nte, wave, xs);
-          stamp(a, S, layer, ph, 3);
-          early_requests();
-          attn_to_lds<WT, G>(st, ga, a.h, xs, wave);
-          attn_finish<G>(ga, a, S, xs, s_flag, epoch, tid);
-        } else if (work || first) {
-          // ---- a GEMV phase ----------------------------------------------------------------------------
-          for (int i = tid; i < g.n_pl * 2 * kStepWaves; i += kStepThreads) part[i] = 0.f;
-          const bool normed = ph == PH_QKV || ph == PH_UP;
-          const bool fused_rms = normed && a.norm_kind == MDI_NORM_RMSNORM;
-          const float *gain1 = L->ln1_g, *gain2 = L->ln2_g;
-          const float* gain = ph == PH_QKV ? gain1 : gain2;
-          float row_scale = 1.f;                       // 1/rms when the norm is folded into the epilogue
-          float share = 0.f;                           // of the sum of squares (RMSNorm) or of the sum
-          if (ph == PH_QKV && layer == 0) {
-            stage_input<WT>(a, S, xs, load_geo(1, nullptr, wave), epoch, tid);
-            // same arithmetic, element order and thread mapping as stage_coherent, so that a layer gives the same
-            // bits whether it is the first of its partition or not (where the model is cut changes nothing)
-            __syncthreads();                            // stage_input has read its rows of xs
-            for (int i0 = tid; i0 < a.d; i0 += 8 * kStepThreads) {
-#pragma unroll
-              for (int jj = 0; jj < 8; ++jj) {
-                const int i = i0 + jj * kStepThreads;
-                if (i < a.d) { const float x = xs[i]; share += fused_rms ? x * x : x; if (fused_rms) xs[i] = x * gain[i]; }
-              }
-            }
-          } else {
-            share = stage_coherent(vec, vec_src(S, ph), vec_len(ph), xs, fused_rms ? gain : nullptr, fused_rms, epoch, a.spin_limit, a.err, tid);
-          }
-          // zeros behind the vector up to a whole 64-lane chunk (the host sizes the LDS for it): see gemv_compute
-          for (int i = g.units * Storage<WT>::kVec + tid; i < g.cpp * 64 * Storage<WT>::kVec; i += kStepThreads) xs[i] = 0.f;
-          if (fused_rms) {
-            row_scale = 1.f / sqrtf(step_sum(share, red, tid) / (float)a.d + a.eps);
-          } else {
-            if (normed) {
-              const float *b1 = L->ln1_b, *b2 = L->ln2_b;
-              layer_norm(xs, a.d, share, a.eps, gain, ph == PH_QKV ? b1 : b2, red, tid);
-            }
-            __syncthreads();
-          }
-          if (s_flag[kFailed]) return;
-          // residual phases: fetch this thread's rows of x now, the stream below hides the latency
-          tagged_t x0 = 0ull, x1 = 0ull;
-          if ((ph == PH_OPROJ || ph == PH_DOWN) && tid < g.n_pl) {
-            const int r0 = ops.r0;
-            x0 = ld_raw(S.xres + r0);
-            if (r0 + 1 < g.N) x1 = ld_raw(S.xres + r0 + 1);
-          }
-          stamp(a, S, layer, ph, 2);
-
-          const int nte = ((g.n_k + kTile - 1) / kTile + 1) & ~1;
-#pragma nounroll
-          for (int t = 2; t < nte; t += 2) {
-            gemv_compute<WT, true>(A, g, t - 2, cc, wave, lane, xs, part, acc0, acc1);
-            gemv_issue(A, g, ci, lane);
-            gemv_compute<WT, true>(B, g, t - 1, cc, wave, lane, xs, part, acc0, acc1);
-            gemv_issue(B, g, ci, lane);
-          }
-          if (nte) {                                   // (the last two tiles: nothing more to ask for)
-            gemv_compute<WT, true>(A, g, nte - 2, cc, wave, lane, xs, part, acc0, acc1);
-            gemv_compute<WT, true>(B, g, nte - 1, cc, wave, lane, xs, part, acc0, acc1);
-          }
-          stamp(a, S, layer, ph, 3);
-          early_requests();
-          gemv_finish<WT>(ph, g, L, layer, a, S, part, row_scale, x0, x1, ops, epoch, tid);
-        } else {
-          vec = VecAsk{}; early = false;
-        }
-
-        // ---- publish: this workgroup is done with the phase ---------------------------------------------
-        stamp(a, S, layer, ph, 5);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // this thread's stores have completed
-        __syncthreads();
-        stamp(a, S, layer, ph, 6);
-        if (s_flag[kFailed]) return;
-        if (a.n_sets == 2 && tid == 0) __hip_atomic_store(S.flags + wg, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-  }
-}
-
-template <typename WT>
-static void launch_step_t(hipStream_t s, int G, int nwg, size_t lds, const StepArgs& a) {
-  const dim3 grid(nwg * a.n_sets), block(kStepThreads);
-  // G = query heads per attention work item: the host asks for 1 or 2 (larger groups were measured slower)
-  if (G == 2) hipLaunchKernelGGL((k_step<WT, 2>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((k_step<WT, 1>), grid, block, lds, s, a);
-}
-
-#if MDI_STEP_WAVES == 8
-// ---------------------------------------------------------------------------
-// Output layers (Alg. 1: "process output layers ... get token"): final norm, vocabulary projection and greedy
-// argmax as one launch that streams the vocabulary matrix the way a GEMV phase of k_step does (same work split,
-// same two register tiles in flight per wavefront across row boundaries), without any exchange: every workgroup
-// normalises the activation itself.  Logits are optional; the argmax (lowest index on exact ties) is folded per
-// workgroup and then by the last workgroup to arrive, in index order.
-__device__ __forceinline__ bool better_logit(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
-
-template <typename WT>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_logits(LogitsArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wg = blockIdx.x, nwg = gridDim.x;
-  float* part = lds_part();
-  float* xs = lds_vec(a.part_floats);
-  float* red = lds_red();
-  const Geo g = make_geo<WT>(a.W, a.N, a.Kd, 0, wg, nwg, wave);
-  Tile A, B;
-  Cursor ci = cursor_start(g, wave), cc = ci;
-  gemv_issue(A, g, ci, lane);
-  gemv_issue(B, g, ci, lane);
-  for (int i = threadIdx.x; i < a.Kd; i += kStepThreads) xs[i] = load_kind(a.x, a.x_kind, i);
-  for (int i = threadIdx.x; i < g.n_pl * 2 * kStepWaves; i += kStepThreads) part[i] = 0.f;
-  __syncthreads();
-  normalise(xs, a.Kd, a.norm_kind, a.eps, a.g, a.b, red);
-  __syncthreads();
-  float acc0 = 0.f, acc1 = 0.f;
-  const int nte = ((g.n_k + kTile - 1) / kTile + 1) & ~1;
-#pragma nounroll
-  for (int t = 0; t < nte; t += 2) {
-    gemv_compute<WT, false>(A, g, t, cc, wave, lane, xs, part, acc0, acc1);
-    gemv_issue(A, g, ci, lane);
-    gemv_compute<WT, false>(B, g, t + 1, cc, wave, lane, xs, part, acc0, acc1);
-    gemv_issue(B, g, ci, lane);
-  }
-  __syncthreads();                                           // all wavefronts' partials are in LDS
-  float bv = -INFINITY; int bi = 0x7FFFFFFF;
-  for (int pl = threadIdx.x; pl < g.n_pl; pl += kStepThreads) {
-    float v0 = 0.f, v1 = 0.f;
-#pragma unroll
-    for (int w = 0; w < kStepWaves; ++w) { v0 += part[(pl * 2) * kStepWaves + w]; v1 += part[(pl * 2 + 1) * kStepWaves + w]; }
-    const int r0 = 2 * geo_pair(g, pl), r1 = r0 + 1;
-    if (a.out) a.out[r0] = v0;
-    if (better_logit(v0, r0, bv, bi)) { bv = v0; bi = r0; }
-    if (r1 < a.N) {
-      if (a.out) a.out[r1] = v1;
-      if (better_logit(v1, r1, bv, bi)) { bv = v1; bi = r1; }
-    }
-  }
-  // workgroup best, then the last workgroup to arrive folds the per-workgroup candidates
-  __shared__ float sv[kStepWaves];
-  __shared__ int si[kStepWaves];
-  __shared__ int s_last;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(bv, off, 64); const int oi = __shfl_xor(bi, off, 64);
-    if (better_logit(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-  }
-  if (lane == 0) { sv[wave] = bv; si[wave] = bi; }
-  __syncthreads();
-  // The candidate crosses workgroups as two 8-byte words that carry the call's counter (value | tag, index | tag),
-  // stored and loaded at agent scope; the last workgroup to arrive reloads a word until its tag is this call's.  No
-  // fence: on this chip an agent-scope fence writes back a die's L2 (measured: about 5 us per wavefront that runs one).
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < kStepWaves; ++k) if (better_logit(sv[k], si[k], bv, bi)) { bv = sv[k]; bi = si[k]; }
-    __hip_atomic_store(a.cand + 2 * wg, ((tagged_t)a.tag << 32) | __float_as_uint(bv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a.cand + 2 * wg + 1, ((tagged_t)a.tag << 32) | (uint32_t)bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned ticket = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = ticket == (unsigned)nwg - 1;
-  }
-  __syncthreads();
-  if (s_last) {
-    bv = -INFINITY; bi = 0x7FFFFFFF;
-    for (int k = threadIdx.x; k < nwg; k += kStepThreads) {
-      tagged_t uv = ld_raw(a.cand + 2 * k), ui = ld_raw(a.cand + 2 * k + 1);
-      int it = 0;
-      while ((uint32_t)(uv >> 32) != a.tag || (uint32_t)(ui >> 32) != a.tag) {
-        if (++it > a.spin_limit) { __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
-        __builtin_amdgcn_s_sleep(1);
-        uv = ld_raw(a.cand + 2 * k); ui = ld_raw(a.cand + 2 * k + 1);
-      }
-      const float v = __uint_as_float((uint32_t)uv);
-      const int i = (int)(uint32_t)ui;
-      if (better_logit(v, i, bv, bi)) { bv = v; bi = i; }
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const float ov = __shfl_xor(bv, off, 64); const int oi = __shfl_xor(bi, off, 64);
-      if (better_logit(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-    }
-    __syncthreads();
-    if (lane == 0) { sv[wave] = bv; si[wave] = bi; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int k = 1; k < kStepWaves; ++k) if (better_logit(sv[k], si[k], bv, bi)) { bv = sv[k]; bi = si[k]; }
-      *a.token_out = bi;
-      __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
-}
-#endif
-
 }  // namespace step_w<waves>
-
-#if MDI_STEP_WAVES == 8
-void launch_logits(hipStream_t s, int dtype, int nwg, size_t lds, const LogitsArgs& a) {
-  using namespace step_w8;
-  const dim3 grid(nwg), block(kStepThreads);
-  if (dtype == MDI_BF16) hipLaunchKernelGGL(k_logits<bf16_t>, grid, block, lds, s, a);
-  else hipLaunchKernelGGL(k_logits<float>, grid, block, lds, s, a);
-}
-#endif
-
-void MDI_STEP_CAT(launch_step_w, MDI_STEP_WAVES)(hipStream_t s, int dtype, int G, int nwg, size_t lds, const StepArgs& a) {
-  using namespace MDI_STEP_CAT(step_w, MDI_STEP_WAVES);
-  if (dtype == MDI_BF16) launch_step_t<bf16_t>(s, G, nwg, lds, a); else launch_step_t<float>(s, G, nwg, lds, a);
-}
-
 }  // namespace mdi

@@ -1,7 +1,5 @@
-// The persistent decode step for workgroups of 8 wavefronts (one workgroup per compute unit): launches that carry one
-// message (k_step), launches that take several messages through one pass over the weights (k_step_batch), and the
-// output layers (k_logits for one sample, k_logits_batch for several).
+// The persistent decode step for workgroups of 8 wavefronts (one workgroup per compute unit: launches that carry one message), bf16 storage.
 #define MDI_STEP_WAVES 8
-#include "step_impl.h"
-#include "step_batch.h"
-#include "head_batch.h"
+#define MDI_STEP_TYPE bf16_t
+#define MDI_STEP_TYPE_NAME _bf16
+#include "step_kernel.h"
