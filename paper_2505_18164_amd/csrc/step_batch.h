@@ -89,19 +89,13 @@ __device__ __forceinline__ void await_two(u32x4 (&raw)[N], const ASK& ask, bool 
   }, ask, spin_limit, err);
 }
 // Eight column steps of 16 weight rows as the matrix instruction's first operand: lane (i = l mod 16, kg = l div 16) takes
-// 16 bytes of row i.  off: the lane's offset; `uniform`: the first row's and column's; n: steps there are
-// (fewer than eight: the last one again).  Always eight loads, so that the compiler can tell how many are on their way;
-// where there is nothing to load (!on) they read nothing.
-__device__ __forceinline__ void w_issue(Tile& t, Buffer b, uint32_t off, uint32_t uniform, int n, bool on) {
-  off = on ? off : kNowhere;
-  uniform = on ? uniform : 0u;           // (what lies outside is told by off + uniform not exceeding 32 bits)
-  if (n >= 8) {
+// 16 bytes of row i.  off: the lane's offset; `uniform`: the first row's and column's; n: steps there are.
+// Always eight loads, so that the compiler can tell how many are on their way; those past the last step read nothing.  (Two
+// cases, one of them without the choice per step, make it copy what the first has loaded, and wait for it.)
+__device__ __forceinline__ void w_issue(Tile& t, Buffer b, uint32_t off, uint32_t uniform, int n) {
+  uniform = __builtin_amdgcn_readfirstlane(n > 0 ? uniform : 0u);   // (what lies outside is told by off + uniform not exceeding 32 bits)
 #pragma unroll
-    for (int s = 0; s < 8; ++s) t.r[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off + s * 64, (int)uniform, 0));
-  } else {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) t.r[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, (int)uniform + max(min(s, n - 1), 0) * 64, 0));
-  }
+  for (int s = 0; s < 8; ++s) t.r[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)((s < n ? off : kNowhere) + s * 64), (int)uniform, 0));
 }
 __device__ __forceinline__ f32x4 mac(const u32x4& w, const u32x4& v, f32x4 acc) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, v), acc, 0, 0, 0);
@@ -450,7 +444,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   __syncthreads();
 
   const int ks_q = wg / a0.str_S, ks_s = wg - ks_q * a0.str_S;
-  long w_off = 0, kv_off = 0;                    // bytes from the first layer's matrices / pages to this layer's
+  long w_off = 0, kv_off = 0, nc_off = 0;        // bytes from the first layer's matrices / pages / corrections to this layer's
   unsigned epoch = a0.epoch0;                    // what the phase that runs expects its input's words to carry; it writes epoch + 1
 
 #pragma nounroll
@@ -494,10 +488,11 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       const Buffer sqb = buffer_at(up ? a.ssq[1] : a.ssq[0]), smb = buffer_at(kLn ? (up ? a.ssum[1] : a.ssum[0]) : nullptr);
       const int stride = a.sq_stride;
       const bool long_vec = (a.d >> 1) * m > kWatchWords;
-      tagged_t gate[1];
-      auto gate_at = [&](int, uint32_t z) __attribute__((always_inline)) { return (uint32_t)tid * 8u + z; };
-      auto gated = [&](int) __attribute__((always_inline)) { return long_vec && tid < stride; };
-      ask_words(gate, sqb, gate_at, gated);
+      uint32_t gate = 0;                                            // (the counter alone: half a loaded pair left unused is reused, and waited for)
+      auto ask_gate = [&](int w) __attribute__((always_inline)) {
+        gate = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sqb, (int)fresh(long_vec && w < stride ? (uint32_t)w * 8u + 4u : kNowhere), 0, kAgentScope);
+      };
+      ask_gate(tid);
       // the sums: 32 threads per message, eight words each
       const int sj = tid >> 5, sc = tid & 31;
       const bool sums = sj < m;
@@ -533,7 +528,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       struct Ops { float c, s, b0, b1, n[4]; };
       const Buffer biasb = buffer_at(P.bias ? (const char*)P.bias + w_off : nullptr);
       // LayerNorm corrections of this phase's product: [W g | W b], N floats each (QKV's first, then the up product's)
-      const float* ncp = kLn ? a.nc0 + (long)layer * a.nc_stride + (up ? 2L * a.pr[0].N : 0L) : nullptr;
+      const float* ncp = kLn ? (const float*)((const char*)a.nc0 + nc_off) + (up ? 2 * a.pr[0].N : 0) : nullptr;
       const Buffer n0b = buffer_at(ncp), n1b = buffer_at(kLn ? ncp + N : nullptr), ropeb = buffer_at(a.rope);
       auto ops_of = [&](const Item& it, bool own) __attribute__((always_inline)) {
         Ops o{};
@@ -559,18 +554,19 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       const int wi = n & (R - 1);
       const uint32_t w_lane = (uint32_t)((up ? wi : (wi & (half - 1)) + (wi >= half ? 1 << hh_sh : 0)) * rb + (kg << 4));
       auto issue = [&](Tile& t, int lb, int h8) __attribute__((always_inline)) {
-        w_issue(t, wb, w_lane, (uint32_t)(first_row(lb * nwg + wg) * rb + ks0 * 64 + h8 * 512), nks - 8 * h8, lb < nb && nks > 0);
+        w_issue(t, wb, w_lane, (uint32_t)(first_row(lb * nwg + wg) * rb + ks0 * 64 + h8 * 512), lb < nb ? nks - 8 * h8 : 0);
       };
       const bool two = nks > 8;                                     // two tiles per block, else one
-      if (two) { issue(A, 0, 0); issue(B, 0, 1); } else { issue(A, 0, 0); issue(B, 1, 0); }
+      issue(A, 0, 0); issue(B, two ? 0 : 1, two ? 1 : 0);
       bstamp(a, layer, ph, 1);
       // ---- Vectors of more than kWatchWords words are looked at only after every workgroup's first sum of
       // squares (which it stores last) is there: 256 workgroups that watch 32 KB each crowd out the stores they wait
       // for (TinyLlama, 4 messages: 629 us, ungated 644; the 7B shape with 8: 979 and 975).
       if (long_vec) {
-        await_words(gate, sqb, gate_at, epoch, a.spin_limit, a.err, gated);
-        for (int i = tid + kStepThreads; i < stride; i += kStepThreads)
-          poll_words(gate, sqb, [&](int, uint32_t z) { return (uint32_t)i * 8u + z; }, epoch, a.spin_limit, a.err);
+        for (int w = tid; w < stride; w += kStepThreads) {
+          if (w != tid) ask_gate(w);
+          poll_while([&]() { return gate != epoch; }, [&]() { ask_gate(w); }, a.spin_limit, a.err);
+        }
         __syncthreads();
       }
       float sum2 = 0.f, sum1 = 0.f;                                 // this thread's share of its message's sums
@@ -729,7 +725,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       __syncthreads();
       bstamp(a, layer, ph, 6);
       epoch = wtag;
-      return !s_flag[kFailed];                                      // a bounded wait expired: everybody else's will, too
+      return __builtin_amdgcn_readfirstlane(s_flag[kFailed]) == 0;    // (else a bounded wait expired: everybody else's will, too)
     };
 
     // ---- attention: one work item = (message, head group, context split); items dealt round-robin
@@ -778,7 +774,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       __syncthreads();
       bstamp(a, layer, ph, 6);
       ++epoch;
-      return !s_flag[kFailed];
+      return __builtin_amdgcn_readfirstlane(s_flag[kFailed]) == 0;
     };
 
     // ---- a product whose inner dimension is split among workgroups.  Every workgroup used to read the whole
@@ -815,7 +811,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         }
       };
       ask(raw[0], tid);
-      if (n_units > 2 * kStepThreads) ask(raw[1], tid + 2 * kStepThreads);
+      ask(raw[1], tid + 2 * kStepThreads);
       // the rows this workgroup owns: what their epilogue needs
       const int j = tid >> 3, p = tid & 7, r0 = wg * 16 + 2 * p;
       const bool mine = j < m && r0 < a.d, last = down && layer == a.n_layer - 1;
@@ -828,7 +824,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       Tile A, B;
       const Buffer wb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.W + w_off), 0, (int)P.bytes, 0x00020000);
       const uint32_t w_lane = (uint32_t)(n * rb + (kg << 4)), w_base = (uint32_t)(blk * 16 * rb + k0 * 64);
-      auto issue = [&](Tile& t, int ti) __attribute__((always_inline)) { w_issue(t, wb, w_lane, w_base + ti * 512, nk - ti * 8, live && ti * 8 < nk); };
+      auto issue = [&](Tile& t, int ti) __attribute__((always_inline)) { w_issue(t, wb, w_lane, w_base + ti * 512, live ? nk - ti * 8 : 0); };
       issue(A, 0);
       issue(B, 1);
       bstamp(a, layer, ph, 1);
@@ -931,7 +927,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       __syncthreads();
       bstamp(a, layer, ph, 6);
       epoch = wtag;
-      return !s_flag[kFailed];
+      return __builtin_amdgcn_readfirstlane(s_flag[kFailed]) == 0;
     };
 
     if (!normed(std::integral_constant<int, PH_QKV>())) return;
@@ -939,7 +935,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
     if (!split(std::integral_constant<int, PH_OPROJ>())) return;
     if (!normed(std::integral_constant<int, PH_UP>())) return;
     if (!split(std::integral_constant<int, PH_DOWN>())) return;
-    w_off += a0.w_stride; kv_off += a0.kv_stride;
+    w_off += a0.w_stride; kv_off += a0.kv_stride; nc_off += 4 * a0.nc_stride;
   }
 }
 

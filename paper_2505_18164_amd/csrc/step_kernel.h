@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             }
             __syncthreads();
           }
-          if (s_flag[kFailed]) return false;
+          if (__builtin_amdgcn_readfirstlane(s_flag[kFailed])) return false;
           stamp(a, S, layer, ph, 2);
 
           const int nte = ((g.n_k + kTile - 1) / kTile + 1) & ~1;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       stamp(a, S, layer, ph, 5);
       __syncthreads();
       stamp(a, S, layer, ph, 6);
-      if (s_flag[kFailed]) return false;
+      if (__builtin_amdgcn_readfirstlane(s_flag[kFailed])) return false;
       if (!kOne && a.n_sets == 2 && tid == 0) __hip_atomic_store((MDI_GLOBAL unsigned*)S.flags + wg, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return true;
