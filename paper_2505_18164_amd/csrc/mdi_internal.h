@@ -304,7 +304,7 @@ struct BatchArgs {
   unsigned m_magic;                  // 0xFFFFFFFF / m + 1: e / m is the high word of e * m_magic, exact while e * m < 2^32
   unsigned epoch0;
   // Exchange buffers.  Vectors that feed a matrix product travel as pairs of bf16 with the writing phase's counter
-  // in one 8-byte word, one array [group of 4 pairs][m messages][4] per kind for the whole launch (xn: the
+  // in one 8-byte word, one array per kind for the whole launch (layout: vec_word in step_batch.h; xn: the
   // residual stream times the gain of the norm that follows; ob: attention output; ub: MLP hidden).  What attention
   // needs per message - q, the newest K/V row, split partials as (float, counter) like in StepSlot, tickets - sits
   // in one block per message: message j's are message 0's advanced by j * slot_stride bytes.

@@ -42,8 +42,8 @@
 //     word, already multiplied by the gain of the RMSNorm that follows (1/rms is applied to the finished products;
 //     the sum of squares travels as one partial per workgroup and message).  Bytes exchanged per message are half
 //     those of k_step's (float, counter) words, which matters now that 16 messages share a pass.  A vector kind is
-//     ONE array [group of 4 pairs][messages][4] for the whole launch: the eight columns that a lane of the matrix
-//     instruction takes are 32 consecutive bytes, and no line carries room for messages the launch does not have.
+//     ONE array for the whole launch, laid out for the loads of the matrix instruction's second operand (vec_word), and no
+//     line carries room for messages the launch does not have.
 //   * The residual stream never leaves the workgroup that owns its rows: it stays in LDS for the whole launch.
 //   * Products whose input is the d-sized normalised vector (QKV, MLP up) keep each wavefront's column slice of all
 //     messages in registers for all the blocks of the phase; the others (output projection, MLP down: one block per
@@ -137,9 +137,14 @@ __device__ __forceinline__ float part_sum(const float* part, int lb, int i, int 
   return v;
 }
 
-// Where pair `pair` of message j stands in an exchange vector: [group of 4 pairs][message][pair of the group], so that the 8
-// columns a lane of the matrix instruction takes are 32 consecutive bytes.
-__device__ __forceinline__ int vec_word(int pair, int j, int m) { return (((pair >> 2) * m + j) << 2) + (pair & 3); }
+// Where pair `pair` of message j stands in an exchange vector: [step of 16 pairs][half][group][message][pair of the half],
+// a group being the 4 pairs (8 columns) that a lane of the matrix instruction takes and a half two of them.  So what the
+// lanes of a wavefront ask for with one instruction - a half of a step, 16 bytes a lane - is one contiguous piece of memory.
+// With the 4 pairs of a group next to each other, 32 bytes a lane in two instructions, each instruction touched all lines of
+// the step and used half of every one.
+__device__ __forceinline__ int vec_word(int pair, int j, int m) {
+  return ((((((pair >> 4) << 1) + ((pair >> 1) & 1)) * 4 + ((pair >> 2) & 3)) * m + j) << 1) + (pair & 1);
+}
 
 // Wavefront records -> split partial, or the finished output when there is one split; the last workgroup of a head
 // group to arrive folds the splits in split order (as attn_finish in step_impl.h).  The output leaves as bf16 pairs.
@@ -548,6 +553,34 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         const Item it = item_at(tid < n_items ? tid : 0);
         ops = ops_of(it, tid < n_items && it.r1 < N);
       }
+      // The vectors: steps of 32 columns, 32 bytes per lane and step, eight steps at a time; steps past the slice repeat its
+      // last one (the second four read nothing if the slice has no more than four).
+      const bool two = nks > 8, half8 = nks > 4;                    // two tiles per block, else one
+      const Buffer vb = buffer_at(up ? a.xn[1] : a.xn[0]);
+      const bool has = n < m && nks > 0;
+      const uint32_t v_off = has ? (uint32_t)(kg * m + n) * 16u : kNowhere;
+      const uint32_t v_step = (uint32_t)m * 128u, v_base = (uint32_t)ks0 * v_step;
+      u32x4 raw[16];
+      auto ask_vec = [&](int k0) __attribute__((always_inline)) {
+        const uint32_t o = fresh(v_off), o4 = half8 ? o : kNowhere;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t u = v_base + (uint32_t)max(min(k0 + k, nks - 1), 0) * v_step;
+          raw[2 * k] = ld_two(vb, k < 4 ? o : o4, u); raw[2 * k + 1] = ld_two(vb, k < 4 ? o : o4, u + (v_step >> 1));
+        }
+      };
+      auto await_vec = [&](int k0) __attribute__((always_inline)) {
+        poll_while([&]() {
+          uint32_t bad = 0, bad4 = 0;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            bad |= (raw[k].y ^ epoch) | (raw[k].w ^ epoch);
+            bad4 |= (raw[8 + k].y ^ epoch) | (raw[8 + k].w ^ epoch);
+          }
+          return has && (bad | (half8 ? bad4 : 0u)) != 0;
+        }, [&]() { ask_vec(k0); }, a.spin_limit, a.err);
+      };
+      ask_vec(0);
       // the first two tiles of weights
       Tile A, B;
       const Buffer wb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.W + w_off), 0, (int)P.bytes, 0x00020000);
@@ -556,7 +589,6 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       auto issue = [&](Tile& t, int lb, int h8) __attribute__((always_inline)) {
         w_issue(t, wb, w_lane, (uint32_t)(first_row(lb * nwg + wg) * rb + ks0 * 64 + h8 * 512), lb < nb ? nks - 8 * h8 : 0);
       };
-      const bool two = nks > 8;                                     // two tiles per block, else one
       issue(A, 0, 0); issue(B, two ? 0 : 1, two ? 1 : 0);
       bstamp(a, layer, ph, 1);
       // ---- Vectors of more than kWatchWords words are looked at only after every workgroup's first sum of
@@ -589,38 +621,21 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           sum1 += __uint_as_float(one[0].x) + __uint_as_float(one[0].z);
         }
       }
-      // the vectors: steps of 32 columns, 32 bytes per lane and step; steps past the slice repeat its last one
       u32x4 Bv[kResSteps];
-      const Buffer vb = buffer_at(up ? a.xn[1] : a.xn[0]);
-      const bool has = n < m && nks > 0;
-      const uint32_t v_off = has ? (uint32_t)(kg * m + n) * 32u : kNowhere;
-      const uint32_t v_step = (uint32_t)m * 128u, v_base = (uint32_t)ks0 * v_step;
-      auto fetch = [&](auto first, auto count) __attribute__((always_inline)) {
-        constexpr int k0 = decltype(first)::value, kn = decltype(count)::value;
-        u32x4 raw[2 * kn];
-        auto ask = [&]() __attribute__((always_inline)) {
-          const uint32_t o = fresh(v_off);
+      auto take = [&](auto first) __attribute__((always_inline)) {
+        constexpr int k0 = decltype(first)::value;
+        await_vec(k0);
 #pragma unroll
-          for (int k = 0; k < kn; ++k) {
-            const uint32_t u = v_base + (uint32_t)max(min(k0 + k, nks - 1), 0) * v_step;
-            raw[2 * k] = ld_two(vb, o, u); raw[2 * k + 1] = ld_two(vb, o + 16, u);
-          }
-        };
-        ask();
-        await_two(raw, ask, has, epoch, a.spin_limit, a.err);
-#pragma unroll
-        for (int k = 0; k < kn; ++k) Bv[k0 + k] = u32x4{raw[2 * k].x, raw[2 * k].z, raw[2 * k + 1].x, raw[2 * k + 1].z};
+        for (int k = 0; k < 8; ++k) Bv[k0 + k] = u32x4{raw[2 * k].x, raw[2 * k].z, raw[2 * k + 1].x, raw[2 * k + 1].z};
       };
-      auto none = [&](auto first, auto count) __attribute__((always_inline)) {
-        constexpr int k0 = decltype(first)::value, kn = decltype(count)::value;
+      take(std::integral_constant<int, 0>());
+      if (two) {
+        ask_vec(8);
+        take(std::integral_constant<int, 8>());
+      } else {
 #pragma unroll
-        for (int k = 0; k < kn; ++k) Bv[k0 + k] = Bv[0];
-      };
-      constexpr std::integral_constant<int, 0> c0{}; constexpr std::integral_constant<int, 4> c4{};
-      constexpr std::integral_constant<int, 8> c8{}; constexpr std::integral_constant<int, 12> c12{};
-      fetch(c0, c4);
-      if (nks > 4) fetch(c4, c4); else none(c4, c4);
-      if (nks > 8) { fetch(c8, c4); fetch(c12, c4); } else { none(c8, c4); none(c12, c4); }
+        for (int k = 8; k < kResSteps; ++k) Bv[k] = Bv[0];
+      }
       bstamp(a, layer, ph, 2);
       // ---- the stream: two tiles in flight, each multiplied while the other's rows arrive
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -667,6 +682,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           rcen[sj] = mean;                                          // what the next norm's vector is published around
         }
       }
+      loads_done();
       __syncthreads();                                              // every wavefront's partial products are in LDS
       bstamp(a, layer, ph, 4);
       // ---- epilogue: one thread per (block, message, row pair or quad)
@@ -765,6 +781,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
           const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
           attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, V, kv, nte, wave, part);
         }
+        loads_done();
         if (item == wg) bstamp(a, layer, ph, 3);
         attn_to_lds<WT, G>(st, ga, a.h, part, wave);
         attn_finish_pairs<G>(ga, a, V, part, s_flag, epoch, tid);
@@ -798,20 +815,21 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       const int ktot = rb >> 6, k0 = min(ks_s * c, ktot), nk = ks_q < a.str_oct ? max(0, min(c, ktot - ks_s * c)) : 0;   // column steps of the slice
       const int blk = ks_q * kStepWaves + wave;                     // this wavefront's block
       const bool has = ks_q < a.str_oct && blk < nblk, live = has && nk > 0;
-      // the slice of every message's vector to LDS; unit: eight columns of one message
+      // the slice of every message's vector to LDS, by pieces of four columns of one message (see vec_word)
       const Buffer vb = buffer_at(down ? a.ub : a.ob);
-      const int n_units = nk * 4 * m;
+      const int n_pieces = nk * 8 * m;
       const uint32_t v_base = (uint32_t)k0 * (uint32_t)m * 128u;
-      u32x4 raw[2][4];
-      auto ask = [&](u32x4 (&r)[4], int u) __attribute__((always_inline)) {
+      constexpr int kAsk = 4;                                       // pieces of a thread that are asked for together
+      u32x4 raw[2][kAsk];
+      auto ask = [&](u32x4 (&r)[kAsk], int u) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const uint32_t o = fresh(u + k * kStepThreads < n_units ? (uint32_t)(u + k * kStepThreads) * 32u : kNowhere);
-          r[2 * k] = ld_two(vb, o, v_base); r[2 * k + 1] = ld_two(vb, o + 16, v_base);
+        for (int k = 0; k < kAsk; ++k) {
+          const int uk = u + k * kStepThreads;
+          r[k] = ld_two(vb, fresh(uk < n_pieces ? (uint32_t)uk * 16u : kNowhere), v_base);
         }
       };
       ask(raw[0], tid);
-      ask(raw[1], tid + 2 * kStepThreads);
+      ask(raw[1], tid + kAsk * kStepThreads);
       // the rows this workgroup owns: what their epilogue needs
       const int j = tid >> 3, p = tid & 7, r0 = wg * 16 + 2 * p;
       const bool mine = j < m && r0 < a.d, last = down && layer == a.n_layer - 1;
@@ -829,29 +847,28 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       issue(B, 1);
       bstamp(a, layer, ph, 1);
       char* Bs = reinterpret_cast<char*>(part);
-      auto stage = [&](u32x4 (&r)[4], int u) __attribute__((always_inline)) {
-        // (pieces past the last unit are zeros: only a thread with none of a piece may skip its counter)
-        const bool l0 = u < n_units, l1 = u + kStepThreads < n_units;
+      auto stage = [&](u32x4 (&r)[kAsk], int u) __attribute__((always_inline)) {
+        if (u - tid >= n_pieces) return;                            // uniform
         poll_while([&]() {
-          const uint32_t bad0 = (r[0].y ^ epoch) | (r[0].w ^ epoch) | (r[1].y ^ epoch) | (r[1].w ^ epoch);
-          const uint32_t bad1 = (r[2].y ^ epoch) | (r[2].w ^ epoch) | (r[3].y ^ epoch) | (r[3].w ^ epoch);
-          return (l0 && bad0 != 0) || (l1 && bad1 != 0);
+          bool bad = false;
+#pragma unroll
+          for (int k = 0; k < kAsk; ++k) bad |= u + k * kStepThreads < n_pieces && ((r[k].y ^ epoch) | (r[k].w ^ epoch)) != 0;
+          return bad;
         }, [&]() { ask(r, u); }, a.spin_limit, a.err);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int uk = u + k * kStepThreads, gi = (int)__umulhi((unsigned)uk, a.m_magic), nm = uk - gi * m;
-          if (uk < n_units) *reinterpret_cast<u32x4*>(Bs + gi * 256 + ((nm ^ (gi & 15)) << 4)) = u32x4{r[2 * k].x, r[2 * k].z, r[2 * k + 1].x, r[2 * k + 1].z};
+        for (int k = 0; k < kAsk; ++k) {
+          const int uk = u + k * kStepThreads, x = (int)__umulhi((unsigned)uk, a.m_magic), nm = uk - x * m;   // x: (step, half, group)
+          const int gi = ((x >> 3) << 2) + (x & 3);
+          if (uk < n_pieces) *reinterpret_cast<u32x2*>(Bs + gi * 256 + ((nm ^ (gi & 15)) << 4) + ((x >> 2) & 1) * 8) = u32x2{r[k].x, r[k].z};
         }
       };
-      if (n_units <= 2 * kStepThreads) {
-        stage(raw[0], tid);
-      } else {
-        for (int u = tid; u < n_units; u += 4 * kStepThreads) {
-          stage(raw[0], u);
-          ask(raw[0], u + 4 * kStepThreads);
-          stage(raw[1], u + 2 * kStepThreads);
-          ask(raw[1], u + 6 * kStepThreads);
-        }
+      for (int u = tid;;) {
+        stage(raw[0], u);
+        if (u - tid + 2 * kAsk * kStepThreads < n_pieces) ask(raw[0], u + 2 * kAsk * kStepThreads);
+        stage(raw[1], u + kAsk * kStepThreads);
+        u += 2 * kAsk * kStepThreads;
+        if (u - tid >= n_pieces) break;
+        ask(raw[1], u + kAsk * kStepThreads);
       }
       __syncthreads();
       bstamp(a, layer, ph, 2);
@@ -875,6 +892,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         ks_compute(B, bs + 8192, vl, nk - t * 8 - 8, acc);
       }
       bstamp(a, layer, ph, 3);
+      loads_done();
       // the partial of (block, slice), zeros from a slice without columns, to the block's owner
       const Buffer pb = buffer_at(a.ppart);
       {

@@ -128,6 +128,11 @@ __device__ __forceinline__ float* lds_red() { extern __shared__ float smem[]; re
 __device__ __forceinline__ float* lds_part() { extern __shared__ float smem[]; return smem + kLdsPart; }
 __device__ __forceinline__ float* lds_vec(int part_floats) { extern __shared__ float smem[]; return smem + kLdsPart + part_floats; }
 
+// Waits for every load of this wavefront, those of no interest any more (a stream's tiles past its end) too: placed before a
+// phase's results are stored.  A register that such a load may still write is waited for when it is next used, at the start
+// of the next phase, and by then that means waiting for the stores as well: they share the counter with the loads.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
 // N words at once, asked for again until all of a thread's carry the counter `tag`: one round trip however many were
 // early (word by word, eight early words cost eight).  Asked for before a phase's weights, awaited after: loads return
 // in order, and the workgroup that everybody waits for finds its words there.

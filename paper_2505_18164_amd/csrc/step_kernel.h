@@ -161,6 +161,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         stamp(a, S, layer, ph, 2);
         const int nte = ((ga.n_k + kTile - 1) / kTile + 1) & ~1;
         attn_stream<WT, G>(st, A, B, pgA, pgB, ga, a, S, kv, nte, wave, xs);
+        loads_done();
         stamp(a, S, layer, ph, 3);
         early_requests();
         attn_to_lds<WT, G>(st, ga, a.h, xs, wave);
@@ -220,6 +221,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
             gemv_compute<WT, true>(A, g, nte - 2, cc, wave, lane, xs, part, acc0, acc1);
             gemv_compute<WT, true>(B, g, nte - 1, cc, wave, lane, xs, part, acc0, acc1);
           }
+          loads_done();
           stamp(a, S, layer, ph, 3);
           early_requests();
           __syncthreads();                             // all wavefronts' partials are in LDS
