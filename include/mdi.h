@@ -46,15 +46,16 @@
  * (the number travels with the per-workgroup argmax candidates, so that a
  * candidate left behind by an earlier launch is never taken for a new one).
  *
- * Two tuning knobs are read from the environment when a partition is created:
+ * Three tuning knobs are read from the environment when a partition is created:
  * MDI_GROUP_CTX = context length from which, in models whose query heads share
  * kv heads in even groups, the decode kernel lets two query heads take one pass
  * over the cache together (default 4096; below it every head takes its own).
  * Results are within the parity bar either way; the order of additions differs.
  * MDI_BATCH_GROUP = 1, 2 or 4 fixes the number of query heads per attention
  * work item of mdi_decode_batch (by default chosen per call from the number of
- * messages and their contexts); used by tests to reach every variant on small
- * shapes.
+ * messages and their contexts), MDI_BATCH_WAVES = 4 or 8 the wavefronts per
+ * workgroup of its launch where the shape allows both; used by tests to reach
+ * every variant on small shapes.
  */
 #ifndef MDI_H
 #define MDI_H

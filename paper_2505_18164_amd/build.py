@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmdi.so")
 SOURCES = ["mdi_api.hip", "decode.hip", "prefill.hip", "gemm_bf16.hip", "gemm_f32.hip", "step_w4.hip", "step_w4_f32.hip",
-           "step_w8.hip", "step_w8_f32.hip", "step_batch_ln.hip", "step_batch_rms.hip", "heads.hip", "attn_prefill.hip"]
+           "step_w8.hip", "step_w8_f32.hip", "step_batch_ln.hip", "step_batch_rms.hip", "step_batch_ln_w4.hip", "step_batch_rms_w4.hip", "heads.hip", "attn_prefill.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]

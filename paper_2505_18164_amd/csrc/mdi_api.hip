@@ -37,6 +37,12 @@ struct Carver {
 
 }  // namespace
 
+// Geometry of a launch that takes several messages through one pass over the weights (plan_batch_waves).
+struct BatchPlan {
+  int waves = 0, res_c = 0, S = 0, groups = 0, R[4] = {};   // see BatchArgs
+  size_t lds = 0;
+};
+
 struct mdi_partition {
   mdi_config cfg;
   uint32_t lo, hi, flags;
@@ -98,11 +104,12 @@ struct mdi_partition {
   size_t b_vec_words = 0;
   tagged_t* b_ssq[2] = {};
   tagged_t* b_ssum[2] = {}; float* b_nc = nullptr; size_t b_nc_stride = 0;   // LayerNorm in the batched pass (BatchArgs)
-  tagged_t* b_ppart = nullptr; int b_S = 0, b_oct = 0;   // streamed products split among workgroups (plan_batch)
+  tagged_t* b_ppart = nullptr;         // partial results of the products that are split among workgroups
   unsigned b_epoch = 0;
-  int b_R[4] = {16, 16, 16, 16};
+  BatchPlan b_plan[2];                 // workgroups of eight wavefronts, of four
+  bool use_batch4 = false;             // ... the latter is possible
+  int batch_waves = 0;                 // MDI_BATCH_WAVES: wavefronts per workgroup of a batched pass (0: chosen per launch)
   int batch_group = 0;                 // MDI_BATCH_GROUP: query heads per attention work item of a batched pass (0: chosen per launch)
-  size_t b_lds = 0;
   int n_cu = 0;
   int device = 0;         // HIP device the partition was created on (index into the per-device launch chain)
 };
@@ -271,6 +278,7 @@ void plan_step(mdi_partition* p, int n_cu) {
   p->G = group % 2 == 0 ? 2 : 1;
   p->group_ctx = 4096;
   if (const char* e = getenv("MDI_GROUP_CTX")) p->group_ctx = std::max(0, atoi(e));   // tuning / test knob, see mdi.h
+  if (const char* e = getenv("MDI_BATCH_WAVES")) { const int v = atoi(e); p->batch_waves = (v == 4 || v == 8) ? v : 0; }
   if (const char* e = getenv("MDI_BATCH_GROUP")) { const int v = atoi(e); p->batch_group = (v == 1 || v == 2 || v == 4) ? v : 0; }
   p->n_hg = H;                           // the most head groups a launch has (one head each)
   p->nwg = std::min(n_cu, 1024);
@@ -288,58 +296,66 @@ void plan_step(mdi_partition* p, int n_cu) {
   p->use_step = true;
 }
 
-const void* batch_kernel(const mdi_partition* p, int G, bool scores_on_mfma) {
-  const bool swiglu = p->cfg.mlp_kind == MDI_MLP_SWIGLU;
-  return p->cfg.norm_kind == MDI_NORM_LAYERNORM ? step_batch_kernel<true>(G, scores_on_mfma, swiglu) : step_batch_kernel<false>(G, scores_on_mfma, swiglu);
+const void* batch_kernel(const mdi_partition* p, int waves, int G, bool scores_on_mfma) {
+  const bool ln = p->cfg.norm_kind == MDI_NORM_LAYERNORM, swiglu = p->cfg.mlp_kind == MDI_MLP_SWIGLU;
+  if (waves == 4) return ln ? step_batch_kernel<4, true>(G, scores_on_mfma, swiglu) : step_batch_kernel<4, false>(G, scores_on_mfma, swiglu);
+  return ln ? step_batch_kernel<8, true>(G, scores_on_mfma, swiglu) : step_batch_kernel<8, false>(G, scores_on_mfma, swiglu);
 }
 
-// Decides whether several queued messages can share one pass over the weights (step_batch.h) and lays out its LDS.
-void plan_batch(mdi_partition* p) {
+// Decides whether several queued messages can share one pass over the weights (step_batch.h) with workgroups of `waves`
+// wavefronts, and lays out its LDS.
+bool plan_batch_waves(const mdi_partition* p, int waves, BatchPlan* b) {
   const mdi_config& c = p->cfg;
-  p->use_batch = false;
-  if (!p->use_step || !p->batch_region) return;
   const int H = c.n_head, K = c.n_kv_head, h = c.head_dim, d = c.d_model, F = c.d_ff, nwg = p->nwg;
-  if (d % 32 || (H * h) % 32 || F % 32) return;                 // a column step of the matrix instruction is 32 wide
-  if (((d / 32 + kStepWavesMax - 1) / kStepWavesMax) > 16) return;   // a wavefront keeps its slice of a d-sized vector in registers
+  if (d % 32 || (H * h) % 32 || F % 32) return false;           // a column step of the matrix instruction is 32 wide
+  b->waves = waves;
+  b->res_c = (d / 32 + waves - 1) / waves;
+  if (b->res_c > 16) return false;                              // a wavefront keeps its slice of a d-sized vector in registers
   const int nup = c.mlp_kind == MDI_MLP_SWIGLU ? 2 * F : F;
   const int rows[4] = {(H + 2 * K) * h, d, nup, d};
   int nb_max = 1;
   for (int j = 0; j < 4; ++j) {
-    if ((size_t)rows[j] * (j == 1 ? H * h : j == 3 ? F : d) * 2 >= (size_t)1 << 31) return;   // offsets into a matrix are 31-bit
-
+    if ((size_t)rows[j] * (j == 1 ? H * h : j == 3 ? F : d) * 2 >= (size_t)1 << 31) return false;   // offsets into a matrix are 31-bit
     // 16 rows per block when that gives every workgroup a block, else 8 (twice the blocks to spread).  Measured on
     // the 7B shape's gate/up product (1376 blocks of 16 over 256 workgroups: 5 or 6 each): blocks of 8 balance better
     // (10 or 11 each) but every load and matrix instruction then carries half the rows, and the phase took twice as long.
     int R = (rows[j] + 15) / 16 >= nwg ? 16 : 8;
     if (j == 0 && (h / 2) % (R / 2)) R = 8;                      // a block holds R/2 rows of a half head and their partners
-    if (j == 0 && (h / 2) % (R / 2)) return;
-    if (j == 2 && c.mlp_kind == MDI_MLP_SWIGLU && rows[j] % 4) return;
-    p->b_R[j] = R;
-    const int nb = ((rows[j] + R - 1) / R + nwg - 1) / nwg;
-    nb_max = std::max(nb_max, nb);
+    if (j == 0 && (h / 2) % (R / 2)) return false;
+    if (j == 2 && c.mlp_kind == MDI_MLP_SWIGLU && rows[j] % 4) return false;
+    b->R[j] = R;
+    nb_max = std::max(nb_max, ((rows[j] + R - 1) / R + nwg - 1) / nwg);
   }
   // The two residual products (output projection, MLP down) split their inner dimension among workgroups: groups
-  // of S workgroups share eight 16-row blocks, one block per wavefront, one column slice per workgroup; the owner
-  // of a block (workgroup = block index) adds the S partial results.
-  int ks_floats = 0;
-  {
-    const int nblk = (d + 15) / 16, octets = (nblk + kStepWavesMax - 1) / kStepWavesMax;
-    if (nblk > nwg) return;
-    const int S = std::min(16, nwg / octets);
-    const int c_max = (std::max(H * h, F) / 32 + S - 1) / S;     // column steps of the longest slice: 1 KiB of LDS each
-    p->b_S = S; p->b_oct = octets;
-    p->b_R[1] = p->b_R[3] = 16;
-    ks_floats = c_max * 256;
-  }
+  // of S workgroups share as many 16-row blocks as a workgroup has wavefronts, one block per wavefront, one column slice
+  // per workgroup; the owner of a block (workgroup = block index) adds the S partial results.
+  const int nblk = (d + 15) / 16;
+  if (nblk > nwg) return false;
+  b->groups = (nblk + waves - 1) / waves;
+  b->S = std::min(16, nwg / b->groups);
+  b->R[1] = b->R[3] = 16;
+  const int c_max = (std::max(H * h, F) / 32 + b->S - 1) / b->S;   // column steps of the longest slice: 1 KiB of LDS each
   const int Gmax = (H / K) % 4 == 0 ? 4 : p->G;
-  const int attn_floats = std::max(Gmax * h, kStepWavesMax * Gmax * (h + 2)) + 64;
-  const int part_floats = std::max(std::max(nb_max * 2048, attn_floats), ks_floats);
-  p->b_lds = (size_t)(kBatchLdsPart + part_floats) * sizeof(float);
-  if (p->b_lds > 160 * 1024) return;
-  if (p->b_lds > 64 * 1024)
+  const int attn_floats = std::max(Gmax * h, waves * Gmax * (h + 2)) + 64;
+  b->lds = (size_t)(kBatchLdsPart + std::max(std::max(nb_max * waves * 256, attn_floats), c_max * 256)) * sizeof(float);
+  if (b->lds > 160 * 1024) return false;
+  if (b->lds > 64 * 1024)
     for (int k = 0; k < 4; ++k)
-      if (hipFuncSetAttribute(batch_kernel(p, k == 3 ? 4 : 1 << k, k == 3), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->b_lds) != hipSuccess) return;
-  p->use_batch = true;
+      if (hipFuncSetAttribute(batch_kernel(p, waves, k == 3 ? 4 : 1 << k, k == 3), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->lds) != hipSuccess) return false;
+  return true;
+}
+void plan_batch(mdi_partition* p) {
+  p->use_batch = p->use_step && p->batch_region && plan_batch_waves(p, 8, &p->b_plan[0]);
+  p->use_batch4 = p->use_batch && plan_batch_waves(p, 4, &p->b_plan[1]);
+}
+// Workgroups of four wavefronts, one per SIMD, execute the instructions of a phase boundary in half the time of eight,
+// which take turns; eight hide the vectors' and the caches' loads better.  So: four where a wavefront can hold its slice of
+// a vector (d up to 2048) and the messages' vectors are short.  Measured, four layers, eight / four wavefronts, us:
+// GPT-2 3 messages 156 / 137, 16 of 512 positions 186 / 193; d = 1024 3 messages 159 / 126, 8 of 512 170 / 156, 16 of 1024
+// 219 / 211; TinyLlama 2 of 512 179 / 163, 4 of 512 185 / 183, 16 of 1024 256 / 278.
+const BatchPlan& batch_plan(const mdi_partition* p, int n) {
+  const bool four = p->batch_waves ? p->batch_waves == 4 : n * (int)p->cfg.d_model <= 8192;
+  return p->b_plan[p->use_batch4 && four ? 1 : 0];
 }
 
 // The one piece of state that partitions share (see mdi.h, "Process-wide state").  A persistent launch needs
@@ -965,18 +981,19 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   a.slot0 = p->b_slot0; a.slot_stride = (long)p->b_stride;
   a.off_q = (long)p->b_off_q; a.off_part = (long)p->b_off_part; a.off_knew = (long)p->b_off_knew; a.off_tickets = (long)p->b_off_tickets;
   a.norm_kind = (int)c.norm_kind; a.nc0 = p->b_nc; a.nc_stride = (long)p->b_nc_stride;
-  a.ppart = p->b_ppart; a.str_S = p->b_S; a.str_oct = p->b_oct;
+  const BatchPlan& bp = batch_plan(p, n);
+  a.ppart = p->b_ppart; a.str_S = bp.S; a.str_groups = bp.groups;
   const int heads = c.n_head * c.head_dim, ff = c.d_ff;
-  a.str_c[0] = (heads / 32 + p->b_S - 1) / p->b_S; a.str_c[1] = (ff / 32 + p->b_S - 1) / p->b_S;
+  a.str_c[0] = (heads / 32 + bp.S - 1) / bp.S; a.str_c[1] = (ff / 32 + bp.S - 1) / bp.S;
   const int rows[4] = {(int)((c.n_head + 2 * c.n_kv_head) * c.head_dim), (int)c.d_model, (int)(c.mlp_kind == MDI_MLP_SWIGLU ? 2 * c.d_ff : c.d_ff), (int)c.d_model};
   const int cols[4] = {(int)c.d_model, heads, (int)c.d_model, ff};
   const void* const mats[4] = {a.l0.wqkv, a.l0.wo, a.l0.wup, a.l0.wdown};
   const float* const bias[4] = {a.l0.bqkv, a.l0.bo, a.l0.bup, a.l0.bdown};
   for (int j = 0; j < 4; ++j) {
-    const int R = p->b_R[j], nblk = (rows[j] + R - 1) / R;
+    const int R = bp.R[j], nblk = (rows[j] + R - 1) / R;
     a.pr[j] = BatchProduct{mats[j], bias[j], rows[j], 2 * cols[j], (unsigned)rows[j] * 2u * (unsigned)cols[j], R, nblk / a.nwg, nblk % a.nwg};
   }
-  a.res_c = ((int)c.d_model / 32 + kStepWavesMax - 1) / kStepWavesMax;
+  a.res_c = bp.res_c;
   a.rope = p->rope;
   a.sq_stride = (a.nwg + 255) & ~255;
   a.trace = p->trace;
@@ -1002,7 +1019,7 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   a.n_items = item;
   const mdi_status st = launch_step_serialised(p, [&]() {
     void* args[] = {&a};
-    (void)hipLaunchKernel(batch_kernel(p, G, G == 4 && mfma_scores), dim3(a.nwg), dim3(64 * kStepWavesMax), args, p->b_lds, p->stream);
+    (void)hipLaunchKernel(batch_kernel(p, bp.waves, G, G == 4 && mfma_scores), dim3(a.nwg), dim3(64 * bp.waves), args, bp.lds, p->stream);
   });
   if (st != MDI_OK) return st;
   p->b_epoch += 5u * (unsigned)p->n_local;

@@ -319,8 +319,8 @@ struct BatchArgs {
   // [W_qkv g1 | W_qkv b1 | W_up g2 | W_up b2] (float), layer l's at nc0 + l * nc_stride floats
   int norm_kind; tagged_t* ssum[2]; const float* nc0; long nc_stride;
   // products split among workgroups along the inner dimension: partials [block][S][4 row quads][m][4 rows], slices per
-  // block, block octets, column steps of a slice (output projection, MLP down)
-  tagged_t* ppart; int str_S, str_oct, str_c[2];
+  // block, groups of as many blocks as a workgroup has wavefronts, column steps of a slice (output projection, MLP down)
+  tagged_t* ppart; int str_S, str_groups, str_c[2];
   int n_items;                       // attention work items of the launch
   unsigned long long* trace;         // optional [workgroup][n_layer][5][8] timestamps (100 MHz ticks), or nullptr
   BatchSlot s[kMaxBatch];
@@ -342,9 +342,11 @@ void launch_logits_batch(hipStream_t s, int nwg, size_t lds_bytes, const LogitsB
 
 // The kernel for a norm (kLn: LayerNorm, else RMSNorm).  G: query heads per attention work item; scores_on_mfma: on the matrix
 // cores (G = 4, heads of 128, pages of a multiple of 16 positions)
-template <bool kLn> const void* step_batch_kernel(int G, bool scores_on_mfma, bool swiglu);
-template <> const void* step_batch_kernel<true>(int G, bool scores_on_mfma, bool swiglu);
-template <> const void* step_batch_kernel<false>(int G, bool scores_on_mfma, bool swiglu);
+template <int kWaves, bool kLn> const void* step_batch_kernel(int G, bool scores_on_mfma, bool swiglu);
+template <> const void* step_batch_kernel<8, true>(int G, bool scores_on_mfma, bool swiglu);
+template <> const void* step_batch_kernel<8, false>(int G, bool scores_on_mfma, bool swiglu);
+template <> const void* step_batch_kernel<4, true>(int G, bool scores_on_mfma, bool swiglu);
+template <> const void* step_batch_kernel<4, false>(int G, bool scores_on_mfma, bool swiglu);
 
 // ---- set-up ---------------------------------------------------------------
 void launch_rope_table(hipStream_t s, float2* table, int max_ctx, int h, double base);

@@ -56,7 +56,7 @@
 #include "step_mfma.h"
 
 namespace mdi {
-namespace step_w8 {
+namespace MDI_STEP_CAT(step_w, MDI_STEP_WAVES) {
 
 // What the attention helpers of step_impl.h read of a message.
 struct BatchView {
@@ -102,6 +102,7 @@ __device__ __forceinline__ f32x4 mac(const u32x4& w, const u32x4& v, f32x4 acc) 
 }
 
 constexpr int kWatchWords = 2048;
+constexpr int kTiles = 2;              // weight tiles a wavefront has on their way
 constexpr int kResSteps = 16;          // column steps a wavefront can keep: widths up to 8 * 16 * 32 = 4096
 // Eight steps of a normed product, the second operand in registers; n as in w_issue.
 template <int HALF>
@@ -378,7 +379,7 @@ __device__ __forceinline__ void publish_sum(float v, int p, tagged_t* row, int w
 
 // G query heads per attention work item; kScoresOnMfma: see Attn4 (G = 4).
 template <int G, bool kScoresOnMfma, bool kLn, bool kSwiglu>
-__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_batch(BatchArgs a0) {
+__global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kStepWaves / 4, kStepWaves / 4))) void k_step_batch(BatchArgs a0) {
   typedef bf16_t WT;
   extern __shared__ float smem[];
   __shared__ BatchLds sl;
@@ -498,20 +499,21 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         gate = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sqb, (int)fresh(long_vec && w < stride ? (uint32_t)w * 8u + 4u : kNowhere), 0, kAgentScope);
       };
       ask_gate(tid);
-      // the sums: 32 threads per message, eight words each
-      const int sj = tid >> 5, sc = tid & 31;
+      // the sums: 2 kStepWaves... threads per message, all 256 words in their first pieces
+      constexpr int kSumThreads = kStepThreads / kMaxBatch, kSumPieces = 128 / kSumThreads;
+      const int sj = tid / kSumThreads, sc = tid % kSumThreads;
       const bool sums = sj < m;
       const uint32_t s_off = sums ? (uint32_t)(sj * stride + 2 * sc) * 8u : kNowhere;
-      u32x4 sq[4], sm[4];
+      u32x4 sq[kSumPieces], sm[kSumPieces];
       auto ask_sq = [&]() __attribute__((always_inline)) {
         const uint32_t o = fresh(s_off);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) sq[k] = ld_two(sqb, o + k * 512, 0);
+        for (int k = 0; k < kSumPieces; ++k) sq[k] = ld_two(sqb, o + k * kSumThreads * 16, 0);
       };
       auto ask_sm = [&]() __attribute__((always_inline)) {
         const uint32_t o = fresh(s_off);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) sm[k] = ld_two(smb, o + k * 512, 0);
+        for (int k = 0; k < kSumPieces; ++k) sm[k] = ld_two(smb, o + k * kSumThreads * 16, 0);
       };
       ask_sq();
       if constexpr (kLn) ask_sm();
@@ -582,14 +584,15 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       };
       ask_vec(0);
       // the first two tiles of weights
-      Tile A, B;
+      Tile T[kTiles];
       const Buffer wb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.W + w_off), 0, (int)P.bytes, 0x00020000);
       const int wi = n & (R - 1);
       const uint32_t w_lane = (uint32_t)((up ? wi : (wi & (half - 1)) + (wi >= half ? 1 << hh_sh : 0)) * rb + (kg << 4));
       auto issue = [&](Tile& t, int lb, int h8) __attribute__((always_inline)) {
         w_issue(t, wb, w_lane, (uint32_t)(first_row(lb * nwg + wg) * rb + ks0 * 64 + h8 * 512), lb < nb ? nks - 8 * h8 : 0);
       };
-      issue(A, 0, 0); issue(B, two ? 0 : 1, two ? 1 : 0);
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) issue(T[k], two ? k >> 1 : k, two ? k & 1 : 0);
       bstamp(a, layer, ph, 1);
       // ---- Vectors of more than kWatchWords words are looked at only after every workgroup's first sum of
       // squares (which it stores last) is there: 256 workgroups that watch 32 KB each crowd out the stores they wait
@@ -605,11 +608,11 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       await_two(sq, ask_sq, sums, epoch, a.spin_limit, a.err);
       if constexpr (kLn) await_two(sm, ask_sm, sums, epoch, a.spin_limit, a.err);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < kSumPieces; ++k) {
         sum2 += __uint_as_float(sq[k].x) + __uint_as_float(sq[k].z);
         if constexpr (kLn) sum1 += __uint_as_float(sm[k].x) + __uint_as_float(sm[k].z);
       }
-      for (int w = 256 + 2 * sc; w < stride && sums; w += 64) {     // (more than 256 workgroups)
+      for (int w = 256 + 2 * sc; w < stride && sums; w += 2 * kSumThreads) {     // (more than 256 workgroups)
         u32x4 one[1];
         auto ask1 = [&](Buffer b) __attribute__((always_inline)) { one[0] = ld_two(b, fresh((uint32_t)(sj * stride + w) * 8u), 0); };
         ask1(sqb);
@@ -642,36 +645,46 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       f32x4* pw = reinterpret_cast<f32x4*>(part) + (wave << 6) + lane;
       auto put = [&](int lb) __attribute__((always_inline)) { pw[lb * (kStepWaves * 64)] = acc; acc = f32x4{0.f, 0.f, 0.f, 0.f}; };
       if (two) {
+        constexpr int kD = kTiles / 2;                              // blocks on their way
+        int lb = 0;
 #pragma nounroll
-        for (int lb = 0; lb < nb; ++lb) {
-          res_compute<0>(A, Bv, nks, acc);
-          issue(A, lb + 1, 0);
-          res_compute<1>(B, Bv, nks - 8, acc);
-          issue(B, lb + 1, 1);
-          put(lb);
+        for (; lb + kD < nb; lb += kD) {
+#pragma unroll
+          for (int b = 0; b < kD; ++b) {
+            res_compute<0>(T[2 * b], Bv, nks, acc);
+            issue(T[2 * b], lb + b + kD, 0);
+            res_compute<1>(T[2 * b + 1], Bv, nks - 8, acc);
+            issue(T[2 * b + 1], lb + b + kD, 1);
+            put(lb + b);
+          }
         }
+#pragma unroll
+        for (int b = 0; b < kD; ++b)
+          if (lb + b < nb) { res_compute<0>(T[2 * b], Bv, nks, acc); res_compute<1>(T[2 * b + 1], Bv, nks - 8, acc); put(lb + b); }
       } else {
         int lb = 0;
 #pragma nounroll
-        for (; lb + 1 < nb; lb += 2) {
-          res_compute<0>(A, Bv, nks, acc);
-          issue(A, lb + 2, 0);
-          put(lb);
-          res_compute<0>(B, Bv, nks, acc);
-          issue(B, lb + 3, 0);
-          put(lb + 1);
+        for (; lb + kTiles < nb; lb += kTiles) {
+#pragma unroll
+          for (int b = 0; b < kTiles; ++b) {
+            res_compute<0>(T[b], Bv, nks, acc);
+            issue(T[b], lb + b + kTiles, 0);
+            put(lb + b);
+          }
         }
-        if (lb < nb) { res_compute<0>(A, Bv, nks, acc); put(lb); }
+#pragma unroll
+        for (int b = 0; b < kTiles; ++b)
+          if (lb + b < nb) { res_compute<0>(T[b], Bv, nks, acc); put(lb + b); }
       }
       bstamp(a, layer, ph, 3);
       // 1/rms of every message.  The shares of all workgroups have been seen before anything of this phase is stored
       // (see the top of the file).
-      auto over32 = [&](float v) __attribute__((always_inline)) {
+      auto over_threads = [&](float v) __attribute__((always_inline)) {
         v = dpp_add<kDppXor1, 0xF>(v); v = dpp_add<kDppXor2, 0xF>(v); v = dpp_add<kDppHalfMirror, 0xF>(v); v = dpp_add<kDppMirror, 0xF>(v);
-        return v + __shfl_xor(v, 16, 64);
+        return kSumThreads == 32 ? v + __shfl_xor(v, 16, 64) : v;
       };
-      sum2 = over32(sum2);
-      if constexpr (kLn) sum1 = over32(sum1);
+      sum2 = over_threads(sum2);
+      if constexpr (kLn) sum1 = over_threads(sum1);
       if (sums && sc == 0) {
         if constexpr (!kLn) {
           rscale[sj] = 1.f / sqrtf(sum2 / (float)a.d + a.eps);
@@ -812,9 +825,9 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       const int lane = tid & 63, kg = lane >> 4, n = lane & 15;
       bstamp(a, layer, ph, 0);
       const int rb = P.row_bytes, S = a.str_S, c = a.str_c[down ? 1 : 0], nblk = (a.d + 15) >> 4;
-      const int ktot = rb >> 6, k0 = min(ks_s * c, ktot), nk = ks_q < a.str_oct ? max(0, min(c, ktot - ks_s * c)) : 0;   // column steps of the slice
+      const int ktot = rb >> 6, k0 = min(ks_s * c, ktot), nk = ks_q < a.str_groups ? max(0, min(c, ktot - ks_s * c)) : 0;   // column steps of the slice
       const int blk = ks_q * kStepWaves + wave;                     // this wavefront's block
-      const bool has = ks_q < a.str_oct && blk < nblk, live = has && nk > 0;
+      const bool has = ks_q < a.str_groups && blk < nblk, live = has && nk > 0;
       // the slice of every message's vector to LDS, by pieces of four columns of one message (see vec_word)
       const Buffer vb = buffer_at(down ? a.ub : a.ob);
       const int n_pieces = nk * 8 * m;
@@ -839,12 +852,12 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
       auto two_at = [&](Buffer b) __attribute__((always_inline)) { return __builtin_amdgcn_raw_buffer_load_b64(b, (int)o0, 0, 0); };
       const u32x2 bias = two_at(biasb), gain = two_at(gainb);
       // weights
-      Tile A, B;
+      Tile T[kTiles];
       const Buffer wb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)P.W + w_off), 0, (int)P.bytes, 0x00020000);
       const uint32_t w_lane = (uint32_t)(n * rb + (kg << 4)), w_base = (uint32_t)(blk * 16 * rb + k0 * 64);
       auto issue = [&](Tile& t, int ti) __attribute__((always_inline)) { w_issue(t, wb, w_lane, w_base + ti * 512, live ? nk - ti * 8 : 0); };
-      issue(A, 0);
-      issue(B, 1);
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) issue(T[k], k);
       bstamp(a, layer, ph, 1);
       char* Bs = reinterpret_cast<char*>(part);
       auto stage = [&](u32x4 (&r)[kAsk], int u) __attribute__((always_inline)) {
@@ -881,15 +894,13 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         const int nt = (nk + 7) >> 3;
         int t = 0;
 #pragma nounroll
-        for (; t + 2 < nt; t += 2) {
-          ks_compute(A, bs, vl, 8, acc);
-          issue(A, t + 2);
-          ks_compute(B, bs + 8192, vl, 8, acc);
-          issue(B, t + 3);
-          bs += 16384;
+        for (; t + kTiles < nt; t += kTiles) {
+#pragma unroll
+          for (int k = 0; k < kTiles; ++k) { ks_compute(T[k], bs + k * 8192, vl, 8, acc); issue(T[k], t + k + kTiles); }
+          bs += kTiles * 8192;
         }
-        ks_compute(A, bs, vl, nk - t * 8, acc);
-        ks_compute(B, bs + 8192, vl, nk - t * 8 - 8, acc);
+#pragma unroll
+        for (int k = 0; k < kTiles; ++k) ks_compute(T[k], bs + k * 8192, vl, nk - (t + k) * 8, acc);
       }
       bstamp(a, layer, ph, 3);
       loads_done();
@@ -957,18 +968,18 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
   }
 }
 
-}  // namespace step_w8
+}  // namespace step_w<waves>
 
-namespace step_w8 {
+namespace MDI_STEP_CAT(step_w, MDI_STEP_WAVES) {
 template <bool kLn, bool kSwiglu> const void* step_batch_kernel(int G, bool scores_on_mfma) {
   if (G == 4) return scores_on_mfma ? (const void*)k_step_batch<4, true, kLn, kSwiglu> : (const void*)k_step_batch<4, false, kLn, kSwiglu>;
   return G == 2 ? (const void*)k_step_batch<2, false, kLn, kSwiglu> : (const void*)k_step_batch<1, false, kLn, kSwiglu>;
 }
-}  // namespace step_w8
+}  // namespace step_w<waves>
 
 // The kernel of a norm: G query heads per attention work item, their scores on the matrix cores (G = 4) or not, MLP kind.
-template <> const void* step_batch_kernel<MDI_BATCH_LN>(int G, bool scores_on_mfma, bool swiglu) {
-  return swiglu ? step_w8::step_batch_kernel<MDI_BATCH_LN, true>(G, scores_on_mfma) : step_w8::step_batch_kernel<MDI_BATCH_LN, false>(G, scores_on_mfma);
+template <> const void* step_batch_kernel<MDI_STEP_WAVES, MDI_BATCH_LN>(int G, bool scores_on_mfma, bool swiglu) {
+  return swiglu ? MDI_STEP_CAT(step_w, MDI_STEP_WAVES)::step_batch_kernel<MDI_BATCH_LN, true>(G, scores_on_mfma) : MDI_STEP_CAT(step_w, MDI_STEP_WAVES)::step_batch_kernel<MDI_BATCH_LN, false>(G, scores_on_mfma);
 }
 
 }  // namespace mdi

@@ -3,7 +3,7 @@
 #include "step_impl.h"
 
 namespace mdi {
-namespace step_w8 {
+namespace MDI_STEP_CAT(step_w, MDI_STEP_WAVES) {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -26,5 +26,5 @@ __device__ __forceinline__ uint32_t settle_bits(const tagged_t* p, tagged_t u, u
   return (uint32_t)u;
 }
 
-}  // namespace step_w8
+}  // namespace step_w<waves>
 }  // namespace mdi
