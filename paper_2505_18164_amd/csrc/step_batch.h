@@ -449,6 +449,31 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
   }
   __syncthreads();
 
+  // The page numbers of this workgroup's first attention item's first two tiles: the same in every layer, and in every layer
+  // a round trip before the first key can be asked for.
+  constexpr int kPages = kScoresOnMfma ? 1 : kTile;
+  int page0A[kPages] = {}, page0B[kPages] = {};
+  auto item_of = [&](int item, int& slot) __attribute__((always_inline)) {
+    const BatchArgs& a = args_again<BatchArgs>();
+    const int lane = threadIdx.x & 63;
+    slot = __popcll(__ballot(lane < m && item >= sl.item_lo[min(lane, m - 1)])) - 1;
+    return item - a.s[slot].item_lo;
+  };
+  if (wg < a0.n_items) {
+    const BatchArgs& a = args_again<BatchArgs>();
+    int slot;
+    const int at = item_of(wg, slot), lane = threadIdx.x & 63;
+    const BatchView V = view_of(a, slot, a.ob);
+    const AttnGeo ga = make_attn_geo<WT, G>(a, V, at, wave, lane);
+    if constexpr (kScoresOnMfma) {
+      Attn4 s4;
+      s4.n_t = max(ga.s1p - ga.s0 + 15, 0) >> 4;
+      page0A[0] = attn4_page(ga, s4, V, 0, wave); page0B[0] = attn4_page(ga, s4, V, 1, wave);
+    } else {
+      attn_pages(page0A, ga, a, V, 0, wave); attn_pages(page0B, ga, a, V, 1, wave);
+    }
+  }
+
   const int ks_q = wg / a0.str_S, ks_s = wg - ks_q * a0.str_S;
   long w_off = 0, kv_off = 0, nc_off = 0;        // bytes from the first layer's matrices / pages / corrections to this layer's
   unsigned epoch = a0.epoch0;                    // what the phase that runs expects its input's words to carry; it writes epoch + 1
@@ -768,9 +793,10 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
       bstamp(a, layer, ph, 0);
       for (int item = wg; item < a.n_items; item += nwg) {
         if (item != wg) __syncthreads();                            // the records in LDS have been read
-        const int slot = __popcll(__ballot(lane < m && item >= sl.item_lo[min(lane, m - 1)])) - 1;
+        int slot;
+        const int at = item_of(item, slot);
         const BatchView V = view_of(a, slot, a.ob);
-        const AttnGeo ga = make_attn_geo<WT, G>(a, V, item - a.s[slot].item_lo, wave, lane);
+        const AttnGeo ga = make_attn_geo<WT, G>(a, V, at, wave, lane);
         AttnState<WT, G> st;
         AttnAsk<WT> ask;
         Tile A, B;
@@ -778,7 +804,8 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
         if constexpr (kScoresOnMfma) {
           Attn4 s4;
           s4.n_t = max(ga.s1p - ga.s0 + 15, 0) >> 4;
-          int pgA = attn4_page(ga, s4, V, 0, wave), pgB = attn4_page(ga, s4, V, 1, wave);
+          int pgA = page0A[0], pgB = page0B[0];
+          if (item != wg) { pgA = attn4_page(ga, s4, V, 0, wave); pgB = attn4_page(ga, s4, V, 1, wave); }
           attn4_issue(A, pgA, ga, s4, a, V, kv, 0, wave, lane); attn4_issue(B, pgB, ga, s4, a, V, kv, 1, wave, lane);
           if (item == wg) bstamp(a, layer, ph, 1);
           attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);
@@ -786,7 +813,9 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
           attn4_stream(s4, st, A, B, pgA, pgB, ga, a, V, kv, wave, lane, part);
         } else {
           int pgA[kTile], pgB[kTile];
-          attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave);
+#pragma unroll
+          for (int k = 0; k < kTile; ++k) { pgA[k] = page0A[k % kPages]; pgB[k] = page0B[k % kPages]; }
+          if (item != wg) { attn_pages(pgA, ga, a, V, 0, wave); attn_pages(pgB, ga, a, V, 1, wave); }
           attn_issue<WT>(A, pgA, ga, a, V, kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, V, kv, 1, wave);
           if (item == wg) bstamp(a, layer, ph, 1);
           attn_begin<WT, G>(st, ask, ga, a, V, part, wave, epoch, tid);

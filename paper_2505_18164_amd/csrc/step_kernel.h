@@ -93,6 +93,15 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
     }
   };
 
+  // The page numbers of the first two tiles of attention: the same in every layer, and in every layer a round trip before the
+  // first key can be asked for.  (Several messages: their streams cover it.)
+  int page0A[kTile] = {}, page0B[kTile] = {};
+  if constexpr (kOne) {
+    const StepArgs& a = args_again<StepArgs>();
+    const AttnGeo ga = make_attn_geo<WT, G>(a, a.s[0], wg, wave, threadIdx.x & 63);
+    attn_pages(page0A, ga, a, a.s[0], 0, wave); attn_pages(page0B, ga, a, a.s[0], 1, wave);
+  }
+
   auto phase = [&](auto ph_const) __attribute__((always_inline)) -> bool {
     constexpr int ph = decltype(ph_const)::value;
     constexpr bool normed = ph == PH_QKV || ph == PH_UP, resid = ph == PH_OPROJ || ph == PH_DOWN, fused_rms = normed && !kLn;
@@ -153,7 +162,12 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
         Tile A, B;
         int pgA[kTile], pgB[kTile];                  // page numbers of the tiles that go into A and B next
         attn_ask<WT, G>(ask, ga, a, S, wave, tid);
-        attn_pages(pgA, ga, a, S, 0, wave); attn_pages(pgB, ga, a, S, 1, wave);
+        if constexpr (kOne) {
+#pragma unroll
+          for (int k = 0; k < kTile; ++k) { pgA[k] = page0A[k]; pgB[k] = page0B[k]; }
+        } else {
+          attn_pages(pgA, ga, a, S, 0, wave); attn_pages(pgB, ga, a, S, 1, wave);
+        }
         attn_issue<WT>(A, pgA, ga, a, S, kv, 0, wave); attn_issue<WT>(B, pgB, ga, a, S, kv, 1, wave);
         stamp(a, S, layer, ph, 1);
         take_pace();
