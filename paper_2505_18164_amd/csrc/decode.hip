@@ -229,7 +229,10 @@ __global__ __launch_bounds__(kBlock) void k_gemv(GemvArgs a) {
 // at k = 50.  Instead: the k-th largest of the threads' own maxima is a lower bound for the k-th largest logit (the
 // threads' elements are disjoint), so a second look at the logits keeps the few that reach it (on average k times
 // 1.03 of them), and a candidate's rank is the number of better candidates: 33 us for the same draw, two passes over
-// half a megabyte per sample by one workgroup each and about 10 us of selection between and after them.
+// half a megabyte per sample by one workgroup each and about 10 us of selection between and after them.  Behind the shared
+// vocabulary pass the first look has been had: each of its wavefronts leaves the best logit of its rows, and only the rows
+// of the wavefronts whose best reaches the bound - about 50 of 2048 at k = 50 - are read (Peaks): 16 us, the most of it the
+// chain of selections.
 __device__ __forceinline__ uint32_t philox4x32_10_first(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1) {
   for (int r = 0; r < 10; ++r) {
     if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
@@ -301,7 +304,12 @@ __device__ void topk_rounds(const SampleArgs& a, float* cv, int* ci, float* rv, 
   }
 }
 
-__device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
+// The best logits of n disjoint groups that make up the sample's: group g = the rows of blocks g, g + n, g + 2 n ... of 16
+// rows (v == nullptr: not known).
+struct Peaks { const float* v; int n; };
+constexpr int kTopkHot = 256;            // groups that may reach the bound; more and the logits are all looked at
+
+__device__ __forceinline__ void sample_topk_body(const SampleArgs& a, const Peaks& pk) {
   __shared__ float cv[kMaxTopK];
   __shared__ int ci[kMaxTopK];
   __shared__ float cand_v[kTopkCand];
@@ -309,17 +317,22 @@ __device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
   __shared__ uint32_t keys[kTopkThreads];
   __shared__ float rv[16];
   __shared__ int ri[16];
-  __shared__ int s_win, s_n;
+  __shared__ int s_win, s_n, s_hot, hot[kTopkHot];
   __shared__ uint32_t s_bound;
   const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) { s_n = 0; s_bound = 1u; }                        // a short vocabulary: everything is a candidate
+  if (tid == 0) { s_n = 0; s_hot = 0; s_bound = 1u; }             // a short vocabulary: everything is a candidate
+  const bool peaks = pk.v && a.V > kTopkCand && pk.n >= kTopkThreads;
   if (a.V > kTopkCand) {                                          // then at least 256 threads own an element, k is at most 64
     float best = -INFINITY;
-    each_logit(a.logits, a.V, [&](float v, int) { best = fmaxf(best, v); });   // (fmaxf drops a NaN)
+    if (peaks) {                                                  // (at least 65 groups have rows: V > 1024)
+      for (int g = tid; g < pk.n; g += kTopkThreads) best = fmaxf(best, pk.v[g]);
+    } else {
+      each_logit(a.logits, a.V, [&](float v, int) { best = fmaxf(best, v); });   // (fmaxf drops a NaN)
+    }
     keys[tid] = rank_key(best);
     __syncthreads();
     if (tid < 64) {
-      // bit by bit, the largest number that at least k of the threads' maxima reach
+      // bit by bit, the largest number that at least k of the threads' maxima reach, or one that a few more do
       uint32_t mine[kTopkThreads / 64];
 #pragma unroll
       for (int j = 0; j < kTopkThreads / 64; ++j) mine[j] = keys[lane + 64 * j];
@@ -330,18 +343,35 @@ __device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
 #pragma unroll
         for (int j = 0; j < kTopkThreads / 64; ++j) reach += __popcll(__ballot(mine[j] >= trial));
         if (reach >= a.k) bound = trial;
+        if (reach >= a.k && reach <= a.k + 4) break;
       }
       if (lane == 0) s_bound = bound ? bound : 1u;
     }
   }
   __syncthreads();
   const uint32_t bound = s_bound;
-  each_logit(a.logits, a.V, [&](float v, int i) {
+  auto look = [&](float v, int i) {
     if (rank_key(v) >= bound) {
       const int at = atomicAdd(&s_n, 1);                          // any order: the ranks decide
       if (at < kTopkCand) { cand_v[at] = v; cand_i[at] = i; }
     }
-  });
+  };
+  if (peaks) {
+    for (int g = tid; g < pk.n; g += kTopkThreads)
+      if (rank_key(pk.v[g]) >= bound) {
+        const int at = atomicAdd(&s_hot, 1);
+        if (at < kTopkHot) hot[at] = g;
+      }
+    __syncthreads();
+  }
+  const int n_hot = s_hot;
+  if (peaks && n_hot <= kTopkHot) {
+    // a wavefront per group, four of its blocks at a time
+    for (int h = tid >> 6; h < n_hot; h += kTopkThreads / 64)
+      for (long row = (long)(hot[h] + (lane >> 4) * pk.n) * 16 + (lane & 15); row < a.V; row += 64L * pk.n) look(a.logits[row], (int)row);
+  } else {
+    each_logit(a.logits, a.V, look);
+  }
   __syncthreads();
   const int n = s_n;
   if (n < a.k || n > kTopkCand) {
@@ -367,12 +397,12 @@ __device__ __forceinline__ void sample_topk_body(const SampleArgs& a) {
     if (lane == 0) *a.token_out = ci[past ? __ffsll((long long)past) - 1 : a.k - 1];
   }
 }
-__global__ __launch_bounds__(1024) void k_sample_topk(SampleArgs a) { sample_topk_body(a); }
+__global__ __launch_bounds__(1024) void k_sample_topk(SampleArgs a) { sample_topk_body(a, Peaks{nullptr, 0}); }
 // one workgroup per sample of a batch: sample j works on row j of the logits with its own counter
 __global__ __launch_bounds__(1024) void k_sample_topk_batch(SampleBatchArgs b) {
   const int j = blockIdx.x;
   const SampleArgs a{b.logits + (long)j * b.stride, b.V, b.k, b.inv_t, b.ctr0[j], b.ctr1[j], b.key0, b.key1, b.token_out + j};
-  sample_topk_body(a);
+  sample_topk_body(a, Peaks{b.peaks + (long)j * b.n_peaks, b.n_peaks});
 }
 void launch_sample_topk(hipStream_t s, const SampleArgs& a) { hipLaunchKernelGGL(k_sample_topk, dim3(1), dim3(1024), 0, s, a); }
 void launch_sample_topk_batch(hipStream_t s, int m, const SampleBatchArgs& a) { hipLaunchKernelGGL(k_sample_topk_batch, dim3(m), dim3(1024), 0, s, a); }

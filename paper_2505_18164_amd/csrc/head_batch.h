@@ -180,6 +180,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(2,
     if (better_logit(ov, oi, bv, bi)) { bv = ov; bi = oi; }
   }
   if (lane < 16) { sv[wave][lane] = bv; si[wave][lane] = bi; }
+  if (a.peaks && lane < a.m) a.peaks[(long)lane * stride_blk + blk0] = bv;    // for the draw (sample_topk_body)
   __syncthreads();
   // Candidates cross workgroups as 8-byte words that carry the call's counter (value | tag, index | tag), stored and
   // loaded at agent scope: the last workgroup to arrive reloads a word until its tag is this call's, so no fence

@@ -95,6 +95,7 @@ void launch_sample_topk(hipStream_t s, const SampleArgs& a);
 void launch_row_dots(hipStream_t s, const void* W, int N, int Kd, const float* g, const float* b, float* c1, float* c2);
 struct SampleBatchArgs {              // the same draw for up to 16 samples, one workgroup each
   const float* logits; long stride;   // row j = sample j's logits [V]
+  const float* peaks; int n_peaks;    // [m][n_peaks] what the vocabulary pass left (LogitsBatchArgs)
   int V, k; float inv_t;
   uint32_t key0, key1;
   int32_t* token_out;                 // [m]
@@ -332,6 +333,7 @@ struct LogitsBatchArgs {
   const void* x[kMaxBatch]; int m;   // activations [Kd] bf16, 16-byte aligned, one per sample
   const float* g; const float* b; int norm_kind; float eps;   // the final norm: gain, bias (LayerNorm; may be nullptr), kind
   float* out; long out_stride;       // logits: row j = sample j, [N] floats each, rows out_stride floats apart; or nullptr
+  float* peaks;                      // [m][8 * workgroups] the best logit of every wavefront's rows, or nullptr
   tagged_t* cand; unsigned tag;      // candidates [kMaxBatch][workgroups][2] as (value | tag), (index | tag); tag = this call's
   unsigned* counter;                 // arrival counter, zero between calls
   int32_t* token_out;                // [m]
