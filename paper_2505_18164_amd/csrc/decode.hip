@@ -402,7 +402,7 @@ __global__ __launch_bounds__(1024) void k_sample_topk(SampleArgs a) { sample_top
 __global__ __launch_bounds__(1024) void k_sample_topk_batch(SampleBatchArgs b) {
   const int j = blockIdx.x;
   const SampleArgs a{b.logits + (long)j * b.stride, b.V, b.k, b.inv_t, b.ctr0[j], b.ctr1[j], b.key0, b.key1, b.token_out + j};
-  sample_topk_body(a, Peaks{b.peaks + (long)j * b.n_peaks, b.n_peaks});
+  sample_topk_body(a, Peaks{b.peaks ? b.peaks + (long)j * b.n_peaks : nullptr, b.n_peaks});
 }
 void launch_sample_topk(hipStream_t s, const SampleArgs& a) { hipLaunchKernelGGL(k_sample_topk, dim3(1), dim3(1024), 0, s, a); }
 void launch_sample_topk_batch(hipStream_t s, int m, const SampleBatchArgs& a) { hipLaunchKernelGGL(k_sample_topk_batch, dim3(m), dim3(1024), 0, s, a); }

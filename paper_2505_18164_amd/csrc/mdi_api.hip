@@ -177,7 +177,7 @@ size_t carve(mdi_partition* p, void* arena) {
     if (c.dtype == MDI_BF16) {
       p->hb_cand = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 2 * sizeof(tagged_t));
       p->hb_logits = (float*)cv.take((size_t)kMaxBatch * V * 4);
-      p->hb_peaks = (float*)cv.take((size_t)kMaxBatch * 1024 * kStepWavesMax * 4);
+      p->hb_peaks = (float*)cv.take((size_t)kMaxBatch * kMaxPeaks * 4);
     }
   }
   p->counters = (unsigned*)cv.take((H + 2) * 4);
@@ -1183,18 +1183,19 @@ mdi_status mdi_sample_batch(mdi_partition* p, uint32_t n, const uint32_t* seqs, 
     const int m = (int)std::min<uint32_t>(kMaxBatch, n - i);
     float* user = logits_out ? logits_out + (size_t)i * V : nullptr;
     float* rows = user ? user : top_k > 1 ? p->hb_logits : nullptr;   // a draw needs them whether the caller does or not
+    const int n_peaks = kStepWavesMax * p->hb_nwg;
     LogitsBatchArgs a{};
     a.W = p->lm_head; a.N = (int)V; a.Kd = (int)c.d_model;
     for (int j = 0; j < m; ++j) a.x[j] = acts_in[i + j];
     a.m = m; a.g = p->lnf_g; a.b = p->lnf_b; a.norm_kind = (int)c.norm_kind; a.eps = c.norm_eps;
-    a.out = rows; a.out_stride = (long)V; a.peaks = top_k > 1 ? p->hb_peaks : nullptr;
+    a.out = rows; a.out_stride = (long)V; a.peaks = top_k > 1 && n_peaks <= kMaxPeaks ? p->hb_peaks : nullptr;
     a.cand = p->hb_cand; a.tag = next_head_tag(); a.counter = p->counters + c.n_head + 1;
     a.err = p->herr; a.spin_limit = 1 << 21;
     a.token_out = tokens_out + i;
     launch_logits_batch(p->stream, p->hb_nwg, p->hb_lds, a);
     if (top_k > 1) {
       SampleBatchArgs sb{};
-      sb.logits = rows; sb.stride = (long)V; sb.peaks = p->hb_peaks; sb.n_peaks = kStepWavesMax * p->hb_nwg; sb.V = (int)V; sb.k = (int)std::min<uint32_t>(top_k, c.vocab);
+      sb.logits = rows; sb.stride = (long)V; sb.peaks = a.peaks; sb.n_peaks = n_peaks; sb.V = (int)V; sb.k = (int)std::min<uint32_t>(top_k, c.vocab);
       sb.inv_t = 1.f / temperature; sb.key0 = (uint32_t)(seed & 0xFFFFFFFFu); sb.key1 = (uint32_t)(seed >> 32);
       sb.token_out = tokens_out + i;
       for (int j = 0; j < m; ++j) { sb.ctr0[j] = seqs[i + j]; sb.ctr1[j] = steps[i + j]; }

@@ -83,6 +83,7 @@ void launch_attn(hipStream_t s, int dtype, const AttnArgs& a);
 
 // ---- stochastic sampling of the output pmf (Alg. 1) -----------------------
 constexpr int kMaxTopK = 64;
+constexpr int kMaxPeaks = 2048;      // wavefronts of a vocabulary pass whose best logits are kept (eight on each of 256 compute units)
 struct SampleArgs {
   const float* logits;  // [V] fp32
   int V, k;             // k <= kMaxTopK and k <= V
@@ -95,7 +96,7 @@ void launch_sample_topk(hipStream_t s, const SampleArgs& a);
 void launch_row_dots(hipStream_t s, const void* W, int N, int Kd, const float* g, const float* b, float* c1, float* c2);
 struct SampleBatchArgs {              // the same draw for up to 16 samples, one workgroup each
   const float* logits; long stride;   // row j = sample j's logits [V]
-  const float* peaks; int n_peaks;    // [m][n_peaks] what the vocabulary pass left (LogitsBatchArgs)
+  const float* peaks; int n_peaks;    // [m][n_peaks] what the vocabulary pass left (LogitsBatchArgs), or nullptr
   int V, k; float inv_t;
   uint32_t key0, key1;
   int32_t* token_out;                 // [m]

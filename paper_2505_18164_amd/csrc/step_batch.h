@@ -10,7 +10,8 @@
 //
 // Same skeleton as k_step (one persistent launch, five phases per layer, self-validating tagged exchange), with these
 // differences:
-//   * One set of 8-wavefront workgroups, all messages in lockstep.
+//   * One set of workgroups, all messages in lockstep: of eight wavefronts, or of four where the messages' vectors are short
+//     (batch_plan in mdi_api.hip: one wavefront per SIMD executes a phase boundary's instructions without taking turns).
 //   * No barrier: a phase waits for the words it reads, by reloading those whose counter is not the writing phase's
 //     yet.  Phase counters, watched by every workgroup before it fetched the data, cost 3.2 us a round; 256
 //     workgroups that watch 2048 words of data themselves take 1.65 us from store to store.  What binds a phase of the
@@ -27,7 +28,7 @@
 //     the output projection to the up product and once from the down projection to QKV; every other vector is
 //     written at least two such points after it was last read.
 //   * Work unit of a product = a block of R (16 or 8) weight rows; blocks are dealt round-robin to workgroups; the
-//     eight wavefronts of a workgroup split the block's columns among them and their partial 16 x 16 results are
+//     wavefronts of a workgroup split the block's columns among them and their partial 16 x 16 results are
 //     added in LDS in wavefront order (deterministic, no float atomics).  RoPE partners (i, i + h/2) and SwiGLU
 //     partners (gate_f, up_f) sit in the same block, so the epilogue of a row pair needs no other workgroup.
 //   * What a phase boundary costs beyond the exchange is instructions: the two wavefronts of a SIMD issue theirs in turn.
@@ -35,9 +36,10 @@
 //     and 300 to 430 scalar registers lived in lanes of vector registers.  Now norm and MLP kind are template arguments,
 //     every phase is code of its own that loads what it needs of the arguments when it starts (85 to 108 such lanes, here
 //     and in k_step 45 to 60), words are requested two at a time through buffer descriptors and without branches, and
-//     a wavefront polls as one.  4 layers of GPT-2 with 3 messages 199 -> 174 us, TinyLlama starter with 4 634 -> 581, 8
-//     layers of the 7B shape with 8 1029 -> 979, of the 8B shape with 16 and 6144 positions 1504 -> 1419; one message
-//     (k_step): 4 fp32 GPT-2 layers with output layers 202 -> 152, 8 of the 7B shape 763 -> 704.
+//     a wavefront polls as one.  With that, with requests that no hidden wait holds up, and with workgroups of four
+//     wavefronts, per call: 4 layers of GPT-2 with 3 messages 199 -> 140 us, TinyLlama starter with 4 634 -> 572, 8 layers of
+//     the 7B shape with 8 1027 -> 956, of the 8B shape with 16 and 6144 positions 1502 -> 1390; one message (k_step): 4 fp32
+//     GPT-2 layers with output layers 202 -> 149, 8 of the 7B shape 762 -> 697.
 //   * Vectors that feed a product cross workgroups as bf16 PAIRS with the writing phase's counter in one 8-byte
 //     word, already multiplied by the gain of the RMSNorm that follows (1/rms is applied to the finished products;
 //     the sum of squares travels as one partial per workgroup and message).  Bytes exchanged per message are half
@@ -524,7 +526,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
         gate = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sqb, (int)fresh(long_vec && w < stride ? (uint32_t)w * 8u + 4u : kNowhere), 0, kAgentScope);
       };
       ask_gate(tid);
-      // the sums: 2 kStepWaves... threads per message, all 256 words in their first pieces
+      // the sums: 32 threads per message (16 in a workgroup of four wavefronts), the first 256 words at once
       constexpr int kSumThreads = kStepThreads / kMaxBatch, kSumPieces = 128 / kSumThreads;
       const int sj = tid / kSumThreads, sc = tid % kSumThreads;
       const bool sums = sj < m;
@@ -838,9 +840,9 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
 
     // ---- a product whose inner dimension is split among workgroups.  Every workgroup used to read the whole
     // vector of all messages for its one block of rows: 256 copies of it through the dies' L2s, twice the bytes of
-    // the matrix itself in the MLP down projection.  Here workgroup (q, s) takes column slice s of the eight row
-    // blocks 8 q .. 8 q + 7, one block per wavefront: it reads 1 / S of the vector - once, validated, into LDS, from
-    // where its eight wavefronts take the matrix instruction's second operand - and hands the 16 x 16 partial result
+    // the matrix itself in the MLP down projection.  Here workgroup (q, s) takes column slice s of the q-th group of row
+    // blocks, one block per wavefront: it reads 1 / S of the vector - once, validated, into LDS, from
+    // where its wavefronts take the matrix instruction's second operand - and hands the 16 x 16 partial result
     // of every block, as tagged words, to the workgroup that owns the block's residual rows, which adds the S partials
     // in slice order.
     auto split = [&](auto ph_const) __attribute__((always_inline)) -> bool {
