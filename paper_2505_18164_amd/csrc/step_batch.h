@@ -563,15 +563,18 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
       const Buffer biasb = buffer_at(P.bias ? (const char*)P.bias + w_off : nullptr);
       // LayerNorm corrections of this phase's product: [W g | W b], N floats each (QKV's first, then the up product's)
       const float* ncp = kLn ? (const float*)((const char*)a.nc0 + nc_off) + (up ? 2 * a.pr[0].N : 0) : nullptr;
-      const Buffer n0b = buffer_at(ncp), n1b = buffer_at(kLn ? ncp + N : nullptr), ropeb = buffer_at(a.rope);
+      const Buffer n0b = buffer_at(ncp), n1b = buffer_at(kLn ? ncp + N : nullptr);
+      // The table of angles may be longer than a descriptor reaches (2^31 bytes are 4 million positions of heads of 128), so
+      // its entries are loaded by address.  Without a table: any 8 bytes, not used.
+      const MDI_GLOBAL u32x2* angles = (const MDI_GLOBAL u32x2*)(a.rope ? (const void*)a.rope : P.W);
+      const long angle_mask = a.rope ? -1L : 0L;
       auto ops_of = [&](const Item& it, bool own) __attribute__((always_inline)) {
         Ops o{};
         if constexpr (quads) return o;
         const uint32_t o0 = own ? (uint32_t)it.r0 * 4u : kNowhere, o1 = own ? (uint32_t)it.r1 * 4u : kNowhere;
         o.b0 = ld_f32(biasb, o0); o.b1 = ld_f32(biasb, o1);
         if constexpr (!up) {
-          const uint32_t at = (uint32_t)((sl.pos[it.j] << hh_sh) + (it.r0 & ((1 << hh_sh) - 1))) * 8u;
-          const u32x2 cs = __builtin_amdgcn_raw_buffer_load_b64(ropeb, (int)(own ? at : kNowhere), 0, 0);
+          const u32x2 cs = angles[(((long)sl.pos[it.j] << hh_sh) + (it.r0 & ((1 << hh_sh) - 1))) & angle_mask];   // (no item: item 0's)
           o.c = __uint_as_float(cs.x); o.s = __uint_as_float(cs.y);
         }
         if constexpr (kLn) { o.n[0] = ld_f32(n0b, o0); o.n[1] = ld_f32(n0b, o1); o.n[2] = ld_f32(n1b, o0); o.n[3] = ld_f32(n1b, o1); }
