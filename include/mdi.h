@@ -46,11 +46,14 @@
  * (the number travels with the per-workgroup argmax candidates, so that a
  * candidate left behind by an earlier launch is never taken for a new one).
  *
- * Three tuning knobs are read from the environment when a partition is created:
+ * Four tuning knobs are read from the environment when a partition is created:
  * MDI_GROUP_CTX = context length from which, in models whose query heads share
  * kv heads in even groups, the decode kernel lets two query heads take one pass
  * over the cache together (default 4096; below it every head takes its own).
  * Results are within the parity bar either way; the order of additions differs.
+ * MDI_WHOLE_CTX = context length up to which the decode kernels leave a sample's
+ * context to one workgroup per head (default: 96 KiB of one head's keys and
+ * values; longer ones are split into pieces of at least 128 positions).
  * MDI_BATCH_GROUP = 1, 2 or 4 fixes the number of query heads per attention
  * work item of mdi_decode_batch (by default chosen per call from the number of
  * messages and their contexts), MDI_BATCH_WAVES = 4 or 8 the wavefronts per
@@ -392,8 +395,10 @@ MDI_API mdi_status mdi_time_kernel(mdi_partition *part, int which, uint32_t reps
  * 3 = arena bytes in use, 4 = messages one pass of mdi_decode_batch can take
  * (0: this partition forwards them one pass each), 5 = bytes of the local
  * layers' matrices (what one pass over the weights reads), 6 = samples one
- * pass of mdi_sample_batch can take (0: it serves them one by one).  value:
- * host pointer.
+ * pass of mdi_sample_batch can take (0: it serves them one by one); of the
+ * last persistent decode launch (0 before the first): 7 = wavefronts per
+ * workgroup, 8 = pieces that the context of its most divided sample was split
+ * into.  value: host pointer.
  */
 MDI_API mdi_status mdi_partition_info(const mdi_partition *part, uint32_t what, uint64_t *value);
 

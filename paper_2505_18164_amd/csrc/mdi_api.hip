@@ -81,6 +81,8 @@ struct mdi_partition {
   bool use_step = false;
   int nwg = 0, G = 1, n_hg = 0, part_floats = 0;
   int group_ctx = 4096;   // context length from which a launch lets G query heads share a pass over the cache
+  int whole_ctx = 0;      // context length up to which a launch does not split a sample's context (plan_step)
+  int last_waves = 0, last_splits = 0;   // of the last persistent decode launch, see mdi_partition_info
   size_t step_lds = 0;
   std::vector<StepLayer> h_step_layers;
   StepLayer* d_step_layers = nullptr;
@@ -279,6 +281,12 @@ void plan_step(mdi_partition* p, int n_cu) {
   p->G = group % 2 == 0 ? 2 : 1;
   p->group_ctx = 4096;
   if (const char* e = getenv("MDI_GROUP_CTX")) p->group_ctx = std::max(0, atoi(e));   // tuning / test knob, see mdi.h
+  // Contexts up to this many positions are not split among workgroups: what the splits of a head cost once more - counting
+  // arrivals, exchanging the partial results - against 96 KiB of keys and values for one workgroup.  Measured with limits of
+  // 0 / 96 / 160 KiB, four layers, us: GPT-2 3 messages of 128 positions 136 / 132 / 132, of 400 134 / 134 / 145, one message of 300
+  // 101 / 97 / 97, fp32 of 160 101 / 98 / 97, TinyLlama 4 of 512 185 / 185 / 194.
+  p->whole_ctx = 96 * 1024 / (2 * h * p->esz);
+  if (const char* e = getenv("MDI_WHOLE_CTX")) p->whole_ctx = std::max(0, atoi(e));
   if (const char* e = getenv("MDI_BATCH_WAVES")) { const int v = atoi(e); p->batch_waves = (v == 4 || v == 8) ? v : 0; }
   if (const char* e = getenv("MDI_BATCH_GROUP")) { const int v = atoi(e); p->batch_group = (v == 1 || v == 2 || v == 4) ? v : 0; }
   p->n_hg = H;                           // the most head groups a launch has (one head each)
@@ -757,12 +765,6 @@ mdi_status plan_message(mdi_partition* p, uint32_t seq, MessagePlan* m) {
   return MDI_OK;
 }
 
-// Contexts up to this many positions are not split among workgroups: what the splits of a head cost once more - counting
-// arrivals, exchanging the partial results - against 96 KiB of keys and values for one workgroup.  Measured with limits of
-// 0 / 96 / 160 KiB, four layers, us: GPT-2 3 messages of 128 positions 136 / 132 / 132, of 400 134 / 134 / 145, one message of 300
-// 101 / 97 / 97, fp32 of 160 101 / 98 / 97, TinyLlama 4 of 512 185 / 185 / 194.
-int whole_context(const mdi_config& c) { return 96 * 1024 / (int)(2 * c.head_dim * (c.dtype == MDI_BF16 ? 2 : 4)); }
-
 // Query heads per attention work item for a launch whose longest context is ctx (see plan_step).
 int step_group(const mdi_partition* p, int ctx) { return ctx >= p->group_ctx ? p->G : 1; }
 
@@ -809,7 +811,7 @@ void fill_step_slot(const mdi_partition* p, int m, int nwg, int n_hg, const Mess
   const int max_splits = std::max(1, std::min(kMaxSplits, nwg / n_hg));
   int chunk = std::max((mp.ctx + max_splits - 1) / max_splits, 128);
   chunk = (chunk + 15) / 16 * 16;
-  if (mp.ctx <= whole_context(c)) chunk = mp.ctx;
+  if (mp.ctx <= p->whole_ctx) chunk = mp.ctx;
   s->chunk = chunk; s->n_splits = (mp.ctx + chunk - 1) / chunk;
   s->act_out = act_out;
   s->trace = nullptr;
@@ -832,6 +834,9 @@ mdi_status launch_messages(mdi_partition* p, int n, const uint32_t* seqs, const 
     a.s[0].trace = p->trace;
     if (second < n) a.s[second].trace = p->trace + (size_t)a.nwg * p->n_local * 40;
   }
+  p->last_waves = n == 1 ? kStepWavesMax : 4;
+  p->last_splits = 0;
+  for (int m = 0; m < n; ++m) p->last_splits = std::max(p->last_splits, a.s[m].n_splits);
   const mdi_status st = launch_step_serialised(p, [&]() {
     if (n == 1) (p->cfg.dtype == MDI_BF16 ? launch_step_w8_bf16 : launch_step_w8_f32)(p->stream, G, a.nwg, p->step_lds, a);
     else (p->cfg.dtype == MDI_BF16 ? launch_step_w4_bf16 : launch_step_w4_f32)(p->stream, G, a.nwg, p->step_lds, a);
@@ -1012,6 +1017,8 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   int chunk = (int)std::max<long>(128, (ctx_sum * a.n_hg + a.nwg - 1) / a.nwg);
   chunk = (chunk + 15) / 16 * 16;
   auto items_at = [&](int ch) { long t = 0; for (int j = 0; j < n; ++j) t += (long)a.n_hg * std::min(kMaxSplits, (mp[j].ctx + ch - 1) / ch); return t; };
+  // (A context that will not be split counts as if it were.  That can raise the chunk up to the context's own length, no
+  // further, and an item of that length is there anyway.)
   while (items_at(chunk) > a.nwg && chunk < ctx_max) chunk += 16;
   int item = 0;
   for (int j = 0; j < n; ++j) {
@@ -1021,13 +1028,16 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
     s.table = mp[j].drow; s.table_entry = mp[j].new_entry; s.new_page = mp[j].page;
     s.kv_tok_off = (long)mp[j].page * c.n_kv_head * 2 * a.pt_h + (long)mp[j].slot * c.head_dim;
     int ch = chunk;
-    if (mp[j].ctx <= whole_context(c)) ch = (mp[j].ctx + 15) & ~15;
+    if (mp[j].ctx <= p->whole_ctx) ch = (mp[j].ctx + 15) & ~15;
     if ((mp[j].ctx + ch - 1) / ch > kMaxSplits) ch = ((mp[j].ctx + kMaxSplits - 1) / kMaxSplits + 15) / 16 * 16;
     s.chunk = ch; s.n_splits = (mp[j].ctx + ch - 1) / ch;
     s.item_lo = item;
     item += a.n_hg * s.n_splits;
   }
   a.n_items = item;
+  p->last_waves = bp.waves;
+  p->last_splits = 0;
+  for (int j = 0; j < n; ++j) p->last_splits = std::max(p->last_splits, a.s[j].n_splits);
   const mdi_status st = launch_step_serialised(p, [&]() {
     void* args[] = {&a};
     (void)hipLaunchKernel(batch_kernel(p, bp.waves, G, G == 4 && mfma_scores), dim3(a.nwg), dim3(64 * bp.waves), args, bp.lds, p->stream);
@@ -1307,6 +1317,8 @@ mdi_status mdi_partition_info(const mdi_partition* p, uint32_t what, uint64_t* v
     case 2: *value = p->use_step ? (uint64_t)p->step_lds : 0; return MDI_OK;
     case 3: *value = p->arena_bytes; return MDI_OK;
     case 4: *value = p->use_batch ? (uint64_t)kMaxBatch : 0; return MDI_OK;
+    case 7: *value = (uint64_t)p->last_waves; return MDI_OK;
+    case 8: *value = (uint64_t)p->last_splits; return MDI_OK;
     case 6: *value = p->hb_nwg ? (uint64_t)kMaxBatch : 0; return MDI_OK;
     case 5: {
       const mdi_config& c = p->cfg;

@@ -34,9 +34,16 @@ SHAPES = {
 }
 
 
+@pytest.fixture(params=[4, 8], ids=["4 wavefronts", "8 wavefronts"])
+def waves(request, monkeypatch):
+    """Wavefronts per workgroup of the shared pass (short vectors like those here take four by themselves)."""
+    monkeypatch.setenv("MDI_BATCH_WAVES", str(request.param))
+    return request.param
+
+
 @pytest.mark.parametrize("n_msg", [2, 5, 16])
 @pytest.mark.parametrize("name", list(SHAPES))
-def test_batched_pass_against_the_oracle(name, n_msg):
+def test_batched_pass_against_the_oracle(name, n_msg, waves):
     cfg = S.tiny(n_layer=3, dtype=S.DT_BF16, max_ctx=64, vocab=211, **SHAPES[name])
     w = scale_matrices(S.make_weights(cfg, 17, exercise=True), 2.0)   # every sub-layer moves the residual stream, bf16 noise stays small
     o, g = pair(cfg, w, 0, 3, embed=True, head=False, max_seqs=n_msg, kv_page_tokens=8)
@@ -53,6 +60,7 @@ def test_batched_pass_against_the_oracle(name, n_msg):
         outs = g.decode_batch(order, [dev_ids([t]) for t in toks])
         for s, t, got in zip(order, toks, outs):
             worst = max(worst, check(got, o.decode_step(s, t), cfg, ("batched decode", step, s)))
+    assert g.info(7) == waves
     for s in range(n_msg):
         assert g.seq_len(s) == len(prompts[s]) + 12
     g.sync()
@@ -61,7 +69,7 @@ def test_batched_pass_against_the_oracle(name, n_msg):
 
 @pytest.mark.parametrize("page", [16, 48, 8])
 @pytest.mark.parametrize("n_head,n_kv_head", [(4, 1), (8, 2)])
-def test_batched_pass_with_four_heads_of_128_per_item(n_head, n_kv_head, page, monkeypatch):
+def test_batched_pass_with_four_heads_of_128_per_item(n_head, n_kv_head, page, waves, monkeypatch):
     """Scores of four query heads on the matrix cores: tiles of 16 positions of one page (pages that are no multiple of
     16 keep the vector ALUs), contexts at the edges of tiles, of pages and of a split (more than 128 positions)."""
     monkeypatch.setenv("MDI_BATCH_GROUP", "4")
@@ -78,11 +86,12 @@ def test_batched_pass_with_four_heads_of_128_per_item(n_head, n_kv_head, page, m
         toks = [int(rng.integers(0, cfg["vocab"])) for _ in order]
         for s, t, got in zip(order, toks, g.decode_batch(order, [dev_ids([t]) for t in toks])):
             check(got, o.decode_step(s, t), cfg, ("batched decode", step, s))
+        assert (g.info(7), g.info(8)) == (waves, 5)
     g.sync()
 
 
 @pytest.mark.parametrize("name", ["gqa_h16", "wide", "gpt2_like"])
-def test_the_number_of_messages_changes_from_pass_to_pass(name):
+def test_the_number_of_messages_changes_from_pass_to_pass(name, waves):
     """The exchange vectors are packed by the pass's number of messages: passes of different sizes leave words at
     different places of the same arrays, and none may pass for a later one's."""
     cfg = S.tiny(n_layer=3, dtype=S.DT_BF16, max_ctx=64, vocab=211, **SHAPES[name])
@@ -97,15 +106,17 @@ def test_the_number_of_messages_changes_from_pass_to_pass(name):
         outs = g.decode_batch(order, [dev_ids([t]) for t in toks])
         for s, t, got in zip(order, toks, outs):
             check(got, o.decode_step(s, t), cfg, ("batched decode", step, s))
+        assert g.info(7) == waves
     g.sync()
 
 
 @pytest.mark.parametrize("heads", [2, 4])
 @pytest.mark.parametrize("name", ["gqa_h16", "gqa8_h8", "h64", "idle_wavefronts"])
-def test_batched_pass_with_pairs_of_query_heads_and_context_splits(name, heads, monkeypatch):
+def test_batched_pass_with_pairs_of_query_heads_and_context_splits(name, heads, waves, monkeypatch):
     """Long contexts (or more attention work items than workgroups) let two query heads share a pass over their kv
-    head's cache, and contexts of more than 128 positions are split among workgroups and folded; both are reached
-    here on small shapes by lowering the switch-over length and by a context of a few hundred positions."""
+    head's cache, and long contexts are split among workgroups, 128 positions or more each, and folded; both are reached
+    here on small shapes by lowering the two lengths where that begins and by a context of a few hundred positions."""
+    monkeypatch.setenv("MDI_WHOLE_CTX", "0")
     shape = dict(SHAPES[name])
     if heads == 4:                                                 # four heads per work item need groups of a multiple of four
         if name != "gqa8_h8":
@@ -125,6 +136,7 @@ def test_batched_pass_with_pairs_of_query_heads_and_context_splits(name, heads, 
         outs = g.decode_batch([2, 0, 1], [dev_ids([toks[s]]) for s in (2, 0, 1)])
         for s, got in zip((2, 0, 1), outs):
             check(got, o.decode_step(s, toks[s]), cfg, ("batched decode", step, s))
+        assert (g.info(7), g.info(8)) == (waves, 3)
     g.sync()
 
 
@@ -256,7 +268,7 @@ def test_driver_with_shared_passes_on_a_three_node_ring():
                 assert int(t2[s, j]) == O.sample_topk(lg2[s, j], 0.9, 8, u), (s, j)
 
 
-def test_layernorm_vectors_far_from_zero_mean():
+def test_layernorm_vectors_far_from_zero_mean(waves):
     """LayerNorm in the shared pass publishes (x - c) g in bf16 with c close to the vector's mean.  With a residual
     stream whose mean is far from zero (embeddings with a large common offset) the bf16 hand-off itself limits what
     any path can deliver, so the measure is the error relative to the centred vector - the part that carries
@@ -286,4 +298,5 @@ def test_layernorm_vectors_far_from_zero_mean():
     g.sync()
     g1.sync()
     print(f"far-from-zero mean: worst error relative to the centred vector {worst:.2e} (one message at a time: {worst1:.2e})", flush=True)
+    assert g.info(7) == waves
     assert worst < 1.5 * worst1 + 2e-3

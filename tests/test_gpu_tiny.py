@@ -426,10 +426,12 @@ def test_more_queued_messages_than_one_launch_carries():
 
 
 @pytest.mark.parametrize("dtype", [S.DT_F32, S.DT_BF16], ids=["f32", "bf16"])
-def test_the_number_of_context_splits_changes_from_launch_to_launch(dtype):
-    """Contexts of more than 128 positions are split among workgroups, whose arrivals a counter per head counts and the
-    last one folds: samples of one, two, three and five splits take turns in the same launches' places, one at a time
-    and together, so every count starts where another number of splits ended."""
+def test_the_number_of_context_splits_changes_from_launch_to_launch(dtype, monkeypatch):
+    """Contexts of more than 128 positions are split among workgroups (the limit below which they are not is lowered to
+    nothing), whose arrivals a counter per head counts and the last one folds: samples of one, two, three and five splits
+    take turns in the same launches' places, one at a time and together, so every count starts where another number of
+    splits ended."""
+    monkeypatch.setenv("MDI_WHOLE_CTX", "0")
     cfg = S.tiny(n_layer=3, dtype=dtype, max_ctx=640, vocab=97, d_model=64, n_head=4, n_kv_head=2, head_dim=16, d_ff=96)
     w = scale_matrices(S.make_weights(cfg, 61, exercise=True), 3.0)
     lens = (20, 127, 300, 600)                           # the second one grows from one split to two
@@ -445,9 +447,11 @@ def test_the_number_of_context_splits_changes_from_launch_to_launch(dtype):
             outs = [g.decode_step(order[0], ins[0])] if len(order) == 1 else g.decode_steps(order, ins)
             for s, t, got in zip(order, toks, outs):
                 check(got, o.decode_step(s, t), cfg, ("decode", step, s, len(order)))
+            assert g.info(8) == max(-(-g.seq_len(s) // 128) for s in order)
         if g.info(4):
             order = [2, 0, 3, 1] if step % 2 else [3, 1]
             toks = [int(rng.integers(0, cfg["vocab"])) for _ in order]
             for s, t, got in zip(order, toks, g.decode_batch(order, [dev_ids([t]) for t in toks])):
                 check(got, o.decode_step(s, t), cfg, ("shared pass", step, s))
+            assert g.info(8) == max(-(-g.seq_len(s) // 128) for s in order)
     g.sync()
