@@ -53,7 +53,8 @@
  * Results are within the parity bar either way; the order of additions differs.
  * MDI_WHOLE_CTX = context length up to which the decode kernels leave a sample's
  * context to one workgroup per head (default: 96 KiB of one head's keys and
- * values; longer ones are split into pieces of at least 128 positions).
+ * values, 64 KiB in launches whose workgroups have four wavefronts; longer ones
+ * are split into pieces of at least 128 positions).
  * MDI_BATCH_GROUP = 1, 2 or 4 fixes the number of query heads per attention
  * work item of mdi_decode_batch (by default chosen per call from the number of
  * messages and their contexts), MDI_BATCH_WAVES = 4 or 8 the wavefronts per

@@ -81,7 +81,7 @@ struct mdi_partition {
   bool use_step = false;
   int nwg = 0, G = 1, n_hg = 0, part_floats = 0;
   int group_ctx = 4096;   // context length from which a launch lets G query heads share a pass over the cache
-  int whole_ctx = 0;      // context length up to which a launch does not split a sample's context (plan_step)
+  int whole_ctx = -1;     // MDI_WHOLE_CTX: context length up to which a launch does not split a sample's context (-1: whole_context)
   int last_waves = 0, last_splits = 0;   // of the last persistent decode launch, see mdi_partition_info
   size_t step_lds = 0;
   std::vector<StepLayer> h_step_layers;
@@ -281,11 +281,6 @@ void plan_step(mdi_partition* p, int n_cu) {
   p->G = group % 2 == 0 ? 2 : 1;
   p->group_ctx = 4096;
   if (const char* e = getenv("MDI_GROUP_CTX")) p->group_ctx = std::max(0, atoi(e));   // tuning / test knob, see mdi.h
-  // Contexts up to this many positions are not split among workgroups: what the splits of a head cost once more - counting
-  // arrivals, exchanging the partial results - against 96 KiB of keys and values for one workgroup.  Measured with limits of
-  // 0 / 96 / 160 KiB, four layers, us: GPT-2 3 messages of 128 positions 136 / 132 / 132, of 400 134 / 134 / 145, one message of 300
-  // 101 / 97 / 97, fp32 of 160 101 / 98 / 97, TinyLlama 4 of 512 185 / 185 / 194.
-  p->whole_ctx = 96 * 1024 / (2 * h * p->esz);
   if (const char* e = getenv("MDI_WHOLE_CTX")) p->whole_ctx = std::max(0, atoi(e));
   if (const char* e = getenv("MDI_BATCH_WAVES")) { const int v = atoi(e); p->batch_waves = (v == 4 || v == 8) ? v : 0; }
   if (const char* e = getenv("MDI_BATCH_GROUP")) { const int v = atoi(e); p->batch_group = (v == 1 || v == 2 || v == 4) ? v : 0; }
@@ -765,6 +760,19 @@ mdi_status plan_message(mdi_partition* p, uint32_t seq, MessagePlan* m) {
   return MDI_OK;
 }
 
+// Contexts up to this many positions are not split among workgroups: what the splits of a head cost once more - counting
+// arrivals, exchanging the partial results - against up to 96 KiB of keys and values for one workgroup of eight wavefronts, 64 KiB
+// for one of four: a wavefront's two tiles are 16 KiB, so four have asked for 64 KiB before the first of it is there, and what
+// follows comes a round trip later.  Measured split / whole at 44, 60, 76 and 92 KiB, four layers, us.  Four wavefronts: GPT-2 3
+// messages 132/128 133/132 136/144 136/144, TinyLlama 4 170/169 173/168 174/180 174/180, heads of 16 3 106/98 108/98 111/109 113/112,
+// one pass per message: GPT-2 3 207/197 208/202 209/218 209/221, fp32 heads of 64 3 250/251 254/253 267/270 266/274, the 7B shape 4
+// 901/890 899/909 918/918 906/918.  Eight: one message of GPT-2 101/95 100/96 100/96 102/97, of the 7B shape 334/334 335/334 342/335
+// 341/337; at 160 KiB 3 messages of GPT-2 lost 11 of 134 us, 4 of TinyLlama 9 of 185.
+int whole_context(const mdi_partition* p, int waves) {
+  if (p->whole_ctx >= 0) return p->whole_ctx;
+  return (waves == 4 ? 64 : 96) * 1024 / (int)(2 * p->cfg.head_dim * p->esz);
+}
+
 // Query heads per attention work item for a launch whose longest context is ctx (see plan_step).
 int step_group(const mdi_partition* p, int ctx) { return ctx >= p->group_ctx ? p->G : 1; }
 
@@ -793,8 +801,8 @@ void fill_step_shared(const mdi_partition* p, int G, int n, StepArgs* a) {
   a->part_floats = p->part_floats;
 }
 
-// One message's part of the arguments: message m of a launch whose sets have nwg workgroups each.
-void fill_step_slot(const mdi_partition* p, int m, int nwg, int n_hg, const MessagePlan& mp, const void* act_in, void* act_out, StepSlot* s) {
+// One message's part of the arguments: message m of a launch whose sets have nwg workgroups of `waves` wavefronts each.
+void fill_step_slot(const mdi_partition* p, int m, int nwg, int waves, int n_hg, const MessagePlan& mp, const void* act_in, void* act_out, StepSlot* s) {
   const mdi_config& c = p->cfg;
   const int h = c.head_dim, K = c.n_kv_head;
   const long pt_h = (long)p->pt * h;
@@ -811,7 +819,7 @@ void fill_step_slot(const mdi_partition* p, int m, int nwg, int n_hg, const Mess
   const int max_splits = std::max(1, std::min(kMaxSplits, nwg / n_hg));
   int chunk = std::max((mp.ctx + max_splits - 1) / max_splits, 128);
   chunk = (chunk + 15) / 16 * 16;
-  if (mp.ctx <= p->whole_ctx) chunk = mp.ctx;
+  if (mp.ctx <= whole_context(p, waves)) chunk = mp.ctx;
   s->chunk = chunk; s->n_splits = (mp.ctx + chunk - 1) / chunk;
   s->act_out = act_out;
   s->trace = nullptr;
@@ -828,13 +836,13 @@ mdi_status launch_messages(mdi_partition* p, int n, const uint32_t* seqs, const 
   a.n_sets = n >= 2 ? 2 : 1;             // two sets of 4-wavefront workgroups share the compute units
   a.nwg = p->nwg;
   a.set_lo[0] = 0; a.set_lo[1] = a.n_sets == 2 ? (n + 1) / 2 : n; a.set_lo[2] = n;
-  for (int m = 0; m < n; ++m) fill_step_slot(p, m, a.nwg, a.n_hg, mp[m], ins[m], outs[m], &a.s[m]);
+  p->last_waves = n == 1 ? kStepWavesMax : 4;
+  for (int m = 0; m < n; ++m) fill_step_slot(p, m, a.nwg, p->last_waves, a.n_hg, mp[m], ins[m], outs[m], &a.s[m]);
   if (p->trace) {                      // timeline of the first message of each set (of the first two messages with one set)
     const int second = a.n_sets == 2 ? a.set_lo[1] : 1;
     a.s[0].trace = p->trace;
     if (second < n) a.s[second].trace = p->trace + (size_t)a.nwg * p->n_local * 40;
   }
-  p->last_waves = n == 1 ? kStepWavesMax : 4;
   p->last_splits = 0;
   for (int m = 0; m < n; ++m) p->last_splits = std::max(p->last_splits, a.s[m].n_splits);
   const mdi_status st = launch_step_serialised(p, [&]() {
@@ -1028,7 +1036,7 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
     s.table = mp[j].drow; s.table_entry = mp[j].new_entry; s.new_page = mp[j].page;
     s.kv_tok_off = (long)mp[j].page * c.n_kv_head * 2 * a.pt_h + (long)mp[j].slot * c.head_dim;
     int ch = chunk;
-    if (mp[j].ctx <= p->whole_ctx) ch = (mp[j].ctx + 15) & ~15;
+    if (mp[j].ctx <= whole_context(p, bp.waves)) ch = (mp[j].ctx + 15) & ~15;
     if ((mp[j].ctx + ch - 1) / ch > kMaxSplits) ch = ((mp[j].ctx + kMaxSplits - 1) / kMaxSplits + 15) / 16 * 16;
     s.chunk = ch; s.n_splits = (mp[j].ctx + ch - 1) / ch;
     s.item_lo = item;

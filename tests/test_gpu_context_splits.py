@@ -36,3 +36,25 @@ def test_samples_that_grow_across_the_limit(dtype, norm, heads, monkeypatch):
             check(got, o.decode_step(s, t), cfg, (kind, step, s))
         assert g.info(8) == splits, (step, [g.seq_len(s) for s in order])
     g.sync()
+
+
+@pytest.mark.parametrize("dtype", [S.DT_F32, S.DT_BF16], ids=["f32", "bf16"])
+def test_default_limit(dtype):
+    """64 KiB of one head's keys and values with workgroups of four wavefronts (several messages), 96 KiB with eight (one):
+    heads of 16 need 64 bytes a position in bf16, twice that in fp32."""
+    four = 64 * 1024 // (64 if dtype == S.DT_BF16 else 128)
+    cfg = S.tiny(n_layer=2, dtype=dtype, max_ctx=2048, vocab=97, d_model=64, n_head=4, n_kv_head=2, head_dim=16, d_ff=96)
+    w = scale_matrices(S.make_weights(cfg, 89, exercise=True), 2.0)
+    lens = (four - 1, 9, four * 3 // 2 - 1)
+    o, g = pair(cfg, w, 0, 2, embed=True, max_seqs=len(lens), kv_page_tokens=16)
+    for s, T in enumerate(lens):
+        ids = S.make_prompts(cfg, 89 + s, 1, T)[0]
+        check(g.prefill(s, dev_ids(ids)), o.prefill(s, ids), cfg, ("prefill", s))
+    for step, (order, waves, splits) in enumerate([([0, 1], 4, 1), ([0], 8, 1), ([1, 0], 4, four // 128 + 1), ([2], 8, 1),
+                                                   ([2], 8, four * 3 // 256 + 1)]):
+        ins = [dev_ids([t + step]) for t in order]
+        outs = [g.decode_step(order[0], ins[0])] if len(order) == 1 else g.decode_batch(order, ins)
+        for s, got in zip(order, outs):
+            check(got, o.decode_step(s, s + step), cfg, (step, s))
+        assert (g.info(7), g.info(8)) == (waves, splits), step
+    g.sync()
