@@ -233,9 +233,9 @@ size_t carve(mdi_partition* p, void* arena) {
       p->b_xn[1] = p->b_xn[0] ? p->b_xn[0] + d / 2 * kMaxBatch : nullptr;
       p->b_ob = p->b_xn[0] ? p->b_xn[1] + d / 2 * kMaxBatch : nullptr;
       p->b_ub = p->b_xn[0] ? p->b_ob + H * h / 2 * kMaxBatch : nullptr;
-      for (auto& q : p->b_ssq) q = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 8);
+      for (auto& q : p->b_ssq) q = (tagged_t*)cv.take((size_t)kMaxBatch * kBatchWgs * 8);
       if (ln) {
-        for (auto& q : p->b_ssum) q = (tagged_t*)cv.take((size_t)kMaxBatch * 1024 * 8);
+        for (auto& q : p->b_ssum) q = (tagged_t*)cv.take((size_t)kMaxBatch * kBatchWgs * 8);
         p->b_nc_stride = 2 * (nqkv + nup);
         p->b_nc = (float*)cv.take(p->n_local * p->b_nc_stride * 4);
       }
@@ -311,6 +311,7 @@ const void* batch_kernel(const mdi_partition* p, int waves, int G, bool scores_o
 bool plan_batch_waves(const mdi_partition* p, int waves, BatchPlan* b) {
   const mdi_config& c = p->cfg;
   const int H = c.n_head, K = c.n_kv_head, h = c.head_dim, d = c.d_model, F = c.d_ff, nwg = p->nwg;
+  if (nwg > kBatchWgs) return false;
   if (d % 32 || (H * h) % 32 || F % 32) return false;           // a column step of the matrix instruction is 32 wide
   b->waves = waves;
   b->res_c = (d / 32 + waves - 1) / waves;
@@ -547,9 +548,9 @@ mdi_status mdi_partition_create(const mdi_config* cfg, uint32_t layer_lo, uint32
     if (p->batch_region) {
       launch_fill_u32(p->stream, (uint32_t*)p->b_slot0, (long)(p->b_stride * kMaxBatch / 4), 0u);
       launch_fill_u32(p->stream, (uint32_t*)p->b_xn[0], (long)p->b_vec_words * 2, 0u);
-      for (auto* q : p->b_ssq) launch_fill_u32(p->stream, (uint32_t*)q, (long)kMaxBatch * 1024 * 2, 0u);
+      for (auto* q : p->b_ssq) launch_fill_u32(p->stream, (uint32_t*)q, (long)kMaxBatch * kBatchWgs * 2, 0u);
       if (p->b_ssum[0]) {
-        for (auto* q : p->b_ssum) launch_fill_u32(p->stream, (uint32_t*)q, (long)kMaxBatch * 1024 * 2, 0u);
+        for (auto* q : p->b_ssum) launch_fill_u32(p->stream, (uint32_t*)q, (long)kMaxBatch * kBatchWgs * 2, 0u);
         const int nq = (int)((H + 2 * K) * h), nu = (int)(c.mlp_kind == MDI_MLP_SWIGLU ? 2 * F : F);
         for (int i = 0; i < p->n_local; ++i) {       // what the mean and the norm's bias add to the two normed products
           const LayerPacked& L = p->layers[i];
@@ -993,7 +994,6 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   a.mlp_kind = c.mlp_kind; a.eps = c.norm_eps;
   a.wte = p->wte; a.wpe = p->wpe; a.vocab = (int)c.vocab;
   a.in_kind = (p->flags & MDI_HAS_EMBED) ? IN_TOKEN : act_kind(c);
-  a.act_kind = act_kind(c);
   a.err = p->err; a.spin_limit = 1 << 21;
   a.n_hg = (int)c.n_head / G;
   a.scale = 1.f / sqrtf((float)c.head_dim);
@@ -1003,7 +1003,7 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   for (int k = 0; k < 2; ++k) { a.xn[k] = p->b_xn[k]; a.ssq[k] = p->b_ssq[k]; a.ssum[k] = p->b_ssum[k]; }
   a.slot0 = p->b_slot0; a.slot_stride = (long)p->b_stride;
   a.off_q = (long)p->b_off_q; a.off_part = (long)p->b_off_part; a.off_knew = (long)p->b_off_knew; a.off_tickets = (long)p->b_off_tickets;
-  a.norm_kind = (int)c.norm_kind; a.nc0 = p->b_nc; a.nc_stride = (long)p->b_nc_stride;
+  a.nc0 = p->b_nc; a.nc_stride = (long)p->b_nc_stride;
   const BatchPlan& bp = batch_plan(p, n);
   a.ppart = p->b_ppart; a.str_S = bp.S; a.str_groups = bp.groups;
   const int heads = c.n_head * c.head_dim, ff = c.d_ff;
@@ -1018,7 +1018,6 @@ mdi_status launch_batch(mdi_partition* p, int n, const uint32_t* seqs, const Mes
   }
   a.res_c = bp.res_c;
   a.rope = p->rope;
-  a.sq_stride = (a.nwg + 255) & ~255;
   a.trace = p->trace;
   // Attention work items: (message, head group, context split).  Splits of about equal length over all messages,
   // as many items as there are workgroups when the contexts allow it, no split shorter than 128 positions.

@@ -275,6 +275,7 @@ void launch_logits(hipStream_t s, int dtype, int nwg, size_t lds_bytes, const Lo
 // taken through every layer together: a weight tile is fetched once and multiplied with all their vectors on the
 // matrix cores (the messages are the second operand's columns), attention stays per sample.
 constexpr int kMaxBatch = 16;        // messages one pass can carry: the matrix instruction's column count
+constexpr int kBatchWgs = 256;       // its workgroups, at most: one per compute unit
 
 struct BatchSlot {                   // what belongs to one message of the launch
   const void* in;                    // token id (int32) or activation [d] in storage dtype
@@ -299,7 +300,7 @@ struct BatchArgs {
   int d, H, K, h, F, pt; long pt_h;
   int mlp_kind; float eps;
   const void* wte; const void* wpe; int vocab;
-  int in_kind, act_kind;
+  int in_kind;
   int* err; int spin_limit;          // as in StepArgs
   int n_hg; float scale;
   int nwg, m;                        // workgroups (one set), messages (2 .. kMaxBatch)
@@ -315,11 +316,11 @@ struct BatchArgs {
   tagged_t *xn[2], *ob, *ub;
   char* slot0; long slot_stride;
   long off_q, off_part, off_knew, off_tickets;
-  tagged_t* ssq[2]; int sq_stride;   // [kMaxBatch][sq_stride] per-workgroup sums of squares of the residual rows they own (nwg, rounded up to 256)
-  // LayerNorm (norm_kind = MDI_NORM_LAYERNORM): the sums of those rows travel too, and the products of a normalised
+  tagged_t* ssq[2];                  // [kMaxBatch][kBatchWgs] per-workgroup sums of squares of the residual rows they own
+  // LayerNorm: the sums of those rows travel too, and the products of a normalised
   // vector are corrected in the epilogue, y = rstd (W (x g)) - rstd mean (W g) + W b: per layer the four vectors
   // [W_qkv g1 | W_qkv b1 | W_up g2 | W_up b2] (float), layer l's at nc0 + l * nc_stride floats
-  int norm_kind; tagged_t* ssum[2]; const float* nc0; long nc_stride;
+  tagged_t* ssum[2]; const float* nc0; long nc_stride;
   // products split among workgroups along the inner dimension: partials [block][S][4 row quads][m][4 rows], slices per
   // block, groups of as many blocks as a workgroup has wavefronts, column steps of a slice (output projection, MLP down)
   tagged_t* ppart; int str_S, str_groups, str_c[2];

@@ -371,12 +371,11 @@ __device__ __forceinline__ float batch_input(const BatchArgs& a, const BatchLds&
 }
 
 // Sums over the eight lanes of a message's row pairs, published by the first of them.  Workgroup wg's share is word wg of a
-// message's row; the words from nwg to the row's end (a multiple of 256) are published too, as zeros, so that readers need
-// not tell them apart.
-__device__ __forceinline__ void publish_sum(float v, int p, tagged_t* row, int wg, int nwg, int stride, unsigned tag) {
+// message's row; the words from nwg to the row's end are published too, as zeros, so that readers need not tell them apart.
+__device__ __forceinline__ void publish_sum(float v, int p, tagged_t* row, int wg, int nwg, unsigned tag) {
   v = dpp_add<kDppXor1, 0xF>(v); v = dpp_add<kDppXor2, 0xF>(v); v = dpp_add<kDppHalfMirror, 0xF>(v);
   if (p == 0)
-    for (int w = wg; w < stride; w += nwg) st_tag(row + w, w == wg ? v : 0.f, tag);
+    for (int w = wg; w < kBatchWgs; w += nwg) st_tag(row + w, w == wg ? v : 0.f, tag);
 }
 
 // G query heads per attention work item; kScoresOnMfma: see Attn4 (G = 4).
@@ -445,8 +444,8 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
         st_pair(a.xn[0] + vec_word(r0 >> 1, j, m), pack_bf16x2((x0 - rcen[j]) * gain[r0], (x1 - rcen[j]) * gain[r0 + 1]), a.epoch0);
         s2 = x0 * x0 + x1 * x1; s1 = x0 + x1;
       }
-      publish_sum(s2, p, a.ssq[0] + j * a.sq_stride, wg, nwg, a.sq_stride, a.epoch0);
-      if constexpr (kLn) publish_sum(s1, p, a.ssum[0] + j * a.sq_stride, wg, nwg, a.sq_stride, a.epoch0);
+      publish_sum(s2, p, a.ssq[0] + j * kBatchWgs, wg, nwg, a.epoch0);
+      if constexpr (kLn) publish_sum(s1, p, a.ssum[0] + j * kBatchWgs, wg, nwg, a.epoch0);
     }
   }
   __syncthreads();
@@ -519,18 +518,18 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
       };
       // ---- requests
       const Buffer sqb = buffer_at(up ? a.ssq[1] : a.ssq[0]), smb = buffer_at(kLn ? (up ? a.ssum[1] : a.ssum[0]) : nullptr);
-      const int stride = a.sq_stride;
       const bool long_vec = (a.d >> 1) * m > kWatchWords;
       uint32_t gate = 0;                                            // (the counter alone: half a loaded pair left unused is reused, and waited for)
-      auto ask_gate = [&](int w) __attribute__((always_inline)) {
-        gate = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sqb, (int)fresh(long_vec && w < stride ? (uint32_t)w * 8u + 4u : kNowhere), 0, kAgentScope);
+      auto ask_gate = [&]() __attribute__((always_inline)) {
+        gate = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(sqb, (int)fresh(long_vec && tid < kBatchWgs ? (uint32_t)tid * 8u + 4u : kNowhere), 0, kAgentScope);
       };
-      ask_gate(tid);
-      // the sums: 32 threads per message (16 in a workgroup of four wavefronts), the first 256 words at once
-      constexpr int kSumThreads = kStepThreads / kMaxBatch, kSumPieces = 128 / kSumThreads;
+      ask_gate();
+      // the sums: 32 threads per message (16 in a workgroup of four wavefronts), all words at once
+      constexpr int kSumThreads = kStepThreads / kMaxBatch, kSumPieces = kBatchWgs / 2 / kSumThreads;
+      static_assert(kStepThreads >= kBatchWgs, "a thread for every word that is watched");
       const int sj = tid / kSumThreads, sc = tid % kSumThreads;
       const bool sums = sj < m;
-      const uint32_t s_off = sums ? (uint32_t)(sj * stride + 2 * sc) * 8u : kNowhere;
+      const uint32_t s_off = sums ? (uint32_t)(sj * kBatchWgs + 2 * sc) * 8u : kNowhere;
       u32x4 sq[kSumPieces], sm[kSumPieces];
       auto ask_sq = [&]() __attribute__((always_inline)) {
         const uint32_t o = fresh(s_off);
@@ -628,10 +627,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
       // squares (which it stores last) is there: 256 workgroups that watch 32 KB each crowd out the stores they wait
       // for (TinyLlama, 4 messages: 629 us, ungated 644; the 7B shape with 8: 979 and 975).
       if (long_vec) {
-        for (int w = tid; w < stride; w += kStepThreads) {
-          if (w != tid) ask_gate(w);
-          poll_while([&]() { return gate != epoch; }, [&]() { ask_gate(w); }, a.spin_limit, a.err);
-        }
+        if (wave < kBatchWgs / 64) poll_while([&]() { return gate != epoch; }, ask_gate, a.spin_limit, a.err);
         __syncthreads();
       }
       float sum2 = 0.f, sum1 = 0.f;                                 // this thread's share of its message's sums
@@ -641,18 +637,6 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
       for (int k = 0; k < kSumPieces; ++k) {
         sum2 += __uint_as_float(sq[k].x) + __uint_as_float(sq[k].z);
         if constexpr (kLn) sum1 += __uint_as_float(sm[k].x) + __uint_as_float(sm[k].z);
-      }
-      for (int w = 256 + 2 * sc; w < stride && sums; w += 2 * kSumThreads) {     // (more than 256 workgroups)
-        u32x4 one[1];
-        auto ask1 = [&](Buffer b) __attribute__((always_inline)) { one[0] = ld_two(b, fresh((uint32_t)(sj * stride + w) * 8u), 0); };
-        ask1(sqb);
-        await_two(one, [&]() { ask1(sqb); }, true, epoch, a.spin_limit, a.err);
-        sum2 += __uint_as_float(one[0].x) + __uint_as_float(one[0].z);
-        if constexpr (kLn) {
-          ask1(smb);
-          await_two(one, [&]() { ask1(smb); }, true, epoch, a.spin_limit, a.err);
-          sum1 += __uint_as_float(one[0].x) + __uint_as_float(one[0].z);
-        }
       }
       u32x4 Bv[kResSteps];
       auto take = [&](auto first) __attribute__((always_inline)) {
@@ -981,8 +965,8 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
           }
         }
         if (!last) {
-          publish_sum(s2, p, (down ? a.ssq[0] : a.ssq[1]) + j * a.sq_stride, wg, nwg, a.sq_stride, wtag);
-          if constexpr (kLn) publish_sum(s1, p, (down ? a.ssum[0] : a.ssum[1]) + j * a.sq_stride, wg, nwg, a.sq_stride, wtag);
+          publish_sum(s2, p, (down ? a.ssq[0] : a.ssq[1]) + j * kBatchWgs, wg, nwg, wtag);
+          if constexpr (kLn) publish_sum(s1, p, (down ? a.ssum[0] : a.ssum[1]) + j * kBatchWgs, wg, nwg, wtag);
         }
       }
       // ---- the vector's slice in LDS has been read

@@ -156,11 +156,6 @@ __device__ __forceinline__ void await_words(tagged_t (&raw)[N], Buffer b, const 
     return bad != 0;
   }, [&]() { ask_words(raw, b, at, live); }, spin_limit, err);
 }
-template <int N, typename AT, typename LT = AllLive>
-__device__ __forceinline__ void poll_words(tagged_t (&raw)[N], Buffer b, const AT& at, unsigned tag, int spin_limit, int* err, const LT& live = LT()) {
-  ask_words(raw, b, at, live);
-  await_words(raw, b, at, tag, spin_limit, err, live);
-}
 
 // ---------------------------------------------------------------------------
 // vector staging: n floats written earlier in this launch by other workgroups -> LDS
