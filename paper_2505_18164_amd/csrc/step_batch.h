@@ -638,6 +638,7 @@ __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(kS
         sum2 += __uint_as_float(sq[k].x) + __uint_as_float(sq[k].z);
         if constexpr (kLn) sum1 += __uint_as_float(sm[k].x) + __uint_as_float(sm[k].z);
       }
+      asm volatile("" : "+v"(sum2), "+v"(sum1));                    // (added up here: left to where they are used, the words stay in registers)
       u32x4 Bv[kResSteps];
       auto take = [&](auto first) __attribute__((always_inline)) {
         constexpr int k0 = decltype(first)::value;
