@@ -356,8 +356,10 @@ void plan_batch(mdi_partition* p) {
 // Workgroups of four wavefronts, one per SIMD, execute the instructions of a phase boundary in half the time of eight,
 // which take turns; eight hide the vectors' and the caches' loads better.  So: four where a wavefront can hold its slice of
 // a vector (d up to 2048) and the messages' vectors are short.  Measured, four layers, eight / four wavefronts, us:
-// GPT-2 3 messages 156 / 137, 16 of 512 positions 186 / 193; d = 1024 3 messages 159 / 126, 8 of 512 170 / 156, 16 of 1024
-// 219 / 211; TinyLlama 2 of 512 179 / 163, 4 of 512 185 / 183, 16 of 1024 256 / 278.
+// GPT-2 3 messages 156 / 137, 10 of 128 positions 161 / 151, 10 of 900 175 / 176, 16 of 512 186 / 193; d = 1024 3 messages 159 / 126,
+// 8 of 512 170 / 156; TinyLlama 2 of 512 179 / 163, 4 of 128 174 / 167, 4 of 512 185 / 183, 4 of 1536 203 / 206, 16 of 1024 256 / 278.
+// The limit is where four begin to lose with long contexts; past it they still win with short ones (12 of 128: GPT-2 165 / 153,
+// d = 1024 153 / 133; TinyLlama 8 of 128 185 / 177) and for d = 1024 with 16 (of 1536 223 / 217).
 const BatchPlan& batch_plan(const mdi_partition* p, int n) {
   const bool four = p->batch_waves ? p->batch_waves == 4 : n * (int)p->cfg.d_model <= 8192;
   return p->b_plan[p->use_batch4 && four ? 1 : 0];

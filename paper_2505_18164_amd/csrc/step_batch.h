@@ -34,8 +34,8 @@
 //   * What a phase boundary costs beyond the exchange is instructions: the two wavefronts of a SIMD issue theirs in turn.
 //     With one body for all norms, MLPs and phases a wavefront executed 700 scalar and 800 vector instructions per phase,
 //     and 300 to 430 scalar registers lived in lanes of vector registers.  Now norm and MLP kind are template arguments,
-//     every phase is code of its own that loads what it needs of the arguments when it starts (85 to 108 such lanes, here
-//     and in k_step 45 to 60), words are requested two at a time through buffer descriptors and without branches, and
+//     every phase is code of its own that loads what it needs of the arguments when it starts (55 to 89 such lanes here, in
+//     k_step 38 to 48 with eight wavefronts and 75 to 113 with four), words are requested two at a time through buffer descriptors and without branches, and
 //     a wavefront polls as one.  With that, with requests that no hidden wait holds up, and with workgroups of four
 //     wavefronts, per call: 4 layers of GPT-2 with 3 messages 199 -> 140 us, TinyLlama starter with 4 634 -> 572, 8 layers of
 //     the 7B shape with 8 1027 -> 956, of the 8B shape with 16 and 6144 positions 1502 -> 1390; one message (k_step): 4 fp32
@@ -54,7 +54,8 @@
 // Needs bf16 storage and widths that are multiples of 32; other shapes keep one pass per message.  With LayerNorm the vectors still travel as x * gain: the mean and the norm's bias enter the finished
 // products through two precomputed vectors per matrix (W g and W b), see BatchArgs.
 //
-// step_batch_ln.hip and step_batch_rms.hip compile it for one norm each (MDI_BATCH_LN).
+// step_batch_ln*.hip and step_batch_rms*.hip compile it for one norm each (MDI_BATCH_LN), and for workgroups of eight and (_w4) of
+// four wavefronts (MDI_STEP_WAVES).
 #include "step_mfma.h"
 
 namespace mdi {

@@ -261,8 +261,8 @@ struct Geo {
   int p_lo, n_pl;        // this workgroup owns n_pl pairs: blocks of 2^bshift consecutive pairs, block b of the
   int bshift, nwg;       // matrix going to workgroup b % nwg (p_lo = workgroup index).  At any moment the grid
                          // reads one contiguous window of the matrix, and a workgroup stays >= 64 KiB in place.
-  int n_k;               // this wavefront's items: item k is flat index wave + 8k, flat = pair * cpp + chunk
-  int dq, dr;            // 8 / cpp and 8 % cpp: how (pair, chunk) moves from one item to the next
+  int n_k;               // this wavefront's items: item k is flat index wave + k * wavefronts, flat = pair * cpp + chunk
+  int dq, dr;            // wavefronts div and mod cpp: how (pair, chunk) moves from one item to the next
   int pl0, c0;           // the wavefront's first item
   // first row of pair p = (p >> rsh) * rmul + (p & rmask), its partner rstep rows on: rows (2p, 2p + 1), or RoPE partners
   // (i, i + h/2) inside heads of h rows (head sizes are powers of two)
@@ -371,7 +371,7 @@ __device__ __forceinline__ void gemv_issue(Tile& t, const Geo& g, Cursor& cur, i
 }
 
 // kPadded: the caller has zeros in xs behind the vector, up to a whole number of 64-lane chunks, so the lanes past the
-// end of a row (which hold the row's first bytes) multiply by zero and need no case of their own.
+// end of a row (which hold zeros, see gemv_issue) find finite numbers there and need no case of their own.
 template <typename WT, bool kPadded>
 __device__ __forceinline__ void gemv_compute(const Tile& t, const Geo& g, int ti, Cursor& cur, int wave, int lane, const float* xs,
                                              float* part, float& acc0, float& acc1) {
@@ -502,7 +502,7 @@ struct AttnGeo {
   bool active;
   int hg, split, kvh, s0, s1, s1p;
   int L, tpw, sub, hoff;
-  int n_k;                // this wavefront's steps: step k covers tokens s0 + (8k + wave) * tpw ..
+  int n_k;                // this wavefront's steps: step k covers tokens s0 + (k * wavefronts + wave) * tpw ..
   float f2, f4, f8, f16;  // 1 when a position's values are spread over at least that many lanes, else 0
   int pt_sh;              // log2(tokens per page) when that is a power of two, else -1 ...
   unsigned pt_magic;      // ... and then position / page size = high word of position * pt_magic (exact while
