@@ -35,11 +35,11 @@
 //     With one body for all norms, MLPs and phases a wavefront executed 700 scalar and 800 vector instructions per phase,
 //     and 300 to 430 scalar registers lived in lanes of vector registers.  Now norm and MLP kind are template arguments,
 //     every phase is code of its own that loads what it needs of the arguments when it starts (55 to 89 such lanes here, in
-//     k_step 38 to 48 with eight wavefronts and 75 to 113 with four), words are requested two at a time through buffer descriptors and without branches, and
-//     a wavefront polls as one.  With that, with requests that no hidden wait holds up, and with workgroups of four
-//     wavefronts, per call: 4 layers of GPT-2 with 3 messages 199 -> 140 us, TinyLlama starter with 4 634 -> 572, 8 layers of
-//     the 7B shape with 8 1027 -> 956, of the 8B shape with 16 and 6144 positions 1502 -> 1390; one message (k_step): 4 fp32
-//     GPT-2 layers with output layers 202 -> 149, 8 of the 7B shape 762 -> 697.
+//     k_step 38 to 48 with eight wavefronts and 75 to 113 with four), words are requested two at a time through buffer
+//     descriptors and without branches, and a wavefront polls as one.  With that, with requests that no hidden wait holds up,
+//     and with workgroups of four wavefronts, per call: 4 layers of GPT-2 with 3 messages 199 -> 140 us, TinyLlama starter with
+//     4 634 -> 572, 8 layers of the 7B shape with 8 1027 -> 956, of the 8B shape with 16 and 6144 positions 1502 -> 1390; one
+//     message (k_step): 4 fp32 GPT-2 layers with output layers 202 -> 149, 8 of the 7B shape 762 -> 697.
 //   * Vectors that feed a product cross workgroups as bf16 PAIRS with the writing phase's counter in one 8-byte
 //     word, already multiplied by the gain of the RMSNorm that follows (1/rms is applied to the finished products;
 //     the sum of squares travels as one partial per workgroup and message).  Bytes exchanged per message are half
