@@ -7,20 +7,27 @@
 // dimension is 128 bytes of every row; both operands travel global -> LDS without passing registers
 // (buffer_load_dwordx4 ... lds), a ring of NBW / NBA steps deep, so that a step has one to three steps of arithmetic
 // to arrive; one barrier per step.  Fragments of the next half step are read from LDS between the matrix
-// instructions of the current one.  The 16-byte pieces of a row are permuted by the row number (the permutation is
+// instructions of the current one.  The steps that still ask for others are a loop of their own without a condition in it.  The 16-byte pieces of a row are permuted by the row number (the permutation is
 // applied to the global address, LDS then holds it for free), which spreads the reads over the banks.
 //
-// What bounds it, by the counters of the large products of the 7B and 8B shapes (1024 and 2048 positions): the matrix
-// cores work in 47 - 58 % of the cycles, at a clock of 2.1 - 2.3 GHz where 2.4 is the highest.  So most of what is missing
-// is a stall inside the step, a smaller part the clock: a step of a 192 x 256 tile takes about 2700 cycles, of which 1536
-// are matrix instructions.  Which wait it is has not been found out.  16x16x32 instructions against 32x32x16 ones, half
-// the accumulator traffic per product: 283 against 310 us at 4096 x 4096 x 11008 (1.30 PFLOP/s).  Products of few
-// positions are bound by the weights' way from memory through few tiles.
-//
+// What bounds it depends on the tile.  Timed with one of the three parts of a step left out at a time (1024 positions, cold
+// weights): 128 x 128 tiles take 0.60 us a step to load (53 bytes per ns and compute unit, at a depth of three steps as at
+// five: what a compute unit keeps on its way over the latency of memory; 75 with the weights in the memory-side cache, 86
+// from L2), 0.41 to multiply, 0.35 to read LDS, 0.68 together.  256 x 256: 1.25 to load, 1.37 to multiply, 0.66 to read
+// LDS, 1.8 together; there the clock gives way as well, 1.6 - 1.9 GHz (2.1 with small tiles; a loop of nothing but matrix
+// instructions on random operands runs at 1.9 - 2.1).  So few positions want tiles with few bytes per product, many
+// positions tiles that divide their number well.  16x16x32 instructions against 32x32x16 ones, half the accumulator traffic
+// per product: 283 against 310 us at 4096 x 4096 x 11008, and a clock 10 % higher.
+// The loop without conditions is 1 to 6 % faster than one with a test before every load (192 x 256: 2.5 %, 64 x 64: 6 %).
+// Spreading a step's loads over both halves, or over the first quarter, reading the fragments earlier, wavefront priority
+// around the products: between nothing and 5 % slower.
+
 // Included by gemm_bf16.hip and gemm_f32.hip, which hold the tile shapes of their storage type.
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "device_utils.h"
 
@@ -74,6 +81,13 @@ template <> __device__ __forceinline__ void put4<float>(void* base, long o, floa
 template <> __device__ __forceinline__ void put4<bf16_t>(void* base, long o, float a, float b, float c, float d) {
   *reinterpret_cast<u32x2*>((bf16_t*)base + o) = u32x2{pack2(a, b), pack2(c, d)};
 }
+
+// f(0), ..., f(N - 1) with the numbers as constants.  (A loop for the compiler to unroll is left as a loop when a tile has many
+// products, and the fragments then end up in scratch memory.)
+template <typename F, int... I> __device__ __forceinline__ void each_of(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void each(F&& f) { each_of(static_cast<F&&>(f), std::make_integer_sequence<int, N>{}); }
+// n things spread evenly over `over` places: the first that is due at place q or later.
+constexpr int due(int q, int n, int over) { const int v = (q * n + over - 1) / over; return v < n ? v : n; }
 
 // A workgroup is WN x WT wavefronts, each (BN / WN) weight rows x (BT / WT) positions.
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
@@ -178,47 +192,49 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
 
   constexpr int NF = TN + TT, NM = TN * TT, NL = LW + LA;
   int bw = 0, ba = 0;
-  for (int kt = 0; kt < nk; ++kt) {
+  auto step = [&](auto steady, int kt) __attribute__((always_inline)) {
+    constexpr bool STEADY = decltype(steady)::value;               // both buffers that this step frees are filled again
     const int nbw = bw + 1 == NBW ? 0 : bw + 1, nba = ba + 1 == NBA ? 0 : ba + 1;
-    const bool more_w = kt + NBW < nk, more_a = kt + NBA < nk;
+    const bool more_a = STEADY || kt + NBA < nk;
     const int kw = k_of(kt + NBW), ka = k_of(kt + NBA);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int cur = s, nxt = s ^ 1;
+    each<2>([&](auto half) __attribute__((always_inline)) {
+      constexpr int s = half, cur = s, nxt = s ^ 1;
       const unsigned char* wp = w_wave + (s ? nbw : bw) * WB;      // where the next half step's fragments are
       const unsigned char* ap = a_wave + (s ? nba : ba) * AB;
-      if (s == 1) {
+      if constexpr (s == 1) {
         // this wavefront has read all of step kt; the next step must have landed, for every wavefront.  Loads return
         // in order: what may still be on its way are the pieces issued after the next step's.
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (kt + NBW <= nk) wait_loads<(NBW > NBA ? LW + (NBA - 2) * (LW + LA) : (NBW - 2) * (LW + LA))>(); else wait_loads<0>();
+        if (STEADY || kt + NBW <= nk) wait_loads<(NBW > NBA ? LW + (NBA - 2) * (LW + LA) : (NBW - 2) * (LW + LA))>(); else wait_loads<0>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
       }
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < NM; ++q) {
-        const int i = q / TT, j = q % TT;
+      each<NM>([&](auto place) __attribute__((always_inline)) {
+        constexpr int q = place, i = q / TT, j = q % TT;
         acc[i][j] = M::go(xw[cur][i], xa[cur][j], acc[i][j]);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          if (f * NM / NF != q) continue;
-          if (f < TT) xa[nxt][f] = *reinterpret_cast<const typename M::frag*>(ap + fa[nxt] + f * 2048);
-          else { const int i2 = f - TT; xw[nxt][i2] = *reinterpret_cast<const typename M::frag*>(wp + fw[nxt][i2 & 1] + (i2 >> 1) * 4096); }
-        }
-        if (s == 1) {                                              // refill the buffers this step has just freed
-#pragma unroll
-          for (int l = 0; l < NL; ++l) {
-            if (l * NM / NL != q) continue;
-            if (l < LA) { if (more_a) load_a(l, ka, ba); }
-            else if (more_w) load_w(l - LA, kw, bw);
-          }
+        constexpr int f0 = due(q, NF, NM), f1 = due(q + 1, NF, NM);
+        each<f1 - f0>([&](auto n) __attribute__((always_inline)) {
+          constexpr int f = f0 + n;
+          if constexpr (f < TT) xa[nxt][f] = *reinterpret_cast<const typename M::frag*>(ap + fa[nxt] + f * 2048);
+          else { constexpr int i2 = f - TT; xw[nxt][i2] = *reinterpret_cast<const typename M::frag*>(wp + fw[nxt][i2 & 1] + (i2 >> 1) * 4096); }
+        });
+        if constexpr (s == 1) {                                    // refill the buffers this step has just freed
+          constexpr int l0 = due(q, NL, NM), l1 = due(q + 1, NL, NM);
+          each<l1 - l0>([&](auto n) __attribute__((always_inline)) {
+            constexpr int l = l0 + n;
+            if constexpr (l < LA) { if (more_a) load_a(l, ka, ba); }
+            else if constexpr (STEADY) load_w(l - LA, kw, bw);
+          });
         }
         __builtin_amdgcn_sched_barrier(0);                         // keep this order: reads and loads between the products
-      }
-    }
+      });
+    });
     bw = nbw; ba = nba;
-  }
+  };
+  int kt = 0;
+  for (; kt + NBW < nk; ++kt) step(std::true_type{}, kt);
+  for (; kt < nk; ++kt) step(std::false_type{}, kt);
 
   // ---- epilogue: lane = position t, outputs n .. n + 7 (N is a multiple of 8)
 #pragma unroll

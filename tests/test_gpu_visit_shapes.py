@@ -53,6 +53,23 @@ def test_first_visits_with_every_tile_shape(dtype, d, heads, kv, h, d_ff, T):
     g.sync()
 
 
+# Tiles of 256 x 256, 256 x 192, 192 x 192, 128 x 192, 96 x 128 and 64 x 96: each in the QKV, split, residual and MLP product
+@pytest.mark.parametrize("T,d,heads,kv,d_ff,mlp", [
+    (2090, 72, 32, 32, 2056, GELU), (1473, 72, 2, 2, 4104, {}),                                                    # 256 x 256
+    (1068, 72, 32, 32, 2056, GELU), (973, 3080, 8, 2, 5512, GELU), (1971, 3080, 2, 1, 24, GELU), (1199, 72, 2, 2, 5144, GELU),   # 256 x 192
+    (1408, 1032, 32, 32, 24, GELU), (1182, 3208, 4, 1, 4104, {}), (2475, 3080, 16, 2, 24, {}), (688, 1032, 4, 4, 5656, {}),      # 192 x 192
+    (543, 72, 32, 32, 5360, GELU), (328, 3080, 64, 2, 24, GELU), (1195, 3080, 2, 1, 24, GELU), (394, 72, 2, 2, 4104, {}),        # 128 x 192
+    (400, 72, 32, 32, 24, GELU), (2092, 1032, 2, 1, 4104, GELU), (195, 72, 2, 1, 4104, {}),                        # 96 x 128
+    (70, 72, 16, 4, 24, GELU), (267, 1032, 2, 2, 24, GELU), (83, 72, 4, 2, 2056, {})])                             # 64 x 96
+def test_first_visits_with_tiles_that_are_no_power_of_two(T, d, heads, kv, d_ff, mlp):
+    cfg = S.tiny(n_layer=1, d_model=d, n_head=heads, n_kv_head=kv, head_dim=64, d_ff=d_ff, vocab=61, max_ctx=T, **{**mlp, "dtype": S.DT_BF16})
+    w = S.make_weights(cfg, 57, exercise=True)
+    o, g = pair(cfg, w, 0, 1, max_prefill=T)
+    x = S.make_activations(cfg, 58, 0, T)
+    check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", T))
+    g.sync()
+
+
 @pytest.mark.parametrize("T", [5, 300])
 def test_output_rows_off_a_16_byte_boundary(T):
     cfg = ragged()
