@@ -658,15 +658,17 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
   const int d = c.d_model, H = c.n_head, K = c.n_kv_head, h = c.head_dim, F = c.d_ff;
   const int ak = act_kind(c);
   const bool embed = p->flags & MDI_HAS_EMBED, swiglu = c.mlp_kind == MDI_MLP_SWIGLU;
-  RowsInArgs ri{acts_in, embed ? IN_TOKEN : ak, p->wte, p->wpe, (int)c.dtype, (int)T, d, p->p_xres, (int)c.vocab, p->err, pos0};
-  launch_rows_input(s, ri);
+  const size_t four = 4 * p->esz;
+  RowSource src{acts_in, embed ? IN_TOKEN : ak, (uintptr_t)acts_in % four == 0, p->wte, p->wpe, (int)c.vocab, p->err, pos0};   // until the first norm has taken it
   // Residual products with few positions split their inner dimension; the norm that follows adds the partial results.
   int pend_S = 1;
   const float* pend_bias = nullptr;
   auto norm = [&](const float* g, const float* b, void* out, void* hand_off) {
-    NormRowsArgs n{p->p_xres, (int)T, d, (int)c.norm_kind, g, b, c.norm_eps, out, ak, pend_S, p->p_part, (long)T * d, pend_bias, hand_off};
+    NormRowsArgs n{p->p_xres, (int)T, d, (int)c.norm_kind, g, b, c.norm_eps, out, ak, pend_S, p->p_part, (long)T * d, pend_bias, hand_off,
+                   (uintptr_t)hand_off % four == 0, src};
     launch_norm_rows(s, n);
     pend_S = 1;
+    src.in = nullptr;
   };
   const int aligned = ((uintptr_t)acts_out & 15) == 0;
   auto resid = [&](const void* A, const void* W, const float* bias, int Kd, void* hand_off) {

@@ -105,22 +105,24 @@ struct SampleBatchArgs {              // the same draw for up to 16 samples, one
 void launch_sample_topk_batch(hipStream_t s, int m, const SampleBatchArgs& a);
 
 // ---- prefill (first visit: T positions at once; Alg. 2) -------------------
-struct RowsInArgs {
-  const void* in; int in_kind; const void* wte; const void* wpe; int dtype;
-  int T, d; float* xres;
+// Where the rows of a call come from: token ids (embedded on the way) or hidden states in the storage type.
+struct RowSource {
+  const void* in;                    // nullptr: the rows are in the residual stream
+  int in_kind, aligned;              // aligned: `in` may be read four values at a time
+  const void* wte; const void* wpe;
   int vocab; int* err;               // a token id outside [0, vocab) sets *err = 2 and is read as token 0
   int pos0;                          // position of row 0 (a first visit in several chunks continues at the cache length)
 };
-void launch_rows_input(hipStream_t s, const RowsInArgs& a);
 
-// Residual rows x [T, d]: adds what the product before left as partial results (S > 1: part[0 .. S - 1], each [T, d]
-// part_stride floats apart, and the product's bias), keeps the sum in x, then normalises it into `out` (nullptr: no
-// norm follows) and / or copies it to act_out.
+// Residual rows x [T, d], or those of `src`: adds what the product before left as partial results (S > 1: part[0 .. S - 1],
+// each [T, d] part_stride floats apart, and the product's bias), normalises the sum into `out` and keeps it in x (out =
+// nullptr: neither) and / or copies it to act_out.
 struct NormRowsArgs {
   float* x; int T, d; int norm_kind; const float* g; const float* b; float eps;
-  void* out; int out_kind;
+  void* out; int out_kind;           // out_kind: the storage type, of everything here that is not fp32
   int S; const float* part; long part_stride; const float* part_bias;
-  void* act_out;                     // hand-off copy in the storage type (same kind as out) or nullptr
+  void* act_out; int act_aligned;    // hand-off copy in the storage type or nullptr; may it be written four values at a time
+  RowSource src;
 };
 void launch_norm_rows(hipStream_t s, const NormRowsArgs& a);
 

@@ -3,104 +3,137 @@
 // iteration for current sample").  With T rows the linear layers are dense
 // contractions, which run on the matrix cores (gemm_impl.h); this file holds what
 // stands between them, and the set-up kernels.
+#include <type_traits>
+
 #include "device_utils.h"
 
 namespace mdi {
 
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_rows_input(RowsInArgs a) {
-  const int t = blockIdx.x;
-  float* xr = a.xres + (long)t * a.d;
-  if (a.in_kind == IN_TOKEN) {
-    const long tok = checked_token(a.in, t, a.vocab, a.err);
-    const int wk = a.dtype == MDI_BF16 ? IN_BF16 : IN_F32;
-    for (int i = threadIdx.x; i < a.d; i += kBlock) {
-      float v = load_kind(a.wte, wk, tok * a.d + i);
-      if (a.wpe) v += load_kind(a.wpe, wk, (long)(a.pos0 + t) * a.d + i);
-      xr[i] = v;
-    }
+
+// four consecutive values in the storage type, at a multiple of four from an aligned base
+__device__ __forceinline__ void put_four(void* base, int kind, long at, const float4& v) {
+  if (kind == IN_BF16) {
+    uint2 w;
+    w.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
+    w.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
+    *reinterpret_cast<uint2*>((bf16_t*)base + at) = w;
   } else {
-    for (int i = threadIdx.x; i < a.d; i += kBlock) xr[i] = load_kind(a.in, a.in_kind, (long)t * a.d + i);
+    *reinterpret_cast<float4*>((float*)base + at) = v;
   }
-}
-void launch_rows_input(hipStream_t s, const RowsInArgs& a) {
-  hipLaunchKernelGGL(k_rows_input, dim3(a.T), dim3(kBlock), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------
 // One workgroup per row, the row in registers (NV pieces of four values per thread; NV = 0: rows beyond 8192 values
-// are read again for every pass).  Bound by memory: the row is read once - with S partial results of the product
-// before, S times more - and written once or twice.  Adding the partial results here costs no launch and no pass of
-// its own.
+// are read again for every pass).  The first one of a call takes the row from the node's input (embeds a token, or widens
+// the hidden state that arrived), the others from the residual stream, and adds the partial results of the product before.
+// Bound by memory: the row is read once - with S partial results S times more - and written once or twice.  Adding the
+// partial results here costs no launch and no pass of its own, nor does taking the input.
+//
+// With few rows what counts is how many round trips to memory a row takes: everything that can be asked for is, before
+// anything is stored (a store between two loads keeps the compiler from asking for the second before the first is there).
+// 256 rows of 4096 with two to four partial results 7.5 -> 6.8 us, 1024 rows 12.9 -> 11.6; a kernel of its own for the input took 10
+// to 14 us there (41 at 6000 rows) and left the row to be read again.
 template <int NV>
 __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
-  __shared__ float red[8];
+  __shared__ float red[2][kBlock / kWave];
   const int t = blockIdx.x, d4 = a.d >> 2;
   float4* x = reinterpret_cast<float4*>(a.x + (long)t * a.d);
   const float4* g4 = reinterpret_cast<const float4*>(a.g);
   const float4* b4 = reinterpret_cast<const float4*>(a.b);
   constexpr int NR = NV ? NV : 1;
-  float4 v[NR];
-  auto fetch = [&](int i) {                          // the row's piece i with the partial results added, split by split
-    float4 r = x[i];
-    if (a.S > 1) {
-      if (a.part_bias) { const float4 p = reinterpret_cast<const float4*>(a.part_bias)[i]; r.x += p.x; r.y += p.y; r.z += p.z; r.w += p.w; }
-      const float4* p4 = reinterpret_cast<const float4*>(a.part + (long)t * a.d) + i;
-#pragma unroll 4
-      for (int s = 0; s < a.S; ++s) {
-        const float4 p = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p4) + s * a.part_stride);
-        r.x += p.x; r.y += p.y; r.z += p.z; r.w += p.w;
-      }
-      x[i] = r;
-    }
-    if (a.act_out) {
-      const long at = (long)t * a.d + 4 * i;
-      store_kind(a.act_out, a.out_kind, at, r.x); store_kind(a.act_out, a.out_kind, at + 1, r.y);
-      store_kind(a.act_out, a.out_kind, at + 2, r.z); store_kind(a.act_out, a.out_kind, at + 3, r.w);
-    }
+  float4 v[NR], g[NR];
+  auto add = [](float4& r, const float4& p) { r.x += p.x; r.y += p.y; r.z += p.z; r.w += p.w; };
+  // four values of a row in the storage type; `aligned`: the base may be read in pieces of four
+  auto four = [](const void* base, int kind, bool aligned, long at) __attribute__((always_inline)) {
+    if (!aligned) return float4{load_kind(base, kind, at), load_kind(base, kind, at + 1), load_kind(base, kind, at + 2), load_kind(base, kind, at + 3)};
+    if (kind == IN_F32) return *reinterpret_cast<const float4*>((const float*)base + at);
+    const uint2 w = *reinterpret_cast<const uint2*>((const bf16_t*)base + at);
+    return float4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u)};
+  };
+  const int kind = a.out_kind;                       // storage type: of embeddings, hidden states, and what is written here
+  const long tok = a.src.in && a.src.in_kind == IN_TOKEN ? checked_token(a.src.in, t, a.src.vocab, a.src.err) : 0;
+  auto start = [&](int i) __attribute__((always_inline)) {         // piece i of the row before partial results
+    if (!a.src.in) return x[i];
+    if (a.src.in_kind != IN_TOKEN) return four(a.src.in, kind, a.src.aligned, (long)t * a.d + 4 * i);
+    float4 r = four(a.src.wte, kind, true, tok * a.d + 4 * i);
+    if (a.src.wpe) add(r, four(a.src.wpe, kind, true, (long)(a.src.pos0 + t) * a.d + 4 * i));
     return r;
   };
-  auto each = [&](auto&& f) {                        // f(piece, its values)
-    if (NV) {
-#pragma unroll
-      for (int j = 0; j < NR; ++j) { const int i = threadIdx.x + j * kBlock; if (i < d4) f(i, v[j]); }
+  auto part = [&](int s, int i) __attribute__((always_inline)) { return reinterpret_cast<const float4*>(a.part + s * a.part_stride + (long)t * a.d)[i]; };
+  auto keep = [&](int i, const float4& r) __attribute__((always_inline)) {
+    if (a.out && (a.S > 1 || a.src.in)) x[i] = r;    // without a norm to follow nobody reads the stream again
+    if (!a.act_out) return;
+    const long at = (long)t * a.d + 4 * i;
+    if (!a.act_aligned) {
+      store_kind(a.act_out, kind, at, r.x); store_kind(a.act_out, kind, at + 1, r.y);
+      store_kind(a.act_out, kind, at + 2, r.z); store_kind(a.act_out, kind, at + 3, r.w);
     } else {
-      for (int i = threadIdx.x; i < d4; i += kBlock) f(i, x[i]);
+      put_four(a.act_out, kind, at, r);
     }
   };
-  if (NV) {
+  auto each = [&](auto&& f) __attribute__((always_inline)) {       // f(number in this thread, piece)
 #pragma unroll
-    for (int j = 0; j < NR; ++j) { const int i = threadIdx.x + j * kBlock; if (i < d4) v[j] = fetch(i); }
+    for (int j = 0; j < NR; ++j) { const int i = threadIdx.x + j * kBlock; if (i < d4) f(j, i); }
+  };
+  if (NV) {
+    each([&](int j, int i) { v[j] = start(i); });
+    if (a.out) each([&](int j, int i) { g[j] = g4[i]; });
+    if (a.S > 1) {
+      if (a.part_bias) each([&](int j, int i) { add(v[j], reinterpret_cast<const float4*>(a.part_bias)[i]); });
+      constexpr int U = 4;                           // partial results asked for at a time
+      int s = 0;
+      auto some = [&](auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        float4 p[N][NR];
+#pragma unroll
+        for (int u = 0; u < N; ++u) each([&](int j, int i) { p[u][j] = part(s + u, i); });
+#pragma unroll
+        for (int u = 0; u < N; ++u) each([&](int j, int) { add(v[j], p[u][j]); });
+        s += N;
+      };
+      while (s + U <= a.S) some(std::integral_constant<int, U>{});
+      if (s + 2 <= a.S) some(std::integral_constant<int, 2>{});
+      if (s < a.S) some(std::integral_constant<int, 1>{});
+    }
+    each([&](int j, int i) { keep(i, v[j]); });
   } else {
-    for (int i = threadIdx.x; i < d4; i += kBlock) (void)fetch(i);
+    for (int i = threadIdx.x; i < d4; i += kBlock) {
+      float4 r = start(i);
+      if (a.S > 1) {
+        if (a.part_bias) add(r, reinterpret_cast<const float4*>(a.part_bias)[i]);
+        for (int s = 0; s < a.S; ++s) add(r, part(s, i));
+      }
+      keep(i, r);
+    }
   }
   if (!a.out) return;
+  auto row = [&](auto&& f) __attribute__((always_inline)) {        // f(values, gain, piece)
+    if (NV) each([&](int j, int i) { f(v[j], g[j], i); });
+    else for (int i = threadIdx.x; i < d4; i += kBlock) f(x[i], g4[i], i);
+  };
+  auto row_sum = [&](float s, float* r) __attribute__((always_inline)) {
+    s = wave_sum_to_lane63(s);
+    if ((threadIdx.x & 63) == 63) r[threadIdx.x >> 6] = s;
+    __syncthreads();
+    return (r[0] + r[1]) + (r[2] + r[3]);
+  };
   float mean = 0.f, s2 = 0.f;
   if (a.norm_kind == MDI_NORM_LAYERNORM) {
     float s = 0.f;
-    each([&](int, const float4& r) { s += (r.x + r.y) + (r.z + r.w); });
-    mean = block_sum(s, red) / (float)a.d;
-    each([&](int, const float4& r) {
+    row([&](const float4& r, const float4&, int) { s += (r.x + r.y) + (r.z + r.w); });
+    mean = row_sum(s, red[0]) / (float)a.d;
+    row([&](const float4& r, const float4&, int) {
       const float c0 = r.x - mean, c1 = r.y - mean, c2 = r.z - mean, c3 = r.w - mean;
       s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
     });
   } else {
-    each([&](int, const float4& r) { s2 += (r.x * r.x + r.y * r.y) + (r.z * r.z + r.w * r.w); });
+    row([&](const float4& r, const float4&, int) { s2 += (r.x * r.x + r.y * r.y) + (r.z * r.z + r.w * r.w); });
   }
-  const float rstd = 1.f / sqrtf(block_sum(s2, red) / (float)a.d + a.eps);
-  each([&](int i, const float4& r) {
-    const float4 g = g4[i];
-    float4 o = {(r.x - mean) * rstd * g.x, (r.y - mean) * rstd * g.y, (r.z - mean) * rstd * g.z, (r.w - mean) * rstd * g.w};
-    if (a.b) { const float4 b = b4[i]; o.x += b.x; o.y += b.y; o.z += b.z; o.w += b.w; }
-    const long at = (long)t * a.d + 4 * i;
-    if (a.out_kind == IN_BF16) {
-      uint2 p;
-      p.x = (uint32_t)f32_to_bf16(o.x) | ((uint32_t)f32_to_bf16(o.y) << 16);
-      p.y = (uint32_t)f32_to_bf16(o.z) | ((uint32_t)f32_to_bf16(o.w) << 16);
-      *reinterpret_cast<uint2*>((bf16_t*)a.out + at) = p;
-    } else {
-      *reinterpret_cast<float4*>((float*)a.out + at) = o;
-    }
+  const float rstd = 1.f / sqrtf(row_sum(s2, red[1]) / (float)a.d + a.eps);
+  row([&](const float4& r, const float4& gain, int i) {
+    float4 o = {(r.x - mean) * rstd * gain.x, (r.y - mean) * rstd * gain.y, (r.z - mean) * rstd * gain.z, (r.w - mean) * rstd * gain.w};
+    if (a.b) add(o, b4[i]);
+    put_four(a.out, kind, (long)t * a.d + 4 * i, o);
   });
 }
 void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
@@ -122,18 +155,8 @@ __global__ __launch_bounds__(kBlock) void k_rope_scatter(RopeScatterArgs a) {
   const int pos = a.pos0 + t;
   const int page = a.table[pos / a.pt], slot = pos % a.pt;
   const long pt_h = (long)a.pt * h;
-  const bool bf = a.dtype == MDI_BF16;
+  const int bf = a.dtype == MDI_BF16 ? IN_BF16 : IN_F32;
   // four consecutive pairs (i, i + h/2) per thread: h/2 is a multiple of 4, so everything moves in 8- or 16-byte pieces
-  auto put4 = [&](void* base, bool as_bf16, long o, const float4& v) __attribute__((always_inline)) {
-    if (as_bf16) {
-      uint2 w;
-      w.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
-      w.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
-      *reinterpret_cast<uint2*>((bf16_t*)base + o) = w;
-    } else {
-      *reinterpret_cast<float4*>((float*)base + o) = v;
-    }
-  };
   const int q4 = half >> 2;
   for (int p = threadIdx.x; p < n_heads * q4; p += kBlock) {
     const int head = p / q4, i = (p - head * q4) * 4;
@@ -148,18 +171,18 @@ __global__ __launch_bounds__(kBlock) void k_rope_scatter(RopeScatterArgs a) {
     }
     if (head < a.H) {
       const long o = (long)t * a.H * h + head * h + i;
-      if (a.q_out) { put4(a.q_out, false, o, v0); put4(a.q_out, false, o + half, v1); }
+      if (a.q_out) { put_four(a.q_out, IN_F32, o, v0); put_four(a.q_out, IN_F32, o + half, v1); }
       if (a.q_bf) {
         const float sc = a.scale;
-        put4(a.q_bf, true, o, float4{v0.x * sc, v0.y * sc, v0.z * sc, v0.w * sc});
-        put4(a.q_bf, true, o + half, float4{v1.x * sc, v1.y * sc, v1.z * sc, v1.w * sc});
+        put_four(a.q_bf, IN_BF16, o, float4{v0.x * sc, v0.y * sc, v0.z * sc, v0.w * sc});
+        put_four(a.q_bf, IN_BF16, o + half, float4{v1.x * sc, v1.y * sc, v1.z * sc, v1.w * sc});
       }
     } else {
       const bool is_v = head >= a.H + a.K;
       const int kvh = head - a.H - (is_v ? a.K : 0);
       const long o = (((long)page * a.K + kvh) * 2 + (is_v ? 1 : 0)) * pt_h + (long)slot * h + i;
-      put4(a.pool, bf, o, v0);
-      put4(a.pool, bf, o + half, v1);
+      put_four(a.pool, bf, o, v0);
+      put_four(a.pool, bf, o + half, v1);
     }
   }
 }

@@ -85,6 +85,21 @@ def test_output_rows_off_a_16_byte_boundary(T):
     assert np.array_equal(got[1:-1].reshape(T, 520), host(want))
 
 
+@pytest.mark.parametrize("kw", [{}, F32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("d,T", [(520, 5), (8200, 3)])
+def test_input_rows_off_a_boundary_of_four_values(d, T, kw):
+    """(Rows of 8200 values are not held in registers.)"""
+    cfg = ragged(d_model=d, d_ff=72, **kw)
+    g = mdi.Partition(cfg, S.make_weights(cfg, 62, exercise=True), 0, 1, max_seqs=2)
+    x = dev_acts(S.make_activations(cfg, 63, 0, T), cfg)
+    buf = torch.zeros((T * d + 2,), dtype=x.dtype, device="cuda:0")
+    off = buf[1:T * d + 1].view(T, d)
+    off.copy_(x)
+    got, want = g.prefill(0, off), g.prefill(1, x)
+    g.sync()
+    assert np.array_equal(host(got), host(want))
+
+
 @pytest.mark.parametrize("page,heads,kv,h,cuts", [(64, 4, 2, 128, (130, 62, 1, 200)), (128, 4, 4, 64, (1, 127, 129, 64)), (48, 4, 1, 128, (100, 93, 7)),
                                                   (16, 4, 2, 64, (15, 17, 96, 200)), (5, 2, 2, 64, (64, 70)), (64, 32, 8, 64, (1600,)),
                                                   (24, 32, 4, 128, (1540, 3))])
