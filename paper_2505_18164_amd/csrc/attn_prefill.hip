@@ -29,6 +29,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BQ = 128;       // queries per workgroup (32 per wavefront)
 constexpr int BK = 64;        // keys per step
+constexpr float kRaise = 8.f; // how far (in powers of two) a score may exceed its query's reference
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x2 read_transposed(const bf16_t* p) {
@@ -44,11 +45,13 @@ __device__ __forceinline__ float exp2f_raw(float x) { return __builtin_amdgcn_ex
 // group 0 first, so the result does not depend on timing.  With one, two workgroups share a compute unit and nothing
 // keeps them in step: one multiplies while the other takes exponentials.
 //
-// What bounds it: a block of 64 keys is 32 matrix instructions and about as much time on the vector ALUs (32 scores per
-// lane: subtract, exponential, sum, maximum, conversion), and a wavefront has one or the other to do.
-// 6000 positions of the 8B shape: 576 us a layer with the blocks single-buffered between two barriers, the groups in
-// step, base-e exponentials and a rescaling in every block; now 490 us (0.60 PFLOP/s), of which heads that share keys on
-// one die give 20.
+// What bounds it: a block of 64 keys is 32 matrix instructions (about 1000 cycles of a SIMD), half as much again on the vector
+// ALUs (32 scores per lane: maximum, exponential, sum, conversion), and 32 KiB of LDS reads per wavefront, which take as long
+// as the matrix instructions when all four SIMDs ask.
+// 6000 positions of the 8B shape: 500 us a layer with a mask (four instructions a score) and a subtraction in every block and
+// a rescaling wherever any of a wavefront's 32 queries found a new maximum, which is most blocks; 369 us (0.79 PFLOP/s) with
+// the mask in the last blocks only, scores that come out relative, and a rescaling when it is needed.  1024 positions of the
+// 7B shape 33 -> 28, pieces of 256 23 -> 20 us.  Heads that share keys on one die give 20 of it.
 template <int HD, int NG>
 __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   constexpr int KS = HD + 8;            // LDS row stride of a key (elements): 16 bytes of padding spread the rows over the banks
@@ -58,7 +61,7 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char flash_smem[];
   constexpr int KV = BK * KS + BK * VR;                 // elements of a key block and its values; two blocks per group
 
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // position inside the group
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // position inside the group
   const int grp = threadIdx.x >> 8;
   bf16_t* bufs = (bf16_t*)flash_smem + grp * 2 * KV;
   // Workgroups are handed to the eight compute dies in turn, each with an L2 of its own: a die takes heads that follow
@@ -84,7 +87,14 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   for (int i = 0; i < HT; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
-  float m = -1e30f, l = 0.f;
+  // Scores are kept relative to m, the query's reference: the products start from -m, so nothing is subtracted afterwards.
+  // m is the maximum of the first block and is raised only when a score exceeds it by more than kRaise: a softmax's weights
+  // may be scaled by any number, and 2^8 costs neither bf16 nor fp32 a digit.
+  float m = 0.f, l = 0.f;
+  bool first = true;
+  f32x16 neg_m;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) neg_m[r] = 0.f;
 
   const int p0 = a.p0;                                           // position of query 0: keys 0 .. p0 + query are visible
   const int n_keys = p0 + a.T, n_kb = min((p0 + q0 + BQ + BK - 1) / BK, (n_keys + BK - 1) / BK); // key blocks any query of this workgroup may see
@@ -162,40 +172,45 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
       f32x16 s[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+        s[t] = neg_m;
         const bf16_t* kr = Ks + (32 * t + col) * KS + 8 * half;
 #pragma unroll
         for (int ks = 0; ks < HD / 16; ++ks)
           s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kr + 16 * ks), qf[ks], s[t], 0, 0, 0);
       }
-      // ---- causal mask and the lane's share of the row statistics (row of S = column here = this lane's query)
-      float mloc = -1e30f;
-      const bool diag = k0 + BK - 1 > p0 + qw0;
+      // ---- causal mask (the last blocks only) and the lane's share of the row statistics (row of S = column here = this
+      //      lane's query)
+      if (k0 + BK - 1 > p0 + qw0) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (k0 + 32 * t + 8 * (r >> 2) + 4 * half + (r & 3) > p0 + query) s[t][r] = -1e30f;
+      }
+      float top = -1e30f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + 32 * t + 8 * (r >> 2) + 4 * half + (r & 3);
-          if (diag && key > p0 + query) s[t][r] = -1e30f;
-          mloc = fmaxf(mloc, s[t][r]);
-        }
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-      const float mn = fmaxf(m, mloc);
-      if (__any(mn != m)) {                                        // rare after the first blocks
-        const float alpha = exp2f_raw(m - mn);
-        m = mn;
+        for (int r = 0; r < 16; ++r) top = fmaxf(top, s[t][r]);
+      if (first || __any(top > kRaise)) {
+        top = fmaxf(top, __shfl_xor(top, 32, 64));               // both lanes of a query raise alike
+        const float by = first || top > 0.f ? top : 0.f;
+        const float alpha = first ? 0.f : exp2f_raw(-by);
+        first = false;
+        m += by;
         l *= alpha;
 #pragma unroll
         for (int i = 0; i < HT; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { s[0][r] -= by; s[1][r] -= by; neg_m[r] = -m; }
       }
       float lsum = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { const float p = exp2f_raw(s[t][r] - mn); s[t][r] = p; lsum += p; }
+        for (int r = 0; r < 16; ++r) { const float p = exp2f_raw(s[t][r]); s[t][r] = p; lsum += p; }
       l += lsum;                                                   // the two lanes of a query keep separate sums until the end
 
       // ---- O^T += V^T P^T.  Step (t, pp) contracts keys [32 t + 16 pp, + 16); inside a step this half of the
@@ -229,14 +244,14 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
       for (int i = 0; i < HT; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) fold[(i * 16 + r) * 256 + tid] = o[i][r];
-      fold[(HT * 16) * 256 + tid] = m;
+      fold[(HT * 16) * 256 + tid] = first ? -1e30f : m;
       fold[(HT * 16 + 1) * 256 + tid] = l;
     }
     __syncthreads();
     if (grp == 1) return;
     const float m1 = fold[(HT * 16) * 256 + tid], l1 = fold[(HT * 16 + 1) * 256 + tid];
     const float mn = fmaxf(m, m1);
-    const float a0 = exp2f_raw(m - mn), a1 = exp2f_raw(m1 - mn);   // a group that saw no key has m = -1e30, l = 0, o = 0
+    const float a0 = exp2f_raw(m - mn), a1 = exp2f_raw(m1 - mn);   // group 0 has seen key 0; of a group that saw none m = -1e30 and nothing stays
     l = l * a0 + l1 * a1;
 #pragma unroll
     for (int i = 0; i < HT; ++i)
