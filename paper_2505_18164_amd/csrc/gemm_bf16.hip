@@ -45,12 +45,12 @@ bool allow_epi() {
 GemmPlan plan_gemm_bf16(int n_cu, int T, int N, int Kd, size_t part_floats) { return plan_shape(kShape, kShapes, 2, n_cu, T, N, Kd, part_floats); }
 
 bool allow_gemm_lds_bf16() {
-  return allow_epi<GEPI_F32_BIAS>() && allow_epi<GEPI_RESID>() && allow_epi<GEPI_PART>() && allow_epi<GEPI_SWIGLU>() && allow_epi<GEPI_GELU>();
+  return allow_epi<GEPI_QKV>() && allow_epi<GEPI_RESID>() && allow_epi<GEPI_PART>() && allow_epi<GEPI_SWIGLU>() && allow_epi<GEPI_GELU>();
 }
 
 void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a) {
   switch (epi) {
-    case GEPI_F32_BIAS: launch_epi<GEPI_F32_BIAS>(s, shape, a); break;
+    case GEPI_QKV: launch_epi<GEPI_QKV>(s, shape, a); break;
     case GEPI_RESID: launch_epi<GEPI_RESID>(s, shape, a); break;
     case GEPI_PART: launch_epi<GEPI_PART>(s, shape, a); break;
     case GEPI_SWIGLU: launch_epi<GEPI_SWIGLU>(s, shape, a); break;

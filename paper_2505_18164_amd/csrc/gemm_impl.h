@@ -122,17 +122,26 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   const int rot = (die * nk) >> 3;
   const int tail = row_bytes & 127;                     // bytes of a partial last step: pieces past them are zero
 
-  const u32x4 rw = buffer_of((const char*)a.W + (long)n0 * row_bytes), ra = buffer_of((const char*)a.A + (long)t0 * row_bytes);
+  // Row r of a weight tile is output n0 + r.  The QKV product's outputs are dealt out in eights: four of the first half of a
+  // head and the four they are rotated with, so that a pair is in one lane whatever the tile and wherever it starts.
+  const int base = EPI == GEPI_QKV ? n0 & -a.qkv.h : n0;
+  auto w_row = [&](int r) __attribute__((always_inline)) {          // counted from `base`; rows past the matrix re-read its last row
+    const int n = min(n0 + r, a.N - 1);
+    if constexpr (EPI != GEPI_QKV) return n - base;
+    const int in = n & (a.qkv.h - 1);
+    return n - in - base + 4 * (in >> 3) + (in & 3) + (in & 4 ? a.qkv.h >> 1 : 0);
+  };
+  const u32x4 rw = buffer_of((const char*)a.W + (long)base * row_bytes), ra = buffer_of((const char*)a.A + (long)t0 * row_bytes);
   // Row r of a weight tile keeps its 16-byte piece c at slot c ^ (r bit 1, r bits 3 - 4), of a position tile at
   // c ^ (r bits 1 - 3): the sixteen rows a fragment read touches then differ in (row parity, slot).
   auto w_slot = [](int r) { return ((r >> 1) & 1) | (((r >> 3) & 3) << 1); };
   auto a_slot = [](int r) { return (r >> 1) & 7; };
-  int vw[LW], va[LA];                                   // rows past the matrix re-read its last row
+  int vw[LW], va[LA];
   bool zw[LW], za[LA];                                  // this lane's piece lies past a partial last step
 #pragma unroll
   for (int i = 0; i < LW; ++i) {
     const int r = (i * NW + wave) * 8 + (lane >> 3), c = (lane & 7) ^ w_slot(r);
-    vw[i] = min(r, a.N - 1 - n0) * row_bytes + (c << 4); zw[i] = tail && (c << 4) >= tail;
+    vw[i] = w_row(r) * row_bytes + (c << 4); zw[i] = tail && (c << 4) >= tail;
   }
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
@@ -166,6 +175,33 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   }
   const unsigned char* w_wave = gemm_smem + wn * (BN / WN) * 128;
   const unsigned char* a_wave = gemm_smem + NBW * WB + wt * (BT / WT) * 128;
+
+  // The QKV product's epilogue rotates queries and keys and puts keys and values into the pages.  (A kernel of its own read the
+  // rows back in fp32: 13.8 us at 1024 positions of the 7B shape, 8.2 at 256, 4.9 at 333 of TinyLlama, 50 at 6000 of the 8B
+  // shape; the epilogue takes 3 to 4 us longer.)  What it needs besides the sums, angles and page numbers, small tiles ask for
+  // before the first step - asked for in the epilogue they cost 1.5 to 2 us more - and tiles that need the registers one position ahead.
+  constexpr bool ASK_EARLY = TN * TT <= 12;
+  const int h_sh = EPI == GEPI_QKV ? 31 - __builtin_clz(a.qkv.h) : 0;
+  f32x4 cs[TT][TN / 2][2];                                         // (cos, sin) of four pairs
+  int page[TT];
+  auto head_of = [&](int p) __attribute__((always_inline)) { return (n0 + wn * (BN / WN) + 8 * g + 32 * p) >> h_sh; };
+  auto pair_of = [&](int p) __attribute__((always_inline)) { return ((n0 + wn * (BN / WN) + 8 * g + 32 * p) & (a.qkv.h - 1)) >> 1; };
+  auto page_no = [&](int pos) __attribute__((always_inline)) { return a.qkv.pt_sh >= 0 ? pos >> a.qkv.pt_sh : (int)__umulhi((unsigned)pos, a.qkv.pt_magic); };
+  auto ask_pairs = [&](int j) __attribute__((always_inline)) {
+    const QkvOut& o = a.qkv;
+    const int pos = o.pos0 + min(t0 + wt * (BT / WT) + j * 16 + m, a.T - 1);
+    if (n0 + BN > o.H << h_sh) page[j] = o.table[page_no(pos)];    // a tile of queries alone needs none
+    if (!o.rope) return;
+#pragma unroll
+    for (int p = 0; p < TN / 2; ++p) {                             // (values and rows past the last have no use for theirs)
+      const f32x4* r = reinterpret_cast<const f32x4*>(o.rope + (long)pos * (o.h >> 1) + pair_of(p));
+      cs[j][p][0] = r[0]; cs[j][p][1] = r[1];
+    }
+  };
+  if constexpr (EPI == GEPI_QKV && ASK_EARLY) {
+#pragma unroll
+    for (int j = 0; j < TT; ++j) ask_pairs(j);
+  }
 
   // fill the rings; the first step waits only for its own pieces
 #pragma unroll
@@ -236,6 +272,54 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   for (; kt + NBW < nk; ++kt) step(std::true_type{}, kt);
   for (; kt < nk; ++kt) step(std::false_type{}, kt);
 
+  // ---- epilogue of the QKV product: lane = position t, four pairs (i, i + h / 2) of a head: rotated where the head is one of
+  // the queries' or keys', then stored where it is wanted
+  if constexpr (EPI == GEPI_QKV) {
+    const QkvOut& o = a.qkv;
+    const int half = o.h >> 1;
+    if constexpr (!ASK_EARLY) ask_pairs(0);
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+      if (!ASK_EARLY && j + 1 < TT) ask_pairs(j + 1);
+      const int t = t0 + wt * (BT / WT) + j * 16 + m;
+      if (t >= a.T) continue;
+#pragma unroll
+      for (int p = 0; p < TN / 2; ++p) {
+        const int hd = head_of(p), in = pair_of(p);
+        if (hd >= o.H + 2 * o.K) continue;
+        f32x4 x = acc[2 * p][j], y = acc[2 * p + 1][j];
+        if (a.bias) {
+          const float* b = a.bias + hd * o.h + in;
+          x += *reinterpret_cast<const f32x4*>(b);
+          y += *reinterpret_cast<const f32x4*>(b + half);
+        }
+        if (o.rope && hd < o.H + o.K) {
+          const f32x4 c = {cs[j][p][0][0], cs[j][p][0][2], cs[j][p][1][0], cs[j][p][1][2]}, s = {cs[j][p][0][1], cs[j][p][0][3], cs[j][p][1][1], cs[j][p][1][3]};
+          const f32x4 x0 = x;
+          x = x0 * c - y * s;
+          y = x0 * s + y * c;
+        }
+        if (hd < o.H) {
+          const long to = ((long)t * o.H + hd) * o.h + in;
+          if (o.q_bf) {
+            x *= o.scale; y *= o.scale;
+            put4<bf16_t>(o.q_bf, to, x[0], x[1], x[2], x[3]);
+            put4<bf16_t>(o.q_bf, to + half, y[0], y[1], y[2], y[3]);
+          } else {
+            put4<float>(o.q_out, to, x[0], x[1], x[2], x[3]);
+            put4<float>(o.q_out, to + half, y[0], y[1], y[2], y[3]);
+          }
+        } else {
+          const int is_v = hd >= o.H + o.K, kv = hd - o.H - (is_v ? o.K : 0), pos = o.pos0 + t;
+          const long to = ((((long)page[j] * o.K + kv) * 2 + is_v) * o.pt + (pos - page_no(pos) * o.pt)) * o.h + in;
+          put4<ST>(o.pool, to, x[0], x[1], x[2], x[3]);
+          put4<ST>(o.pool, to + half, y[0], y[1], y[2], y[3]);
+        }
+      }
+    }
+    return;
+  }
+
   // ---- epilogue: lane = position t, outputs n .. n + 7 (N is a multiple of 8)
 #pragma unroll
   for (int j = 0; j < TT; ++j) {
@@ -269,9 +353,7 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
           for (int e = 0; e < 4; ++e) { v[e] += b0[e]; v[4 + e] += b1[e]; }
         }
         const long o = (long)t * a.N + n;
-        if (EPI == GEPI_F32_BIAS) {
-          put8<float>(a.out_f32, o, v);
-        } else if (EPI == GEPI_RESID) {
+        if (EPI == GEPI_RESID) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) { v[e] += res[2 * p][e]; v[4 + e] += res[2 * p + 1][e]; }
           put8<float>(a.out_f32, o, v);

@@ -67,7 +67,7 @@ struct mdi_partition {
   tagged_t* hb_cand = nullptr; tagged_t* cand = nullptr; int* herr = nullptr; float* hb_logits = nullptr; float* hb_peaks = nullptr;
   unsigned* counters = nullptr;  // [H] attention + [1] argmax
   // prefill scratch
-  float *p_xres = nullptr, *p_qkv = nullptr, *p_q = nullptr;
+  float *p_xres = nullptr, *p_q = nullptr;
   void *p_xn = nullptr, *p_o = nullptr, *p_u = nullptr;
   float* p_part = nullptr;       // partial results of products whose inner dimension is split
   size_t part_cap = 0;           // ... in floats
@@ -244,14 +244,13 @@ size_t carve(mdi_partition* p, void* arena) {
     const size_t T = p->Tm;
     p->p_xres = (float*)cv.take(T * d * 4);
     p->p_xn = cv.take(T * d * B);
-    p->p_qkv = (float*)cv.take(T * nqkv * 4);
-    p->p_q = (float*)cv.take(T * H * h * 4);
     p->p_o = cv.take(T * H * h * B);
     p->p_u = cv.take(T * F * B);
     // few positions are cut into up to kMaxKSplits pieces, more positions into fewer: 4096 rows of partial results
     p->part_cap = std::min<size_t>(T * kMaxKSplits, 4096) * d;
     p->p_part = (float*)cv.take(p->part_cap * 4);
     if (flash_supported(c.dtype, (int)h)) p->p_qb = (bf16_t*)cv.take(T * H * h * 2);
+    else p->p_q = (float*)cv.take(T * H * h * 4);
   }
   return (cv.off + 255) & ~(size_t)255;
 }
@@ -679,20 +678,20 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     launch_gemm(s, c.dtype, pl.S > 1 ? GEPI_PART : GEPI_RESID, pl.shape, ga);
     if (pl.S > 1 && hand_off) norm(nullptr, nullptr, nullptr, hand_off);
   };
+  const bool flash = p->p_qb != nullptr;
+  const float scale = 1.f / sqrtf((float)h);
+  const bool pow2 = (p->pt & (p->pt - 1)) == 0;
+  const int pt_sh = pow2 ? __builtin_ctz((unsigned)p->pt) : -1;
+  const unsigned pt_magic = pow2 ? 0u : 0xFFFFFFFFu / (unsigned)p->pt + 1u;
   for (int i = 0; i < p->n_local; ++i) {
     const LayerPacked& L = p->layers[i];
     norm(L.ln1_g, L.ln1_b, p->p_xn, nullptr);
-    GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, p->p_qkv, nullptr, 0, 0, 1};
-    launch_gemm(s, c.dtype, GEPI_F32_BIAS, plan_gemm(c.dtype, p->n_cu, (int)T, g1.N, d, 0).shape, g1);
-    const bool flash = p->p_qb != nullptr;
-    const float scale = 1.f / sqrtf((float)h);
-    RopeScatterArgs rs{p->p_qkv, (int)T, H, K, h, p->pt, p->rope, flash ? nullptr : p->p_q, L.kv, drow, (int)c.dtype,
-                       flash ? p->p_qb : nullptr, scale * 1.44269504f, pos0};   // log2 e: k_flash_prefill's exponentials are powers of two
-    launch_rope_scatter(s, rs);
+    GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, nullptr, nullptr, 0, 0, 1,
+                {H, K, h, p->pt, pt_sh, pt_magic, pos0, p->rope, p->p_q, p->p_qb, scale * 1.44269504f, L.kv, drow}};   // log2 e: k_flash_prefill's exponentials are powers of two
+    launch_gemm(s, c.dtype, GEPI_QKV, plan_gemm(c.dtype, p->n_cu, (int)T, g1.N, d, 0).shape, g1);
     if (flash) {
-      const bool pow2 = (p->pt & (p->pt - 1)) == 0;
       FlashArgs fa{p->p_qb, (const bf16_t*)L.kv, drow, (bf16_t*)p->p_o, (int)T, ((int)T + 127) / 128 * 128, H, K, h, pos0,
-                   p->pt, pow2 ? __builtin_ctz((unsigned)p->pt) : -1, pow2 ? 0u : 0xFFFFFFFFu / (unsigned)p->pt + 1u};
+                   p->pt, pt_sh, pt_magic};
       launch_flash_prefill(s, fa);
     } else {
       AttnArgs at{};

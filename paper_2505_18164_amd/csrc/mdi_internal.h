@@ -126,17 +126,31 @@ struct NormRowsArgs {
 };
 void launch_norm_rows(hipStream_t s, const NormRowsArgs& a);
 
-enum GemmEpi { GEPI_F32_BIAS = 0, GEPI_RESID = 1, GEPI_SWIGLU = 2, GEPI_GELU = 3, GEPI_PART = 4 };
+// Where the QKV product leaves its rows: queries, rotated, for the attention kernel; keys (rotated) and values in the sample's pages.
+struct QkvOut {
+  int H, K, h, pt;        // h: a power of two from 8 on; pt: positions per page
+  int pt_sh; unsigned pt_magic;   // page of a position: as in FlashArgs
+  int pos0;               // position of row 0
+  const float2* rope;     // (cos, sin) [max_ctx][h/2] or nullptr
+  float* q_out;           // [T, H*h] fp32, or nullptr
+  bf16_t* q_bf;           // [T, H*h], times `scale`: the queries of the matrix-core attention, or nullptr
+  float scale;
+  void* pool;             // this layer's pages, storage dtype
+  const int32_t* table;
+};
+
+enum GemmEpi { GEPI_QKV = 0, GEPI_RESID = 1, GEPI_SWIGLU = 2, GEPI_GELU = 3, GEPI_PART = 4 };
 struct GemmArgs {
   const void* A;     // [T, Kd] storage dtype
   const void* W;     // [N, Kd] storage dtype
   const float* bias; // [N] or nullptr
   int T, N, Kd;      // N and Kd multiples of 8
-  float* out_f32;    // GEPI_F32_BIAS: [T, N]; GEPI_RESID: residual stream [T, N], updated in place; GEPI_PART: [S][T, N]
+  float* out_f32;    // GEPI_RESID: residual stream [T, N], updated in place; GEPI_PART: [S][T, N]
   void* out_act;     // SWIGLU: [T, N/2]; GELU: [T, N]; RESID: optional hand-off copy [T, N]; storage dtype
   int gelu_tanh;     // GELU: the tanh form, else the erf form
   int act_aligned;   // out_act may be written 16 bytes at a time
   int S;             // splits of the inner dimension (1 unless GEPI_PART): split s leaves its sums at out_f32 + s T N
+  QkvOut qkv;        // GEPI_QKV: N = (H + 2 K) h
 };
 // gemm_bf16.hip, gemm_f32.hip: the tile shape for a product, and into how many pieces its inner dimension is cut so that
 // few positions still fill the chip; part_floats = room for partial results, 0 forbids a split.
@@ -155,20 +169,6 @@ inline GemmPlan plan_gemm(int dtype, int n_cu, int T, int N, int Kd, size_t part
 inline void launch_gemm(hipStream_t s, int dtype, int epi, int shape, const GemmArgs& a) {
   if (dtype == MDI_BF16) launch_gemm_bf16(s, epi, shape, a); else launch_gemm_f32(s, epi, shape, a);
 }
-
-struct RopeScatterArgs {
-  const float* qkv;  // [T, (H+2K)h] fp32
-  int T, H, K, h, pt;
-  const float2* rope;     // [max_ctx][h/2] or nullptr
-  float* q_out;           // [T, H*h] fp32, or nullptr
-  void* pool;             // this layer's pages
-  const int32_t* table;
-  int dtype;
-  bf16_t* q_bf;           // [T][H*h], rotated and scaled by `scale`: the queries of the matrix-core attention, or nullptr
-  float scale;
-  int pos0;               // position of row 0
-};
-void launch_rope_scatter(hipStream_t s, const RopeScatterArgs& a);
 
 // Causal attention of a first visit on the matrix cores (bf16 operands, fp32 accumulation and softmax).
 struct FlashArgs {

@@ -9,7 +9,6 @@
 
 namespace mdi {
 
-
 // four consecutive values in the storage type, at a multiple of four from an aligned base
 __device__ __forceinline__ void put_four(void* base, int kind, long at, const float4& v) {
   if (kind == IN_BF16) {
@@ -143,51 +142,6 @@ void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
   else if (n <= 4) hipLaunchKernelGGL(k_norm_rows<4>, dim3(a.T), dim3(kBlock), 0, s, a);
   else if (n <= 8) hipLaunchKernelGGL(k_norm_rows<8>, dim3(a.T), dim3(kBlock), 0, s, a);
   else hipLaunchKernelGGL(k_norm_rows<0>, dim3(a.T), dim3(kBlock), 0, s, a);
-}
-
-// ---------------------------------------------------------------------------
-// Rotate q and k by their positions, keep q in fp32 for the attention kernel
-// and scatter k, v into the sample's pages.  One workgroup per prompt position.
-__global__ __launch_bounds__(kBlock) void k_rope_scatter(RopeScatterArgs a) {
-  const int t = blockIdx.x, h = a.h, half = h >> 1;
-  const int n_heads = a.H + 2 * a.K;
-  const float* row = a.qkv + (long)t * n_heads * h;
-  const int pos = a.pos0 + t;
-  const int page = a.table[pos / a.pt], slot = pos % a.pt;
-  const long pt_h = (long)a.pt * h;
-  const int bf = a.dtype == MDI_BF16 ? IN_BF16 : IN_F32;
-  // four consecutive pairs (i, i + h/2) per thread: h/2 is a multiple of 4, so everything moves in 8- or 16-byte pieces
-  const int q4 = half >> 2;
-  for (int p = threadIdx.x; p < n_heads * q4; p += kBlock) {
-    const int head = p / q4, i = (p - head * q4) * 4;
-    float4 v0 = *reinterpret_cast<const float4*>(row + head * h + i);
-    float4 v1 = *reinterpret_cast<const float4*>(row + head * h + i + half);
-    if (a.rope && head < a.H + a.K) {
-      const float4 c01 = *reinterpret_cast<const float4*>(a.rope + (long)pos * half + i);       // (cos, sin) of pairs i, i+1
-      const float4 c23 = *reinterpret_cast<const float4*>(a.rope + (long)pos * half + i + 2);   // ... i+2, i+3
-      const float4 r0 = {v0.x * c01.x - v1.x * c01.y, v0.y * c01.z - v1.y * c01.w, v0.z * c23.x - v1.z * c23.y, v0.w * c23.z - v1.w * c23.w};
-      const float4 r1 = {v0.x * c01.y + v1.x * c01.x, v0.y * c01.w + v1.y * c01.z, v0.z * c23.y + v1.z * c23.x, v0.w * c23.w + v1.w * c23.z};
-      v0 = r0; v1 = r1;
-    }
-    if (head < a.H) {
-      const long o = (long)t * a.H * h + head * h + i;
-      if (a.q_out) { put_four(a.q_out, IN_F32, o, v0); put_four(a.q_out, IN_F32, o + half, v1); }
-      if (a.q_bf) {
-        const float sc = a.scale;
-        put_four(a.q_bf, IN_BF16, o, float4{v0.x * sc, v0.y * sc, v0.z * sc, v0.w * sc});
-        put_four(a.q_bf, IN_BF16, o + half, float4{v1.x * sc, v1.y * sc, v1.z * sc, v1.w * sc});
-      }
-    } else {
-      const bool is_v = head >= a.H + a.K;
-      const int kvh = head - a.H - (is_v ? a.K : 0);
-      const long o = (((long)page * a.K + kvh) * 2 + (is_v ? 1 : 0)) * pt_h + (long)slot * h + i;
-      put_four(a.pool, bf, o, v0);
-      put_four(a.pool, bf, o + half, v1);
-    }
-  }
-}
-void launch_rope_scatter(hipStream_t s, const RopeScatterArgs& a) {
-  hipLaunchKernelGGL(k_rope_scatter, dim3(a.T), dim3(kBlock), 0, s, a);
 }
 
 // ---------------------------------------------------------------------------

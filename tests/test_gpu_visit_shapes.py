@@ -70,6 +70,25 @@ def test_first_visits_with_tiles_that_are_no_power_of_two(T, d, heads, kv, d_ff,
     g.sync()
 
 
+# The QKV product rotates and scatters from its tiles: heads of every size, longer than a tile and shorter, tiles of 192, 96 and
+# 64 rows that begin inside a head of 128 or 256, positions rotated or not; a second piece that begins inside a page.
+@pytest.mark.parametrize("T,d,h,heads,kv,kw", [
+    (1408, 1032, 256, 8, 8, {}), (1408, 1032, 128, 16, 16, GELU), (400, 72, 256, 8, 8, {}), (400, 72, 128, 16, 16, {}),
+    (333, 520, 128, 9, 3, {}), (37, 72, 256, 3, 1, GELU), (333, 72, 8, 6, 3, {}), (65, 520, 16, 12, 2, dict(GELU, pos_kind=S.POS_LEARNED)),
+    (130, 72, 32, 5, 5, dict(pos_kind=S.POS_LEARNED)), (65, 72, 256, 3, 3, F32), (100, 520, 64, 10, 2, F32), (33, 72, 8, 4, 2, dict(GELU, **F32))])
+def test_rotation_and_scatter_of_every_head_size(T, d, h, heads, kv, kw):
+    cfg = S.tiny(n_layer=1, d_model=d, n_head=heads, n_kv_head=kv, head_dim=h, d_ff=72, vocab=61, max_ctx=T + 21, **{"dtype": S.DT_BF16, **kw})
+    w = S.make_weights(cfg, 64, exercise=True)
+    o, g = pair(cfg, w, 0, 1, max_prefill=T)
+    x = S.make_activations(cfg, 65, 0, T + 20)
+    want = o.prefill(0, x)
+    check(g.prefill(0, dev_acts(x[:T], cfg)), want[:T], cfg, ("first piece", T))
+    check(g.prefill_chunk(0, dev_acts(x[T:], cfg)), want[T:], cfg, ("second piece after", T))
+    y = S.make_activations(cfg, 66, 0, 1)[0]
+    check(g.decode_step(0, dev_acts(y, cfg)), o.decode_step(0, y), cfg, ("later visit after", T))
+    g.sync()
+
+
 @pytest.mark.parametrize("T", [5, 300])
 def test_output_rows_off_a_16_byte_boundary(T):
     cfg = ragged()
