@@ -89,9 +89,12 @@ template <int N, typename F> __device__ __forceinline__ void each(F&& f) { each_
 // n things spread evenly over `over` places: the first that is due at place q or later.
 constexpr int due(int q, int n, int over) { const int v = (q * n + over - 1) / over; return v < n ? v : n; }
 
-// A workgroup is WN x WT wavefronts, each (BN / WN) weight rows x (BT / WT) positions.
+// A workgroup is WN x WT wavefronts, each (BN / WN) weight rows x (BT / WT) positions.  bf16 tiles of four wavefronts leave room
+// for a second workgroup: given all 512 registers the compiler keeps sums in the accumulation half and moves them to and fro
+// in every step (96 x 128, 256 x 12288 x 4096: 42.9 -> 38.6 us; 64 x 96, 333 x 2560 x 2048: 16.0 -> 14.1).  In fp32 the same
+// costs 1 %.
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
-__global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmArgs a) {
+__global__ __launch_bounds__(WN * WT * 64, sizeof(ST) == 2 ? 2 : WN * WT * 64 / 256) void k_gemm(GemmArgs a) {
   typedef Mac<ST> M;
   constexpr int NW = WN * WT, ES = (int)sizeof(ST);
   constexpr int TN = BN / WN / 16, TT = BT / WT / 16;   // 16 x 16 tiles per wavefront
@@ -103,6 +106,13 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)gemm_smem;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = wave / WT, wt = wave % WT;
+  // all arguments in one round trip (left alone they are asked for where they are first used, in three)
+  if constexpr (EPI == GEPI_QKV)
+    asm volatile("" ::"s"(a.A), "s"(a.W), "s"(a.bias), "s"(a.T), "s"(a.N), "s"(a.Kd), "s"(a.S), "s"(a.qkv.H), "s"(a.qkv.K), "s"(a.qkv.h), "s"(a.qkv.pt),
+                 "s"(a.qkv.pt_sh), "s"(a.qkv.pt_magic), "s"(a.qkv.pos0), "s"(a.qkv.scale), "s"(a.qkv.rope), "s"(a.qkv.q_out), "s"(a.qkv.q_bf),
+                 "s"(a.qkv.pool), "s"(a.qkv.table));
+  else
+    asm volatile("" ::"s"(a.A), "s"(a.W), "s"(a.bias), "s"(a.T), "s"(a.N), "s"(a.Kd), "s"(a.S), "s"(a.out_f32), "s"(a.out_act));
 
   // Workgroup -> tile.  Workgroups are handed to the eight compute dies in turn, and each die has an L2 of its own:
   // a die takes a contiguous range of tiles, ordered in groups of up to eight position tiles that share a weight
@@ -177,8 +187,8 @@ __global__ __launch_bounds__(WN * WT * 64, WN * WT * 64 / 256) void k_gemm(GemmA
   const unsigned char* a_wave = gemm_smem + NBW * WB + wt * (BT / WT) * 128;
 
   // The QKV product's epilogue rotates queries and keys and puts keys and values into the pages.  (A kernel of its own read the
-  // rows back in fp32: 13.8 us at 1024 positions of the 7B shape, 8.2 at 256, 4.9 at 333 of TinyLlama, 50 at 6000 of the 8B
-  // shape; the epilogue takes 3 to 4 us longer.)  What it needs besides the sums, angles and page numbers, small tiles ask for
+  // rows back in fp32: 13.8 us at 1024 positions of the 7B shape, 8.2 at 256, 4.9 at 333 of TinyLlama;
+  // the epilogue takes 3 to 4 us longer.)  What it needs besides the sums, angles and page numbers, small tiles ask for
   // before the first step - asked for in the epilogue they cost 1.5 to 2 us more - and tiles that need the registers one position ahead.
   constexpr bool ASK_EARLY = TN * TT <= 12;
   const int h_sh = EPI == GEPI_QKV ? 31 - __builtin_clz(a.qkv.h) : 0;

@@ -671,7 +671,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
   };
   const int aligned = ((uintptr_t)acts_out & 15) == 0;
   auto resid = [&](const void* A, const void* W, const float* bias, int Kd, void* hand_off) {
-    GemmArgs ga{A, W, bias, (int)T, d, Kd, p->p_xres, hand_off, 0, aligned, 1};
+    GemmArgs ga{A, W, bias, (int)T, d, Kd, 1, p->p_xres, hand_off, 0, aligned, {}};
     const GemmPlan pl = plan_gemm(c.dtype, p->n_cu, (int)T, d, Kd, p->part_cap);
     ga.S = pl.S;
     if (pl.S > 1) { ga.out_f32 = p->p_part; ga.out_act = nullptr; pend_S = pl.S; pend_bias = bias; }
@@ -686,8 +686,8 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
   for (int i = 0; i < p->n_local; ++i) {
     const LayerPacked& L = p->layers[i];
     norm(L.ln1_g, L.ln1_b, p->p_xn, nullptr);
-    GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, nullptr, nullptr, 0, 0, 1,
-                {H, K, h, p->pt, pt_sh, pt_magic, pos0, p->rope, p->p_q, p->p_qb, scale * 1.44269504f, L.kv, drow}};   // log2 e: k_flash_prefill's exponentials are powers of two
+    GemmArgs g1{p->p_xn, L.wqkv, L.bqkv, (int)T, (H + 2 * K) * h, d, 1, nullptr, nullptr, 0, 0,
+                {H, K, h, p->pt, pt_sh, pt_magic, pos0, scale * 1.44269504f, p->rope, p->p_q, p->p_qb, L.kv, drow}};   // log2 e: k_flash_prefill's exponentials are powers of two
     launch_gemm(s, c.dtype, GEPI_QKV, plan_gemm(c.dtype, p->n_cu, (int)T, g1.N, d, 0).shape, g1);
     if (flash) {
       FlashArgs fa{p->p_qb, (const bf16_t*)L.kv, drow, (bf16_t*)p->p_o, (int)T, ((int)T + 127) / 128 * 128, H, K, h, pos0,
@@ -703,7 +703,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
     }
     resid(p->p_o, L.wo, L.bo, H * h, nullptr);
     norm(L.ln2_g, L.ln2_b, p->p_xn, nullptr);
-    GemmArgs g3{p->p_xn, L.wup, L.bup, (int)T, swiglu ? 2 * F : F, d, nullptr, p->p_u, c.mlp_kind == MDI_MLP_GELU_TANH, 1, 1};
+    GemmArgs g3{p->p_xn, L.wup, L.bup, (int)T, swiglu ? 2 * F : F, d, 1, nullptr, p->p_u, c.mlp_kind == MDI_MLP_GELU_TANH, 1, {}};
     launch_gemm(s, c.dtype, swiglu ? GEPI_SWIGLU : GEPI_GELU, plan_gemm(c.dtype, p->n_cu, (int)T, g3.N, d, 0).shape, g3);
     resid(p->p_u, L.wdown, L.bdown, F, i == p->n_local - 1 ? acts_out : nullptr);
   }

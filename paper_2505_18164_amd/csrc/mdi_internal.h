@@ -131,10 +131,10 @@ struct QkvOut {
   int H, K, h, pt;        // h: a power of two from 8 on; pt: positions per page
   int pt_sh; unsigned pt_magic;   // page of a position: as in FlashArgs
   int pos0;               // position of row 0
+  float scale;
   const float2* rope;     // (cos, sin) [max_ctx][h/2] or nullptr
   float* q_out;           // [T, H*h] fp32, or nullptr
   bf16_t* q_bf;           // [T, H*h], times `scale`: the queries of the matrix-core attention, or nullptr
-  float scale;
   void* pool;             // this layer's pages, storage dtype
   const int32_t* table;
 };
@@ -145,11 +145,11 @@ struct GemmArgs {
   const void* W;     // [N, Kd] storage dtype
   const float* bias; // [N] or nullptr
   int T, N, Kd;      // N and Kd multiples of 8
+  int S;             // splits of the inner dimension (1 unless GEPI_PART): split s leaves its sums at out_f32 + s T N
   float* out_f32;    // GEPI_RESID: residual stream [T, N], updated in place; GEPI_PART: [S][T, N]
   void* out_act;     // SWIGLU: [T, N/2]; GELU: [T, N]; RESID: optional hand-off copy [T, N]; storage dtype
   int gelu_tanh;     // GELU: the tanh form, else the erf form
   int act_aligned;   // out_act may be written 16 bytes at a time
-  int S;             // splits of the inner dimension (1 unless GEPI_PART): split s leaves its sums at out_f32 + s T N
   QkvOut qkv;        // GEPI_QKV: N = (H + 2 K) h
 };
 // gemm_bf16.hip, gemm_f32.hip: the tile shape for a product, and into how many pieces its inner dimension is cut so that
