@@ -27,7 +27,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BQ = 128;       // queries per workgroup (32 per wavefront)
 constexpr int BK = 64;        // keys per step
 constexpr float kRaise = 8.f; // how far (in powers of two) a score may exceed its query's reference
 
@@ -39,11 +38,14 @@ __device__ __forceinline__ u32x2 read_transposed(const bf16_t* p) {
 // 2^x as the hardware gives it (the scores carry log2 e, see the launch)
 __device__ __forceinline__ float exp2f_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// A workgroup is NG groups of four wavefronts that work on the same 128 queries; group g takes the key blocks
-// NG i + g.  With two groups the longest workgroup (the last queries, which see every key) has half as many steps in a
+// A workgroup is NG groups of WQ wavefronts that work on the same 32 WQ queries; group g takes the key blocks
+// NG i + g.  With more groups the longest workgroup (the last queries, which see every key) has fewer steps in a
 // row and a SIMD holds two wavefronts; the groups' running (maximum, sum, output) are folded through LDS at the end,
 // group 0 first, so the result does not depend on timing.  With one, two workgroups share a compute unit and nothing
 // keeps them in step: one multiplies while the other takes exponentials.
+// Where the chip is not full, a step takes 2.7 us whether a SIMD holds one wavefront or two (a chain of products, maxima,
+// exponentials and products): what helps is fewer steps in a row and more workgroups, not less work in one.  (Bringing a
+// head's keys and values into the L2 of the die beforehand: nothing.)
 //
 // What bounds it: a block of 64 keys is 32 matrix instructions (about 1000 cycles of a SIMD), half as much again on the vector
 // ALUs (32 scores per lane: maximum, exponential, sum, conversion), and 32 KiB of LDS reads per wavefront, which take as long
@@ -52,21 +54,23 @@ __device__ __forceinline__ float exp2f_raw(float x) { return __builtin_amdgcn_ex
 // a rescaling wherever any of a wavefront's 32 queries found a new maximum, which is most blocks; 369 us (0.79 PFLOP/s) with
 // the mask in the last blocks only, scores that come out relative, and a rescaling when it is needed.  1024 positions of the
 // 7B shape 33 -> 28, pieces of 256 23 -> 20 us.  Heads that share keys on one die give 20 of it.
-template <int HD, int NG>
-__global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
+template <int HD, int NG, int WQ>
+__global__ __launch_bounds__(WQ * 64 * NG, 2) void k_flash_prefill(FlashArgs a) {
+  constexpr int BQ = 32 * WQ, GT = 64 * WQ;  // queries of a workgroup, threads of a group
   constexpr int KS = HD + 8;            // LDS row stride of a key (elements): 16 bytes of padding spread the rows over the banks
   constexpr int VR = HD + 32;           // LDS row stride of a key's values: 16 dwords past a multiple of 64 (heads of 64: 48), so that the
                                         // eight keys x 32 channels of a transposing read touch every bank twice
   constexpr int HT = HD / 32;           // 32-channel tiles of the output
   extern __shared__ __attribute__((aligned(16))) unsigned char flash_smem[];
-  constexpr int KV = BK * KS + BK * VR;                 // elements of a key block and its values; two blocks per group
+  constexpr int KV = BK * KS + BK * VR;                 // elements of a key block and its values
+  constexpr int NB = NG == 4 ? 1 : 2;                   // blocks per group: two of four groups would not fit
 
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // position inside the group
-  const int grp = threadIdx.x >> 8;
-  bf16_t* bufs = (bf16_t*)flash_smem + grp * 2 * KV;
+  const int tid = threadIdx.x & (GT - 1), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // position inside the group
+  const int grp = threadIdx.x / GT;
+  bf16_t* bufs = (bf16_t*)flash_smem + grp * NB * KV;
   // Workgroups are handed to the eight compute dies in turn, each with an L2 of its own: a die takes heads that follow
   // each other (they share their keys), longest rows first.
-  const int n_qb = a.Tp / BQ, per_die = (n_qb * a.H + 7) >> 3, idx = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
+  const int n_qb = (a.T + BQ - 1) / BQ, per_die = (n_qb * a.H + 7) >> 3, idx = (blockIdx.x & 7) * per_die + (blockIdx.x >> 3);
   if (idx >= n_qb * a.H) return;
   const int head = idx / n_qb, qb = n_qb - 1 - (idx - head * n_qb), kvh = head / (a.H / a.K);
   const int q0 = qb * BQ, qw0 = q0 + 32 * wave;
@@ -103,11 +107,11 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   // Staging: the next block's keys and values travel global -> registers during the arithmetic, its page numbers a block
   // ahead of that.  A thread moves channels 8 oct .. + 7 of KU keys of a block.  Keys past the last repeat
   // it (no query sees them, but they are finite), a group whose last step has no block re-reads the last key.
-  constexpr int KU = HD / 32;
+  constexpr int KU = HD / (8 * WQ);
   const int oct = tid % (HD / 8), ku = tid / (HD / 8);
   u32x4 kreg[KU], vreg[KU];
   int pg[KU];
-  auto key_in = [&](int j) __attribute__((always_inline)) { return ku + j * (2048 / HD); };
+  auto key_in = [&](int j) __attribute__((always_inline)) { return ku + j * (GT * 8 / HD); };
   auto key_of = [&](int kb, int j) __attribute__((always_inline)) { return min(kb * BK + key_in(j), n_keys - 1); };
   auto page_of = [&](int pos) __attribute__((always_inline)) { return a.pt_sh >= 0 ? pos >> a.pt_sh : (int)__umulhi((unsigned)pos, a.pt_magic); };
   const bool block_page = a.pt_sh >= 6;                          // a block of 64 keys lies in one page
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   __syncthreads();
   for (int it = 0; it < n_it; ++it) {
     const int kb = NG * it + grp;
-    const bf16_t* Ks = bufs + (it & 1) * KV;
+    const bf16_t* Ks = bufs + (NB == 2 ? it & 1 : 0) * KV;
     const bf16_t* Vs = Ks + BK * KS;
     if (it + 1 < n_it) fetch(kb + NG);
     const int k0 = kb * BK;
@@ -231,32 +235,36 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
           }
         }
     }
-    if (it + 1 < n_it) stash(bufs + ((it + 1) & 1) * KV);        // the block before this one, which everybody has left
+    if (NB == 1) __syncthreads();
+    if (it + 1 < n_it) stash(bufs + (NB == 2 ? (it + 1) & 1 : 0) * KV);   // over a block which everybody has left
     __syncthreads();
   }
 
-  // ---- fold the two groups: group 1 hands its state over through LDS (the K/V area, no longer needed);
+  // ---- fold the groups: the others hand their states to group 0 through LDS (the K/V area, no longer needed);
   //      element j of thread t at [j][t], so that a wavefront's accesses are consecutive
-  if constexpr (NG == 2) {
-    float* fold = (float*)flash_smem;
-    if (grp == 1) {
+  if constexpr (NG > 1) {
+    float* fold = (float*)flash_smem + (grp > 0 ? grp - 1 : 0) * (HT * 16 + 2) * GT;
+    if (grp > 0) {
 #pragma unroll
       for (int i = 0; i < HT; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) fold[(i * 16 + r) * 256 + tid] = o[i][r];
-      fold[(HT * 16) * 256 + tid] = first ? -1e30f : m;
-      fold[(HT * 16 + 1) * 256 + tid] = l;
+        for (int r = 0; r < 16; ++r) fold[(i * 16 + r) * GT + tid] = o[i][r];
+      fold[(HT * 16) * GT + tid] = first ? -1e30f : m;
+      fold[(HT * 16 + 1) * GT + tid] = l;
     }
     __syncthreads();
-    if (grp == 1) return;
-    const float m1 = fold[(HT * 16) * 256 + tid], l1 = fold[(HT * 16 + 1) * 256 + tid];
-    const float mn = fmaxf(m, m1);
-    const float a0 = exp2f_raw(m - mn), a1 = exp2f_raw(m1 - mn);   // group 0 has seen key 0; of a group that saw none m = -1e30 and nothing stays
-    l = l * a0 + l1 * a1;
+    if (grp > 0) return;
+    for (int g = 1; g < NG; ++g, fold += (HT * 16 + 2) * GT) {
+      const float m1 = fold[(HT * 16) * GT + tid], l1 = fold[(HT * 16 + 1) * GT + tid];
+      const float mn = fmaxf(m, m1);
+      const float a0 = exp2f_raw(m - mn), a1 = exp2f_raw(m1 - mn);   // group 0 has seen key 0; of a group that saw none m = -1e30 and nothing stays
+      l = l * a0 + l1 * a1;
+      m = mn;
 #pragma unroll
-    for (int i = 0; i < HT; ++i)
+      for (int i = 0; i < HT; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[i][r] = o[i][r] * a0 + fold[(i * 16 + r) * 256 + tid] * a1;
+        for (int r = 0; r < 16; ++r) o[i][r] = o[i][r] * a0 + fold[(i * 16 + r) * GT + tid] * a1;
+    }
   }
 
   l += __shfl_xor(l, 32, 64);
@@ -274,36 +282,50 @@ __global__ __launch_bounds__(256 * NG, 2) void k_flash_prefill(FlashArgs a) {
   }
 }
 
-template <int HD, int NG>
+template <int HD, int NG, int WQ>
 constexpr size_t flash_lds_bytes() {
-  // two key blocks and their values per group; the fold at the end needs HD / 2 + 2 floats per thread of one group
-  const size_t kv = (size_t)NG * 2 * BK * (HD + 8 + HD + 32) * sizeof(bf16_t);
-  const size_t fold = NG == 2 ? (size_t)(HD / 2 + 2) * 256 * sizeof(float) : 0;
+  // two key blocks and their values per group, one of four; the fold at the end needs HD / 2 + 2 floats per thread of the
+  // groups but one
+  const size_t kv = (size_t)NG * (NG == 4 ? 1 : 2) * BK * (HD + 8 + HD + 32) * sizeof(bf16_t);
+  const size_t fold = NG > 1 ? (size_t)(NG - 1) * (HD / 2 + 2) * 64 * WQ * sizeof(float) : 0;
   return kv > fold ? kv : fold;
 }
-template <int HD, int NG>
+template <int HD, int NG, int WQ>
 bool allow_flash() {                                             // 64 KiB is what a kernel gets by default
-  constexpr size_t lds = flash_lds_bytes<HD, NG>();
-  return lds <= 64 * 1024 || hipFuncSetAttribute((const void*)k_flash_prefill<HD, NG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+  constexpr size_t lds = flash_lds_bytes<HD, NG, WQ>();
+  return lds <= 64 * 1024 || hipFuncSetAttribute((const void*)k_flash_prefill<HD, NG, WQ>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
 }
-template <int HD, int NG>
+template <int HD, int NG, int WQ>
 void launch_flash(hipStream_t s, const FlashArgs& a) {
-  hipLaunchKernelGGL((k_flash_prefill<HD, NG>), dim3(8 * ((a.Tp / BQ * a.H + 7) / 8)), dim3(256 * NG), (flash_lds_bytes<HD, NG>()), s, a);
+  const int items = (a.T + 32 * WQ - 1) / (32 * WQ) * a.H;
+  hipLaunchKernelGGL((k_flash_prefill<HD, NG, WQ>), dim3(8 * ((items + 7) / 8)), dim3(64 * WQ * NG), (flash_lds_bytes<HD, NG, WQ>()), s, a);
+}
+template <int HD>
+void launch_flash_heads(hipStream_t s, const FlashArgs& a) {
+  const int items = (a.T + 127) / 128 * a.H;
+  // Many workgroups: one group each.  us a layer of one / two groups: 1024 positions of the 7B shape (256 items of 128
+  // queries) 34 / 29, 1280 (320) 44 / 38, 1536 (384) 55 / 53, 2048 (512) 78 / 85; TinyLlama 1500 (384) 34.5 / 34.
+  if (items >= 384) launch_flash<HD, 1, 4>(s, a);
+  // As many items as would leave half the chip idle: 64 queries a workgroup, 128 / 64 queries: 256 positions of the 7B shape
+  // 12.4 / 10.1, 512 (128 items) 18.1 / 16.0, 768 (192) 22.9 / 29.2; TinyLlama 500 (128) 11.3 / 9.6, 750 (192) 14.7 / 17.1.
+  else if (items > 128) launch_flash<HD, 2, 4>(s, a);
+  // Many keys on average: four groups.  Two / four: 256 positions behind 0, 256, 512, ... 1792 of the 8B shape 9.7 / 10.6,
+  // 15.1 / 14.2, 20.6 / 18.4, ... 47.4 / 37.9; 512 of the 7B shape behind none 16.0 / 16.7, TinyLlama 256 6.5 / 6.5.
+  else if (a.p0 + a.T / 2 >= 320) launch_flash<HD, 4, 2>(s, a);
+  else launch_flash<HD, 2, 2>(s, a);
 }
 
 }  // namespace
 
 bool flash_supported(int dtype, int h) { return dtype == MDI_BF16 && (h == 64 || h == 128); }
 
-bool allow_flash_lds() { return allow_flash<64, 1>() && allow_flash<64, 2>() && allow_flash<128, 1>() && allow_flash<128, 2>(); }
+bool allow_flash_lds() {
+  return allow_flash<64, 1, 4>() && allow_flash<64, 2, 4>() && allow_flash<64, 2, 2>() && allow_flash<64, 4, 2>() && allow_flash<128, 1, 4>() && allow_flash<128, 2, 4>() &&
+         allow_flash<128, 2, 2>() && allow_flash<128, 4, 2>();
+}
 
 void launch_flash_prefill(hipStream_t s, const FlashArgs& a) {
-  // One group per workgroup once there are half as many more workgroups than compute units, measured on 4 layers: 1536
-  // positions of the 7B shape (384 workgroups) 2815 -> 2774 us, 2048 3432 -> 3381, TinyLlama's 2048 1179 -> 1151; but 1024
-  // (256 workgroups) 1821 -> 1847.
-  const bool one = (a.Tp / BQ) * a.H >= 384;
-  if (a.h == 128) { if (one) launch_flash<128, 1>(s, a); else launch_flash<128, 2>(s, a); }
-  else { if (one) launch_flash<64, 1>(s, a); else launch_flash<64, 2>(s, a); }
+  if (a.h == 128) launch_flash_heads<128>(s, a); else launch_flash_heads<64>(s, a);
 }
 
 }  // namespace mdi

@@ -690,7 +690,7 @@ mdi_status prefill_rows(mdi_partition* p, uint32_t seq, const void* acts_in, uin
                 {H, K, h, p->pt, pt_sh, pt_magic, pos0, scale * 1.44269504f, p->rope, p->p_q, p->p_qb, L.kv, drow}};   // log2 e: k_flash_prefill's exponentials are powers of two
     launch_gemm(s, c.dtype, GEPI_QKV, plan_gemm(c.dtype, p->n_cu, (int)T, g1.N, d, 0).shape, g1);
     if (flash) {
-      FlashArgs fa{p->p_qb, (const bf16_t*)L.kv, drow, (bf16_t*)p->p_o, (int)T, ((int)T + 127) / 128 * 128, H, K, h, pos0,
+      FlashArgs fa{p->p_qb, (const bf16_t*)L.kv, drow, (bf16_t*)p->p_o, (int)T, H, K, h, pos0,
                    p->pt, pt_sh, pt_magic};
       launch_flash_prefill(s, fa);
     } else {

@@ -176,7 +176,7 @@ struct FlashArgs {
   const bf16_t* pool;     // this layer's cache pages [page][K][2][pt][h]: positions 0 .. p0 + T - 1 of the sample are in them
   const int32_t* table;   // its page ids
   bf16_t* out;            // [T][H*h]
-  int T, Tp, H, K, h;     // Tp: T rounded up to 128 (the query grid)
+  int T, H, K, h;
   int p0;
   int pt, pt_sh; unsigned pt_magic;   // positions per page; log2 of it, or -1 and pos / pt = high word of pos * pt_magic (0xFFFFFFFF / pt + 1)
 };

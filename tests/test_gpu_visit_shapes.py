@@ -121,7 +121,11 @@ def test_input_rows_off_a_boundary_of_four_values(d, T, kw):
 
 @pytest.mark.parametrize("page,heads,kv,h,cuts", [(64, 4, 2, 128, (130, 62, 1, 200)), (128, 4, 4, 64, (1, 127, 129, 64)), (48, 4, 1, 128, (100, 93, 7)),
                                                   (16, 4, 2, 64, (15, 17, 96, 200)), (5, 2, 2, 64, (64, 70)), (64, 32, 8, 64, (1600,)),
-                                                  (24, 32, 4, 128, (1540, 3))])
+                                                  (24, 32, 4, 128, (1540, 3)),
+                                                  # around the rule between 64 and 128 queries per workgroup (128 items of 128 queries)
+                                                  (64, 16, 4, 128, (1024, 65, 1)), (64, 16, 4, 128, (1025, 63)), (24, 16, 8, 64, (1089, 95)), (64, 8, 8, 128, (1, 31, 33, 64, 66)),
+                                                  # ... and between two and four groups (320 keys on average)
+                                                  (64, 8, 2, 128, (639, 1, 64, 65)), (16, 8, 8, 64, (319, 2, 1, 200)), (64, 8, 8, 128, (640,)), (128, 8, 4, 64, (700, 33))])
 def test_first_visits_read_keys_and_values_from_the_pages(page, heads, kv, h, cuts):
     """Pages that hold a block of 64 keys and pages that do not, both head sizes, pieces that end inside pages and blocks,
     and enough query blocks for workgroups of one group of wavefronts (384 of them); every position on its own."""
