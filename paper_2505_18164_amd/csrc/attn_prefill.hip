@@ -305,7 +305,8 @@ void launch_flash_heads(hipStream_t s, const FlashArgs& a) {
   const int items = (a.T + 127) / 128 * a.H;
   // Many workgroups: one group each.  us a layer of one / two groups: 1024 positions of the 7B shape (256 items of 128
   // queries) 34 / 29, 1280 (320) 44 / 38, 1536 (384) 55 / 53, 2048 (512) 78 / 85; TinyLlama 1500 (384) 34.5 / 34.
-  if (items >= 384) launch_flash<HD, 1, 4>(s, a);
+  // So does a single block of keys, which a second group could only wait for: 64 positions of the 7B shape 6.0 / 7.6, TinyLlama 4.1 / 4.8.
+  if (items >= 384 || a.p0 + a.T <= BK) launch_flash<HD, 1, 4>(s, a);
   // As many items as would leave half the chip idle: 64 queries a workgroup, 128 / 64 queries: 256 positions of the 7B shape
   // 12.4 / 10.1, 512 (128 items) 18.1 / 16.0, 768 (192) 22.9 / 29.2; TinyLlama 500 (128) 11.3 / 9.6, 750 (192) 14.7 / 17.1.
   else if (items > 128) launch_flash<HD, 2, 4>(s, a);
