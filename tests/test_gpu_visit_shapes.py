@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2505_18164_amd import mdi, synth as S
+import visit_cases as V
 from gpu_util import check, dev_acts, host, pair
 
 pytestmark = pytest.mark.gpu
@@ -142,6 +143,18 @@ def test_first_visits_read_keys_and_values_from_the_pages(page, heads, kv, h, cu
         at += n
     y = S.make_activations(cfg, 73, 0, 1)[0]
     check(g.decode_step(0, dev_acts(y, cfg)), o.decode_step(0, y), cfg, ("later visit after", T))
+    g.sync()
+
+
+# Each launch of the attention: one group of wavefronts, two of four, two of two, four
+@pytest.mark.parametrize("far", V.FAR)
+@pytest.mark.parametrize("heads,kv,h,T", V.FAR_VISITS)
+def test_scores_far_above_those_of_the_first_keys(heads, kv, h, T, far):
+    """The first 256 keys, which every group begins with, lie 2^26 or 2^120 powers of two below the later ones: what is
+    left of them does not touch the later scores."""
+    cfg, w, x = V.far_visit(heads, kv, h, T, far)
+    o, g = pair(cfg, w, 0, 1, max_prefill=T)
+    check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", T, V.launch_of(T, 0, heads)))
     g.sync()
 
 
