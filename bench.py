@@ -45,7 +45,7 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 KERNEL_SOURCES = ("bounded_wait.h", "step_impl.h", "step_kernel.h", "step_mfma.h", "step_batch.h", "step_batch_ln.hip", "step_batch_rms.hip",
                   "step_batch_ln_w4.hip", "step_batch_rms_w4.hip", "step_w4.hip", "step_w4_f32.hip", "step_w8.hip", "step_w8_f32.hip", "device_utils.h", "mdi_internal.h")
 MEASURED_TRAFFIC = {
-    (4, 8, True): {"bytes": 4.5499e9, "kernel_rev": "d352a98d344b",
+    (4, 8, True): {"bytes": 4.5498e9, "kernel_rev": "03d8478d0cab",
                    "source": "profiles/k_step_batch_c4_decode_hbm_counters.md (FETCH_SIZE x 2.0 KiB + WRITE_SIZE x 1.0 KiB, context about 1030)"},
 }
 

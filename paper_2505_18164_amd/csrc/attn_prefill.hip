@@ -18,6 +18,7 @@
 // pieces 7.16 -> 6.41 ms, 333 of TinyLlama 1.15 -> 1.07 ms, 6000 of the 8B shape 22.0 -> 22.4 ms on one machine.
 // Transposing in registers on the way into LDS: 531 us a layer of 6000 positions, 490 as it is.)
 #include "device_utils.h"
+#include "visit_internal.h"
 
 namespace mdi {
 namespace {

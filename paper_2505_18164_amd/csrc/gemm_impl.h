@@ -30,6 +30,7 @@
 #include <utility>
 
 #include "device_utils.h"
+#include "visit_internal.h"
 
 namespace mdi {
 namespace {

@@ -10,6 +10,7 @@
 
 #include "mdi_internal.h"
 #include "once_per_device.h"
+#include "visit_internal.h"
 
 using namespace mdi;
 

@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "device_utils.h"
+#include "visit_internal.h"
 
 namespace mdi {
 

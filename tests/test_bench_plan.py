@@ -1,5 +1,8 @@
 """bench.py accepts any --steps / --warmup / --queue on every workload: the planning code never refuses, times
 exactly the requested number of steps, and never drives a sample beyond its cache."""
+import os
+import re
+
 import pytest
 
 import bench
@@ -44,3 +47,18 @@ def test_paper_run_flag_parses():
     a = bench.parse(["--paper-run", "tinyllama", "--paper-tokens", "50"])
     assert a.paper_run == "tinyllama" and a.paper_tokens == 50 and a.gpus == 1
     assert bench.parse([]).paper_run is None
+
+
+def test_the_kernels_revision_covers_the_decode_kernels_and_nothing_of_the_first_visits():
+    """The measured traffic of a decode launch stands as long as this revision does."""
+    csrc = os.path.join(bench.ROOT, "paper_2505_18164_amd", "csrc")
+    text = {n: open(os.path.join(csrc, n)).read() for n in os.listdir(csrc)}
+    reached, todo = set(), [n for n in text if n.startswith("step_") and n.endswith(".hip")]
+    while todo:
+        n = todo.pop()
+        if n in text and n not in reached:
+            reached.add(n)
+            todo += re.findall(r'#include "([^"]+)"', text[n])
+    assert reached == set(bench.KERNEL_SOURCES)
+    for n in reached:
+        assert not re.search(r"GemmArgs|FlashArgs|NormRowsArgs", text[n]), n
