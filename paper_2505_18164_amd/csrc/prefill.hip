@@ -33,7 +33,12 @@ __device__ __forceinline__ void put_four(void* base, int kind, long at, const fl
 // anything is stored (a store between two loads keeps the compiler from asking for the second before the first is there).
 // 256 rows of 4096 with two to four partial results 7.5 -> 6.8 us, 1024 rows 12.9 -> 11.6; a kernel of its own for the input took 10
 // to 14 us there (41 at 6000 rows) and left the row to be read again.
-template <int NV>
+// With many rows it is how many of them are in flight, and the partial results asked for at a time are two thirds of the
+// registers (rows of 8192: 203 against 82, two wavefronts a SIMD against five): kernels with and without.  2048 rows of 8192
+// without partial results 21.3 -> 19.5 us and from the input 44 -> 31, of 5120 15.6 -> 13.1 and 31 -> 24, 4000 of 4096
+// from the input 35 -> 28.5; two at a time instead of four for rows
+// beyond 4096: 64 of 8192 8.1 -> 9.3 us, 600 of 5120 15.7 -> 13.3, 256 to 1024 of 8192 within 4 %.
+template <int NV, bool kParts>
 __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
   __shared__ float red[2][kBlock / kWave];
   const int t = blockIdx.x, d4 = a.d >> 2;
@@ -61,7 +66,7 @@ __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
   };
   auto part = [&](int s, int i) __attribute__((always_inline)) { return reinterpret_cast<const float4*>(a.part + s * a.part_stride + (long)t * a.d)[i]; };
   auto keep = [&](int i, const float4& r) __attribute__((always_inline)) {
-    if (a.out && (a.S > 1 || a.src.in)) x[i] = r;    // without a norm to follow nobody reads the stream again
+    if (a.out && (kParts || a.src.in)) x[i] = r;    // without a norm to follow nobody reads the stream again
     if (!a.act_out) return;
     const long at = (long)t * a.d + 4 * i;
     if (!a.act_aligned) {
@@ -78,7 +83,7 @@ __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
   if (NV) {
     each([&](int j, int i) { v[j] = start(i); });
     if (a.out) each([&](int j, int i) { g[j] = g4[i]; });
-    if (a.S > 1) {
+    if (kParts) {
       if (a.part_bias) each([&](int j, int i) { add(v[j], reinterpret_cast<const float4*>(a.part_bias)[i]); });
       constexpr int U = 4;                           // partial results asked for at a time
       int s = 0;
@@ -99,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
   } else {
     for (int i = threadIdx.x; i < d4; i += kBlock) {
       float4 r = start(i);
-      if (a.S > 1) {
+      if (kParts) {
         if (a.part_bias) add(r, reinterpret_cast<const float4*>(a.part_bias)[i]);
         for (int s = 0; s < a.S; ++s) add(r, part(s, i));
       }
@@ -136,13 +141,17 @@ __global__ __launch_bounds__(kBlock) void k_norm_rows(NormRowsArgs a) {
     put_four(a.out, kind, (long)t * a.d + 4 * i, o);
   });
 }
-void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
+template <bool kParts>
+void launch_norm_rows_parts(hipStream_t s, const NormRowsArgs& a) {
   const int n = (a.d / 4 + kBlock - 1) / kBlock;
-  if (n <= 1) hipLaunchKernelGGL(k_norm_rows<1>, dim3(a.T), dim3(kBlock), 0, s, a);
-  else if (n <= 2) hipLaunchKernelGGL(k_norm_rows<2>, dim3(a.T), dim3(kBlock), 0, s, a);
-  else if (n <= 4) hipLaunchKernelGGL(k_norm_rows<4>, dim3(a.T), dim3(kBlock), 0, s, a);
-  else if (n <= 8) hipLaunchKernelGGL(k_norm_rows<8>, dim3(a.T), dim3(kBlock), 0, s, a);
-  else hipLaunchKernelGGL(k_norm_rows<0>, dim3(a.T), dim3(kBlock), 0, s, a);
+  if (n <= 1) hipLaunchKernelGGL((k_norm_rows<1, kParts>), dim3(a.T), dim3(kBlock), 0, s, a);
+  else if (n <= 2) hipLaunchKernelGGL((k_norm_rows<2, kParts>), dim3(a.T), dim3(kBlock), 0, s, a);
+  else if (n <= 4) hipLaunchKernelGGL((k_norm_rows<4, kParts>), dim3(a.T), dim3(kBlock), 0, s, a);
+  else if (n <= 8) hipLaunchKernelGGL((k_norm_rows<8, kParts>), dim3(a.T), dim3(kBlock), 0, s, a);
+  else hipLaunchKernelGGL((k_norm_rows<0, kParts>), dim3(a.T), dim3(kBlock), 0, s, a);
+}
+void launch_norm_rows(hipStream_t s, const NormRowsArgs& a) {
+  if (a.S > 1) launch_norm_rows_parts<true>(s, a); else launch_norm_rows_parts<false>(s, a);
 }
 
 // ---------------------------------------------------------------------------

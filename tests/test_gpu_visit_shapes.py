@@ -169,3 +169,15 @@ def test_norms_across_row_widths(d, kw):
     x = S.make_activations(cfg, 91, 0, 5)
     check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", d))
     g.sync()
+
+
+@pytest.mark.parametrize("kw", [{}, GELU, F32], ids=["bf16_rms", "bf16_ln", "f32_rms"])
+@pytest.mark.parametrize("d", [1016, 1032, 2056, 4104, 8184, 8200])
+def test_norms_of_rows_without_partial_results(d, kw):
+    """Inner dimensions of one step (32 values), which are not split."""
+    cfg = S.tiny(n_layer=2, d_model=d, n_head=1, n_kv_head=1, head_dim=32, d_ff=32, vocab=61, max_ctx=16, **{"dtype": S.DT_BF16, **kw})
+    w = V.loud(cfg, S.make_weights(cfg, 92, exercise=True))
+    o, g = pair(cfg, w, 0, 2)
+    x = S.make_activations(cfg, 93, 0, 5)
+    check(g.prefill(0, dev_acts(x, cfg)), o.prefill(0, x), cfg, ("first visit", d))
+    g.sync()

@@ -9,6 +9,19 @@ from paper_2505_18164_amd import synth as S
 
 BK, RAISE = 64, 8.0          # keys of a block; powers of two a score may exceed its query's reference (attn_prefill.hip)
 
+def loud(cfg, w, scores=1.4, attention=3.0, mlp=1.0):
+    """Scales the matrices by their inner dimensions, so that every one of them moves the result: scores of about
+    N(0, scores^2), an attention output of up to `attention` and an MLP output of about `mlp` times a row of N(0, 1)."""
+    d, H, h, F = cfg["d_model"], cfg["n_head"], cfg["head_dim"], cfg["d_ff"]
+    gain = dict(wq=math.sqrt(scores / d), wk=math.sqrt(scores / d), wv=1 / math.sqrt(d), wo=attention / math.sqrt(H * h),
+                w1=1 / math.sqrt(d), w2=mlp * 2 / math.sqrt(F), wg=1 / math.sqrt(d), wu=1 / math.sqrt(d), wd=mlp * 2 / math.sqrt(F))
+    for lw in w["layers"].values():
+        for name, k in gain.items():
+            if name in lw:
+                lw[name] = S.storage_round(lw[name] * np.float32(k / S.WEIGHT_STD), cfg["dtype"])
+    return w
+
+
 # Channels of a marked row (every entry +1 or -1, so that its norm is exactly 1): 0 - 7 the key's level n in binary, 8 always
 # +1, 9 and 10 the query's sign (their mean), 11 -1 where the key is far away
 _LEVEL, _ONE, _SIGN, _FAR = 8, 8, 9, 11
