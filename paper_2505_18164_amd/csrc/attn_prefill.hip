@@ -28,8 +28,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BK = 64;        // keys per step
-constexpr float kRaise = 8.f; // how far (in powers of two) a score may exceed its query's reference
+constexpr int BK = kFlashKeys;   // keys per step
+constexpr float kRaise = 8.f;    // how far (in powers of two) a score may exceed its query's reference
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x2 read_transposed(const bf16_t* p) {
@@ -320,17 +320,10 @@ void launch_flash(hipStream_t s, const FlashArgs& a) {
 }
 template <int HD>
 void launch_flash_heads(hipStream_t s, const FlashArgs& a) {
-  const int items = (a.T + 127) / 128 * a.H;
-  // Many workgroups: one group each.  us a layer of one / two groups: 1024 positions of the 7B shape (256 items of 128
-  // queries) 34 / 29, 1280 (320) 44 / 38, 1536 (384) 55 / 53, 2048 (512) 78 / 85; TinyLlama 1500 (384) 34.5 / 34.
-  // So does a single block of keys, which a second group could only wait for: 64 positions of the 7B shape 6.0 / 7.6, TinyLlama 4.1 / 4.8.
-  if (items >= 384 || a.p0 + a.T <= BK) launch_flash<HD, 1, 4>(s, a);
-  // As many items as would leave half the chip idle: 64 queries a workgroup, 128 / 64 queries: 256 positions of the 7B shape
-  // 12.4 / 10.1, 512 (128 items) 18.1 / 16.0, 768 (192) 22.9 / 29.2; TinyLlama 500 (128) 11.3 / 9.6, 750 (192) 14.7 / 17.1.
-  else if (items > 128) launch_flash<HD, 2, 4>(s, a);
-  // Many keys on average: four groups.  Two / four: 256 positions behind 0, 256, 512, ... 1792 of the 8B shape 9.7 / 10.6,
-  // 15.1 / 14.2, 20.6 / 18.4, ... 47.4 / 37.9; 512 of the 7B shape behind none 16.0 / 16.7, TinyLlama 256 6.5 / 6.5.
-  else if (a.p0 + a.T / 2 >= 320) launch_flash<HD, 4, 2>(s, a);
+  const FlashPlan p = plan_flash(a.T, a.p0, a.H);
+  if (p.groups == 1) launch_flash<HD, 1, 4>(s, a);
+  else if (p.groups == 4) launch_flash<HD, 4, 2>(s, a);
+  else if (p.waves == 4) launch_flash<HD, 2, 4>(s, a);
   else launch_flash<HD, 2, 2>(s, a);
 }
 

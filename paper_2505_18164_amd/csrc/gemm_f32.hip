@@ -10,8 +10,9 @@ namespace {
 // best.  On vector ALUs with one 64 x 64 tile shape: 69 / 202 (output and down, mean) / 74 us for QKV / residual
 // products / gate-up of the 304M shape at 100 positions, here 16 / 12 / 33.
 #define MDI_GEMM_SHAPES(X) X(0, 64, 32, 2, 2, 4, 4) X(1, 64, 64, 2, 4, 4, 4)
-constexpr int kShapes = 2;
-constexpr Shape kShape[kShapes] = {{64, 32, 4, 1.055f, 2.36f, 0.29f, 4.5f}, {64, 64, 1, 0.578f, 1.37f, 1.0f, 4.5f}};
+#define X(I, BN_, BT_, WN, WT, NBW, NBA) static_assert(kShapesF32[I].BN == BN_ && kShapesF32[I].BT == BT_, "shape I of the plan");
+MDI_GEMM_SHAPES(X)
+#undef X
 
 template <int EPI>
 void launch_epi(hipStream_t s, int shape, const GemmArgs& a) {
@@ -30,8 +31,6 @@ bool allow_epi() {
 }
 
 }  // namespace
-
-GemmPlan plan_gemm_f32(int n_cu, int T, int N, int Kd, size_t part_floats) { return plan_shape(kShape, kShapes, 4, n_cu, T, N, Kd, part_floats); }
 
 bool allow_gemm_lds_f32() {
   return allow_epi<GEPI_QKV>() && allow_epi<GEPI_RESID>() && allow_epi<GEPI_PART>() && allow_epi<GEPI_SWIGLU>() && allow_epi<GEPI_GELU>();

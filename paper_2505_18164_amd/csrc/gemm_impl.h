@@ -25,7 +25,6 @@
 // Included by gemm_bf16.hip and gemm_f32.hip, which hold the tile shapes of their storage type.
 #pragma once
 
-#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -383,12 +382,6 @@ __global__ __launch_bounds__(WN * WT * 64, sizeof(ST) == 2 ? 2 : WN * WT * 64 / 
   }
 }
 
-// What plan_shape goes by: a round of workgroups (`round` per compute unit) takes steps * us + fixed, a last round that is
-// a fraction f full part + (1 - part) f of that, and no product is faster than its weights arrive (tbps).  All are fitted
-// to measured times and none is a count of what fits: the small shapes' `round` is one more workgroup than the LDS of a
-// compute unit holds (the next starts as soon as one ends).
-struct Shape { int BN, BT, round; float us, fixed, part, tbps; };
-
 // Lets the current device's copy of the kernel have its LDS: a kernel gets 64 KiB by default.
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
 bool allow_shape() {
@@ -403,29 +396,6 @@ void launch_shape(hipStream_t s, const GemmArgs& a) {
   constexpr size_t lds = (size_t)128 * (NBW * BN + NBA * BT);
   const int tiles = ((a.T + BT - 1) / BT) * ((a.N + BN - 1) / BN);
   hipLaunchKernelGGL((k_gemm<ST, EPI, BN, BT, WN, WT, NBW, NBA>), dim3(8 * ((tiles + 7) / 8), a.S), dim3(WN * WT * 64), lds, s, a);
-}
-
-inline GemmPlan plan_shape(const Shape* shapes, int n_shapes, int elem_bytes, int compute_units, int T, int N, int Kd, size_t part_floats) {
-  const double n_cu = compute_units > 0 ? compute_units : 256;
-  const int nk = (elem_bytes * Kd + 127) >> 7;
-  GemmPlan best{0, 1};
-  double best_us = 1e30;
-  for (int i = 0; i < n_shapes; ++i) {
-    const Shape& sh = shapes[i];
-    if (elem_bytes == 2 && sh.BT == 32 && T > 32) continue;   // a second position tile would read the weights again
-    const double tiles = (double)((T + sh.BT - 1) / sh.BT) * ((N + sh.BN - 1) / sh.BN);
-    for (int S = 1; S <= kMaxKSplits && S <= nk; ++S) {
-      const int per = (nk + S - 1) / S;
-      if ((nk + per - 1) / per != S) continue;                // no split without a step
-      if (S > 1 && (size_t)S * T * N > part_floats) break;
-      const double u = tiles * S / (n_cu * sh.round), full = (double)(long)u, f = u - full;
-      double us = (full + (f > 0 ? sh.part + (1 - sh.part) * f : 0)) * (per * sh.us + sh.fixed);
-      us = std::max(us, (double)elem_bytes * N * Kd / (sh.tbps * 1e6));
-      if (S > 1) us += (double)S * T * N * 4.0 / 4.5e6;       // the partial results are read again (4.5 TB/s)
-      if (us < best_us) { best_us = us; best = GemmPlan{i, S}; }
-    }
-  }
-  return best;
 }
 
 }  // namespace

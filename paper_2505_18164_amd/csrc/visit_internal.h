@@ -3,6 +3,7 @@
 #pragma once
 
 #include "mdi_internal.h"
+#include "visit_plan.h"
 
 namespace mdi {
 
@@ -53,20 +54,11 @@ struct GemmArgs {
   int act_aligned;   // out_act may be written 16 bytes at a time
   QkvOut qkv;        // GEPI_QKV: N = (H + 2 K) h
 };
-// gemm_bf16.hip, gemm_f32.hip: the tile shape for a product, and into how many pieces its inner dimension is cut so that
-// few positions still fill the chip; part_floats = room for partial results, 0 forbids a split.
-constexpr int kMaxKSplits = 16;
-struct GemmPlan { int shape, S; };
-GemmPlan plan_gemm_bf16(int n_cu, int T, int N, int Kd, size_t part_floats);
-GemmPlan plan_gemm_f32(int n_cu, int T, int N, int Kd, size_t part_floats);
 // Once per device, with it current, before the first launch there: kernels with more than 64 KiB of LDS are let have it.
 bool allow_gemm_lds_bf16();
 bool allow_gemm_lds_f32();
 void launch_gemm_bf16(hipStream_t s, int epi, int shape, const GemmArgs& a);
 void launch_gemm_f32(hipStream_t s, int epi, int shape, const GemmArgs& a);
-inline GemmPlan plan_gemm(int dtype, int n_cu, int T, int N, int Kd, size_t part_floats) {
-  return dtype == MDI_BF16 ? plan_gemm_bf16(n_cu, T, N, Kd, part_floats) : plan_gemm_f32(n_cu, T, N, Kd, part_floats);
-}
 inline void launch_gemm(hipStream_t s, int dtype, int epi, int shape, const GemmArgs& a) {
   if (dtype == MDI_BF16) launch_gemm_bf16(s, epi, shape, a); else launch_gemm_f32(s, epi, shape, a);
 }
