@@ -120,6 +120,13 @@ def test_every_launch_of_the_attention_raises_references(levels):
     assert min(a for (_, g, _), a in apart.items() if g > 1) > 10
 
 
+@pytest.mark.parametrize("T,positions", [(65, 128), (128, 128), (129, 256), (256, 256)])
+def test_matrices_beyond_the_fitted_sizes_take_large_tiles(T, positions):
+    cfg = S.llama2_7b()
+    cfg.update(d_model=8192, n_head=64, n_kv_head=8, d_ff=28672)
+    assert V.products([(cfg, T, T)])[0][2] == ("bf16", "swiglu", 256, positions)
+
+
 @pytest.mark.parametrize("levels", V.LEVELS)
 @pytest.mark.parametrize("page,heads,kv,h,cuts", [c for c in V.PAGES if c[1] * c[3] * sum(c[4]) ** 2 < 1.2e9])
 def test_attention_matters_in_every_piece(page, heads, kv, h, cuts, levels):
