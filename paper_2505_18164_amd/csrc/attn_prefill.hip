@@ -23,6 +23,7 @@
 namespace mdi {
 namespace {
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -94,7 +95,8 @@ __global__ __launch_bounds__(WQ * 64 * NG, 2) void k_flash_prefill(FlashArgs a) 
     for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
   // Scores are kept relative to m, the query's reference: the products start from -m, so nothing is subtracted afterwards.
   // m is the maximum of the first block and is raised only when a score exceeds it by more than kRaise: a softmax's weights
-  // may be scaled by any number, and 2^8 costs neither bf16 nor fp32 a digit.  A score counted from -m is rounded like m, which
+  // may be scaled by any number, and 2^8 costs neither bf16 nor fp32 a digit (the largest weight is no longer 1, which bf16 holds
+  // exactly: the sum makes up for it, see below).  A score counted from -m is rounded like m, which
   // near m is what it is rounded like by itself.  Where a block raises m from much further below zero than the score that
   // raises it (the first keys 2^26 powers of two down, or lower than -1e30) its products start from zero once more.
   // 6000 positions of the 8B shape, scores that grow by 12 powers of two a block for a quarter of the queries: 444 us against
@@ -228,15 +230,17 @@ __global__ __launch_bounds__(WQ * 64 * NG, 2) void k_flash_prefill(FlashArgs a) 
 #pragma unroll
         for (int r = 0; r < 16; ++r) { s[0][r] -= by; s[1][r] -= by; neg_m[r] = -m; }
       }
-      float lsum = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { const float p = exp2f_raw(s[t][r]); s[t][r] = p; lsum += p; }
-      l += lsum;                                                   // the two lanes of a query keep separate sums until the end
+        for (int r = 0; r < 16; ++r) s[t][r] = exp2f_raw(s[t][r]);
 
       // ---- O^T += V^T P^T.  Step (t, pp) contracts keys [32 t + 16 pp, + 16); inside a step this half of the
-      // wavefront supplies keys {0..3, 8..11} + 4 half, which is what registers 8 pp .. 8 pp + 7 of tile t hold
+      // wavefront supplies keys {0..3, 8..11} + 4 half, which is what registers 8 pp .. 8 pp + 7 of tile t hold.  The sum takes the
+      // weights as they are multiplied, rounded to bf16: what one key dominates is then that key's value, whatever its weight
+      // (1600 positions of such scores: 2.61e-3 from 64 bits, 2.71e-3 with the sum of the others; two weights an instruction
+      // take no longer than one, and the instruction's fp32 sum over 6000 of them is as close as additions, 2e-6).  The two
+      // lanes of a query keep separate sums until the end.
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -244,6 +248,8 @@ __global__ __launch_bounds__(WQ * 64 * NG, 2) void k_flash_prefill(FlashArgs a) 
           bf16x8 pf;
 #pragma unroll
           for (int j = 0; j < 8; ++j) pf[j] = (__bf16)s[t][8 * pp + j];
+#pragma unroll
+          for (int j = 0; j < 8; j += 2) l = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[j], pf[j + 1]}, bf16x2{(__bf16)1.f, (__bf16)1.f}, l, false);
 #pragma unroll
           for (int i = 0; i < HT; ++i) {
             const bf16_t* vr = Vs + v_lane + (32 * t + 16 * pp) * VR + 32 * i;

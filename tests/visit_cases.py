@@ -220,6 +220,12 @@ def far_visit(heads, kv, h, T, far):
     return cfg, marked_weights(cfg, 80, far=far), marked_rows(T, 81, far_keys=256)
 
 
+def dominated_visit():
+    """Queries whose weight lies on one key or a few, with references up to 2^8 below it."""
+    cfg = marked_cfg(32, 8, 128, 1600)
+    return cfg, marked_weights(cfg, 70, rise=12.0), marked_rows(1600, 71, run=1, levels="any")
+
+
 # ----------------------------------------------------------------------------
 # Which kernels a first visit's products run on, asked of the plan itself (csrc/visit_plan.h)
 _PLAN = r"""
