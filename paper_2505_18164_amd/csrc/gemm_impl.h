@@ -7,8 +7,9 @@
 // dimension is 128 bytes of every row; both operands travel global -> LDS without passing registers
 // (buffer_load_dwordx4 ... lds), a ring of NBW / NBA steps deep, so that a step has one to three steps of arithmetic
 // to arrive; one barrier per step.  Fragments of the next half step are read from LDS between the matrix
-// instructions of the current one.  The steps that still ask for others are a loop of their own without a condition in it.  The 16-byte pieces of a row are permuted by the row number (the permutation is
-// applied to the global address, LDS then holds it for free), which spreads the reads over the banks.
+// instructions of the current one.  The steps that still ask for others are a loop of their own without a condition in
+// it.  The 16-byte pieces of a row are permuted by the row number (the permutation is applied to the global address, LDS
+// then holds it for free), which spreads the reads over the banks.
 //
 // What bounds it depends on the tile.  Timed with one of the three parts of a step left out at a time (1024 positions, cold
 // weights): 128 x 128 tiles take 0.60 us a step to load (53 bytes per ns and compute unit, at a depth of three steps as at
@@ -89,10 +90,10 @@ template <int N, typename F> __device__ __forceinline__ void each(F&& f) { each_
 // n things spread evenly over `over` places: the first that is due at place q or later.
 constexpr int due(int q, int n, int over) { const int v = (q * n + over - 1) / over; return v < n ? v : n; }
 
-// A workgroup is WN x WT wavefronts, each (BN / WN) weight rows x (BT / WT) positions.  bf16 tiles of four wavefronts leave room
-// for a second workgroup: given all 512 registers the compiler keeps sums in the accumulation half and moves them to and fro
-// in every step (96 x 128, 256 x 12288 x 4096: 42.9 -> 38.6 us; 64 x 96, 333 x 2560 x 2048: 16.0 -> 14.1).  In fp32 the same
-// costs 1 %.
+// A workgroup is WN x WT wavefronts, each (BN / WN) weight rows x (BT / WT) positions.  bf16 tiles of four wavefronts are held to
+// 256 registers: given all 512 the compiler keeps sums in the accumulation half and moves them to and fro in every step (96 x
+// 128, of which a compute unit's LDS holds one anyway, 256 x 12288 x 4096: 42.9 -> 38.6 us; 64 x 96, 333 x 2560 x 2048: 16.0 ->
+// 14.1).  In fp32 the same costs 1 %.
 template <typename ST, int EPI, int BN, int BT, int WN, int WT, int NBW, int NBA>
 __global__ __launch_bounds__(WN * WT * 64, sizeof(ST) == 2 ? 2 : WN * WT * 64 / 256) void k_gemm(GemmArgs a) {
   typedef Mac<ST> M;
@@ -187,8 +188,9 @@ __global__ __launch_bounds__(WN * WT * 64, sizeof(ST) == 2 ? 2 : WN * WT * 64 / 
   const unsigned char* a_wave = gemm_smem + NBW * WB + wt * (BT / WT) * 128;
 
   // The QKV product's epilogue rotates queries and keys and puts keys and values into the pages.  (A kernel of its own read the
-  // rows back in fp32: 13.8 us at 1024 positions of the 7B shape, 8.2 at 256, 4.9 at 333 of TinyLlama;
-  // the epilogue takes 3 to 4 us longer.)  What it needs besides the sums, angles and page numbers, small tiles ask for
+  // rows back in fp32: 13.8 us at 1024 positions of the 7B shape, 8.2 at 256, 4.9 at 333 of TinyLlama.  The product itself, fp32
+  // rows and a test before every load / this epilogue and the loop without, on the same tiles: 7168 outputs of rows of 5120, 64
+  // positions 30.3 / 30.3 us, 192 44.1 / 42.8, 256 45.1 / 44.7.)  What it needs besides the sums, angles and page numbers, small tiles ask for
   // before the first step - asked for in the epilogue they cost 1.5 to 2 us more - and tiles that need the registers one position ahead.
   constexpr bool ASK_EARLY = TN * TT <= 12;
   const int h_sh = EPI == GEPI_QKV ? 31 - __builtin_clz(a.qkv.h) : 0;

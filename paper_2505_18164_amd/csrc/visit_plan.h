@@ -60,6 +60,7 @@ inline GemmPlan plan_gemm(int dtype, int n_cu, int T, int N, int Kd, size_t part
 // group, 32 queries each.
 constexpr int kFlashKeys = 64;         // keys of a step
 struct FlashPlan { int groups, waves; };
+// The numbers of workgroups are those of 256 compute units.
 inline FlashPlan plan_flash(int T, int p0, int H) {
   const int items = (T + 127) / 128 * H;
   // Many workgroups: one group each.  us a layer of one / two groups: 1024 positions of the 7B shape (256 items of 128
@@ -68,6 +69,9 @@ inline FlashPlan plan_flash(int T, int p0, int H) {
   if (items >= 384 || p0 + T <= kFlashKeys) return {1, 4};
   // As many items as would leave half the chip idle: 64 queries a workgroup, 128 / 64 queries: 256 positions of the 7B shape
   // 12.4 / 10.1, 512 (128 items) 18.1 / 16.0, 768 (192) 22.9 / 29.2; TinyLlama 500 (128) 11.3 / 9.6, 750 (192) 14.7 / 17.1.
+  // Between the two it depends on more than the number of items: 160 of the 7B shape, 520 positions 20.4 / 19.8, 576 18.8 / 18.6,
+  // 640 20.4 / 24.1; TinyLlama 11.9 / 11.0, 12.4 / 11.6, 13.4 / 14.6; 16 heads of 64, 1100 positions (144) 19.1 / 14.8, 1400
+  // (176) 23.2 / 17.6.
   if (items > 128) return {2, 4};
   // Many keys on average: four groups.  Two / four: 256 positions behind 0, 256, 512, ... 1792 of the 8B shape 9.7 / 10.6,
   // 15.1 / 14.2, 20.6 / 18.4, ... 47.4 / 37.9; 512 of the 7B shape behind none 16.0 / 16.7, TinyLlama 256 6.5 / 6.5.
