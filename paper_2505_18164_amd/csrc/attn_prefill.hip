@@ -53,7 +53,7 @@ __device__ __forceinline__ float exp2f_raw(float x) { return __builtin_amdgcn_ex
 // ALUs (32 scores per lane: maximum, exponential, sum, conversion), and 32 KiB of LDS reads per wavefront, which take as long
 // as the matrix instructions when all four SIMDs ask.
 // 6000 positions of the 8B shape: 500 us a layer with a mask (four instructions a score) and a subtraction in every block and
-// a rescaling wherever any of a wavefront's 32 queries found a new maximum, which is most blocks; 369 us (0.79 PFLOP/s) with
+// a rescaling wherever any of a wavefront's 32 queries found a new maximum, which is most blocks; 379 us (0.78 PFLOP/s) with
 // the mask in the last blocks only, scores that come out relative, and a rescaling when it is needed.  1024 positions of the
 // 7B shape 33 -> 28, pieces of 256 23 -> 20 us.  Heads that share keys on one die give 20 of it.
 template <int HD, int NG, int WQ>

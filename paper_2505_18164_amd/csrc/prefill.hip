@@ -31,7 +31,7 @@ __device__ __forceinline__ void put_four(void* base, int kind, long at, const fl
 //
 // With few rows what counts is how many round trips to memory a row takes: everything that can be asked for is, before
 // anything is stored (a store between two loads keeps the compiler from asking for the second before the first is there).
-// 256 rows of 4096 with two to four partial results 7.5 -> 6.8 us, 1024 rows 12.9 -> 11.6; a kernel of its own for the input took 10
+// 256 rows of 4096 with two to four partial results 7.5 -> 6.8 us, 1024 rows, half of them with, 12.9 -> 11.6 on average; a kernel of its own for the input took 10
 // to 14 us there (41 at 6000 rows) and left the row to be read again.
 // With many rows it is how many of them are in flight, and the partial results asked for at a time are two thirds of the
 // registers (rows of 8192: 203 against 82, two wavefronts a SIMD against five): kernels with and without.  2048 rows of 8192
