@@ -256,12 +256,15 @@ int main() {
 @functools.lru_cache(None)
 def _plan_program():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    d = tempfile.mkdtemp()
+    d = _plan_program.dir.name
     src, exe = os.path.join(d, "plan.cpp"), os.path.join(d, "plan")
     open(src, "w").write(_PLAN)
     subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(root, "paper_2505_18164_amd", "csrc"), "-I", os.path.join(root, "include"), src, "-o", exe],
                    check=True)
     return exe
+
+
+_plan_program.dir = tempfile.TemporaryDirectory()
 
 
 def _ask(lines):
